@@ -83,7 +83,8 @@ int smoe_abi_version(void);
 
 /* Selects the GEMM kernel family: 0 = automatic (persistent matrix-core kernels whenever the
  * shape allows), 1 = force the plain tiled kernels, 2 = matrix-core kernels with one block per
- * tile (1 and 2 are testing aids).  Host-only; writes the context, so no other call on the same
+ * tile, 3 / 4 = as 0, but the persistent scatter2scatter kernels always with 128 x 256 / 256 x 256
+ * tiles (1 to 4 are testing aids).  Host-only; writes the context, so no other call on the same
  * context may be in progress. */
 int smoe_set_kernel_mode(smoe_ctx *ctx, int mode);
 
@@ -94,7 +95,7 @@ int smoe_set_kernel_mode(smoe_ctx *ctx, int mode);
 int smoe_set_tile_group(smoe_ctx *ctx, int group_m);
 
 /* Measurement aid.  With a device array of 512 uint64 set, every launch of the persistent scatter2scatter
- * kernels (the products of smoe_plinear_fwd / _bwd, smoe_plinear_act_fwd, smoe_mlp_fwd / _bwd) makes block b
+ * kernels (the products of smoe_plinear_fwd / _bwd, smoe_plinear_act_fwd, smoe_mlp_fwd / _bwd) makes block b < 256
  * store, when it ends, the shader-clock cycles and the ticks of the constant 100 MHz counter between its first
  * and last instruction in entries 2b and 2b+1: cycles / ticks * 100 is the clock in MHz the compute unit ran at
  * (blocks b, b+8, ... share an XCD).  Later launches overwrite the array.  NULL (the default) turns it off.

@@ -15,10 +15,15 @@ bool routing_ok(const smoe_routing *r) {
 bool width_ok(smoe_dtype dt, int d) { return d > 0 && d % (int)(16 / dtype_size(dt)) == 0; }
 bool dtype_ok(int dt) { return dt == SMOE_F32 || dt == SMOE_BF16; }
 
-int run_s2s(smoe_ctx *ctx, hipStream_t s, smoe_dtype dt, S2SArgs a) {
+// what every launch of the persistent kernels takes from the context
+void set_launch(const smoe_ctx *ctx, S2SArgs &a) {
   a.grid = ctx->stream_grid;
   a.group_m = ctx->group_m;
+  a.tile_shape = ctx->tile_shape;
   a.clock_probe = ctx->clock_probe;
+}
+int run_s2s(smoe_ctx *ctx, hipStream_t s, smoe_dtype dt, S2SArgs a) {
+  set_launch(ctx, a);
   if (dt == SMOE_BF16 && ctx->kernel_mode == 0 && s2s_decode_supported(a)) return launch_s2s_decode(s, a);
   if (dt == SMOE_BF16 && ctx->kernel_mode == 0 && s2s_stream_supported(a)) return launch_s2s_stream(s, a);
   if (dt == SMOE_BF16 && ctx->kernel_mode != 1 && s2s_mfma_supported(a)) return launch_s2s_mfma(s, a);
@@ -82,6 +87,7 @@ int smoe_create(smoe_ctx **out, int device) {
   c->stream_grid = c->num_cu >= 256 ? 256 : (c->num_cu & ~7);
   c->kernel_mode = 0;
   c->group_m = 4;
+  c->tile_shape = 0;
   c->clock_probe = nullptr;
   c->route_scratch = nullptr;
   // kernel attributes and the address of a __device__ array are per device: set them with this context's device current, then restore the caller's
@@ -104,8 +110,9 @@ int smoe_create(smoe_ctx **out, int device) {
 void smoe_destroy(smoe_ctx *ctx) { delete ctx; }
 
 int smoe_set_kernel_mode(smoe_ctx *ctx, int mode) {
-  if (!ctx || mode < 0 || mode > 2) return SMOE_ERR_INVALID_ARG;
-  ctx->kernel_mode = mode;
+  if (!ctx || mode < 0 || mode > 4) return SMOE_ERR_INVALID_ARG;
+  ctx->kernel_mode = mode > 2 ? 0 : mode;
+  ctx->tile_shape = mode > 2 ? mode - 2 : 0;
   return SMOE_OK;
 }
 
@@ -340,9 +347,7 @@ static int hidden_forward(smoe_ctx *ctx, hipStream_t s, smoe_dtype dtype, smoe_a
   a1.tail_ws = tail_ws;
   S2SArgs fused = a1;
   fused.H = H;
-  fused.grid = ctx->stream_grid;
-  fused.group_m = ctx->group_m;
-  fused.clock_probe = ctx->clock_probe;
+  set_launch(ctx, fused);
   if (act == SMOE_ACT_SWIGLU && dtype == SMOE_BF16 && ctx->kernel_mode == 0 &&
       (s2s_decode_supported(fused) || s2s_stream_swiglu_supported(fused))) {
     // SwiGLU in the product's epilogue: H comes straight from the fp32 accumulators, and the
@@ -548,9 +553,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     }
     x2.row_scale = gsorted;
     x2.dp_part = dp_part;
-    x2.grid = ctx->stream_grid;
-    x2.group_m = ctx->group_m;
-    x2.clock_probe = ctx->clock_probe;
+    set_launch(ctx, x2);
     rc = launch_s2s_stream(s, x2);
     if (rc != SMOE_OK) return rc;
     rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, Tk);

@@ -316,12 +316,6 @@ __global__ void __launch_bounds__(NTHREADS, 1) dw_mfma_kernel(DWArgs a, int tile
 
 constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
 
-template <typename K> int set_lds_limit(K kernel, int bytes) {
-  return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess
-             ? SMOE_OK
-             : SMOE_ERR_HIP;
-}
-
 template <bool TRANS_W> int launch_s2s_cfg(hipStream_t s, const S2SArgs &a) {
   int tiles_n = ceil_div(a.N, TB);
   int tiles_m = ceil_div(a.Tk, TB) + a.E;     // upper bound on sum_e ceil(n_e / 256)

@@ -1,456 +1,130 @@
 // Persistent ("stream") form of the bf16 matrix-core grouped GEMMs.
 //
-// One block per compute unit walks a list of 256x256 output tiles.  The four-stage LDS ring of
-// the contraction loop never drains between tiles: the loader side runs three half-steps ahead
-// of the multiplying side and simply moves on to the next tile's operand rows, so the next
-// tile's first stages land while the current tile is being finished and written out.  Per tile
-// this removes the block launch, the pipeline fill and the tile search from the critical path;
-// what remains is the epilogue (accumulators -> bf16 -> LDS patch -> whole-line stores).
+// Blocks walk lists of output tiles.  The LDS ring of the contraction loop never drains between tiles: the loader runs
+// several half-steps (of 32 contraction elements) ahead of the multiplying side and simply moves on to the next tile's
+// operand rows, so the next tile's first stages land while the current tile is being finished and written out.
 //
-// Both sides visit the same sequence of slots (one per half-step, at least one per tile) with a
-// fixed lag.  Exactly eight tile loads are issued
-// per slot -- slots past the end of the list repeat a valid address -- so one constant
-// `s_waitcnt vmcnt` per slot orders everything.  Row indices travel through LDS by
-// direct-to-LDS loads as well: no ordinary global load sits in the loop, so the compiler never
-// inserts a full wait in front of the loads that are meant to stay in flight.
-#include "mfma_common.h"
+// A half-step has two phases.  Phase A issues the first half's matrix instructions from fragments that are already in
+// registers and reads the second half's fragments behind them; then, in the MIDDLE of the half-step, comes the only
+// barrier: every wavefront holds all of the stage's fragments, so its slot is free, and the next stage has landed.  Phase
+// B multiplies the second half, reads the next stage's first fragments, and starts to refill the freed slot; the refill
+// ends in the next phase A.  With the barrier in the middle a ring of S slots keeps almost S half-steps of loads in flight
+// (at the start of a half-step it would be S - 2 and a bit: the slot just left could only be refilled a half-step later).
+//
+// Two shapes (Shape below):
+//   Big   256 x 256 tiles, four 32 KB slots, one block per compute unit (one wavefront per SIMD, 256 accumulators): the
+//         fewest operand bytes per multiply-add.
+//   Pair  128 x 256 tiles, three 24 KB slots, two blocks per compute unit (128 accumulators, at most 256 registers): one
+//         block's epilogue, barriers and fragment reads run under the other's matrix instructions, and half as many rows
+//         per tile waste fewer rows at segment ends and leave less work over when the tiles do not fill a last round; the
+//         price is 1.5 times the operand traffic.
+//
+// Loads are inline assembly so that the waits are placed by hand; stores share the hardware counter with them and complete
+// in order, and because every epilogue issues a known number of stores at least, the first waits after an epilogue step
+// over them instead of sitting out their acknowledgement.  All loads go through range-checked buffer windows: rows past a
+// segment and contraction elements past K read zeros.  Row indices travel through LDS by direct-to-LDS loads as well: no
+// ordinary global load sits in the loop, so the compiler never inserts a full wait in front of the loads in flight.
+#include "gemm_epilogue.h"
 #include <type_traits>
 
 namespace {
 
-constexpr int RING_BYTES = NSTAGE * STAGE_BYTES;          // 128 KB
-constexpr int EPI_ROW_BYTES = 144;                        // 64 bf16 columns + 16 B pad
-constexpr int EPI_WAVE_BYTES = 32 * EPI_ROW_BYTES;
-constexpr int STREAM_LDS_BYTES = RING_BYTES + 4 * EPI_WAVE_BYTES;
-constexpr int MAX_E = 256;                                // expert offsets are cached in LDS
-constexpr int MAX_STREAM_GRID = 256;                      // persistent blocks: one per CU; the partial-tile scratch holds this many tiles
-
-// Epilogue of one wavefront: its 128x128 accumulators leave in 8 passes of 32 rows x 64
-// columns through a private LDS patch; every store instruction writes full 128-byte lines of
-// 8 destination rows.  dst_row(r) gives the destination row of wave-tile row r or -1.
-// Moves one accumulator element out of the accumulation register file right where it is
-// used.  Left to itself the register allocator copies all 256 accumulators of a lane into
-// ordinary registers at the top of the epilogue, which cannot fit beside the operand
-// fragments and load addresses that stay live for the next tile.
-__device__ __forceinline__ float acc_read(float a) {
-  float v;
-  __asm__ volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
-  return v;
-}
-
-// ---- the LDS patch as a pipeline ------------------------------------------------------------------------
-// A 32 x 64 block of bf16 results goes accumulator layout -> patch (8-byte writes, a lane's 4 consecutive columns)
-// -> whole rows back out (16-byte reads, eight lanes per 128-byte row) -> global memory.  LDS operations of one
-// wavefront execute in order, so the block's row reads may be issued right behind its writes and the next block's
-// writes right behind those reads, with no wait in between; only the global stores need the read data.  The
-// stores of block n are therefore issued after block n+1 has been written and read: the LDS latency of one block
-// hides behind the accumulator reads and conversions of the next one instead of being sat out four times per block.
-struct PatchRows {
-  bf16x8 v[4];
+template <int FM_, int SLOTS_, int BLOCKS_> struct Shape {
+  static constexpr int FM = FM_;                        // 32-row fragments per wavefront (2 x 2 wavefronts, FR = 4 column fragments)
+  static constexpr int TM = FM * 64;                    // tile rows; tile columns are TB = 256
+  static constexpr int A_BYTES = TM * HK * 2;
+  static constexpr int SLOT_BYTES = A_BYTES + TILE_BYTES;
+  static constexpr int SLOTS = SLOTS_;
+  static constexpr int BLOCKS = BLOCKS_;                // blocks per compute unit
+  static constexpr int NLA = FM;                        // load instructions per wavefront and stage: A part,
+  static constexpr int NL = NLA + NLD;                  // both parts
+  static constexpr int HALF = NL / 2;                   // issued in phase B; the rest in the next phase A
+  static constexpr int IN_FLIGHT = (SLOTS - 2) * NL;    // loads issued after those of the next stage, in the middle of a half-step
+  static constexpr int PART = TM * TB;                  // elements of an fp32 partial tile
+  // With two blocks per compute unit the patch of an epilogue is the part of the finished slot that the wavefront loads
+  // itself: nobody else touches it until the same wavefront issues that slot's next loads, held back until after the
+  // epilogue.  The big tile has LDS for a patch of its own and lets its loads run on.
+  static constexpr bool PATCH_IN_SLOT = BLOCKS > 1;
+  static constexpr int LDS_BYTES = SLOTS * SLOT_BYTES + (PATCH_IN_SLOT ? 0 : 4 * EPI_WAVE_BYTES);
 };
-__device__ __forceinline__ PatchRows read_patch_rows(const char *patch, int lane) {
-  PatchRows r;
-#pragma unroll
-  for (int it = 0; it < 4; ++it)
-    r.v[it] = *reinterpret_cast<const bf16x8 *>(patch + (it * 8 + (lane >> 3)) * EPI_ROW_BYTES + (lane & 7) * 16);
-  return r;
-}
-// The rows read from the patch and where they go: destination rows of the lane's four chunks (-1: none), the
-// tensor, its row stride, the lane's column in it, and whether that column exists.
-struct RowStore {
-  PatchRows rows;
-  int drow[4];
-  bf16_t *base;
-  size_t ld;
-  int col;
-  bool col_ok, have;
+using Big = Shape<4, 4, 1>;
+using Pair = Shape<2, 3, 2>;
+constexpr int MAX_STREAM_GRID = 256;                    // compute units used; the partial-tile scratch holds this many big tiles
+
+template <typename S> struct Frags {                    // one wavefront's fragments for 16 contraction elements
+  bf16x8 a[S::FM], b[FR];
 };
-__device__ __forceinline__ void issue_row_store(const RowStore &p, int lane) {
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    bf16_t *dst = (p.drow[it] >= 0 && p.col_ok) ? p.base + (size_t)p.drow[it] * p.ld + p.col : (bf16_t *)g_trash + lane * 8;
-    // Non-temporal: a launch streams gigabytes of output through each XCD's 4 MB L2, which also holds the operand
-    // panels its 32 compute units share; marking the lines for early eviction keeps them from pushing the panels out
-    // (3 % on the first product of the Mixtral-shaped layer, neutral on products with narrow outputs).
-    __builtin_nontemporal_store(p.rows.v[it], reinterpret_cast<bf16x8 *>(dst));   // masked lanes hit the landing zone
-  }
+template <typename S, typename Ops>
+__device__ __forceinline__ void read_frag_group(const Ops &ops, Frags<S> &f, const char *slot, int kk, int group, int wm, int wn, int lane) {
+  auto A = [&](int i) { f.a[i] = ops.frag_a(slot, wm * (S::TM / 2) + i * 32, kk, lane); };
+  auto B = [&](int j) { f.b[j] = ops.frag_b(slot + S::A_BYTES, wn * (TB / 2) + j * 32, kk, lane); };
+  // in the order the next phase consumes them: b0 a0 b1 | b2 b3 a1 | a2 a3
+  if (group == 0) { B(0); A(0); B(1); }
+  if (group == 1) { B(2); B(3); A(1); }
+  if (group == 2 && S::FM == 4) { A(2); A(3); }
 }
-// One block through the pipeline: write_block() fills the patch from the accumulators; the previous block's
-// stores go out behind this block's LDS traffic.  gcol is the block's first column among the `limit` columns of
-// its destination, col0 the offset of those columns inside a row of `base`.
-template <typename WriteFn>
-__device__ __forceinline__ void pipe_block(RowStore &pend, const char *patch, int lane, WriteFn write_block, const int (&drow)[4],
-                                           bf16_t *base, size_t ld, int col0, int gcol, int limit) {
-  sched_fence();
-  write_block();
-  RowStore cur;
-  cur.rows = read_patch_rows(patch, lane);
-  sched_fence();
-  if (pend.have) issue_row_store(pend, lane);
-#pragma unroll
-  for (int it = 0; it < 4; ++it) cur.drow[it] = drow[it];
-  cur.base = base;
-  cur.ld = ld;
-  cur.col = col0 + gcol + (lane & 7) * 8;
-  cur.col_ok = gcol + (lane & 7) * 8 < limit;
-  cur.have = true;
-  pend = cur;
-}
-// destination rows of the lane's chunks in every 32-row fragment row of the wave tile
-template <typename RowFn> __device__ __forceinline__ void chunk_rows(RowFn dst_row, int lane, int (&drow)[FR][4]) {
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) drow[fm][it] = dst_row(fm * 32 + it * 8 + (lane >> 3));
-}
-// accumulators of one 32 x 32 fragment pair (64 columns) -> patch, rounded to bf16
-__device__ __forceinline__ void acc_block_to_patch(const f32x16 &a0, const f32x16 &a1, char *patch, int lane) {
-#pragma unroll
-  for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 v;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = (bf16_t)acc_read(f2 == 0 ? a0[g * 4 + q] : a1[g * 4 + q]);
-      *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = v;
-    }
-}
-
-template <typename RowFn>
-__device__ __forceinline__ void store_wave_tile(const f32x16 (&acc)[FR][FR], char *patch, RowFn dst_row, bf16_t *C,
-                                                int ldc, int wcol, int ncols, int lane) {
-  // the last matrix instructions must have retired before their results are read by hand
-  __asm__ volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  int drow[FR][4];
-  chunk_rows(dst_row, lane, drow);
-  RowStore pend;
-  pend.have = false;
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm)
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-      pipe_block(pend, patch, lane, [&] { acc_block_to_patch(acc[fm][half * 2], acc[fm][half * 2 + 1], patch, lane); }, drow[fm], C,
-                 (size_t)ldc, 0, wcol + half * 64, ncols);
-  sched_fence();
-  issue_row_store(pend, lane);
-}
-
-// Epilogue of a SwiGLU tile: the wavefront's 128 accumulator columns are 64 gate columns (fragments 0, 1)
-// and the 64 up columns that pair with them (fragments 2, 3), so a lane holds both factors of each hidden
-// unit in matching registers.  Writes the pre-activation halves (KEEP) and H = silu(gate) * up, each
-// through the same pipeline as above.  gcol is the first gate column of this wavefront, half_n the number of
-// gate columns of the layer.
-template <bool KEEP, typename RowFn>
-__device__ __forceinline__ void store_wave_tile_swiglu(const f32x16 (&acc)[FR][FR], char *patch, RowFn dst_row, bf16_t *C,
-                                                       bf16_t *H, int half_n, int gcol, int lane) {
-  __asm__ volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  int drow[FR][4];
-  chunk_rows(dst_row, lane, drow);
-  RowStore pend;
-  pend.have = false;
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm) {
-    if (KEEP) {
-#pragma unroll
-      for (int half = 0; half < 2; ++half)   // gate columns, then up columns of the pre-activation
-        pipe_block(pend, patch, lane, [&] { acc_block_to_patch(acc[fm][half * 2], acc[fm][half * 2 + 1], patch, lane); }, drow[fm],
-                   C, (size_t)2 * half_n, half * half_n, gcol, half_n);
-    }
-    pipe_block(pend, patch, lane, [&] {
-#pragma unroll
-      for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          bf16x4 v;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float gate = acc_read(acc[fm][f2][g * 4 + q]), up = acc_read(acc[fm][2 + f2][g * 4 + q]);
-            float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate));
-            v[q] = (bf16_t)(gate * sig * up);
-          }
-          *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = v;
-        }
-    }, drow[fm], H, (size_t)half_n, 0, gcol, half_n);
-  }
-  sched_fence();
-  issue_row_store(pend, lane);
-}
-
-// Epilogue of the second ParallelLinear's input-gradient product with the SwiGLU derivative and Alg. 2's dp folded in.
-// The accumulators hold dH / p for 128 hidden units of 128 expert-sorted rows (the product ran on the unweighted
-// upstream rows).  Per 32-row fragment row the lane fetches the matching gate and up pre-activations (its own row,
-// its own 4-column groups: 8-byte loads, the next 64 columns requested before the current ones are used), forms
-// h = silu(gate) * up and the partial dot <acc, h> (summed over the wavefront's 128 columns: one slab of dp), scales
-// the accumulators by the row's routing weight and writes
-//   dgate = dh * up * (sig + silu * (1 - sig)),  dup = dh * silu
-// to the two halves of dHpre through the patch pipeline.  Rows past the segment read its last row and columns
-// past the width read column 0; neither is stored or added to the dot.
-struct GateUp {
-  bf16x4 gt[2][4], up[2][4];
-};
-__device__ __forceinline__ GateUp load_gate_up(const bf16_t *src, int half_n, int col_base, int lane) {
-  GateUp r;
-#pragma unroll
-  for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = col_base + f2 * 32 + 8 * g + 4 * (lane >> 5);
-      const int cc = col < half_n ? col : 0;
-      r.gt[f2][g] = *reinterpret_cast<const bf16x4 *>(src + cc);
-      r.up[f2][g] = *reinterpret_cast<const bf16x4 *>(src + half_n + cc);
-    }
-  return r;
-}
-template <typename RowFn>
-__device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[FR][FR], char *patch, RowFn dst_row,
-                                                           const bf16_t *Hpre, bf16_t *dHpre, const float *row_scale,
-                                                           float *dp_part, int part_ld, int part_col, int half_n, int gcol,
-                                                           int row_base, int row_end, int lane) {
-  __asm__ volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  const size_t ld = (size_t)2 * half_n;
-  // the lane's own row in a fragment row (source of the pre-activations and of the routing weight); rows past the
-  // segment read its last row
-  auto own_row = [&](int fm) { return min(row_base + fm * 32 + (lane & 31), row_end - 1); };
-  RowStore pend;
-  pend.have = false;
-  GateUp in = load_gate_up(Hpre + (size_t)own_row(0) * ld, half_n, gcol, lane);
-  float scale_next = row_scale[own_row(0)];
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm) {
-    float dp = 0.f;
-    const float scale = scale_next;
-    int drow[4];      // destination rows of the lane's chunks in this fragment row (the rows are expert-sorted, never scattered)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) drow[it] = dst_row(fm * 32 + it * 8 + (lane >> 3));
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const GateUp cur = in;
-      if (fm * 2 + half + 1 < 2 * FR) {   // request the next 64 columns (or the next fragment row) now
-        const int nfm = half == 0 ? fm : fm + 1;
-        in = load_gate_up(Hpre + (size_t)own_row(nfm) * ld, half_n, gcol + (half == 0 ? 64 : 0), lane);
-        if (half == 1) scale_next = row_scale[own_row(nfm)];
-      }
-      bf16x4 du[2][4];
-      pipe_block(pend, patch, lane, [&] {
-#pragma unroll
-        for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int col = gcol + half * 64 + f2 * 32 + 8 * g + 4 * (lane >> 5);
-            bf16x4 dg;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float a = acc_read(acc[fm][half * 2 + f2][g * 4 + q]);
-              const float gate = (float)cur.gt[f2][g][q], u = (float)cur.up[f2][g][q];
-              const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate));
-              const float silu = gate * sig;
-              if (col < half_n) dp = fmaf(a, silu * u, dp);
-              const float dh = scale * a;
-              dg[q] = (bf16_t)(dh * u * (sig + silu * (1.0f - sig)));
-              du[f2][g][q] = (bf16_t)(dh * silu);
-            }
-            *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = dg;
-          }
-      }, drow, dHpre, ld, 0, gcol + half * 64, half_n);
-      pipe_block(pend, patch, lane, [&] {
-#pragma unroll
-        for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = du[f2][g];
-      }, drow, dHpre, ld, half_n, gcol + half * 64, half_n);
-    }
-    dp += __shfl_xor(dp, 32, 64);
-    if (row_base + fm * 32 + lane < row_end && lane < 32) dp_part[(size_t)(row_base + fm * 32 + lane) * part_ld + part_col] = dp;
-  }
-  sched_fence();
-  issue_row_store(pend, lane);
-}
-
-// The activation-agnostic form: the accumulators hold dH / p; the lane fetches the saved hidden activations H of its
-// row and column groups, adds <acc, H> to the row's slab of dp, and writes dH = p * acc (and Hw = p * H when asked).
-template <typename RowFn>
-__device__ __forceinline__ void store_wave_tile_dp(const f32x16 (&acc)[FR][FR], char *patch, RowFn dst_row, const bf16_t *H,
-                                                   bf16_t *dH, bf16_t *Hw, const float *row_scale, float *dp_part, int part_ld,
-                                                   int part_col, int n, int gcol, int row_base, int row_end, int lane) {
-  __asm__ volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  auto own_row = [&](int fm) { return min(row_base + fm * 32 + (lane & 31), row_end - 1); };
-  auto load_h = [&](int fm, int half, bf16x4 (&h)[2][4]) {
-    const bf16_t *src = H + (size_t)own_row(fm) * n;
-#pragma unroll
-    for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = gcol + half * 64 + f2 * 32 + 8 * g + 4 * (lane >> 5);
-        h[f2][g] = *reinterpret_cast<const bf16x4 *>(src + (col < n ? col : 0));
-      }
-  };
-  RowStore pend;
-  pend.have = false;
-  bf16x4 nxt[2][4];
-  load_h(0, 0, nxt);
-  float scale_next = row_scale[own_row(0)];
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm) {
-    float dp = 0.f;
-    const float scale = scale_next;
-    int drow[4];
-#pragma unroll
-    for (int it = 0; it < 4; ++it) drow[it] = dst_row(fm * 32 + it * 8 + (lane >> 3));
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      bf16x4 cur[2][4];
-#pragma unroll
-      for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) cur[f2][g] = nxt[f2][g];
-      if (fm * 2 + half + 1 < 2 * FR) {   // request the next 64 columns (or the next fragment row) now
-        load_h(half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, nxt);
-        if (half == 1) scale_next = row_scale[own_row(fm + 1)];
-      }
-      pipe_block(pend, patch, lane, [&] {
-#pragma unroll
-        for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int col = gcol + half * 64 + f2 * 32 + 8 * g + 4 * (lane >> 5);
-            bf16x4 v;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float a = acc_read(acc[fm][half * 2 + f2][g * 4 + q]);
-              if (col < n) dp = fmaf(a, (float)cur[f2][g][q], dp);
-              v[q] = (bf16_t)(scale * a);
-            }
-            *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = v;
-          }
-      }, drow, dH, (size_t)n, 0, gcol + half * 64, n);
-      if (Hw)
-        pipe_block(pend, patch, lane, [&] {
-#pragma unroll
-          for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              bf16x4 v;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] = (bf16_t)(scale * (float)cur[f2][g][q]);
-              *reinterpret_cast<bf16x4 *>(patch + (lane & 31) * EPI_ROW_BYTES + (f2 * 32 + 8 * g + 4 * (lane >> 5)) * 2) = v;
-            }
-        }, drow, Hw, (size_t)n, 0, gcol + half * 64, n);
-    }
-    dp += __shfl_xor(dp, 32, 64);
-    if (row_base + fm * 32 + lane < row_end && lane < 32) dp_part[(size_t)(row_base + fm * 32 + lane) * part_ld + part_col] = dp;
-  }
-  sched_fence();
-  issue_row_store(pend, lane);
-}
-
-// A wavefront's 128 x 128 accumulators as fp32 into a 256-wide partial tile (chunks of a split contraction).
-__device__ __forceinline__ void store_wave_partial(const f32x16 (&acc)[FR][FR], float *dst, int lane) {
-  __asm__ volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-#pragma unroll
-  for (int fm = 0; fm < FR; ++fm)
-#pragma unroll
-    for (int fn = 0; fn < FR; ++fn) {
-      sched_fence();
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float4 v = make_float4(acc_read(acc[fm][fn][4 * g]), acc_read(acc[fm][fn][4 * g + 1]), acc_read(acc[fm][fn][4 * g + 2]),
-                               acc_read(acc[fm][fn][4 * g + 3]));
-        *reinterpret_cast<float4 *>(dst + (size_t)(fm * 32 + (lane & 31)) * TB + fn * 32 + 8 * g + 4 * (lane >> 5)) = v;
-      }
-    }
-}
-
-// One half-step of the contraction: 32 matrix instructions on the landed stage `cur`, the
-// fragment reads of its second half and of the next stage's first half riding behind them, and
-// the eight loads of the stage being refilled, one per four matrix instructions.  FIRST starts
-// a tile: its first sixteen products overwrite the accumulators instead of adding to them.
-template <bool FIRST, typename Ops>
-__device__ __forceinline__ void half_step(Ops &ops, const char *cur, const char *nxt, uint32_t fill, int wm, int wn,
-                                          int lane, bf16x8 (&fa)[2][FR], bf16x8 (&fb)[2][FR], f32x16 (&acc)[FR][FR]) {
+// Phase A (KK = 0) or B (KK = 1): multiplies `use`, reads `next` from `slot` behind the products (READ), and issues its half
+// of a stage's loads into `fill`, spread over the products (LOAD).  FIRST: the tile's first products overwrite the accumulators.
+template <int KK, bool FIRST, bool READ, bool LOAD, typename S, typename Ops>
+__device__ __forceinline__ void phase(const Ops &ops, const Frags<S> &use, Frags<S> &next, const char *slot, uint32_t fill, int wm, int wn,
+                                      int lane, f32x16 (&acc)[S::FM][FR]) {
   f32x16 zero;
 #pragma unroll
   for (int q = 0; q < 16; ++q) zero[q] = 0.f;
+  constexpr int LO = KK == 1 ? 0 : S::HALF, N = KK == 1 ? S::HALF : S::NL - S::HALF;
   sched_fence();
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    const char *src = kk == 0 ? cur : nxt;
-    const int nkk = 1 - kk;
+  for (int m = 0; m < S::FM; ++m) {
 #pragma unroll
-    for (int g = 0; g < FR; ++g) {
+    for (int n = 0; n < FR; ++n)
+      acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use.b[n], use.a[m], FIRST ? zero : acc[m][n], 0, 0, 0);
+    if (READ) read_frag_group<S>(ops, next, slot, 1 - KK, m, wm, wn, lane);
 #pragma unroll
-      for (int j = 0; j < FR; ++j)
-        acc[g][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][j], fa[kk][g], (FIRST && kk == 0) ? zero : acc[g][j],
-                                                            0, 0, 0);
-      // next fragments in the order the next sub-step consumes them: b0 a0 b1 | b2 b3 a1 | a2 a3
-      if (g == 0) {
-        fb[nkk][0] = ops.frag_b(src + TILE_BYTES, wn * (TB / 2) + 0 * 32, nkk, lane);
-        fa[nkk][0] = ops.frag_a(src, wm * (TB / 2) + 0 * 32, nkk, lane);
-        fb[nkk][1] = ops.frag_b(src + TILE_BYTES, wn * (TB / 2) + 1 * 32, nkk, lane);
-      } else if (g == 1) {
-        fb[nkk][2] = ops.frag_b(src + TILE_BYTES, wn * (TB / 2) + 2 * 32, nkk, lane);
-        fb[nkk][3] = ops.frag_b(src + TILE_BYTES, wn * (TB / 2) + 3 * 32, nkk, lane);
-        fa[nkk][1] = ops.frag_a(src, wm * (TB / 2) + 1 * 32, nkk, lane);
-      } else if (g == 2) {
-        fa[nkk][2] = ops.frag_a(src, wm * (TB / 2) + 2 * 32, nkk, lane);
-        fa[nkk][3] = ops.frag_a(src, wm * (TB / 2) + 3 * 32, nkk, lane);
-      }
-      // the source address of this group's load is worked out in the shadow of the matrix instructions
-      const int I = kk * FR + g;
-      const auto src = ops.prepare(I);
+    for (int q = 0; q < 4; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    sched_fence();
+    if (LOAD) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      }
-      sched_fence();
-      ops.issue(I, src, fill + (I / NLD) * TILE_BYTES + inst_off(ops.uwave, I % NLD));
+      for (int I = LO + (m * N + S::FM - 1) / S::FM; I < LO + ((m + 1) * N + S::FM - 1) / S::FM; ++I) ops.load(I, fill);
       sched_fence();
     }
   }
 }
 
-// ======================================================================================
-// scatter2scatter, persistent
-// ======================================================================================
-struct S2STile {
-  int seq;                    // position in this block's tile list (-1 before the first)
-  int ord;                    // running number of the tile among the block's valid tiles
-  int e, row0, row_end, n0;
-  int h0, hn;                 // first half-step and number of half-steps this block contributes
-  int part;                   // -1: the whole contraction, result stored directly; else index of the fp32 partial
+// The contraction side shared by the kernels below: ring position, fragments, waits.
+template <typename S> struct Ring {
+  static constexpr uint32_t END = (S::SLOTS - 1) * S::SLOT_BYTES;
+  __device__ static uint32_t after(uint32_t slot) { return slot == END ? 0u : slot + S::SLOT_BYTES; }
+  __device__ static uint32_t before(uint32_t slot) { return slot == 0u ? END : slot - S::SLOT_BYTES; }
 };
+// In the middle of a half-step: the next stage has landed for every wavefront, and all of this stage's fragments are in
+// registers.  STORES: that many stores were issued after the next stage's loads at least.
+template <typename S, int STORES> __device__ __forceinline__ void middle() {
+  constexpr int N = S::IN_FLIGHT + STORES;
+  wait_loads<(N < 63 ? N : 63)>();
+  __syncthreads();
+}
 
-// How the tiles of one launch are dealt to the G persistent blocks.  Tiles are numbered densely
-// (groups of group_m M-tiles x all N-tiles); block b takes numbers seq * G + slot(b) for the `rounds`
-// full rounds.  The remaining `rest` < G tiles would leave G - rest blocks idle for a whole tile, so
-// their contraction is cut into `split` chunks of `chunk` half-steps, one block each; the chunks leave
-// fp32 partial tiles that a second kernel adds in chunk order (deterministic) and stores.
+// ======================================================================================
+// scatter2scatter
+// ======================================================================================
+// How the tiles of a launch are dealt to the G blocks.  Tiles are numbered densely (tile_coords); full rounds deal G tiles.
+// Of the rem < G tiles left, with two blocks per compute unit the first G / 2 go one to a compute unit (`whole`), and what
+// remains beyond them (or all of rem) would keep few compute units busy for a whole tile: its contraction is cut into
+// `split` chunks of `chunk` half-steps for the blocks still free; the chunks leave fp32 partial tiles that a second kernel
+// adds in chunk order (deterministic) and stores.
 struct TilePlan {
-  int m_tiles, rounds, rest, split, chunk;
+  int m_tiles, rounds, whole, rest, split, chunk;
 };
-// A chunk's fp32 partial tile costs a 256 KB write and a 256 KB read on top of the second kernel's launch,
-// about what 48 half-steps of multiplying take: a split must shorten the last round by more than that.
-constexpr int SPLIT_MIN_SAVED = 64;
-// Largest number of chunks <= max_split (and <= 4) that pays, with the chunk length; 1 = keep whole tiles.
-__host__ __device__ inline int choose_split(int nh, int max_split, bool static4, int &chunk) {
-  for (int s = max_split < 4 ? max_split : 4; s > 1; --s) {
-    int c = (nh + s - 1) / s;
-    if (static4) c = (c + 3) & ~3;
-    if ((s - 1) * c < nh && nh - c >= SPLIT_MIN_SAVED) {
-      chunk = c;
-      return s;
-    }
-  }
-  chunk = nh;
-  return 1;
-}
-__device__ __forceinline__ TilePlan plan_tiles(const int32_t *offsets, int E, int tiles_n, int nh, int G, bool static4,
-                                               bool may_split, int lane) {
+template <typename S>
+__device__ __forceinline__ TilePlan plan_tiles(const int32_t *offsets, int E, int tiles_n, int nh, int G, bool static4, bool may_split,
+                                               int lane) {
   int sum = 0;
   for (int c0 = 0; c0 < E; c0 += 64) {
     int x = c0 + lane;
-    int n = x < E ? (offsets[x + 1] - offsets[x] + TB - 1) / TB : 0;
+    int n = x < E ? (offsets[x + 1] - offsets[x] + S::TM - 1) / S::TM : 0;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
     sum += n;
@@ -459,314 +133,388 @@ __device__ __forceinline__ TilePlan plan_tiles(const int32_t *offsets, int E, in
   p.m_tiles = __builtin_amdgcn_readfirstlane(sum);
   const long long total = (long long)p.m_tiles * tiles_n;
   p.rounds = (int)(total / G);
-  p.rest = (int)(total - (long long)p.rounds * G);
+  const int rem = (int)(total - (long long)p.rounds * G), half = G / S::BLOCKS;
+  p.whole = S::BLOCKS > 1 && rem > half ? half : 0;
+  p.rest = rem - p.whole;
   p.split = 1;
   p.chunk = nh;
-  if (may_split && p.rest > 0) p.split = choose_split(nh, G / p.rest, static4, p.chunk);
+  if (may_split && p.rest > 0) p.split = choose_split(nh, (p.whole ? G - half : G) / p.rest, static4, p.chunk);
   return p;
 }
-// dense tile number -> (M-tile, N-tile): groups of group_m M-tiles (the last group may be narrower)
-__device__ __forceinline__ void tile_coords(int w, int m_tiles, int tiles_n, int group_m, int &mt, int &nt) {
-  const int per_group = group_m * tiles_n, full = m_tiles / group_m;
-  int grp = w / per_group;
-  if (grp < full) {
-    int in_grp = w - grp * per_group;
-    mt = grp * group_m + in_grp % group_m;
-    nt = in_grp / group_m;
-  } else {
-    int last = m_tiles - full * group_m, in_grp = w - full * per_group;
-    mt = full * group_m + in_grp % last;
-    nt = in_grp / last;
-  }
-}
 
-template <bool TRANS_W> struct S2SStreamOps {
-  // Sources of the loader's current tile: wave-uniform bases plus per-lane 32-bit byte offsets at
-  // contraction offset 0 (the launcher only takes this kernel when every offset fits 32 bits).
-  const char *base_a, *base_b;
-  uint32_t oa[NLD], ob[NLD];
+// Sources of the loader's current tile: range-checked windows, and per-lane 32-bit byte offsets at contraction offset 0.
+template <typename S, bool TRANS_W, bool KTAIL> struct S2SOps {
+  int32x4 win_a, win_b;
+  uint32_t oa[S::NLA], ob[NLD];
+  uint32_t ta[S::NLA], tb[NLD];      // KTAIL: all ones where the lane's chunk of the last half-step lies past K
   uint32_t b_step;                   // bytes the W source moves per half-step
-  int step;                          // half-step the next loads fetch
+  int step, last;                    // half-step the next loads fetch; the contraction's last half-step
   int uwave;
-  __device__ __forceinline__ uint32_t prepare(int I) const {
-    return I < NLD ? oa[I] + (uint32_t)step * (HK * 2) : ob[I - NLD] + (uint32_t)step * b_step;
+  __device__ __forceinline__ void load(int I, uint32_t slot_lds) const {
+    if (I < S::NLA) {
+      uint32_t off = oa[I] + (uint32_t)step * (HK * 2);
+      if (KTAIL) off |= step == last ? ta[I] : 0u;
+      load16_to_lds_checked(win_a, off, slot_lds + (uwave * S::NLA + I) * 1024);
+    } else {
+      const int J = I - S::NLA;
+      uint32_t off = ob[J] + (uint32_t)step * b_step;
+      if (KTAIL && TRANS_W) off |= step == last ? tb[J] : 0u;
+      load16_to_lds_checked(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
+    }
   }
-  __device__ __forceinline__ void issue(int I, uint32_t off, uint32_t lds) const {
-    load16_to_lds(I < NLD ? base_a : base_b, off, lds);
-  }
-  __device__ __forceinline__ void load(int I, uint32_t tile_lds) {
-    issue(I, prepare(I), tile_lds + inst_off(uwave, I % NLD));
-  }
-  __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int lane) {
-    return kc_frag(tile, base, kk, lane);
-  }
-  __device__ __forceinline__ bf16x8 frag_b(const char *tile, int base, int kk, int lane) {
+  __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int lane) const { return kc_frag(tile, base, kk, lane); }
+  __device__ __forceinline__ bf16x8 frag_b(const char *tile, int base, int kk, int lane) const {
     return TRANS_W ? kc_frag(tile, base, kk, lane) : tr_frag(tile, base, kk, lane);
   }
 };
 
 // ACT 1: fused SwiGLU keeping the pre-activation, 2: without, 3: fused SwiGLU derivative and dp (the W2^T input-gradient
 // product of Alg. 3's backward, see store_wave_tile_swiglu_bwd), 4: dp from the saved H in that product's epilogue for any
-// activation (store_wave_tile_dp).  STATIC4: the contraction is a multiple of four
-// half-steps, so every tile starts in LDS stage 0 and the loop is written out four slots at a time with the
-// stage as a compile-time constant: all LDS addresses become a loop-invariant register plus an immediate.
-template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0, bool STATIC4 = false>
-__global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int tiles_n, int group_m, uint32_t magic_a) {
+// activation (store_wave_tile_dp), 5: 4 with the routing-weighted hidden rows written as well.
+// STATIC4 (Big only): the contraction is a multiple of four half-steps, so every tile starts in LDS slot 0 and the loop is
+// written out four half-steps at a time with the slot as a compile-time constant: all LDS addresses become a loop-invariant
+// register plus an immediate.  Without it the contraction may be any multiple of 8 (KTAIL masks the last half-step).
+// WIDE: a scattered output of 4 GB or more.
+template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4, bool WIDE>
+__global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs a, int tiles_n, int group_m, uint32_t magic_a) {
   constexpr bool SWIGLU = ACT == 1 || ACT == 2;
-  constexpr bool SWIGLU_BWD = ACT == 3;
-  constexpr bool DP_EPI = ACT == 4;
+  constexpr bool KTAIL = !STATIC4;
+  constexpr int STORES = EpilogueStores<S::FM, ACT>;
   static_assert(!SWIGLU || (!TRANS_W && !SCATTER_OUT), "the fused activation belongs to the forward, sorted-output product");
-  static_assert(!(SWIGLU_BWD || DP_EPI) || (TRANS_W && !SCATTER_OUT), "the fused derivative belongs to the W^T product with sorted rows in and out");
+  static_assert(ACT < 3 || (TRANS_W && !SCATTER_OUT), "the fused derivative belongs to the W^T product with sorted rows out");
+  static_assert(!STATIC4 || S::SLOTS == 4, "the unrolled loop walks four slots");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_off[MAX_E + 1];
   // Order indices of the rows of up to four open tiles.  With the shortest contraction the kernel takes (three
   // half-steps) the loader has opened tile n+2 and requested the rows of tile n+3 while tile n's epilogue still
   // reads its destination rows, so four entries are live at once.
-  __shared__ int s_idx[4][TB];
+  __shared__ int s_idx[4][S::TM];
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = wave >> 1, wn = wave & 1;
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  const int uwm = uwave >> 1, uwn = uwave & 1;
   const int G = gridDim.x;
-  const int slot_in_round = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);  // XCD-contiguous tiles
-  const int nh = a.K / HK;
-  const int32_t *o = a.a_map.o ? a.a_map.o : a.c_map.o;   // both maps use the same order indices
-  const bf16_t *A = (const bf16_t *)a.A;
+  // Blocks b, b + 8, ... share an XCD and get consecutive tiles.  In the last, partial round of a launch with two blocks per
+  // compute unit (b and b + G / 2) the first G / 2 positions are one block of every compute unit, again XCD by XCD.
+  const int xcd = (int)blockIdx.x & 7, in_xcd = (int)blockIdx.x >> 3, cu_xcd = (G / S::BLOCKS) >> 3;
+  const int full_pos = xcd * (G >> 3) + in_xcd;
+  const int part_pos = (in_xcd / cu_xcd) * (G / S::BLOCKS) + xcd * cu_xcd + in_xcd % cu_xcd;
+  const int nh = (a.K + HK - 1) / HK;
 
-  const unsigned long long probe_c0 = a.clock_probe ? clock64() : 0ull, probe_t0 = a.clock_probe ? wall_clock64() : 0ull;
+  const bool probe = a.clock_probe && blockIdx.x < MAX_STREAM_GRID;
+  const unsigned long long probe_c0 = probe ? clock64() : 0ull, probe_t0 = probe ? wall_clock64() : 0ull;
   for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets[i];
   __syncthreads();
 
-  const TilePlan plan = plan_tiles(s_off, a.E, tiles_n, nh, G, STATIC4, ACT == 0 && a.tail_ws != nullptr, lane);
-  // next tile (or chunk of a tile of the last round) of this block after t
-  auto next_tile = [&](S2STile &t) -> bool {
-    const int seq = t.seq + 1;
-    int w, chunk = 0;
-    bool split = false;
-    if (seq < plan.rounds) {
-      w = seq * G + slot_in_round;
-    } else if (seq == plan.rounds && slot_in_round < plan.rest * plan.split) {
-      w = plan.rounds * G + slot_in_round / plan.split;
-      chunk = slot_in_round % plan.split;
-      split = plan.split > 1;
-    } else {
-      return false;
+  const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, nh, G, STATIC4, ACT == 0 && a.tail_ws != nullptr, lane);
+  // This block's part of the last, partial round: tile number (-1: none), chunk of its contraction, index of the fp32
+  // partial tile it leaves (-1: the tile is whole).
+  int last_tile = -1, last_h0 = 0, last_hn = nh, last_part = -1;
+  if (part_pos < plan.whole) {
+    last_tile = plan.rounds * G + part_pos;
+  } else if (part_pos - plan.whole < plan.rest * plan.split) {
+    const int u = part_pos - plan.whole, chunk = u % plan.split;
+    last_tile = plan.rounds * G + plan.whole + u / plan.split;
+    if (plan.split > 1) {
+      last_h0 = chunk * plan.chunk;
+      last_hn = min(nh, last_h0 + plan.chunk) - last_h0;
+      last_part = u;
     }
+  }
+  const int rounds = plan.rounds, m_tiles = plan.m_tiles;
+  // Arguments needed once per tile are read from the kernel's argument segment again where they are used: kept in scalar
+  // registers they would not fit beside the loader's state, and the loop would fetch spilled registers every half-step.
+  auto args = [&]() {
+    auto p = (const __attribute__((address_space(4))) S2SArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));
+    return p;
+  };
+  struct Tile {
+    int seq;                    // position in this block's tile list (-1 before the first)
+    int e, row0, row_end, n0;
+  };
+  // next tile (or chunk of a tile of the last round) of this block after t
+  auto next_tile = [&](Tile &t) -> bool {
+    const int seq = t.seq + 1;
+    if (seq > rounds || (seq == rounds && last_tile < 0)) return false;
+    const int w = seq < rounds ? seq * G + full_pos : last_tile;
     int mt, nt, e, row0, row_end;
-    tile_coords(w, plan.m_tiles, tiles_n, group_m, mt, nt);
-    locate_tile(s_off, a.E, mt, lane, e, row0, row_end);
+    tile_coords(w, m_tiles, tiles_n, group_m, mt, nt);
+    locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
     t.seq = seq;
-    t.ord += 1;
     t.e = __builtin_amdgcn_readfirstlane(e);
     t.row0 = __builtin_amdgcn_readfirstlane(row0);
     t.row_end = __builtin_amdgcn_readfirstlane(row_end);
     t.n0 = nt * (SWIGLU ? TB / 2 : TB);   // SwiGLU tiles hold 128 gate columns and the 128 up columns pairing with them
-    t.h0 = split ? chunk * plan.chunk : 0;
-    t.hn = split ? min(nh, t.h0 + plan.chunk) - t.h0 : nh;
-    t.part = split ? (w - plan.rounds * G) * plan.split + chunk : -1;
     return true;
   };
-  // order indices of a tile's 256 rows -> s_idx[ord & 3] (rows past the segment repeat its last row)
-  auto fetch_rows = [&](const S2STile &t) {
+  auto half_steps = [&](const Tile &t) { return t.seq < rounds ? nh : last_hn; };
+  auto first_step = [&](const Tile &t) { return t.seq < rounds ? 0 : last_h0; };
+  // order indices of a tile's rows -> s_idx[seq & 3] (rows past the segment repeat its last row); with 128 rows
+  // wavefronts 2 and 3 load the same again, so that every wavefront counts the same loads
+  auto fetch_rows = [&](const Tile &t) {
+    const auto p = args();
+    const int32_t *o = p->a_map.o ? p->a_map.o : p->c_map.o;   // both maps use the same order indices
     if (!o) return;
-    int i = min(t.row0 + wave * 64 + lane, t.row_end - 1);
-    load4_to_lds(o + i, __builtin_amdgcn_readfirstlane(lds_address((const char *)&s_idx[t.ord & 3][0])) + uwave * 256);
+    const int part = wave & (S::TM / 64 - 1);
+    const int i = min(t.row0 + part * 64 + lane, t.row_end - 1);
+    load4_to_lds(o + i, __builtin_amdgcn_readfirstlane(lds_address((const char *)&s_idx[t.seq & 3][0])) + (uwave & (S::TM / 64 - 1)) * 256);
   };
 
-  S2SStreamOps<TRANS_W> ops;
+  S2SOps<S, TRANS_W, KTAIL> ops;
   ops.uwave = uwave;
   ops.b_step = TRANS_W ? (uint32_t)(HK * 2) : (uint32_t)(HK * 2) * (uint32_t)a.ldw;
-  auto setup_pointers = [&](const S2STile &t) {
-    // the tile's (chunk of the) contraction starts at half-step h0
-    ops.base_b = (const char *)((const bf16_t *)a.W + (size_t)t.e * a.w_stride) + (size_t)t.h0 * ops.b_step;
+  ops.last = nh - 1;
+  auto setup_sources = [&](const Tile &t) {
+    const auto p = args();
+    const int K = p->K, N = p->N;
+    const uint32_t row_bytes = (uint32_t)K * 2u, ldw_bytes = (uint32_t)p->ldw * 2u;
+    const bool gathered = p->a_map.o != nullptr;
     // gathered rows are addressed from the start of A, expert-sorted rows from the tile's first row
-    ops.base_a = (const char *)(a.a_map.o ? A : A + (size_t)t.row0 * a.K) + (size_t)t.h0 * (HK * 2);
-    const int *idx = &s_idx[t.ord & 3][0];
-    const uint32_t row_bytes = (uint32_t)a.K * 2u;
+    ops.win_a = buffer_window((const bf16_t *)p->A + (gathered ? 0 : (size_t)t.row0 * K),
+                              (uint32_t)(gathered ? p->Tk / p->a_map.fan : min(S::TM, t.row_end - t.row0)) * row_bytes);
+    ops.win_b = buffer_window((const bf16_t *)p->W + (size_t)t.e * p->w_stride, (uint32_t)(TRANS_W ? N : K) * ldw_bytes);
+    const int *idx = &s_idx[t.seq & 3][0];
 #pragma unroll
-    for (int I = 0; I < NLD; ++I) {
-      int r, c;
-      kc_lane_slot(wave, lane, I, r, c);
-      uint32_t src;
-      if (a.a_map.o) {
-        uint32_t slot = (uint32_t)idx[r];
+    for (int I = 0; I < S::NLA; ++I) {
+      const int r = (wave * S::NLA + I) * 16 + (lane >> 2), c = (lane & 3) ^ kc_swz(r);
+      uint32_t src = (uint32_t)r;
+      if (gathered) {
+        const uint32_t slot = (uint32_t)idx[r];
         src = magic_a ? __umulhi(slot, magic_a) : slot;
-      } else {
-        src = (uint32_t)min(r, t.row_end - 1 - t.row0);
       }
       ops.oa[I] = src * row_bytes + (uint32_t)c * 16u;
+      if (KTAIL) ops.ta[I] = (nh - 1) * HK + c * 8 >= K ? ~0u : 0u;
     }
 #pragma unroll
     for (int I = 0; I < NLD; ++I) {
       int r, c;
       if (TRANS_W) {
         kc_lane_slot(wave, lane, I, r, c);
-        int n = min(t.n0 + r, a.N - 1);
-        ops.ob[I] = (uint32_t)n * (uint32_t)a.ldw * 2u + (uint32_t)c * 16u;
+        ops.ob[I] = (uint32_t)min(t.n0 + r, N - 1) * ldw_bytes + (uint32_t)c * 16u;
+        if (KTAIL) ops.tb[I] = (nh - 1) * HK + c * 8 >= K ? ~0u : 0u;
       } else {
         tr_lane_slot(wave, lane, I, r, c);
         int col = t.n0 + c * 8;
         if (SWIGLU) {
           // tile column v = c * 8: wavefront column half v / 128 takes 64 gate columns then their 64 up columns
           const int v = c * 8, w = v & 127, gate = t.n0 + (v >> 7) * 64 + (w & 63);
-          col = (gate < a.N / 2) ? gate + (w >> 6) * (a.N / 2) : a.N;
+          col = (gate < N / 2) ? gate + (w >> 6) * (N / 2) : N;
         }
-        if (col >= a.N) col = 0;
-        ops.ob[I] = (uint32_t)r * (uint32_t)a.ldw * 2u + (uint32_t)col * 2u;
+        if (col >= N) col = 0;
+        ops.ob[I] = (uint32_t)r * ldw_bytes + (uint32_t)col * 2u;
       }
     }
   };
 
   // ---- open the first two tiles
-  S2STile lt{-1, -1, 0, 0, 0, 0, 0, 0, -1};
+  Tile lt{-1, 0, 0, 0, 0};
   if (!next_tile(lt)) return;
-  S2STile ct = lt;             // the multiplying side starts on the same tile
-  S2STile upcoming = lt;       // tile the loader will open next
+  Tile ct = lt;                // the multiplying side starts on the same tile
+  Tile upcoming = lt;          // tile the loader will open next
   bool have_upcoming = next_tile(upcoming);
   fetch_rows(lt);
   if (have_upcoming) fetch_rows(upcoming);
   wait_loads<0>();
   __syncthreads();
-  setup_pointers(lt);
-  ops.step = 0;
+  setup_sources(lt);
+  ops.step = first_step(lt);
+  int step_end = ops.step + half_steps(lt);
   bool loader_live = true;
-  // loader moves one slot on; at a tile end it opens the upcoming tile and requests the rows of the one after
+  // loader moves one half-step on; at a tile end it opens the upcoming tile and requests the rows of the one after
   auto advance_loader = [&]() {
     if (!loader_live) return;
-    if (++ops.step < lt.hn) return;
+    if (++ops.step < step_end) return;
     if (!have_upcoming) {
       loader_live = false;
-      ops.step = lt.hn - 1;   // slots past the end repeat the last stage's addresses
+      --ops.step;              // stages past the end repeat the last one's addresses
       return;
     }
     lt = upcoming;
-    ops.step = 0;
+    ops.step = first_step(lt);
+    step_end = ops.step + half_steps(lt);
     have_upcoming = next_tile(upcoming);
     if (have_upcoming) fetch_rows(upcoming);
-    setup_pointers(lt);
+    setup_sources(lt);
   };
 
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-  char *patch = smem + RING_BYTES + wave * EPI_WAVE_BYTES;
 #pragma unroll 1
-  for (int st = 0; st < NSTAGE - 1; ++st) {
+  for (int st = 0; st < S::SLOTS - 1; ++st) {
 #pragma unroll
-    for (int I = 0; I < 2 * NLD; ++I) ops.load(I, lds0 + st * STAGE_BYTES + (I / NLD) * TILE_BYTES);
+    for (int I = 0; I < S::NL; ++I) ops.load(I, lds0 + st * S::SLOT_BYTES);
     advance_loader();
   }
-  wait_loads<2 * NLD>();
+#pragma unroll
+  for (int I = 0; I < S::HALF; ++I) ops.load(I, lds0 + (S::SLOTS - 1) * S::SLOT_BYTES);
+  wait_loads<S::IN_FLIGHT + S::HALF>();   // the first stage has landed
   __syncthreads();
-  bf16x8 fa[2][FR], fb[2][FR];
-  f32x16 acc[FR][FR];
+  f32x16 acc[S::FM][FR];
+  Frags<S> f0, f1;
 #pragma unroll
-  for (int i = 0; i < FR; ++i) fa[0][i] = ops.frag_a(smem, wm * (TB / 2) + i * 32, 0, lane);
-#pragma unroll
-  for (int j = 0; j < FR; ++j) fb[0][j] = ops.frag_b(smem + TILE_BYTES, wn * (TB / 2) + j * 32, 0, lane);
+  for (int g = 0; g < 3; ++g) read_frag_group<S>(ops, f0, smem, 0, g, wm, wn, lane);
 
-  int g = 0;   // slot counter: slot g lives in stage g & 3
-  auto open_slot = [&]() {
-    wait_loads<2 * NLD>();   // stage g+1 has landed for every wavefront, stage g-1 is free
-    __syncthreads();
-  };
-  auto one_slot = [&](auto first) {
-    const char *cur = smem + (g & 3) * STAGE_BYTES;
-    const char *nxt = smem + ((g + 1) & 3) * STAGE_BYTES;
-    const uint32_t fill = lds0 + ((g + 3) & 3) * STAGE_BYTES;
-    half_step<decltype(first)::value>(ops, cur, nxt, fill, wm, wn, lane, fa, fb, acc);
+  uint32_t cur = 0;            // LDS slot of the half-step at hand (0 at every tile start with STATIC4)
+  // One half-step in slot `slot`.  `relaxed`: an epilogue's stores were issued after the loads this wait is for.
+  auto half_step = [&](auto first, auto last, uint32_t slot, bool relaxed) {
+    constexpr bool GO_ON = !(decltype(last)::value && S::PATCH_IN_SLOT);
+    phase<0, decltype(first)::value, true, true, S>(ops, f0, f1, smem + slot, lds0 + Ring<S>::before(slot), wm, wn, lane, acc);
     advance_loader();
-    ++g;
+    if (relaxed) middle<S, STORES>(); else middle<S, 0>();
+    phase<1, false, GO_ON, GO_ON, S>(ops, f1, f0, smem + Ring<S>::after(slot), lds0 + slot, wm, wn, lane, acc);
   };
-  auto static_slot = [&](auto first, auto stage) {
-    constexpr int S = decltype(stage)::value;
-    half_step<decltype(first)::value>(ops, smem + S * STAGE_BYTES, smem + ((S + 1) & 3) * STAGE_BYTES,
-                                      lds0 + ((S + 3) & 3) * STAGE_BYTES, wm, wn, lane, fa, fb, acc);
-    advance_loader();
-  };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
-  open_slot();
-  for (;;) {   // one tile per trip; its first slot has been opened already
-    if (STATIC4) {
-      static_slot(std::true_type{}, I0{});
-      open_slot();
-      static_slot(std::false_type{}, I1{});
-      open_slot();
-      static_slot(std::false_type{}, I2{});
-      open_slot();
-      static_slot(std::false_type{}, I3{});
-      for (int h = 4; h < ct.hn; h += 4) {
-        open_slot();
-        static_slot(std::false_type{}, I0{});
-        open_slot();
-        static_slot(std::false_type{}, I1{});
-        open_slot();
-        static_slot(std::false_type{}, I2{});
-        open_slot();
-        static_slot(std::false_type{}, I3{});
+  using No = std::false_type;
+  using Yes = std::true_type;
+  for (;;) {   // one tile per trip
+    // stores of the previous tile's epilogue lie behind the loads that the first SLOTS - 2 waits are for
+    const bool stored = ct.seq > 0;
+    const int hn = half_steps(ct);
+    if constexpr (STATIC4) {
+      half_step(Yes{}, No{}, 0 * S::SLOT_BYTES, stored);
+      half_step(No{}, No{}, 1 * S::SLOT_BYTES, stored);
+      half_step(No{}, No{}, 2 * S::SLOT_BYTES, false);
+      half_step(No{}, No{}, 3 * S::SLOT_BYTES, false);
+      for (int h = 4; h < hn; h += 4) {
+        half_step(No{}, No{}, 0 * S::SLOT_BYTES, false);
+        half_step(No{}, No{}, 1 * S::SLOT_BYTES, false);
+        half_step(No{}, No{}, 2 * S::SLOT_BYTES, false);
+        half_step(No{}, No{}, 3 * S::SLOT_BYTES, false);
       }
     } else {
-      one_slot(std::true_type{});
-      for (int h = 1; h < ct.hn; ++h) {
-        open_slot();
-        one_slot(std::false_type{});
+      half_step(Yes{}, No{}, cur, stored);
+      cur = Ring<S>::after(cur);
+      for (int h = 1; h < hn - 1; ++h) {
+        half_step(No{}, No{}, cur, stored && h < S::SLOTS - 2);
+        cur = Ring<S>::after(cur);
+      }
+      half_step(No{}, Yes{}, cur, false);
+    }
+    char *patch = S::PATCH_IN_SLOT ? smem + cur + S::A_BYTES + uwave * EPI_WAVE_BYTES
+                                   : smem + S::SLOTS * S::SLOT_BYTES + uwave * EPI_WAVE_BYTES;
+    const auto p = args();
+    const int N = p->N;
+    const int rbase = ct.row0 + uwm * (S::TM / 2);            // the wavefront's first row
+    const int left = max(min(S::TM / 2, ct.row_end - rbase), 0);
+    // a 64-column block of an expert-sorted tensor with `ld` columns: `col` its first column, `room` how many exist from there on
+    auto sorted_window = [&](const void *base, int ld, int elem) {
+      return make_window((const char *)base + (size_t)rbase * ld * elem, (uint32_t)left * (uint32_t)ld * (uint32_t)elem);
+    };
+    auto sorted_block = [&](window_t win, int ld, int fm, int col, int room) {
+      BlockDest d{win, {}};
+      const uint32_t mine = (lane & 7) * 8 < room ? (uint32_t)(lane >> 3) * (uint32_t)ld * 2u + (uint32_t)(col + (lane & 7) * 8) * 2u : OFF_WINDOW;
+#pragma unroll
+      for (int it = 0; it < 4; ++it) d.off[it] = mine + (uint32_t)(fm * 32 + it * 8) * (uint32_t)ld * 2u;
+      return d;
+    };
+    if constexpr (SWIGLU) {
+      const int half_n = N / 2, gcol = ct.n0 + uwn * (TB / 4);
+      const window_t win_h = sorted_window(p->H, half_n, 2);
+      const window_t win_p = ACT == 1 ? sorted_window(p->C, N, 2) : win_h;
+      store_wave_tile_swiglu<ACT == 1>(
+          acc, patch, [&](int fm, int half) { return sorted_block(win_p, N, fm, half * half_n + gcol, half_n - gcol); },
+          [&](int fm) { return sorted_block(win_h, half_n, fm, gcol, half_n - gcol); }, lane);
+    } else if constexpr (ACT >= 3) {
+      const int gcol = ct.n0 + uwn * (TB / 2), ldc = ACT == 3 ? 2 * N : N;
+      const window_t win_c = sorted_window(p->C, ldc, 2);
+      BwdRows b;
+      b.saved = sorted_window(ACT == 3 ? p->Hpre_in : p->H_in, ldc, 2);
+      b.saved_bytes = (uint32_t)ldc * 2u;
+      b.scale = sorted_window(p->row_scale, 1, 4);
+      b.dp = sorted_window(p->dp_part, 2 * tiles_n, 4);
+      b.part_bytes = (uint32_t)tiles_n * 8u;
+      b.part_col = (uint32_t)(ct.n0 / TB) * 2u + uwn;
+      b.n = N;
+      b.gcol = gcol;
+      if constexpr (ACT == 3) {
+        store_wave_tile_swiglu_bwd<S::BLOCKS == 1>(
+            acc, patch, b,
+            [&](int fm, int half, int up) { return sorted_block(win_c, ldc, fm, up * N + gcol + half * 64, N - gcol - half * 64); }, lane);
+      } else {
+        const window_t win_w = ACT == 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
+        store_wave_tile_dp<S::BLOCKS == 1, ACT == 5>(
+            acc, patch, b, [&](int fm, int half) { return sorted_block(win_c, ldc, fm, gcol + half * 64, N - gcol - half * 64); },
+            [&](int fm, int half) { return sorted_block(win_w, N, fm, gcol + half * 64, N - gcol - half * 64); },
+            lane);
+      }
+    } else {
+      const int wcol = ct.n0 + uwn * (TB / 2);
+      const int *idx = &s_idx[ct.seq & 3][uwm * (S::TM / 2)];
+      if (ct.seq == rounds && last_part >= 0) {
+        store_wave_partial(acc, p->tail_ws + (size_t)last_part * S::PART + (size_t)(uwm * (S::TM / 2)) * TB + uwn * (TB / 2), lane);
+      } else if constexpr (SCATTER_OUT && WIDE) {
+        bf16_t *C = (bf16_t *)p->C;
+        store_wave_tile(acc, patch, [&](int fm, int half) {
+          WideBlockDest d;
+          const int col = wcol + half * 64 + (lane & 7) * 8;
+#pragma unroll
+          for (int it = 0; it < 4; ++it) {
+            const int r = fm * 32 + it * 8 + (lane >> 3);
+            d.p[it] = r < left && col < N ? C + (size_t)idx[r] * N + col : (bf16_t *)g_trash + lane * 8;
+          }
+          return d;
+        }, lane);
+      } else if constexpr (SCATTER_OUT) {
+        const window_t win = make_window(p->C, (uint32_t)p->Tk * (uint32_t)N * 2u);
+        store_wave_tile(acc, patch, [&](int fm, int half) {
+          BlockDest d{win, {}};
+          const int col = wcol + half * 64 + (lane & 7) * 8;
+#pragma unroll
+          for (int it = 0; it < 4; ++it) {
+            const int r = fm * 32 + it * 8 + (lane >> 3);
+            const uint32_t off = (uint32_t)idx[r] * ((uint32_t)N * 2u) + (uint32_t)col * 2u;
+            d.off[it] = r < left && col < N ? off : ~0u;
+          }
+          return d;
+        }, lane);
+      } else {
+        const window_t win = sorted_window(p->C, N, 2);
+        store_wave_tile(acc, patch, [&](int fm, int half) { return sorted_block(win, N, fm, wcol + half * 64, N - wcol - half * 64); },
+                        lane);
       }
     }
-    // The next tile's first slot is opened before the epilogue: stores share the load counter,
-    // so this wait would otherwise also sit out the acknowledgement of every store below.
-    open_slot();
-    const int *idx = &s_idx[ct.ord & 3][wm * (TB / 2)];
-    const int rbase = ct.row0 + wm * (TB / 2);
-    auto dst_row = [&](int r) -> int {
-      int i = rbase + r;
-      int row = SCATTER_OUT ? idx[r] : i;
-      return (i < ct.row_end) ? row : -1;
-    };
-    if (SWIGLU)
-      store_wave_tile_swiglu<ACT == 1>(acc, patch, dst_row, (bf16_t *)a.C, (bf16_t *)a.H, a.N / 2, ct.n0 + wn * (TB / 4), lane);
-    else if (SWIGLU_BWD)
-      store_wave_tile_swiglu_bwd(acc, patch, dst_row, (const bf16_t *)a.Hpre_in, (bf16_t *)a.C, a.row_scale, a.dp_part, 2 * tiles_n,
-                                 (ct.n0 / TB) * 2 + wn, a.N, ct.n0 + wn * (TB / 2), rbase, ct.row_end, lane);
-    else if (DP_EPI)
-      store_wave_tile_dp(acc, patch, dst_row, (const bf16_t *)a.H_in, (bf16_t *)a.C, (bf16_t *)a.Hw_out, a.row_scale, a.dp_part, 2 * tiles_n,
-                         (ct.n0 / TB) * 2 + wn, a.N, ct.n0 + wn * (TB / 2), rbase, ct.row_end, lane);
-    else if (ct.part >= 0)
-      store_wave_partial(acc, a.tail_ws + (size_t)ct.part * TB * TB + (size_t)(wm * (TB / 2)) * TB + wn * (TB / 2), lane);
-    else
-      store_wave_tile(acc, patch, dst_row, (bf16_t *)a.C, a.N, ct.n0 + wn * (TB / 2), a.N, lane);
+    if constexpr (S::PATCH_IN_SLOT) {   // what the last phase B held back
+#pragma unroll
+      for (int I = 0; I < S::HALF; ++I) ops.load(I, lds0 + cur);
+#pragma unroll
+      for (int g = 0; g < 3; ++g) read_frag_group<S>(ops, f0, smem + Ring<S>::after(cur), 0, g, wm, wn, lane);
+    }
+    if constexpr (!STATIC4) cur = Ring<S>::after(cur);
     if (!next_tile(ct)) break;
   }
   wait_loads<0>();
-  if (a.clock_probe && threadIdx.x == 0) {
-    a.clock_probe[2 * blockIdx.x] = clock64() - probe_c0;
-    a.clock_probe[2 * blockIdx.x + 1] = wall_clock64() - probe_t0;
+  if (probe && threadIdx.x == 0) {
+    unsigned long long *report = args()->clock_probe;
+    report[2 * blockIdx.x] = clock64() - probe_c0;
+    report[2 * blockIdx.x + 1] = wall_clock64() - probe_t0;
   }
 }
 
 // Second pass of a split last round: adds the chunks' fp32 partial tiles in chunk order, rounds once and
 // stores the rows where the unsplit epilogue would have (expert-sorted or scattered).  TAIL_SLICES blocks
-// (32 rows each) per tile of the last round; the plan is recomputed from the same inputs as in the main kernel.
-constexpr int TAIL_SLICES = 8;
-template <bool SCATTER_OUT>
+// per tile of the last round; the plan is recomputed from the same inputs as in the main kernel.  Few tiles are left over
+// (16 of 256 rows at 8192 x 1024 outputs), so a tile is spread over 32 blocks: with 8 the pass took 22 us there, latency of
+// each thread's chain of loads rather than bandwidth.
+constexpr int TAIL_SLICES = 32;
+template <typename S, bool SCATTER_OUT>
 __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int tiles_n, int group_m, int G, int static4) {
   __shared__ int s_off[MAX_E + 1];
   const int lane = threadIdx.x & 63;
   for (int i = threadIdx.x; i <= a.E; i += 256) s_off[i] = a.offsets[i];
   __syncthreads();
-  const TilePlan plan = plan_tiles(s_off, a.E, tiles_n, a.K / HK, G, static4 != 0, true, lane);
+  const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, (a.K + HK - 1) / HK, G, static4 != 0, true, lane);
   if (plan.split <= 1 || (int)blockIdx.x >= plan.rest) return;
   int mt, nt, e, row0, row_end;
-  tile_coords(plan.rounds * G + (int)blockIdx.x, plan.m_tiles, tiles_n, group_m, mt, nt);
-  locate_tile(s_off, a.E, mt, lane, e, row0, row_end);
+  tile_coords(plan.rounds * G + plan.whole + (int)blockIdx.x, plan.m_tiles, tiles_n, group_m, mt, nt);
+  locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
   const int n0 = nt * TB;
-  const float *part = a.tail_ws + (size_t)blockIdx.x * plan.split * TB * TB;
+  const float *part = a.tail_ws + (size_t)blockIdx.x * plan.split * S::PART;
   bf16_t *C = (bf16_t *)a.C;
-  constexpr int PER_SLICE = TB * TB / 4 / TAIL_SLICES;
+  constexpr int PER_SLICE = S::PART / 4 / TAIL_SLICES;
   for (int i = (int)blockIdx.y * PER_SLICE + threadIdx.x; i < ((int)blockIdx.y + 1) * PER_SLICE; i += 256) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int c = 0; c < plan.split; ++c) {
-      const float4 v = reinterpret_cast<const float4 *>(part + (size_t)c * TB * TB)[i];
+      const float4 v = reinterpret_cast<const float4 *>(part + (size_t)c * S::PART)[i];
       acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
     const int row = row0 + (i * 4) / TB, col = n0 + (i * 4) % TB;
@@ -806,13 +554,12 @@ struct DWStreamOps {
   int32x4 win_a, win_b;
   uint32_t oa[NLD], ob[NLD];
   uint32_t sub_a, sub_b;
-  __device__ __forceinline__ uint32_t prepare(int I) const { return I < NLD ? oa[I] + sub_a : ob[I - NLD] + sub_b; }
-  __device__ __forceinline__ void issue(int I, uint32_t off, uint32_t lds) const {
-    load16_to_lds_checked(I < NLD ? win_a : win_b, off, lds);
+  __device__ __forceinline__ void load(int I, uint32_t slot_lds) const {
+    load16_to_lds_checked(I < NLD ? win_a : win_b, I < NLD ? oa[I] + sub_a : ob[I - NLD] + sub_b,
+                          slot_lds + (I / NLD) * TILE_BYTES + inst_off(uwave, I % NLD));
   }
-  __device__ __forceinline__ void load(int I, uint32_t tile_lds) { issue(I, prepare(I), tile_lds + inst_off(uwave, I % NLD)); }
-  __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int l) { return tr_frag(tile, base, kk, l); }
-  __device__ __forceinline__ bf16x8 frag_b(const char *tile, int base, int kk, int l) { return tr_frag(tile, base, kk, l); }
+  __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int l) const { return tr_frag(tile, base, kk, l); }
+  __device__ __forceinline__ bf16x8 frag_b(const char *tile, int base, int kk, int l) const { return tr_frag(tile, base, kk, l); }
 };
 
 // tile number inside an expert -> first row and column of the tile: bands of group_m M-tiles, N-tile by
@@ -840,6 +587,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int ti
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = wave >> 1, wn = wave & 1;
+  const int uwm = __builtin_amdgcn_readfirstlane(wm), uwn = __builtin_amdgcn_readfirstlane(wn);
   const int G = gridDim.x;
   const int slot_in_round = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);  // XCD-contiguous tiles
   const int per_expert = tiles_m * tiles_n;
@@ -921,65 +669,63 @@ __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int ti
   if (!cc.live) return;
   lc = cc;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-  char *patch = smem + RING_BYTES + wave * EPI_WAVE_BYTES;
+  char *patch = smem + Big::SLOTS * Big::SLOT_BYTES + ops.uwave * EPI_WAVE_BYTES;
 #pragma unroll 1
-  for (int st = 0; st < NSTAGE - 1; ++st) {
+  for (int st = 0; st < Big::SLOTS - 1; ++st) {
     resolve(lc);
 #pragma unroll
-    for (int I = 0; I < 2 * NLD; ++I) ops.load(I, lds0 + st * STAGE_BYTES + (I / NLD) * TILE_BYTES);
+    for (int I = 0; I < Big::NL; ++I) ops.load(I, lds0 + st * Big::SLOT_BYTES);
     advance(lc);
   }
-  wait_loads<2 * NLD>();
+  resolve(lc);
+#pragma unroll
+  for (int I = 0; I < Big::HALF; ++I) ops.load(I, lds0 + (Big::SLOTS - 1) * Big::SLOT_BYTES);
+  wait_loads<Big::IN_FLIGHT + Big::HALF>();
   __syncthreads();
-  bf16x8 fa[2][FR], fb[2][FR];
+  Frags<Big> f0, f1;
   f32x16 acc[FR][FR];
 #pragma unroll
-  for (int i = 0; i < FR; ++i) fa[0][i] = ops.frag_a(smem, wm * (TB / 2) + i * 32, 0, lane);
-#pragma unroll
-  for (int j = 0; j < FR; ++j) fb[0][j] = ops.frag_b(smem + TILE_BYTES, wn * (TB / 2) + j * 32, 0, lane);
+  for (int g = 0; g < 3; ++g) read_frag_group<Big>(ops, f0, smem, 0, g, wm, wn, lane);
 
-  auto open_slot = [&]() {
-    wait_loads<2 * NLD>();
-    __syncthreads();
-  };
-  auto static_slot = [&](auto first, auto stage) {
-    constexpr int S = decltype(stage)::value;
-    resolve(lc);
-    half_step<decltype(first)::value>(ops, smem + S * STAGE_BYTES, smem + ((S + 1) & 3) * STAGE_BYTES,
-                                      lds0 + ((S + 3) & 3) * STAGE_BYTES, wm, wn, lane, fa, fb, acc);
+  auto half_step = [&](auto first, auto slot_c, bool relaxed) {
+    constexpr uint32_t SLOT = decltype(slot_c)::value * Big::SLOT_BYTES;
+    phase<0, decltype(first)::value, true, true, Big>(ops, f0, f1, smem + SLOT, lds0 + Ring<Big>::before(SLOT), wm, wn, lane, acc);
     advance(lc);
+    resolve(lc);
+    if (relaxed) middle<Big, EpilogueStores<Big::FM, 0>>(); else middle<Big, 0>();
+    phase<1, false, true, true, Big>(ops, f1, f0, smem + Ring<Big>::after(SLOT), lds0 + SLOT, wm, wn, lane, acc);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
-  open_slot();
-  for (;;) {   // one tile per trip; its first slot has been opened already
-    static_slot(std::true_type{}, I0{});
-    open_slot();
-    static_slot(std::false_type{}, I1{});
-    open_slot();
-    static_slot(std::false_type{}, I2{});
-    open_slot();
-    static_slot(std::false_type{}, I3{});
+  for (;;) {   // one tile per trip
+    const bool stored = cc.seq > 0;
+    half_step(std::true_type{}, I0{}, stored);
+    half_step(std::false_type{}, I1{}, stored);
+    half_step(std::false_type{}, I2{}, false);
+    half_step(std::false_type{}, I3{}, false);
     for (int h = 4; h < cc.ns; h += 4) {
-      open_slot();
-      static_slot(std::false_type{}, I0{});
-      open_slot();
-      static_slot(std::false_type{}, I1{});
-      open_slot();
-      static_slot(std::false_type{}, I2{});
-      open_slot();
-      static_slot(std::false_type{}, I3{});
+      half_step(std::false_type{}, I0{}, false);
+      half_step(std::false_type{}, I1{}, false);
+      half_step(std::false_type{}, I2{}, false);
+      half_step(std::false_type{}, I3{}, false);
     }
-    open_slot();   // the next tile's first slot, before the stores below join the load counter
-    const int mbase = cc.m0 + wm * (TB / 2);
-    auto dst_row = [&](int r) -> int { return (mbase + r < a.M) ? mbase + r : -1; };
-    if (split > 1)
-      store_wave_partial(acc, a.split_ws + (size_t)(cc.seq * G + slot_in_round) * TB * TB + (size_t)(wm * (TB / 2)) * TB + wn * (TB / 2), lane);
-    else
-      store_wave_tile(acc, patch, dst_row, (bf16_t *)a.dW + (size_t)cc.e * a.M * a.N, a.N, cc.n0 + wn * (TB / 2), a.N,
-                      lane);
+    const int mbase = cc.m0 + uwm * (TB / 2), wcol = cc.n0 + uwn * (TB / 2);
+    if (split > 1) {
+      store_wave_partial(acc, a.split_ws + (size_t)(cc.seq * G + slot_in_round) * TB * TB + (size_t)(uwm * (TB / 2)) * TB + uwn * (TB / 2), lane);
+    } else {
+      const int left = max(min(TB / 2, a.M - mbase), 0);
+      const window_t win = make_window((const bf16_t *)a.dW + (size_t)cc.e * a.M * a.N + (size_t)min(mbase, a.M) * a.N, (uint32_t)left * row_b);
+      store_wave_tile(acc, patch, [&](int fm, int half) {
+        BlockDest d{win, {}};
+        const int col = wcol + half * 64 + (lane & 7) * 8;
+        const uint32_t mine = col < a.N ? (uint32_t)(lane >> 3) * row_b + (uint32_t)col * 2u : OFF_WINDOW;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) d.off[it] = mine + (uint32_t)(fm * 32 + it * 8) * row_b;
+        return d;
+      }, lane);
+    }
     open_tile(cc, cc.seq + 1);
     if (!cc.live) break;
   }
@@ -1010,36 +756,68 @@ __global__ void __launch_bounds__(256) dw_split_reduce_kernel(DWArgs a, int tile
   }
 }
 
-template <typename K> int set_lds_limit(K kernel, int bytes) {
-  return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess
-             ? SMOE_OK
-             : SMOE_ERR_HIP;
-}
-
-uint32_t division_magic(int fan) { return fan > 1 ? (uint32_t)((0x100000000ULL + fan - 1) / fan) : 0u; }
-
-template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0, bool STATIC4 = false> int launch_s2s_stream_one(hipStream_t s, const S2SArgs &a);
-template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_stream_cfg(hipStream_t s, const S2SArgs &a) {
-  return a.K % (4 * HK) == 0 ? launch_s2s_stream_one<TRANS_W, SCATTER_OUT, ACT, true>(s, a)
-                             : launch_s2s_stream_one<TRANS_W, SCATTER_OUT, ACT, false>(s, a);
-}
-template <bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4> int launch_s2s_stream_one(hipStream_t s, const S2SArgs &a) {
-  int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
-  long long tiles_m = ceil_div(a.Tk, TB) + a.E;     // upper bound on sum_e ceil(n_e / 256)
-  const int group_m = a.group_m;
+template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4, bool WIDE> int launch_s2s_one(hipStream_t s, const S2SArgs &a) {
+  const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
+  const long long tiles_m = ceil_div(a.Tk, S::TM) + a.E;     // upper bound on sum_e ceil(n_e / TM)
+  const int group_m = a.group_m * (TB / S::TM), grid = a.grid * S::BLOCKS;
   if (tiles_m * tiles_n > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
   S2SArgs args = a;
   int chunk;
-  if (ACT != 0 || choose_split(a.K / HK, 4, STATIC4, chunk) == 1) args.tail_ws = nullptr;   // too short to pay: no second kernel
-  hipLaunchKernelGGL((s2s_stream_kernel<TRANS_W, SCATTER_OUT, ACT, STATIC4>), dim3(a.grid), dim3(NTHREADS), STREAM_LDS_BYTES, s, args, tiles_n,
-                     group_m, division_magic(a.a_map.o ? a.a_map.fan : 1));
+  if (ACT != 0 || choose_split(ceil_div(a.K, HK), 4, STATIC4, chunk) == 1) args.tail_ws = nullptr;   // too short to pay: no second kernel
+  hipLaunchKernelGGL((s2s_stream_kernel<S, TRANS_W, SCATTER_OUT, ACT, STATIC4, WIDE>), dim3(grid), dim3(NTHREADS), S::LDS_BYTES, s, args,
+                     tiles_n, group_m, division_magic(a.a_map.o ? a.a_map.fan : 1));
   SMOE_LAUNCH_CHECK();
   if (args.tail_ws) {   // adds and stores the partial tiles of a split last round (no-op when nothing was split)
-    hipLaunchKernelGGL(s2s_tail_reduce_kernel<SCATTER_OUT>, dim3(a.grid - 1, TAIL_SLICES), dim3(256), 0, s, a, tiles_n, group_m,
-                       a.grid, STATIC4 ? 1 : 0);
+    hipLaunchKernelGGL((s2s_tail_reduce_kernel<S, SCATTER_OUT>), dim3(a.grid, TAIL_SLICES), dim3(256), 0, s, a, tiles_n, group_m, grid, STATIC4 ? 1 : 0);
     SMOE_LAUNCH_CHECK();
   }
   return SMOE_OK;
+}
+// Which shape a launch takes.  The row counts are on the device, so an expert is taken to have r = Tk / E rows: r / TM + 1/2
+// tiles on average, one when it has few rows.  Estimated time in microseconds:
+//   a half-step: 0.85 (Big), 1.03 for two pair tiles sharing a compute unit, 0.5 for one alone; epilogue and tile set-up 6 / 6 / 4;
+//   a split's partial tiles: written and read at 4.5 TB/s, and 5 for the second kernel.
+// Many rounds of long contractions are the Big tile's (they run at the package's power limit, and the pair's operand traffic
+// costs power), so the pair is only asked where it measured faster: contractions up to 2048, or up to 6144 with little more
+// than two pair tiles per compute unit, and not for an estimated gain under 5 % (at 1 % it lost as often as it won).  Measured, Big / Pair in us:
+//   8192 rows, 8 experts: 1024 -> 5632 with SwiGLU 120 / 108, 2816 -> 1024 77 / 75, its W1^T counterpart (5632 -> 1024) 160 / 140;
+//   6216 rows, 64 experts: 2048 -> 1024 with SwiGLU 63 / 52, 512 -> 2048 36 / 28;  8192 rows, 1 expert: 2048 -> 1024 62 / 42;
+//   32768 rows, 8 experts: 1024 -> 5632 372 / 393, 5632 -> 1024 400 / 458;  65536 rows, 64 experts: 2048 -> 1024 286 / 308;
+//   2048 rows, 8 experts: 4096 -> 28672 590 / 810;  4096 rows, 8 experts: 4096 -> 8192 320 / 340.
+template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static4, bool may_split, long long &total) {
+  const float rows = (float)a.Tk / a.E;
+  const int nh = ceil_div(a.K, HK), G = a.grid * S::BLOCKS;
+  const float m_tiles = a.E == 1 ? (float)ceil_div(a.Tk, S::TM) : (rows >= S::TM ? rows / S::TM + 0.5f : 1.0f) * (a.Tk < a.E ? a.Tk : a.E);
+  total = (long long)(m_tiles * tiles_n + 0.5f);
+  const float full = (S::BLOCKS == 1 ? 0.85f : 1.03f) * nh + 6.f, one = S::BLOCKS == 1 ? full : 0.5f * nh + 4.f;
+  const int rem = (int)(total % G), whole = S::BLOCKS > 1 && rem > a.grid ? a.grid : 0, rest = rem - whole;
+  float t = (total / G) * full;
+  int chunk = nh, split = 1;
+  if (may_split && rest > 0) split = choose_split(nh, (whole ? a.grid : G) / rest, static4, chunk);
+  const bool crowded = rest * split > a.grid;     // some compute unit has two blocks in the last round
+  if (whole) t += split > 1 ? one + (full - one) / split : (rest ? full : one);
+  else if (rest) t += (crowded ? full : one) / split;
+  if (split > 1) t += 5.f + rest * split * (S::PART * 8.f / 4.5e6f);
+  return t;
+}
+bool prefer_pair(const S2SArgs &a, int tiles_n, bool may_split) {
+  long long big, pair;
+  const float t_big = launch_estimate<Big>(a, tiles_n, a.K % (4 * HK) == 0, may_split, big);
+  const float t_pair = launch_estimate<Pair>(a, tiles_n, false, may_split, pair);
+  return (a.K <= 2048 || (a.K <= 6144 && pair * 4 <= a.grid * 9LL)) && t_pair < 0.95f * t_big;
+}
+template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStream_t s, const S2SArgs &a) {
+  const bool static4 = a.K % (4 * HK) == 0;
+  if (SCATTER_OUT && (long long)a.Tk * a.N * 2 > 0xfffffff0LL) {   // rows a 32-bit offset does not reach
+    if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, SCATTER_OUT>(s, a);
+    return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, SCATTER_OUT>(s, a);
+  }
+  const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
+  const bool may_split = ACT == 0 && a.tail_ws;
+  if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split)))
+    return launch_s2s_one<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+  if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, false>(s, a);
+  return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
 }
 
 int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
@@ -1053,7 +831,7 @@ int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
     split = (int)(a.grid / tiles < 8 ? a.grid / tiles : 8);
     if (nh - nh / split < SPLIT_MIN_SAVED) split = 1;
   }
-  hipLaunchKernelGGL(dw_stream_kernel, dim3(a.grid), dim3(NTHREADS), STREAM_LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  hipLaunchKernelGGL(dw_stream_kernel, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
   SMOE_LAUNCH_CHECK();
   if (split > 1) {
     hipLaunchKernelGGL(dw_split_reduce_kernel, dim3((unsigned)tiles, TAIL_SLICES), dim3(256), 0, s, a, tiles_m, tiles_n, split);
@@ -1063,20 +841,18 @@ int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
 }
 }  // namespace
 
-// The persistent kernel keeps three half-steps in flight across tile boundaries, so a tile must
-// have at least three; the expert offsets must fit their LDS cache; order indices are divided
-// by the fan-out with a multiply-high that is exact while Tk * fan < 2^32.
+// A tile must have at least three half-steps (the index ring assumes it); the expert offsets must fit their LDS cache; order
+// indices are divided by the fan-out with a multiply-high that is exact while Tk * fan < 2^32.  Every source offset (from
+// the start of a gathered A, of an expert's matrix, of a tile's first row) must fit 32 bits with the last half-step's
+// overhang, and a tile's rows of an output 31 bits.
 bool s2s_stream_supported(const S2SArgs &a) {
-  long long fan = a.a_map.o ? a.a_map.fan : 1;
-  // every per-lane source offset (from the start of a gathered A, from a tile's first row of a
-  // sorted A, from the start of an expert's matrix) must fit the 32-bit offset of the loads
-  long long a_rows = a.a_map.o ? (long long)a.Tk / fan + 1 : TB;
-  long long w_rows = a.trans_w ? a.N : a.K;
-  return a.grid >= 8 && a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && a.group_m >= 1 && a.K % HK == 0 && a.K >= 3 * HK && a.N % 8 == 0 && a.ldw % 8 == 0 && a.Tk > 0 && a.E <= MAX_E &&
-         (long long)a.Tk * fan < 0x100000000LL && a_rows * a.K * 2 < 0x100000000LL &&
-         (w_rows + HK) * a.ldw * 2 < 0x100000000LL;
+  const long long fan = a.a_map.o ? a.a_map.fan : 1;
+  const long long a_rows = a.a_map.o ? (long long)a.Tk / fan + 1 : TB;
+  const long long w_rows = a.trans_w ? a.N : a.K;
+  return a.grid >= 8 && a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && a.group_m >= 1 && a.K % 8 == 0 && a.K > 2 * HK && a.N % 8 == 0 &&
+         a.ldw % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && (long long)a.Tk * fan < 0x100000000LL && (a_rows * a.K + HK) * 2 < 0x100000000LL &&
+         (w_rows + HK) * a.ldw * 2 < 0x100000000LL && (long long)TB * a.N * 4 < 0x80000000LL;
 }
-
 bool s2s_stream_swiglu_bwd_supported(const S2SArgs &a) {
   return s2s_stream_supported(a) && a.trans_w && !a.c_map.o && a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
 }
@@ -1093,41 +869,48 @@ int launch_s2s_stream(hipStream_t s, const S2SArgs &a) {
   const bool scatter_out = a.c_map.o != nullptr;
   if (a.dp_part && a.Hpre_in) {
     if (!s2s_stream_swiglu_bwd_supported(a)) return SMOE_ERR_UNSUPPORTED;
-    return launch_s2s_stream_cfg<true, false, 3>(s, a);
+    return launch_s2s_cfg<true, false, 3>(s, a);
   }
   if (a.dp_part) {
     if (!s2s_stream_dp_supported(a)) return SMOE_ERR_UNSUPPORTED;
-    return launch_s2s_stream_cfg<true, false, 4>(s, a);
+    return a.Hw_out ? launch_s2s_cfg<true, false, 5>(s, a) : launch_s2s_cfg<true, false, 4>(s, a);
   }
   if (a.H) {
     if (!s2s_stream_swiglu_supported(a)) return SMOE_ERR_UNSUPPORTED;
-    return a.C ? launch_s2s_stream_cfg<false, false, 1>(s, a) : launch_s2s_stream_cfg<false, false, 2>(s, a);
+    return a.C ? launch_s2s_cfg<false, false, 1>(s, a) : launch_s2s_cfg<false, false, 2>(s, a);
   }
-  if (a.trans_w) return scatter_out ? launch_s2s_stream_cfg<true, true>(s, a) : launch_s2s_stream_cfg<true, false>(s, a);
-  return scatter_out ? launch_s2s_stream_cfg<false, true>(s, a) : launch_s2s_stream_cfg<false, false>(s, a);
+  if (a.trans_w) return scatter_out ? launch_s2s_cfg<true, true>(s, a) : launch_s2s_cfg<true, false>(s, a);
+  return scatter_out ? launch_s2s_cfg<false, true>(s, a) : launch_s2s_cfg<false, false>(s, a);
 }
 
 bool dw_stream_supported(const DWArgs &a) {
   long long tiles = (long long)a.E * ceil_div(a.M, TB) * ceil_div(a.N, TB);
-  return a.M % 8 == 0 && a.N % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 && a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID;
+  return a.M % 8 == 0 && a.N % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 && a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL;
 }
 
 int launch_dw_stream(hipStream_t s, const DWArgs &a) { return launch_dw_stream_impl(s, a); }
 
 // Raises the dynamic LDS limit of every persistent kernel on the current device (once per context).
-template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s_pair() {
-  int rc = set_lds_limit(s2s_stream_kernel<TRANS_W, SCATTER_OUT, ACT, false>, STREAM_LDS_BYTES);
-  return rc != SMOE_OK ? rc : set_lds_limit(s2s_stream_kernel<TRANS_W, SCATTER_OUT, ACT, true>, STREAM_LDS_BYTES);
+template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s() {
+  int rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, false>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, false>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
+  if (SCATTER_OUT) {
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, SCATTER_OUT>, Big::LDS_BYTES);
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, SCATTER_OUT>, Big::LDS_BYTES);
+  }
+  return rc;
 }
 int init_stream_kernels() {
-  int rc = init_s2s_pair<false, false, 0>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<false, true, 0>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<true, false, 0>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<true, true, 0>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<false, false, 1>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<false, false, 2>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<true, false, 3>();
-  if (rc == SMOE_OK) rc = init_s2s_pair<true, false, 4>();
-  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel, STREAM_LDS_BYTES);
+  int rc = init_s2s<false, false, 0>();
+  if (rc == SMOE_OK) rc = init_s2s<false, true, 0>();
+  if (rc == SMOE_OK) rc = init_s2s<true, false, 0>();
+  if (rc == SMOE_OK) rc = init_s2s<true, true, 0>();
+  if (rc == SMOE_OK) rc = init_s2s<false, false, 1>();
+  if (rc == SMOE_OK) rc = init_s2s<false, false, 2>();
+  if (rc == SMOE_OK) rc = init_s2s<true, false, 3>();
+  if (rc == SMOE_OK) rc = init_s2s<true, false, 4>();
+  if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel, Big::LDS_BYTES);
   return rc;
 }

@@ -151,4 +151,46 @@ __device__ __forceinline__ int xcd_contiguous_id(int pid, int grid) {
   return (pid & 7) * per + (pid >> 3);
 }
 
+constexpr int MAX_E = 256;          // the persistent kernels cache the expert offsets in LDS
+
+// A chunk's fp32 partial tile costs a 256 KB write and a 256 KB read on top of the second kernel's launch,
+// about what 48 half-steps of multiplying take: a split must shorten the last round by more than that.
+constexpr int SPLIT_MIN_SAVED = 64;
+// Largest number of chunks <= max_split (and <= 4) that pays, with the chunk length; 1 = keep whole tiles.
+__host__ __device__ inline int choose_split(int nh, int max_split, bool static4, int &chunk) {
+  for (int s = max_split < 4 ? max_split : 4; s > 1; --s) {
+    int c = (nh + s - 1) / s;
+    if (static4) c = (c + 3) & ~3;
+    if ((s - 1) * c < nh && nh - c >= SPLIT_MIN_SAVED) {
+      chunk = c;
+      return s;
+    }
+  }
+  chunk = nh;
+  return 1;
+}
+// dense tile number -> (M-tile, N-tile): groups of group_m M-tiles (the last group may be narrower)
+__device__ __forceinline__ void tile_coords(int w, int m_tiles, int tiles_n, int group_m, int &mt, int &nt) {
+  const int per_group = group_m * tiles_n, full = m_tiles / group_m;
+  int grp = w / per_group;
+  if (grp < full) {
+    int in_grp = w - grp * per_group;
+    mt = grp * group_m + in_grp % group_m;
+    nt = in_grp / group_m;
+  } else {
+    int last = m_tiles - full * group_m, in_grp = w - full * per_group;
+    mt = full * group_m + in_grp % last;
+    nt = in_grp / last;
+  }
+}
+
+// order index -> source row by a multiply-high (exact while Tk * fan < 2^32); 0: fan-out 1
+inline uint32_t division_magic(int fan) { return fan > 1 ? (uint32_t)((0x100000000ULL + fan - 1) / fan) : 0u; }
+
+template <typename K> int set_lds_limit(K kernel, int bytes) {
+  return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess
+             ? SMOE_OK
+             : SMOE_ERR_HIP;
+}
+
 }  // namespace
