@@ -1,6 +1,7 @@
 // Routing kernels: top-k gate (Sec. 3.1 step 1) and the stable bucket sort of the routed
 // slots by expert (Sec. 3.1 step 2), integer-exact.
 #include "common.h"
+#include <limits.h>
 
 // ---------------------------------------------------------------------------------------
 // top-k gate: one thread per token.  Slot j takes the largest logit that comes after slot
@@ -92,10 +93,79 @@ __global__ void __launch_bounds__(256) topk_gate_wave_kernel(const float *__rest
     }
 }
 
+// The same selection for few picks: k rounds of a wavefront maximum over order-preserving integer keys.  The ranking above
+// compares every pair of a token's logits (64 experts: about 300 vector instructions, whatever k is); a round here is six
+// cross-lane maxima (DPP, no LDS) and a ballot, about 14 instructions.
+__device__ __forceinline__ int wave_max_i32(int v) {
+  // rows of 16 lanes, then row 0 -> 1, 2 -> 3 (row_bcast:15) and the low half -> the high half (row_bcast:31); lane 63 holds the result
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+template <int VPL>
+__global__ void __launch_bounds__(256) topk_gate_rounds_kernel(const float *__restrict__ logits, int T, int E, int k,
+                                                               int32_t *__restrict__ idx, float *__restrict__ gates) {
+  const int lane = threadIdx.x & 63;
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= T) return;
+  int key[VPL];   // signed order of the logits; INT_MIN lies below every logit's key: padding and picks already made
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) {
+    const int e = lane + 64 * i;
+    float v = e < E ? logits[(size_t)t * E + e] : -INFINITY;
+    v = v != v ? -INFINITY : v + 0.0f;            // NaN counts as -inf, -0 ties with +0
+    const int b = __float_as_int(v);
+    key[i] = e < E ? b ^ ((b >> 31) & 0x7fffffff) : INT_MIN;
+  }
+  int my_e = 0, my_key = INT_MIN;                 // lane j: the j-th pick
+  for (int j = 0; j < k; ++j) {
+    int best = key[0];
+#pragma unroll
+    for (int i = 1; i < VPL; ++i) best = max(best, key[i]);
+    const int top = wave_max_i32(best);
+    int e = -1;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {               // ascending ids: ties go to the lower one
+      const unsigned long long at = __ballot(key[i] == top);
+      if (e < 0 && at) e = 64 * i + __ffsll((long long)at) - 1;
+    }
+#pragma unroll
+    for (int i = 0; i < VPL; ++i)
+      if (lane + 64 * i == e) key[i] = INT_MIN;
+    if (lane == j) { my_e = e; my_key = top; }
+  }
+  const float v = __int_as_float(my_key ^ ((my_key >> 31) & 0x7fffffff));
+  const float top = __shfl(v, 0, 64);
+  float w = lane < k ? (top == -INFINITY ? 1.0f : expf(v - top)) : 0.f;
+  float sum = w;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+  if (lane < k) {
+    idx[(size_t)t * k + lane] = my_e;
+    gates[(size_t)t * k + lane] = w / sum;
+  }
+}
+// us at 32768 tokens, rounds / ranking: 64 experts k = 2 7.5 / 29.8, k = 8 12.2 / 29.9, k = 16 18.3 / 30.1 (the lines meet
+// near k = 30); 256 experts k = 8 19.5 / 283.  A lane keeps one pick, so k <= 64.
+static bool topk_by_rounds(int E, int k) { return k <= (E <= 64 ? 24 : 64); }
+
 int launch_topk_gate(hipStream_t s, const float *logits, int T, int E, int k, int32_t *idx, float *gates) {
   if (T == 0) return SMOE_OK;
   dim3 grid(ceil_div(T, 4)), block(256);
-  if (E <= 64)
+  const bool rounds = topk_by_rounds(E, k);
+  if (rounds && E <= 64)
+    hipLaunchKernelGGL(topk_gate_rounds_kernel<1>, grid, block, 0, s, logits, T, E, k, idx, gates);
+  else if (rounds && E <= 128)
+    hipLaunchKernelGGL(topk_gate_rounds_kernel<2>, grid, block, 0, s, logits, T, E, k, idx, gates);
+  else if (rounds && E <= 256)
+    hipLaunchKernelGGL(topk_gate_rounds_kernel<4>, grid, block, 0, s, logits, T, E, k, idx, gates);
+  else if (rounds && E <= 1024)
+    hipLaunchKernelGGL(topk_gate_rounds_kernel<16>, grid, block, 0, s, logits, T, E, k, idx, gates);
+  else if (E <= 64)
     hipLaunchKernelGGL(topk_gate_wave_kernel<1>, grid, block, 0, s, logits, T, E, k, idx, gates);
   else if (E <= 128)
     hipLaunchKernelGGL(topk_gate_wave_kernel<2>, grid, block, 0, s, logits, T, E, k, idx, gates);
@@ -139,36 +209,174 @@ int launch_topk_gate_bwd(hipStream_t s, const int32_t *idx, const float *gates, 
 }
 
 // ---------------------------------------------------------------------------------------
-// Stable bucket sort by expert in three launches:
-//   1. each 64-lane block counts the experts of its contiguous chunk of slots,
-//   2. one block turns the [chunk][expert] counts into start positions (expert-major
-//      exclusive scan) and writes expert_offsets,
-//   3. each block walks its chunk again 64 slots at a time; a lane's rank among the lanes
-//      of the same expert comes from wavefront ballots over the bits of the expert id.
-// Slots keep their order inside an expert because chunks, steps and lanes are all visited
-// in ascending slot order.
+// Stable bucket sort by expert.  Slots are taken in chunks of 1024, one block each, a wavefront per 64 slots; a slot's place
+// is (rows of earlier experts) + (rows of its expert in earlier chunks) + (in earlier wavefronts of its chunk) + (in lower
+// lanes), the last one from ballots over the bits of the expert id.  Slots keep their order inside an expert because
+// chunks, wavefronts and lanes are all counted in ascending slot order.  Everything here is latency: the data are a few
+// hundred KB at most and a launch costs 3 to 5 us of the stream whatever it does, so the counts of the earlier chunks come
+// from where fewest launches are needed (us for both kinds, top-k excluded; before: three launches of one-wavefront blocks):
+//   one launch     (Tk <= ROUTE_ONE_LAUNCH) every block counts all slots itself, those before its chunk apart:
+//                  6216 slots 21.2 -> 6.7, 16382 slots 15.1 -> 6.7, 32768 slots with 64 experts 21.8 -> 9.8;
+//   two launches   (at most ROUTE_TWO_LAUNCH counters) a first kernel leaves one count per (expert, chunk), every block of
+//                  the second adds up what it needs: 65536 slots 21.7 -> 10.5, 262144 slots 31.0 -> 15.6;
+//   three launches (many experts times many chunks) a scan of the counters in between, so that it is done once.
 // ---------------------------------------------------------------------------------------
-static constexpr int ROUTE_CHUNK = 1024;  // slots per block
+static constexpr int ROUTE_CHUNK = 1024;            // slots (and threads) per block
+static constexpr int ROUTE_WAVES = ROUTE_CHUNK / 64;
+static constexpr int ROUTE_ONE_LAUNCH = 32768;
+static constexpr int ROUTE_TWO_LAUNCH = 32768;
+static constexpr int ROUTE_COPIES = 16;             // LDS histograms are kept in 16 copies, picked by lane, for up to
+static constexpr int ROUTE_COPIES_MAX_E = 256;      // this many experts: popular experts otherwise serialise a wavefront's atomics
 
 __device__ __forceinline__ int clamp_expert(int e, int E) { return e < 0 ? 0 : (e >= E ? E - 1 : e); }
+__host__ __device__ inline int route_copies(int E, int threads) { return threads == ROUTE_CHUNK && E <= ROUTE_COPIES_MAX_E ? ROUTE_COPIES : 1; }
 
-__global__ void __launch_bounds__(64) route_count_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
-                                                         int32_t *__restrict__ counts /*[E][nchunk]*/) {
-  extern __shared__ int32_t hist[];
-  for (int e = threadIdx.x; e < E; e += 64) hist[e] = 0;
-  __syncthreads();
-  int base = blockIdx.x * ROUTE_CHUNK;
-  int end = min(base + ROUTE_CHUNK, Tk);
-  for (int s = base + threadIdx.x; s < end; s += 64) atomicAdd(&hist[clamp_expert(expert_idxs[s], E)], 1);
-  __syncthreads();
-  // expert-major so that the scan below reads each expert's chunk counts contiguously
-  for (int e = threadIdx.x; e < E; e += 64) counts[(size_t)e * gridDim.x + blockIdx.x] = hist[e];
+// rows of expert e in one of the LDS histograms
+__device__ __forceinline__ int route_count_of(const int32_t *hist, int e, int copies) {
+  int n = 0;
+  for (int c = 0; c < copies; ++c) n += hist[e * copies + c];
+  return n;
 }
 
-// counts[e][c] -> start position of (chunk c, expert e); offsets[e] = rows before expert e.  One wavefront
+// total(e), before(e): rows of expert e over all slots and in the chunks before this block's (called by one thread per
+// expert).  Leaves in next[e] the place of this chunk's first slot of expert e; block 0 writes the expert offsets.
+template <int THREADS, typename TotalFn, typename BeforeFn>
+__device__ __forceinline__ void route_first_places(int32_t *next, int E, int32_t *__restrict__ offsets, TotalFn total, BeforeFn before) {
+  __shared__ int32_t s_wave[(THREADS / 64)];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int run = 0;
+  for (int e0 = 0; e0 < E; e0 += THREADS) {
+    const int e = e0 + (int)threadIdx.x;
+    const int n = e < E ? total(e) : 0, b = e < E ? before(e) : 0;
+    int incl = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += up;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();          // also: every total and count has been read before `next` overwrites it
+    int base = run;
+    for (int w = 0; w < (THREADS / 64); ++w) {
+      const int v = s_wave[w];
+      if (w < wave) base += v;
+      run += v;
+    }
+    if (e < E) {
+      next[e] = base + incl - n + b;
+      if (blockIdx.x == 0) offsets[e] = base + incl - n;
+    }
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) offsets[E] = run;
+}
+
+// Places this block's chunk; `e` is the (clamped) expert of the thread's slot.
+template <int THREADS>
+__device__ __forceinline__ void route_place_chunk(int32_t *next, int s, bool live, int e, int E, int32_t *__restrict__ sorted_e,
+                                                  int32_t *__restrict__ sorted_s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nbits = 32 - __clz(max(E - 1, 1));
+  unsigned long long peers = __ballot(live);
+  for (int b = 0; b < nbits; ++b) {
+    const unsigned long long set = __ballot(live && ((e >> b) & 1));
+    peers &= ((e >> b) & 1) ? set : ~set;
+  }
+  const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const int rank = __popcll(peers & below), count = __popcll(peers);
+  int pos = 0;
+  for (int w = 0; w < THREADS / 64; ++w) {           // the wavefronts take their places in slot order
+    if (w == wave && live) {
+      pos = next[e] + rank;
+      if (rank == 0) next[e] = pos + count;         // LDS operations of a wavefront execute in order: all its reads come first
+    }
+    __syncthreads();
+  }
+  if (live) {
+    sorted_e[pos] = e;
+    sorted_s[pos] = s;
+  }
+}
+
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) route_one_launch_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
+                                                                       int32_t *__restrict__ offsets, int32_t *__restrict__ sorted_e,
+                                                                       int32_t *__restrict__ sorted_s) {
+  extern __shared__ int32_t hist[];   // [2][E][copies]: slots before this block's chunk, the others
+  const int copies = route_copies(E, THREADS), per = E * copies, copy = threadIdx.x & (copies - 1);
+  const int base = blockIdx.x * THREADS, s = base + (int)threadIdx.x;
+  const bool live = s < Tk;
+  const int e = live ? clamp_expert(expert_idxs[s], E) : 0;
+  for (int i = threadIdx.x; i < 2 * per; i += THREADS) hist[i] = 0;
+  __syncthreads();
+  constexpr int AHEAD = THREADS == ROUTE_CHUNK ? 8 : 1;   // loads in flight per thread
+  for (int s0 = 0; s0 < Tk; s0 += AHEAD * THREADS) {
+    int v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const int q = s0 + u * THREADS + (int)threadIdx.x;
+      v[u] = q < Tk ? expert_idxs[q] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const int q = s0 + u * THREADS + (int)threadIdx.x;
+      if (q < Tk) atomicAdd(&hist[(q < base ? 0 : per) + clamp_expert(v[u], E) * copies + copy], 1);
+    }
+  }
+  __syncthreads();
+  // `next` takes the place of the first histogram: [e] is written after all of row e and of the rows below it was read
+  route_first_places<THREADS>(hist, E, offsets, [&](int x) { return route_count_of(hist, x, copies) + route_count_of(hist + per, x, copies); },
+                     [&](int x) { return route_count_of(hist, x, copies); });
+  route_place_chunk<THREADS>(hist, s, live, e, E, sorted_e, sorted_s);
+}
+
+__global__ void __launch_bounds__(ROUTE_CHUNK) route_count_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
+                                                                  int32_t *__restrict__ counts /*[E][nchunk]*/) {
+  extern __shared__ int32_t hist[];
+  const int copies = route_copies(E, ROUTE_CHUNK);
+  const int s = blockIdx.x * ROUTE_CHUNK + (int)threadIdx.x;
+  const int e = s < Tk ? clamp_expert(expert_idxs[s], E) : 0;
+  for (int i = threadIdx.x; i < E * copies; i += ROUTE_CHUNK) hist[i] = 0;
+  __syncthreads();
+  if (s < Tk) atomicAdd(&hist[e * copies + (threadIdx.x & (copies - 1))], 1);
+  __syncthreads();
+  // expert-major, so that what follows reads each expert's chunk counts contiguously
+  for (int x = threadIdx.x; x < E; x += ROUTE_CHUNK) counts[(size_t)x * gridDim.x + blockIdx.x] = route_count_of(hist, x, copies);
+}
+
+// Second of two launches: the counts of all chunks are added up here, a wavefront per expert.
+__global__ void __launch_bounds__(ROUTE_CHUNK) route_place_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
+                                                                  const int32_t *__restrict__ counts /*[E][nchunk]*/,
+                                                                  int32_t *__restrict__ offsets, int32_t *__restrict__ sorted_e,
+                                                                  int32_t *__restrict__ sorted_s) {
+  extern __shared__ int32_t sums[];   // [2][E]: rows in earlier chunks (then next place), in all chunks
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = gridDim.x;
+  const int s = blockIdx.x * ROUTE_CHUNK + (int)threadIdx.x;
+  const bool live = s < Tk;
+  const int e = live ? clamp_expert(expert_idxs[s], E) : 0;
+  for (int x = wave; x < E; x += ROUTE_WAVES) {
+    int all = 0, before = 0;
+    for (int c = lane; c < nchunk; c += 64) {
+      const int n = counts[(size_t)x * nchunk + c];
+      all += n;
+      before += c < (int)blockIdx.x ? n : 0;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      all += __shfl_xor(all, d, 64);
+      before += __shfl_xor(before, d, 64);
+    }
+    if (lane == 0) { sums[x] = before; sums[E + x] = all; }
+  }
+  __syncthreads();
+  route_first_places<ROUTE_CHUNK>(sums, E, offsets, [&](int x) { return sums[E + x]; }, [&](int x) { return sums[x]; });
+  route_place_chunk<ROUTE_CHUNK>(sums, s, live, e, E, sorted_e, sorted_s);
+}
+
+// Three launches: counts[e][c] -> start position of (chunk c, expert e); offsets[e] = rows before expert e.  One wavefront
 // per expert at a time: lanes take chunks, a wave prefix sum orders them.
 __global__ void __launch_bounds__(1024) route_scan_kernel(int32_t *__restrict__ counts, int nchunk, int E,
-                                                          int32_t *__restrict__ offsets, int Tk) {
+                                                          int32_t *__restrict__ offsets) {
   extern __shared__ int32_t totals[];  // [E] rows per expert, then exclusive prefix
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
   for (int e = wave; e < E; e += nwave) {
@@ -179,17 +387,7 @@ __global__ void __launch_bounds__(1024) route_scan_kernel(int32_t *__restrict__ 
     if (lane == 0) totals[e] = sum;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int e = 0; e < E; ++e) {
-      int n = totals[e];
-      totals[e] = run;
-      offsets[e] = run;
-      run += n;
-    }
-    offsets[E] = run;
-  }
-  __syncthreads();
+  route_first_places<ROUTE_CHUNK>(totals, E, offsets, [&](int x) { return totals[x]; }, [](int) { return 0; });
   for (int e = wave; e < E; e += nwave) {
     int run = totals[e];
     for (int c0 = 0; c0 < nchunk; c0 += 64) {
@@ -206,93 +404,16 @@ __global__ void __launch_bounds__(1024) route_scan_kernel(int32_t *__restrict__ 
     }
   }
 }
-
-__global__ void __launch_bounds__(64) route_place_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
-                                                         const int32_t *__restrict__ starts /*[E][nchunk]*/,
-                                                         int32_t *__restrict__ sorted_e,
-                                                         int32_t *__restrict__ sorted_s) {
-  extern __shared__ int32_t next[];  // next free position per expert for this chunk
-  for (int e = threadIdx.x; e < E; e += 64) next[e] = starts[(size_t)e * gridDim.x + blockIdx.x];
+__global__ void __launch_bounds__(ROUTE_CHUNK) route_place_scanned_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
+                                                                          const int32_t *__restrict__ starts /*[E][nchunk]*/,
+                                                                          int32_t *__restrict__ sorted_e, int32_t *__restrict__ sorted_s) {
+  extern __shared__ int32_t next[];
+  const int s = blockIdx.x * ROUTE_CHUNK + (int)threadIdx.x;
+  const bool live = s < Tk;
+  const int e = live ? clamp_expert(expert_idxs[s], E) : 0;
+  for (int x = threadIdx.x; x < E; x += ROUTE_CHUNK) next[x] = starts[(size_t)x * gridDim.x + blockIdx.x];
   __syncthreads();
-  int nbits = 32 - __clz(max(E - 1, 1));
-  int base = blockIdx.x * ROUTE_CHUNK;
-  int end = min(base + ROUTE_CHUNK, Tk);
-  int lane = threadIdx.x;
-  unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int s0 = base; s0 < end; s0 += 64) {
-    int s = s0 + lane;
-    bool live = s < end;
-    int e = live ? clamp_expert(expert_idxs[s], E) : 0;
-    unsigned long long peers = __ballot(live);
-    for (int b = 0; b < nbits; ++b) {
-      unsigned long long set = __ballot(live && ((e >> b) & 1));
-      peers &= ((e >> b) & 1) ? set : ~set;
-    }
-    int rank = __popcll(peers & lt_mask);
-    int pos = 0;
-    if (live) pos = next[e] + rank;
-    __syncthreads();
-    if (live && rank == 0) next[e] += __popcll(peers);  // lowest lane of each expert updates
-    __syncthreads();
-    if (live) {
-      sorted_e[pos] = e;
-      sorted_s[pos] = s;
-    }
-  }
-}
-
-// All three steps in one wavefront when the slots fit one chunk (decoding batches): histogram, exclusive
-// scan over the experts, stable placement.  Nothing passes through global memory in between.
-__global__ void __launch_bounds__(64) route_single_chunk_kernel(const int32_t *__restrict__ expert_idxs, int Tk, int E,
-                                                                int32_t *__restrict__ offsets,
-                                                                int32_t *__restrict__ sorted_e,
-                                                                int32_t *__restrict__ sorted_s) {
-  extern __shared__ int32_t next[];  // rows per expert, then next free position per expert
-  const int lane = threadIdx.x;
-  for (int e = lane; e < E; e += 64) next[e] = 0;
-  __syncthreads();
-  for (int s = lane; s < Tk; s += 64) atomicAdd(&next[clamp_expert(expert_idxs[s], E)], 1);
-  __syncthreads();
-  int run = 0;
-  for (int c0 = 0; c0 < E; c0 += 64) {
-    const int e = c0 + lane;
-    const int n = e < E ? next[e] : 0;
-    int incl = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      int up = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += up;
-    }
-    if (e < E) {
-      next[e] = run + incl - n;
-      offsets[e] = run + incl - n;
-    }
-    run += __shfl(incl, 63, 64);
-  }
-  if (lane == 0) offsets[E] = run;
-  __syncthreads();
-  const int nbits = 32 - __clz(max(E - 1, 1));
-  const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int s0 = 0; s0 < Tk; s0 += 64) {
-    const int s = s0 + lane;
-    const bool live = s < Tk;
-    const int e = live ? clamp_expert(expert_idxs[s], E) : 0;
-    unsigned long long peers = __ballot(live);
-    for (int b = 0; b < nbits; ++b) {
-      unsigned long long set = __ballot(live && ((e >> b) & 1));
-      peers &= ((e >> b) & 1) ? set : ~set;
-    }
-    const int rank = __popcll(peers & lt_mask);
-    int pos = 0;
-    if (live) pos = next[e] + rank;
-    __syncthreads();
-    if (live && rank == 0) next[e] += __popcll(peers);  // lowest lane of each expert updates
-    __syncthreads();
-    if (live) {
-      sorted_e[pos] = e;
-      sorted_s[pos] = s;
-    }
-  }
+  route_place_chunk<ROUTE_CHUNK>(next, s, live, e, E, sorted_e, sorted_s);
 }
 
 // Scratch of the no-allocation routing entry point: the per-chunk expert counts that smoe_route keeps in
@@ -316,21 +437,32 @@ size_t route_workspace_bytes(int Tk, int E) {
 
 int launch_route(hipStream_t s, const int32_t *expert_idxs, int Tk, int E, int32_t *sorted_e, int32_t *sorted_s,
                  int32_t *offsets, void *ws) {
-  int nchunk = ceil_div(Tk > 0 ? Tk : 1, ROUTE_CHUNK);
+  const int nchunk = ceil_div(Tk > 0 ? Tk : 1, ROUTE_CHUNK);
   int32_t *counts = (int32_t *)ws;
-  size_t shm = (size_t)E * sizeof(int32_t);
-  if (nchunk == 1) {
-    hipLaunchKernelGGL(route_single_chunk_kernel, dim3(1), dim3(64), shm, s, expert_idxs, Tk, E, offsets, sorted_e, sorted_s);
+  const size_t one = (size_t)E * sizeof(int32_t), hist = one * route_copies(E, ROUTE_CHUNK);
+  if (Tk <= ROUTE_ONE_LAUNCH && 2 * hist <= 65536) {
+    // a decoding batch fits one or four wavefronts, which start and meet sooner than sixteen (32 slots: 4.8 us with sixteen, 3.9 with four)
+    if (Tk <= 64)
+      hipLaunchKernelGGL(route_one_launch_kernel<64>, dim3(1), dim3(64), 2 * one, s, expert_idxs, Tk, E, offsets, sorted_e, sorted_s);
+    else if (Tk <= 256)
+      hipLaunchKernelGGL(route_one_launch_kernel<256>, dim3(1), dim3(256), 2 * one, s, expert_idxs, Tk, E, offsets, sorted_e, sorted_s);
+    else
+      hipLaunchKernelGGL(route_one_launch_kernel<ROUTE_CHUNK>, dim3(nchunk), dim3(ROUTE_CHUNK), 2 * hist, s, expert_idxs, Tk, E, offsets, sorted_e,
+                         sorted_s);
     SMOE_LAUNCH_CHECK();
     return SMOE_OK;
   }
-  hipLaunchKernelGGL(route_count_kernel, dim3(nchunk), dim3(64), shm, s, expert_idxs, Tk, E, counts);
+  hipLaunchKernelGGL(route_count_kernel, dim3(nchunk), dim3(ROUTE_CHUNK), hist, s, expert_idxs, Tk, E, counts);
   SMOE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(1024), shm, s, counts, nchunk, E, offsets, Tk);
+  if ((long long)E * nchunk <= ROUTE_TWO_LAUNCH && 2 * one <= 65536) {
+    hipLaunchKernelGGL(route_place_kernel, dim3(nchunk), dim3(ROUTE_CHUNK), 2 * one, s, expert_idxs, Tk, E, counts, offsets, sorted_e, sorted_s);
+    SMOE_LAUNCH_CHECK();
+    return SMOE_OK;
+  }
+  hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(1024), one, s, counts, nchunk, E, offsets);
   SMOE_LAUNCH_CHECK();
   if (Tk > 0) {
-    hipLaunchKernelGGL(route_place_kernel, dim3(nchunk), dim3(64), shm, s, expert_idxs, Tk, E, counts, sorted_e,
-                       sorted_s);
+    hipLaunchKernelGGL(route_place_scanned_kernel, dim3(nchunk), dim3(ROUTE_CHUNK), one, s, expert_idxs, Tk, E, counts, sorted_e, sorted_s);
     SMOE_LAUNCH_CHECK();
   }
   return SMOE_OK;
