@@ -293,6 +293,34 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   if (!aligned16(dY) || !aligned16(X) || (W && !aligned16(W)) || (dX && !aligned16(dX)) || (dW && !aligned16(dW)))
     return SMOE_ERR_UNSUPPORTED;
 
+  if (dtype == SMOE_F32) {
+    // The fp32 kernels read the rows of dY and X through the order indices and apply the routing weights themselves: no
+    // sorted copies, and no launches to make them.
+    if (gates && dgates) {
+      rc = launch_rowdot(s, dtype, dY, Yhat, dgates, Tk, gates_k, d_out);
+      if (rc != SMOE_OK) return rc;
+    }
+    const RowMap x_map{grouped_in ? nullptr : r->sorted_scattered_idxs, k};
+    const RowMap y_map{grouped_out ? nullptr : r->sorted_scattered_idxs, gates ? gates_k : 1};
+    if (dW) {
+      DWArgs a{X, dY, dW, r->expert_offsets, r->E, Tk, d_in, d_out};
+      a.a_map = x_map;
+      a.b_map = y_map;
+      a.gates = gates;
+      rc = launch_dw_plain(s, dtype, a);
+      if (rc != SMOE_OK) return rc;
+    }
+    if (!dX) return rc;
+    const bool need_sum = !grouped_in && k > 1;
+    void *dst = need_sum ? (void *)((char *)ws + off_xbar) : dX;
+    S2SArgs a = make_s2s(dY, W, dst, r, d_in, d_out, true, grouped_out != 0, y_map.fan, grouped_in != 0);
+    a.gates = gates;
+    a.slots = r->sorted_scattered_idxs;
+    rc = launch_s2s_plain(s, dtype, a);
+    if (rc != SMOE_OK || !need_sum) return rc;
+    return launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in);
+  }
+
   // dp = bmm(dY, Yhat); dYbar = group(dY, o, p)  (Alg. 2: "weight and group")
   const void *dYbar = dY;
   if (!grouped_out) {
@@ -355,9 +383,15 @@ static int hidden_forward(smoe_ctx *ctx, hipStream_t s, smoe_dtype dtype, smoe_a
     if (!keep_hpre) fused.C = nullptr;
     return s2s_decode_supported(fused) ? launch_s2s_decode(s, fused) : launch_s2s_stream(s, fused);
   }
+  if (dtype == SMOE_F32) {   // the fp32 kernels apply any activation in the epilogue
+    a1.H = H;
+    a1.act = act;
+    if (!keep_hpre) a1.C = nullptr;
+    return launch_s2s_plain(s, dtype, a1);
+  }
   int rc = run_s2s(ctx, s, dtype, a1);
   if (rc != SMOE_OK) return rc;
-  return launch_act_fwd(s, dtype, act, Hpre, H, r->Tk, d_expert);
+  return launch_act_fwd(s, act, Hpre, H, r->Tk, d_expert);
 }
 
 size_t smoe_plinear_act_fwd_workspace_bytes(smoe_dtype dtype, smoe_act act, int T, int k, int d_model, int d_expert,
@@ -559,7 +593,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, Tk);
     if (rc != SMOE_OK) return rc;
     if (mode == 2) {
-      rc = launch_act_bwd(s, dtype, act, saved_Hpre, dH, dHpre, Tk, d_expert);
+      rc = launch_act_bwd(s, act, saved_Hpre, dH, dHpre, Tk, d_expert);
       if (rc != SMOE_OK) return rc;
     }
     DWArgs w2{L.use_hw ? (const void *)second : saved_H, L.use_hw ? (const void *)dYu : (const void *)second, dW2,
@@ -590,6 +624,29 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
   // ---- second ParallelLinear (grouped in, scattered weighted out)
   rc = launch_rowdot(s, dtype, dY, saved_Yhat, dgates, Tk, k, d_model);                 // dp = bmm(dY, Yhat)
   if (rc != SMOE_OK) return rc;
+  if (dtype == SMOE_F32) {
+    // The fp32 kernels gather and weight rows where they read them and apply the activation's derivative in the epilogue.
+    const RowMap tokens{r->sorted_scattered_idxs, k};
+    DWArgs w2{saved_H, dY, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};
+    w2.b_map = tokens;
+    w2.gates = gates;
+    rc = launch_dw_plain(s, dtype, w2);
+    if (rc != SMOE_OK) return rc;
+    S2SArgs x2 = make_s2s(dY, W2, dHpre, r, d_expert, d_model, true, false, k, true);
+    x2.Hpre_in = saved_Hpre;
+    x2.act = act;
+    x2.gates = gates;
+    x2.slots = r->sorted_scattered_idxs;
+    rc = launch_s2s_plain(s, dtype, x2);
+    if (rc != SMOE_OK) return rc;
+    DWArgs w1{X, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
+    w1.a_map = tokens;
+    rc = launch_dw_plain(s, dtype, w1);
+    if (rc != SMOE_OK) return rc;
+    rc = launch_s2s_plain(s, dtype, make_s2s(dHpre, W1, k == 1 ? dX : Xbar, r, d_model, d_h, true, true, 1, false));
+    if (rc != SMOE_OK || k == 1) return rc;
+    return launch_combine(s, dtype, Xbar, nullptr, dX, T, k, d_model);
+  }
   rc = launch_group(s, dtype, dY, r->sorted_scattered_idxs, k, gates, dYbar, Tk, d_model);  // weight and group
   if (rc != SMOE_OK) return rc;
   DWArgs w2{saved_H, dYbar, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};
@@ -601,7 +658,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
   rc = run_s2s(ctx, s, dtype, x2);
   if (rc != SMOE_OK) return rc;
   // ---- activation
-  rc = launch_act_bwd(s, dtype, act, saved_Hpre, dH, dHpre, Tk, d_expert);
+  rc = launch_act_bwd(s, act, saved_Hpre, dH, dHpre, Tk, d_expert);
   if (rc != SMOE_OK) return rc;
   // ---- first ParallelLinear (scattered in with fan-out k, grouped out): its one `group`
   rc = launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, Xbar, Tk, d_model);

@@ -34,6 +34,15 @@ template <typename T> __device__ __forceinline__ T from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return (bf16_t)v; }  // RNE
 
+// point-wise non-linearities of Alg. 3 (GELU is the exact erf form)
+__device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f)); }
+__device__ __forceinline__ float gelu_grad_f(float x) {
+  float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752440f));
+  float pdf = expf(-0.5f * x * x) * 0.39894228040143267794f;
+  return cdf + x * pdf;
+}
+__device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + expf(-x)); }
+
 // How a GEMM operand's rows are addressed through the routing arrays.
 //   sorted position i -> row i (grouped) or o[i] / fan (scattered source with fan-out)
 //   or o[i] (scattered destination).
@@ -65,9 +74,8 @@ int launch_route(hipStream_t s, const int32_t *expert_idxs, int Tk, int E, int32
                  int32_t *sorted_s, int32_t *offsets, void *ws);
 
 // ---- elementwise.hip
-int launch_act_fwd(hipStream_t s, smoe_dtype dt, smoe_act act, const void *Hpre, void *H, int rows, int d_expert);
-int launch_act_bwd(hipStream_t s, smoe_dtype dt, smoe_act act, const void *Hpre, const void *dH, void *dHpre,
-                   int rows, int d_expert);
+int launch_act_fwd(hipStream_t s, smoe_act act, const void *Hpre, void *H, int rows, int d_expert);
+int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert);
 // Y[t] = sum_j g[t*k+j] * Yhat[t*k+j]; g == nullptr means all ones.
 int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d);
 int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o, int fan, const float *g,
@@ -120,6 +128,11 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   // that let groupXTY take the unweighted sorted dY for dW2 as well).  The activation's derivative stays a row kernel.
   const void *H_in = nullptr;
   void *Hw_out = nullptr;
+  // fp32 kernels (gemm_plain.hip): with H set the activation `act` is applied in the epilogue (C may be NULL), with Hpre_in
+  // set C receives act'(Hpre) times the product; gates (fp32, slot order, through the order indices `slots`) scales its rows.
+  int act = SMOE_ACT_NONE;
+  const float *gates = nullptr;
+  const int32_t *slots = nullptr;
 };
 struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both operands expert-sorted)
   const void *A;      // [Tk, M]
@@ -132,6 +145,10 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both 
   // that leave fp32 partial tiles here, added in chunk order by a second kernel.
   float *split_ws = nullptr;
   int grid = 256;     // blocks of the persistent kernel (smoe_ctx::stream_grid)
+  // fp32 kernels (gemm_plain.hip): rows of A and B read through the order indices instead of from sorted copies, and B's rows
+  // scaled by the routing weights (fp32, slot order; needs b_map).
+  RowMap a_map{nullptr, 1}, b_map{nullptr, 1};
+  const float *gates = nullptr;
 };
 int launch_s2s_plain(hipStream_t s, smoe_dtype dt, const S2SArgs &a);
 int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a);

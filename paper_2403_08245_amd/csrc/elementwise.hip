@@ -17,14 +17,6 @@ template <typename T> __device__ __forceinline__ void store_vec(T *p, const floa
   *reinterpret_cast<Vec16<T> *>(p) = r;
 }
 
-__device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f)); }
-__device__ __forceinline__ float gelu_grad_f(float x) {
-  float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752440f));
-  float pdf = expf(-0.5f * x * x) * 0.39894228040143267794f;
-  return cdf + x * pdf;
-}
-__device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + expf(-x)); }
-
 // ---- activation forward: H = act(Hpre).  Work item = VEC consecutive hidden units of a row.
 template <typename T, int ACT>
 __global__ void __launch_bounds__(256) act_fwd_kernel(const T *__restrict__ Hpre, T *__restrict__ H, size_t rows,
@@ -177,40 +169,32 @@ static inline int grid_for(size_t work_items) {
 }
 template <typename T> static bool vec_ok(int d) { return d % (16 / (int)sizeof(T)) == 0; }
 
-template <typename T>
-static int act_fwd_t(hipStream_t s, smoe_act act, const void *Hpre, void *H, int rows, int d_expert) {
-  if (!vec_ok<T>(d_expert)) return SMOE_ERR_UNSUPPORTED;
-  size_t items = (size_t)rows * (d_expert / (16 / sizeof(T)));
+// bf16 only: the fp32 products apply the activation and its derivative in their epilogues
+int launch_act_fwd(hipStream_t s, smoe_act act, const void *Hpre, void *H, int rows, int d_expert) {
+  if (!vec_ok<bf16_t>(d_expert)) return SMOE_ERR_UNSUPPORTED;
+  const size_t items = (size_t)rows * (d_expert / 8);
   if (!items) return SMOE_OK;
-  dim3 g(grid_for(items)), b(256);
-  const T *in = (const T *)Hpre;
-  T *out = (T *)H;
-  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_fwd_kernel<T, SMOE_ACT_SWIGLU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
-  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_fwd_kernel<T, SMOE_ACT_GELU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
-  else hipLaunchKernelGGL((act_fwd_kernel<T, SMOE_ACT_NONE>), g, b, 0, s, in, out, (size_t)rows, d_expert);
+  const dim3 g(grid_for(items)), b(256);
+  const bf16_t *in = (const bf16_t *)Hpre;
+  bf16_t *out = (bf16_t *)H;
+  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
+  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
+  else hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, in, out, (size_t)rows, d_expert);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
-int launch_act_fwd(hipStream_t s, smoe_dtype dt, smoe_act act, const void *Hpre, void *H, int rows, int d_expert) {
-  return dt == SMOE_BF16 ? act_fwd_t<bf16_t>(s, act, Hpre, H, rows, d_expert) : act_fwd_t<float>(s, act, Hpre, H, rows, d_expert);
-}
-
-template <typename T>
-static int act_bwd_t(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert) {
-  if (!vec_ok<T>(d_expert)) return SMOE_ERR_UNSUPPORTED;
-  size_t items = (size_t)rows * (d_expert / (16 / sizeof(T)));
+int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert) {
+  if (!vec_ok<bf16_t>(d_expert)) return SMOE_ERR_UNSUPPORTED;
+  const size_t items = (size_t)rows * (d_expert / 8);
   if (!items) return SMOE_OK;
-  dim3 g(grid_for(items)), b(256);
-  const T *a = (const T *)Hpre; const T *gr = (const T *)dH; T *out = (T *)dHpre;
-  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_bwd_kernel<T, SMOE_ACT_SWIGLU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
-  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_bwd_kernel<T, SMOE_ACT_GELU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
-  else hipLaunchKernelGGL((act_bwd_kernel<T, SMOE_ACT_NONE>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
+  const dim3 g(grid_for(items)), b(256);
+  const bf16_t *a = (const bf16_t *)Hpre, *gr = (const bf16_t *)dH;
+  bf16_t *out = (bf16_t *)dHpre;
+  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
+  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
+  else hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
-}
-int launch_act_bwd(hipStream_t s, smoe_dtype dt, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert) {
-  return dt == SMOE_BF16 ? act_bwd_t<bf16_t>(s, act, Hpre, dH, dHpre, rows, d_expert)
-                         : act_bwd_t<float>(s, act, Hpre, dH, dHpre, rows, d_expert);
 }
 
 template <typename T>
