@@ -31,20 +31,34 @@ constexpr float NEG_BIG = -1.0e30f; // finite stand-in for -inf: exp2 of it is 0
 // 4 different 64-byte segments).
 __device__ __forceinline__ int a_swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 
-// One wavefront's share (8 / NW instructions, NW wavefronts per block) of loading a [32 x 128]
-// tile whose row r comes from `base + row_index(r) * ld`; rows past `last` repeat row `last`.
-template <int NW = 4>
-__device__ __forceinline__ void load_tile_rows(const bf16_t *base, size_t ld, int row0, int last, uint32_t lds_tile,
-                                               int wave, int uwave, int lane) {
-  constexpr int PER = 8 / NW;
+// One wavefront's share (8 / NW instructions, NW wavefronts per block) of loading [32 x 128] tiles whose rows lie `ld`
+// elements apart.  A tile is a range-checked window over its own rows, so a request is scalar arithmetic and one constant
+// 32-bit lane offset per instruction (a 64-bit multiply-add and a clamp per lane and instruction took a quarter of the
+// vector instructions of a step); rows from `rows` on land zeros, which the causal mask or the row mask removes.
+template <int NW> struct TileLoader {
+  static constexpr int PER = 8 / NW;
+  uint32_t off[PER];
+  int uwave;
+  __device__ __forceinline__ TileLoader(size_t ld, int wave, int lane) : uwave(__builtin_amdgcn_readfirstlane(wave)) {
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    int i = wave * PER + u;
-    int row = 4 * i + (lane >> 4);
-    int chunk = (lane & 15) ^ a_swz(row);
-    int src = min(row0 + row, last);
-    load16_to_lds(base + (size_t)src * ld + chunk * 8, lds_tile + (uwave * PER + u) * 1024);
+    for (int u = 0; u < PER; ++u) {
+      const int row = 4 * (wave * PER + u) + (lane >> 4);
+      off[u] = (uint32_t)row * (uint32_t)ld * 2u + (uint32_t)(((lane & 15) ^ a_swz(row)) * 16);
+    }
   }
+  __device__ __forceinline__ void load(const bf16_t *base, size_t ld, int row0, int rows, uint32_t lds_tile) const {
+    const int left = min(max(rows - row0, 0), AKT);
+    const int32x4 win = buffer_window(base + (size_t)min(row0, rows) * ld, (uint32_t)left * (uint32_t)ld * 2u);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) load16_to_lds_checked(win, off[u], lds_tile + (uwave * PER + u) * 1024);
+  }
+};
+// the larger value of lanes l and l + 32, for both
+__device__ __forceinline__ float max_halves(float x) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const unsigned int b = __builtin_bit_cast(unsigned int, x);
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return fmaxf(__builtin_bit_cast(float, r[0]), __builtin_bit_cast(float, r[1]));
 }
 
 // A operand, tile rows as matrix rows: lane -> row (lane % 32), columns 16*ks + 8*(lane/32) + 0..7
@@ -74,7 +88,7 @@ __device__ __forceinline__ bf16x8 a_cols_frag(const char *tile, int c0, int s, i
 // register plus an immediate, instead of a dozen integer instructions per read.
 struct FragOffsets {
   int rows[8];          // a_rows_frag(tile, ks)
-  int cols[4][2][2];    // a_cols_frag(tile, 32 * f, s), first and second transposing read
+  int cols[4][2];       // a_cols_frag(tile, 32 * f, 0), first and second transposing read; s = 1 lies 16 rows further on (same swizzle)
 };
 __device__ __forceinline__ FragOffsets frag_offsets(int lane) {
   FragOffsets o;
@@ -85,14 +99,11 @@ __device__ __forceinline__ FragOffsets frag_offsets(int lane) {
   }
 #pragma unroll
   for (int f = 0; f < 4; ++f)
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        int col = f * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        int row = 16 * s + 4 * (lane >> 5) + ((lane & 15) >> 2) + 8 * t;
-        o.cols[f][s][t] = row * AROW + (((col >> 3) ^ a_swz(row)) << 4) + ((col & 7) << 1);
-      }
+    for (int t = 0; t < 2; ++t) {
+      int col = f * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      int row = 4 * (lane >> 5) + ((lane & 15) >> 2) + 8 * t;
+      o.cols[f][t] = row * AROW + (((col >> 3) ^ a_swz(row)) << 4) + ((col & 7) << 1);
+    }
   return o;
 }
 __device__ __forceinline__ bf16x8 rows_frag(const char *tile, const FragOffsets &o, int ks) {
@@ -101,7 +112,7 @@ __device__ __forceinline__ bf16x8 rows_frag(const char *tile, const FragOffsets 
 __device__ __forceinline__ bf16x8 cols_frag(const char *tile, const FragOffsets &o, int f, int s) {
   union { bf16x8 v; s16x4 h[2]; } u;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(tile + o.cols[f][s][t]));
+  for (int t = 0; t < 2; ++t) u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(tile + o.cols[f][t] + 16 * s * AROW));
   return u.v;
 }
 
@@ -148,7 +159,6 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
                                                        float *__restrict__ LSE, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[AFS * 2 * ATILE];   // stages of (K tile, V tile)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
   // Blocks are numbered longest key walk first across ALL (sequence, head) pairs: the hardware starts blocks
   // in index order, so the short walks fill in behind the long ones everywhere at once (numbering each pair's
   // tiles separately left the last pairs' long walks to start late: 1.6x the balanced makespan).
@@ -181,12 +191,13 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
     for (int q = 0; q < 16; ++q) acc[f][q] = 0.f;
   float m = NEG_BIG, l = 0.f;
 
-  // Every step requests one tile (four loads per wavefront), also past the last one (rows clamp to the
-  // sequence's last key and the tile is never read), so that one constant wait count orders the ring.
+  // Every step requests one tile (four loads per wavefront), also past the last one (zeros, never read), so that one
+  // constant wait count orders the ring.
+  const TileLoader<4> tiles(d.ldkv, wave, lane);
   auto request = [&](int tile, int stage) {
     const uint32_t dst = lds0 + stage * 2 * ATILE;
-    load_tile_rows(Kb, d.ldkv, tile * AKT, d.T - 1, dst, wave, uwave, lane);
-    load_tile_rows(Vb, d.ldkv, tile * AKT, d.T - 1, dst + ATILE, wave, uwave, lane);
+    tiles.load(Kb, d.ldkv, tile * AKT, d.T, dst);
+    tiles.load(Vb, d.ldkv, tile * AKT, d.T, dst + ATILE);
   };
 #pragma unroll
   for (int t = 0; t < AFS - 1; ++t) request(t, t);
@@ -216,7 +227,7 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
     }
 #pragma unroll
     for (int q = 0; q < 16; ++q) mx = fmaxf(mx, s[q]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = max_halves(mx);
     const float m_new = fmaxf(m, mx);
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * d.scale_log2);
     const float shift = -m_new * d.scale_log2;
@@ -296,13 +307,12 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restric
 //   S^T = K Q^T, P^T = exp2(S^T * c - lse), dP^T = V dO^T, dS^T = P^T (dP^T - delta) / sqrt(d),
 //   dQ^T += K^T dS^T
 // ======================================================================================
-__global__ void __launch_bounds__(256) attn_bwd_dq_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+__global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                           const float *__restrict__ LSE, const float *__restrict__ delta,
                                                           bf16_t *__restrict__ dQ, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[ADS * 2 * ATILE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const int nbh = d.h * d.B, rank = (int)blockIdx.x / nbh, bh = (int)blockIdx.x - rank * nbh;   // as in the forward
   const int qt = (int)gridDim.x / nbh - 1 - rank;
   const int hh = bh % d.h, b = bh / d.h;
@@ -340,10 +350,11 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_kernel(const bf16_t *__restri
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[f][q] = 0.f;
 
+  const TileLoader<4> tiles(d.ldkv, wave, lane);
   auto request = [&](int tile, int stage) {   // as in the forward: one tile per step, also past the end
     const uint32_t dst = lds0 + stage * 2 * ATILE;
-    load_tile_rows(Kb, d.ldkv, tile * AKT, d.T - 1, dst, wave, uwave, lane);
-    load_tile_rows(Vb, d.ldkv, tile * AKT, d.T - 1, dst + ATILE, wave, uwave, lane);
+    tiles.load(Kb, d.ldkv, tile * AKT, d.T, dst);
+    tiles.load(Vb, d.ldkv, tile * AKT, d.T, dst + ATILE);
   };
 #pragma unroll
   for (int t = 0; t < ADS - 1; ++t) request(t, t);
@@ -477,7 +488,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
   const int k0 = kb * 32 * NW;
   const int key = min(k0 + wave * 32 + (lane & 31), d.T - 1);
   const bool key_valid = k0 + wave * 32 + (lane & 31) < d.T;
-  const int wave_key0 = k0 + wave * 32;
+  const int wave_key0 = k0 + uwave * 32;
+  const int wave_row0 = wave_key0 * d.G, first_row = key * d.G;   // first rows that see the wavefront's first key and the lane's key
 
   const size_t krow = ((size_t)b * d.T + key) * d.ldkv + hh * AD;
   // K fragments stay in registers; the V fragments are re-read from LDS at every use (keeping both
@@ -488,8 +500,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) settle(kf[ks]);
   const char *vmine = s_v + wave * ATILE;
-  load_tile_rows<1>(V + (size_t)b * d.T * d.ldkv + hh * AD, d.ldkv, wave_key0, d.T - 1,
-                    __builtin_amdgcn_readfirstlane(lds_address(s_v)) + uwave * ATILE, 0, 0, lane);
+  TileLoader<1>(d.ldkv, 0, lane)
+      .load(V + (size_t)b * d.T * d.ldkv + hh * AD, d.ldkv, wave_key0, d.T, __builtin_amdgcn_readfirstlane(lds_address(s_v)) + uwave * ATILE);
   const bf16_t *Qb = Q + (size_t)b * rows * d.ldq + hh * AD;
   const bf16_t *dOb = dO + (size_t)b * rows * d.ldq + hh * AD;
   const float *Lb = LSE + (size_t)b * rows * d.h + hh;
@@ -517,8 +529,9 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
       load4_to_lds(Db + (size_t)r * d.h, lds_dlt + stage * 256);
     }
   };
-  load_tile_rows<NW>(Qb, d.ldq, t_first * AKT, rows - 1, lds0, wave, uwave, lane);
-  load_tile_rows<NW>(dOb, d.ldq, t_first * AKT, rows - 1, lds0 + ATILE, wave, uwave, lane);
+  const TileLoader<NW> tiles(d.ldq, wave, lane);
+  tiles.load(Qb, d.ldq, t_first * AKT, rows, lds0);
+  tiles.load(dOb, d.ldq, t_first * AKT, rows, lds0 + ATILE);
   load_stats(t_first, 0);
   const FragOffsets fo = frag_offsets(lane);
   // the loop is unrolled by the two LDS stages so that every tile address below is register + constant
@@ -529,13 +542,12 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     const int tile = t_first + j;
     if (j + 1 < n_tiles) {
       uint32_t nxt = lds0 + (1 - STAGE) * 2 * ATILE;
-      load_tile_rows<NW>(Qb, d.ldq, (tile + 1) * AKT, rows - 1, nxt, wave, uwave, lane);
-      load_tile_rows<NW>(dOb, d.ldq, (tile + 1) * AKT, rows - 1, nxt + ATILE, wave, uwave, lane);
+      tiles.load(Qb, d.ldq, (tile + 1) * AKT, rows, nxt);
+      tiles.load(dOb, d.ldq, (tile + 1) * AKT, rows, nxt + ATILE);
       load_stats(tile + 1, (j + 1) & 1);
     }
     const int r0 = tile * AKT;
-    const int tile_last_tok = min(r0 + AKT - 1, rows - 1) / d.G;
-    if (tile_last_tok < wave_key0) return;                    // none of these rows sees any key of this wavefront
+    if (min(r0 + AKT, rows) <= wave_row0) return;             // none of these rows sees any key of this wavefront
     const char *qt = smem + STAGE * 2 * ATILE;
     const char *dot = qt + ATILE;
     f32x16 s, dp;
@@ -548,8 +560,6 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
       for (int ks = 0; ks < 8; ++ks)
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(dot, fo, ks), rows_frag(vmine, fo, ks), dp, 0, 0, 0);
     }
-    // rows of this tile that are earlier than the wavefront's last key, or past the end, need the mask
-    const bool edge = (r0 / d.G < wave_key0 + 31) || (r0 + AKT > rows);
     f32x16 p;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -560,13 +570,20 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int q = 4 * g + c;
-        float pv = __builtin_amdgcn_exp2f(s[q] * d.scale_log2 - lv[c] * 1.4426950408889634f);
-        if (edge) {
-          int r = r0 + rr + c;
-          if (r >= rows || r / d.G < key) pv = 0.f;
-        }
+        const float pv = __builtin_amdgcn_exp2f(fmaf(s[q], d.scale_log2, lv[c] * -1.4426950408889634f));
         p[q] = pv;
         s[q] = pv * (dp[q] - dv[c]) * scale;
+      }
+    }
+    // rows of this tile that are earlier than the wavefront's last key, or past the end, are masked (wave-uniform): the key
+    // neither receives from them nor sees what they hold
+    if (r0 < wave_row0 + 31 * d.G || r0 + AKT > rows) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int r = r0 + acc_row(q, lane);
+        const bool off = r >= rows || r < first_row;
+        p[q] = off ? 0.f : p[q];
+        s[q] = off ? 0.f : s[q];
       }
     }
     bf16x8 pb[2] = {pack8(p, 0), pack8(p, 1)};
