@@ -242,16 +242,24 @@ int smoe_plinear_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   return rc;
 }
 
+// Sorted copies of rows that k slots share are spread from the source rows when that saves more than the launch that inverts
+// the order indices costs (about 3 us): grouping 20500 rows of 3 KB took 21 us and spreading them 15, so from 16 MB on.  With
+// k = 1 no row is read twice and there is nothing to save.
+static bool spreads(int Tk, int k, int d) { return k > 1 && (size_t)Tk * d >= ((size_t)8 << 20); }
+
 // ------------------------------------------------------------------------------ Alg. 2
 // Workspace: [dYbar: Tk x d_out, when dY arrives scattered (weighted or not) -- Alg. 2's group(dY, o, p)]
 //            [Xbar:  Tk x d_in, when X was scattered -- Alg. 2's group(X, o); the same array then
 //                    receives dXbar, the reuse Sec. 3.2.1 points out]
+//            [inverse of the order indices: Tk]
 static void plinear_bwd_layout(smoe_dtype dt, int d_in, int d_out, int Tk, int grouped_in, int grouped_out,
-                               size_t &off_dybar, size_t &off_xbar, size_t &total) {
+                               size_t &off_dybar, size_t &off_xbar, size_t &off_inv, size_t &total) {
   size_t es = dtype_size(dt), off = 0;
   off_dybar = off_xbar = (size_t)-1;
   if (!grouped_out) { off_dybar = off; off += align256((size_t)Tk * d_out * es); }
   if (!grouped_in) { off_xbar = off; off += align256((size_t)Tk * d_in * es); }
+  off_inv = off;
+  off += align256((size_t)Tk * sizeof(int32_t));
   total = off + S2S_TAIL_WS_BYTES;   // fp32 partial tiles of the input-gradient product's split last round
 }
 
@@ -259,8 +267,8 @@ size_t smoe_plinear_bwd_workspace_bytes(smoe_dtype dtype, int x_rows, int d_in, 
                                         int has_gates, int grouped_in, int grouped_out) {
   (void)x_rows; (void)k; (void)has_gates;
   if (!dtype_ok(dtype) || d_in < 1 || d_out < 1 || Tk < 0) return 0;
-  size_t a, b, total;
-  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, a, b, total);
+  size_t a, b, c, total;
+  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, a, b, c, total);
   return total;
 }
 
@@ -277,8 +285,8 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   if (dgates && !Yhat) return SMOE_ERR_INVALID_ARG;
   if (!width_ok(dtype, d_in) || !width_ok(dtype, d_out)) return SMOE_ERR_UNSUPPORTED;
   if (!W && dX) return SMOE_ERR_INVALID_ARG;
-  size_t off_dybar, off_xbar, need;
-  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, off_dybar, off_xbar, need);
+  size_t off_dybar, off_xbar, off_inv, need;
+  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, off_dybar, off_xbar, off_inv, need);
   if (need && (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)) return SMOE_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   int rc = SMOE_OK;
@@ -322,6 +330,12 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   }
 
   // dp = bmm(dY, Yhat); dYbar = group(dY, o, p)  (Alg. 2: "weight and group")
+  int32_t *inv = (int32_t *)((char *)ws + off_inv);
+  const bool spread_y = spreads(Tk, gates ? gates_k : 1, d_out), spread_x = spreads(Tk, k, d_in);
+  if ((!grouped_out && spread_y) || (!grouped_in && dW && spread_x)) {
+    rc = launch_invert(s, r->sorted_scattered_idxs, inv, nullptr, nullptr, Tk);
+    if (rc != SMOE_OK) return rc;
+  }
   const void *dYbar = dY;
   if (!grouped_out) {
     if (gates && dgates) {
@@ -329,7 +343,8 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
       if (rc != SMOE_OK) return rc;
     }
     void *buf = (char *)ws + off_dybar;
-    rc = launch_group(s, dtype, dY, r->sorted_scattered_idxs, gates ? gates_k : 1, gates, buf, Tk, d_out);
+    rc = spread_y ? launch_spread(s, dY, inv, gates_k, gates, buf, Tk, d_out)
+                  : launch_group(s, dtype, dY, r->sorted_scattered_idxs, gates ? gates_k : 1, gates, buf, Tk, d_out);
     if (rc != SMOE_OK) return rc;
     dYbar = buf;
   }
@@ -338,7 +353,8 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   if (dW) {
     const void *Xg = X;
     if (!grouped_in) {
-      rc = launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, xbar, Tk, d_in);
+      rc = spread_x ? launch_spread(s, X, inv, k, nullptr, xbar, Tk, d_in)
+                    : launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, xbar, Tk, d_in);
       if (rc != SMOE_OK) return rc;
       Xg = xbar;
     }
@@ -478,9 +494,9 @@ int smoe_mlp_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
 //   mode 2 (other activations): dp from the saved H; scratch = the weighted sorted copy of dY or, when d_expert < d_model
 //     makes them the smaller tensor, the plain sorted copy plus the routing-weighted hidden rows Hw [Tk,d_expert] that let
 //     groupXTY form dW2 from the plain copy; dH [Tk,d_expert]; dHpre [Tk,d_h].
-//   both: the sorted routing weights [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
+//   both: the sorted routing weights [Tk], the inverse of the order indices [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
 struct MlpBwdEpiLayout {
-  size_t dybar_u, second, dh, dhpre, gsorted, dp_part, total;
+  size_t dybar_u, second, dh, dhpre, gsorted, inv, dp_part, total;
   int part_ld;
   bool use_hw;
 };
@@ -494,6 +510,7 @@ static MlpBwdEpiLayout mlp_bwd_epi_layout(int mode, size_t es, size_t Tk, int d_
   L.dh = off;       off += mode == 2 ? align256(Tk * (size_t)d_expert * es) : 0;
   L.dhpre = off;    off += align256(Tk * (size_t)d_h * es);
   L.gsorted = off;  off += align256(Tk * sizeof(float));
+  L.inv = off;      off += align256(Tk * sizeof(int32_t));
   L.dp_part = off;  off += align256(Tk * (size_t)L.part_ld * sizeof(float));
   L.total = off + S2S_TAIL_WS_BYTES;
   return L;
@@ -574,9 +591,15 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     float *tail_ws = (float *)(base + L.total - S2S_TAIL_WS_BYTES);
     // The W2^T product gathers the rows of dY itself (Alg. 1's scattered input, fan-out k); groupXTY needs sorted rows, so
     // one sorted copy is made for it: the routing-weighted one, or the plain one when the weights go into Hw instead.
-    rc = launch_group(s, dtype, dY, r->sorted_scattered_idxs, k, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second, Tk, d_model);
+    int32_t *inv = (int32_t *)(base + L.inv);
+    const bool spread = k > 1;   // the order indices are walked for the sorted weights anyway
+    auto sorted_copy = [&](const void *rows, const float *weights, void *out) {
+      return spread ? launch_spread(s, rows, inv, k, weights, out, Tk, d_model)
+                    : launch_group(s, dtype, rows, r->sorted_scattered_idxs, k, weights, out, Tk, d_model);
+    };
+    rc = launch_invert(s, r->sorted_scattered_idxs, spread ? inv : nullptr, gates, gsorted, Tk);
     if (rc != SMOE_OK) return rc;
-    rc = launch_sorted_weights(s, r->sorted_scattered_idxs, gates, gsorted, Tk);
+    rc = sorted_copy(dY, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
     if (rc != SMOE_OK) return rc;
     S2SArgs x2 = make_s2s(dY, W2, mode == 1 ? dHpre : dH, r, d_expert, d_model, true, false, k, true);
     if (mode == 1) {
@@ -602,7 +625,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     rc = run_dw(ctx, s, dtype, w2);
     if (rc != SMOE_OK) return rc;
     void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead: its array holds Xbar, then dXbar
-    rc = launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, Xbar, Tk, d_model);
+    rc = sorted_copy(X, nullptr, Xbar);
     if (rc != SMOE_OK) return rc;
     DWArgs w1{Xbar, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
     w1.split_ws = tail_ws;
@@ -682,12 +705,12 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
 // ------------------------------------------------------------------------------ Alg. 4
 namespace {
 struct MomhaSizes {
-  size_t kv, q, lse, yhat, x;   // bytes, each rounded up to 256
+  size_t kv, q, lse, yhat, x, inv;   // bytes, each rounded up to 256
 };
 MomhaSizes momha_sizes(int B, int T, int k, int d_model, int h_expert, int d_head) {
   size_t N = (size_t)B * T, Tk = N * k, d_out = (size_t)h_expert * d_head;
   return MomhaSizes{align256(N * d_out * 2), align256(Tk * d_out * 2), align256(Tk * h_expert * sizeof(float)),
-                    align256(Tk * d_model * 2), align256(N * d_model * 2)};
+                    align256(Tk * d_model * 2), align256(N * d_model * 2), align256(Tk * sizeof(int32_t))};
 }
 int momha_args_ok(smoe_ctx *ctx, smoe_dtype dtype, int B, int T, int d_model, int h_expert, int d_head,
                   const smoe_routing *r, int k) {
@@ -760,9 +783,9 @@ size_t smoe_momha_bwd_workspace_bytes(int B, int T, int k, int d_model, int h_ex
   if (B < 1 || T < 1 || k < 1 || d_model < 1 || h_expert < 1 || d_head < 1) return 0;
   MomhaSizes z = momha_sizes(B, T, k, d_model, h_expert, d_head);
   // dense offsets, dOhat, dQ, dK, dV, three partial dX, delta, and the ParallelLinear backward scratch
-  // (a grouped [Tk, d_model] and a grouped [Tk, d_out] array, used by both projections in turn)
+  // (a grouped [Tk, d_model] and a grouped [Tk, d_out] array and the inverse order indices, used by both projections in turn)
   return 256 + 2 * z.q + 2 * z.kv + 3 * z.x + smoe_attention_bwd_workspace_bytes(B, T, k, h_expert) + z.yhat + z.q +
-         S2S_TAIL_WS_BYTES;
+         z.inv + S2S_TAIL_WS_BYTES;
 }
 
 int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO, const void *X, int B, int T,
@@ -791,8 +814,8 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   void *dXv = p;    p += z.x;
   void *attn_ws = p;  p += smoe_attention_bwd_workspace_bytes(B, T, k, h_expert);
   void *sub = p;
-  const size_t sub_bytes = z.yhat + z.q + S2S_TAIL_WS_BYTES;
-  float *tail_ws = (float *)((char *)sub + z.yhat + z.q);   // where the ParallelLinear backward puts its own, too
+  const size_t sub_bytes = z.yhat + z.q + z.inv + S2S_TAIL_WS_BYTES;
+  float *tail_ws = (float *)((char *)sub + z.yhat + z.q + z.inv);   // where the ParallelLinear backward puts its own, too
   hipStream_t s = (hipStream_t)stream;
   rc = launch_dense_offsets(s, dense_off, N);
   if (rc != SMOE_OK) return rc;
@@ -808,7 +831,7 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   if (rc != SMOE_OK) return rc;
   // dense key / value projections
   DWArgs wk{X, dK, dW_K, dense_off, 1, N, d_model, d_out}, wv{X, dV, dW_V, dense_off, 1, N, d_model, d_out};
-  wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q);
+  wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q + z.inv);
   rc = run_dw(ctx, s, dtype, wk);
   if (rc != SMOE_OK) return rc;
   rc = run_dw(ctx, s, dtype, wv);

@@ -78,13 +78,16 @@ int launch_act_fwd(hipStream_t s, smoe_act act, const void *Hpre, void *H, int r
 int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert);
 // Y[t] = sum_j g[t*k+j] * Yhat[t*k+j]; g == nullptr means all ones.
 int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d);
+// out[i] = g[o[i]] * in[o[i] / fan]; g == nullptr means all ones
 int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o, int fan, const float *g,
                  void *out, int Tk, int d);
-// dg[o[i]] = sum_c part[i, c] (c ascending): finishes the routing-weight gradient left in slabs by the fused
-// SwiGLU backward epilogue.
+// inv[o[i]] = i and g_sorted[i] = g[o[i]] (inv, and g with g_sorted, may be NULL)
+int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk);
+// the copy launch_group makes of bf16 rows, by the inverse of the order indices: Tk / fan source rows, each read once
+int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d);
+// dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even): finishes the routing-weight gradient left in slabs by the fused
+// backward epilogues.
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int Tk);
-// g_sorted[i] = g[o[i]]: the routing weight of every expert-sorted row
-int launch_sorted_weights(hipStream_t s, const int32_t *o, const float *g, float *g_sorted, int Tk);
 // dg[s] = <dY[s / kp], Yhat[s]>
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 

@@ -17,17 +17,52 @@ template <typename T> __device__ __forceinline__ void store_vec(T *p, const floa
   *reinterpret_cast<Vec16<T> *>(p) = r;
 }
 
-// ---- activation forward: H = act(Hpre).  Work item = VEC consecutive hidden units of a row.
+typedef uint32_t raw16 __attribute__((ext_vector_type(4)));
+// read once and dead afterwards: no line is kept (combine of 262144 rows of 8 KB: 459 -> 403 us, 6.0 TB/s)
+template <typename T> __device__ __forceinline__ Vec16<T> load_once(const T *p) {
+  const raw16 r = __builtin_nontemporal_load(reinterpret_cast<const raw16 *>(p));
+  return __builtin_bit_cast(Vec16<T>, r);
+}
+
+// How a block's threads are laid over rows of `per_row` 16-byte chunks, chosen on the host so that no thread divides: rows
+// of up to 64 chunks get the next power of two lanes each, longer ones one to four whole wavefronts that walk the row
+// together.  (With one chunk per thread numbered through the tensor, the 64-bit division of that number cost more than the
+// 16 bytes it located: 65536 sorted rows of 4 KB were grouped at 3.8 TB/s.)
+struct RowLanes {
+  int shift;     // thread >> shift = row inside the block
+  int lanes;     // threads of a row
+  int rows;      // rows side by side in a block
+};
+static RowLanes row_lanes(int per_row) {
+  RowLanes l{0, 1, 256};
+  while (l.lanes < per_row && l.lanes < 64) {
+    ++l.shift;
+    l.lanes *= 2;
+    l.rows /= 2;
+  }
+  if (per_row > 64) {
+    const int waves = per_row > 192 ? 4 : (per_row + 63) / 64;
+    l.lanes = 64 * waves;
+    l.rows = waves == 2 ? 2 : 1;
+    l.shift = waves == 2 ? 7 : 8;
+  }
+  return l;
+}
+
+static int row_blocks(long long rows, int per_block) {
+  const long long b = (rows + per_block - 1) / per_block;
+  return (int)(b < 256 * 64 ? b : 256 * 64);
+}
+
+// ---- activation forward: H = act(Hpre)
 template <typename T, int ACT>
-__global__ void __launch_bounds__(256) act_fwd_kernel(const T *__restrict__ Hpre, T *__restrict__ H, size_t rows,
-                                                      int d_expert) {
+__global__ void __launch_bounds__(256) act_fwd_kernel(const T *__restrict__ Hpre, T *__restrict__ H, int rows,
+                                                      int d_expert, RowLanes l) {
   constexpr int V = 16 / sizeof(T);
   const int d_h = (ACT == SMOE_ACT_SWIGLU) ? 2 * d_expert : d_expert;
-  const size_t per_row = d_expert / V;
-  const size_t total = rows * per_row;
-  for (size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x; w < total; w += (size_t)gridDim.x * blockDim.x) {
-    size_t r = w / per_row;
-    int c = (int)(w % per_row) * V;
+  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
+  for (long long r = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); r < rows; r += (long long)gridDim.x * l.rows)
+  for (int c = lane * V; c < d_expert; c += l.lanes * V) {
     float a[V], out[V];
     load_vec<T>(Hpre + r * d_h + c, a);
     if (ACT == SMOE_ACT_SWIGLU) {
@@ -49,14 +84,12 @@ __global__ void __launch_bounds__(256) act_fwd_kernel(const T *__restrict__ Hpre
 // ---- activation backward: dHpre = act'(Hpre) * dH.
 template <typename T, int ACT>
 __global__ void __launch_bounds__(256) act_bwd_kernel(const T *__restrict__ Hpre, const T *__restrict__ dH,
-                                                      T *__restrict__ dHpre, size_t rows, int d_expert) {
+                                                      T *__restrict__ dHpre, int rows, int d_expert, RowLanes l) {
   constexpr int V = 16 / sizeof(T);
   const int d_h = (ACT == SMOE_ACT_SWIGLU) ? 2 * d_expert : d_expert;
-  const size_t per_row = d_expert / V;
-  const size_t total = rows * per_row;
-  for (size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x; w < total; w += (size_t)gridDim.x * blockDim.x) {
-    size_t r = w / per_row;
-    int c = (int)(w % per_row) * V;
+  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
+  for (long long r = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); r < rows; r += (long long)gridDim.x * l.rows)
+  for (int c = lane * V; c < d_expert; c += l.lanes * V) {
     float a[V], g[V], o1[V];
     load_vec<T>(Hpre + r * d_h + c, a);
     load_vec<T>(dH + r * d_expert + c, g);
@@ -81,61 +114,127 @@ __global__ void __launch_bounds__(256) act_bwd_kernel(const T *__restrict__ Hpre
 }
 
 // ---- weighted sum over a token's k slots: Y[t] = sum_j g[t*k+j] * Yhat[t*k+j]  (g may be null = 1)
-template <typename T>
+// Bound by HBM (the k slot rows are read once).  K > 0: k known, all slot rows of a chunk in flight at once.
+template <typename T, int K>
 __global__ void __launch_bounds__(256) combine_kernel(const T *__restrict__ Yhat, const float *__restrict__ g,
-                                                      T *__restrict__ Y, size_t T_rows, int k, int d) {
+                                                      T *__restrict__ Y, int T_rows, int k_any, int d, RowLanes l) {
   constexpr int V = 16 / sizeof(T);
-  const size_t per_row = d / V;
-  const size_t total = T_rows * per_row;
-  for (size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x; w < total; w += (size_t)gridDim.x * blockDim.x) {
-    size_t t = w / per_row;
-    int c = (int)(w % per_row) * V;
-    float acc[V];
+  const int k = K ? K : k_any;
+  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
+  for (long long t = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); t < T_rows; t += (long long)gridDim.x * l.rows) {
+    const T *in = Yhat + t * k * d;
+    const float *gt = g ? g + t * k : nullptr;
+    for (int c = lane * V; c < d; c += l.lanes * V) {
+      float acc[V];
 #pragma unroll
-    for (int i = 0; i < V; ++i) acc[i] = 0.f;
-    for (int j = 0; j < k; ++j) {
-      float a[V];
-      load_vec<T>(Yhat + (t * k + j) * d + c, a);
-      float gj = g ? g[t * k + j] : 1.0f;
+      for (int i = 0; i < V; ++i) acc[i] = 0.f;
+      if constexpr (K > 0) {
+        Vec16<T> rows[K];
 #pragma unroll
-      for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, a[i], acc[i]);
+        for (int j = 0; j < K; ++j) rows[j] = load_once<T>(in + (size_t)j * d + c);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          const float gj = gt ? gt[j] : 1.0f;
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, to_f32<T>(rows[j].v[i]), acc[i]);
+        }
+      } else {
+        for (int j = 0; j < k; ++j) {
+          float a[V];
+          load_vec<T>(in + (size_t)j * d + c, a);
+          const float gj = gt ? gt[j] : 1.0f;
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, a[i], acc[i]);
+        }
+      }
+      store_vec<T>(Y + t * d + c, acc);
     }
-    store_vec<T>(Y + t * d + c, acc);
   }
 }
 
-// ---- group: out[i] = scale * in[o[i] / fan]
+// ---- group: out[i] = g[o[i]] * in[o[i] / fan]  (g may be null = 1).  GROUP_ROWS rows per thread at a time: their loads are in
+// flight together.
+constexpr int GROUP_ROWS = 4;
 template <typename T>
 __global__ void __launch_bounds__(256) group_kernel(const T *__restrict__ in, const int32_t *__restrict__ o, int fan,
-                                                    const float *__restrict__ g, T *__restrict__ out, size_t Tk,
-                                                    int d) {
+                                                    const float *__restrict__ g, T *__restrict__ out, int Tk, int d, RowLanes l) {
   constexpr int V = 16 / sizeof(T);
-  const size_t per_row = d / V;
-  const size_t total = Tk * per_row;
-  for (size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x; w < total; w += (size_t)gridDim.x * blockDim.x) {
-    size_t i = w / per_row;
-    int c = (int)(w % per_row) * V;
-    int s = o[i];
-    float a[V];
-    load_vec<T>(in + (size_t)(s / fan) * d + c, a);
-    if (g) {
-      float gs = g[s];
+  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1), sub = (int)threadIdx.x >> l.shift;
+  const long long step = (long long)gridDim.x * l.rows * GROUP_ROWS;
+  for (long long i0 = (long long)blockIdx.x * l.rows * GROUP_ROWS + sub; i0 < Tk; i0 += step) {
+    const T *src[GROUP_ROWS];
+    float gs[GROUP_ROWS];
+    int slot[GROUP_ROWS];
 #pragma unroll
-      for (int q = 0; q < V; ++q) a[q] *= gs;
+    for (int u = 0; u < GROUP_ROWS; ++u) slot[u] = o[min(i0 + u * l.rows, (long long)Tk - 1)];
+#pragma unroll
+    for (int u = 0; u < GROUP_ROWS; ++u) {
+      src[u] = in + (size_t)((unsigned)slot[u] / (unsigned)fan) * d;
+      gs[u] = g ? g[slot[u]] : 1.0f;
     }
-    store_vec<T>(out + i * d + c, a);
+    for (int c = lane * V; c < d; c += l.lanes * V) {
+      Vec16<T> a[GROUP_ROWS];
+#pragma unroll
+      for (int u = 0; u < GROUP_ROWS; ++u) a[u] = *reinterpret_cast<const Vec16<T> *>(src[u] + c);
+#pragma unroll
+      for (int u = 0; u < GROUP_ROWS; ++u) {
+        if (i0 + u * l.rows >= Tk) break;
+        if (g)
+#pragma unroll
+          for (int q = 0; q < V; ++q) a[u].v[q] = from_f32<T>(to_f32<T>(a[u].v[q]) * gs[u]);
+        *reinterpret_cast<Vec16<T> *>(out + (size_t)(i0 + u * l.rows) * d + c) = a[u];
+      }
+    }
   }
 }
 
-// ---- dg[o[i]] = sum_c part[i, c], c ascending (fixed order): one thread per sorted row
-__global__ void __launch_bounds__(256) dp_reduce_kernel(const float *__restrict__ part, int ld, const int32_t *__restrict__ o,
-                                                        float *__restrict__ dg, int Tk) {
+// ---- inv[o[i]] = i, the sorted position of every slot; with g_sorted, also g_sorted[i] = g[o[i]]  (either may be null)
+__global__ void __launch_bounds__(256) invert_kernel(const int32_t *__restrict__ o, int32_t *__restrict__ inv, const float *__restrict__ g,
+                                                     float *__restrict__ g_sorted, int Tk) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= Tk) return;
-  const float *p = part + (size_t)i * ld;
+  const int slot = o[i];
+  if (inv) inv[slot] = i;
+  if (g_sorted) g_sorted[i] = g[slot];
+}
+
+// ---- spread: the copy `group` makes, from the side of the source: out[inv[t * fan + j]] = g[t * fan + j] * in[t].  Bound by the
+// write of the Tk rows; `group` read every source row fan times as well, from whichever XCD's L2 its sorted row fell to.
+template <int K>
+__global__ void __launch_bounds__(256) spread_kernel(const bf16_t *__restrict__ in, const int32_t *__restrict__ inv, int fan_any,
+                                                     const float *__restrict__ g, bf16_t *__restrict__ out, int rows, int d, RowLanes l) {
+  const int fan = K ? K : fan_any;
+  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
+  for (long long t = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); t < rows; t += (long long)gridDim.x * l.rows) {
+    const int32_t *pos = inv + t * fan;
+    const float *gt = g ? g + t * fan : nullptr;
+    for (int c = lane * 8; c < d; c += l.lanes * 8) {
+      const Vec16<bf16_t> a = *reinterpret_cast<const Vec16<bf16_t> *>(in + t * d + c);
+#pragma unroll
+      for (int j = 0; j < (K ? K : fan); ++j) {
+        Vec16<bf16_t> v = a;
+        if (gt) {
+          const float gs = gt[j];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v.v[q] = (bf16_t)((float)a.v[q] * gs);
+        }
+        *reinterpret_cast<Vec16<bf16_t> *>(out + (size_t)pos[j] * d + c) = v;
+      }
+    }
+  }
+}
+
+// ---- dg[o[i]] = sum_c part[i, c]: eight lanes per sorted row, each adds the pairs of slabs lane, lane + 8, ... in ascending
+// order, then a fixed tree (a thread per row read its 448 bytes at a stride: 23 us for 32768 rows of 112 slabs)
+__global__ void __launch_bounds__(256) dp_reduce_kernel(const float2 *__restrict__ part, int ld2, const int32_t *__restrict__ o,
+                                                        float *__restrict__ dg, int Tk) {
+  const int i = blockIdx.x * 32 + ((int)threadIdx.x >> 3), lane = (int)threadIdx.x & 7;
+  const float2 *p = part + (size_t)min(i, Tk - 1) * ld2;
   float acc = 0.f;
-  for (int c = 0; c < ld; ++c) acc += p[c];
-  dg[o[i]] = acc;
+  for (int c = lane; c < ld2; c += 8) acc += p[c].x + p[c].y;
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (lane == 0 && i < Tk) dg[o[i]] = acc;
 }
 
 // ---- dg[s] = <dY[s / kp], Yhat[s]> : one wavefront per slot, lanes stride the row.
@@ -172,37 +271,47 @@ template <typename T> static bool vec_ok(int d) { return d % (16 / (int)sizeof(T
 // bf16 only: the fp32 products apply the activation and its derivative in their epilogues
 int launch_act_fwd(hipStream_t s, smoe_act act, const void *Hpre, void *H, int rows, int d_expert) {
   if (!vec_ok<bf16_t>(d_expert)) return SMOE_ERR_UNSUPPORTED;
-  const size_t items = (size_t)rows * (d_expert / 8);
-  if (!items) return SMOE_OK;
-  const dim3 g(grid_for(items)), b(256);
+  if (rows < 1) return SMOE_OK;
+  const RowLanes l = row_lanes(d_expert / 8);
+  const dim3 g(row_blocks(rows, l.rows)), b(l.lanes * l.rows);
   const bf16_t *in = (const bf16_t *)Hpre;
   bf16_t *out = (bf16_t *)H;
-  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
-  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, in, out, (size_t)rows, d_expert);
-  else hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, in, out, (size_t)rows, d_expert);
+  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, in, out, rows, d_expert, l);
+  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, in, out, rows, d_expert, l);
+  else hipLaunchKernelGGL((act_fwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, in, out, rows, d_expert, l);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
 int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert) {
   if (!vec_ok<bf16_t>(d_expert)) return SMOE_ERR_UNSUPPORTED;
-  const size_t items = (size_t)rows * (d_expert / 8);
-  if (!items) return SMOE_OK;
-  const dim3 g(grid_for(items)), b(256);
+  if (rows < 1) return SMOE_OK;
+  const RowLanes l = row_lanes(d_expert / 8);
+  const dim3 g(row_blocks(rows, l.rows)), b(l.lanes * l.rows);
   const bf16_t *a = (const bf16_t *)Hpre, *gr = (const bf16_t *)dH;
   bf16_t *out = (bf16_t *)dHpre;
-  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
-  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
-  else hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, a, gr, out, (size_t)rows, d_expert);
+  if (act == SMOE_ACT_SWIGLU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_SWIGLU>), g, b, 0, s, a, gr, out, rows, d_expert, l);
+  else if (act == SMOE_ACT_GELU) hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_GELU>), g, b, 0, s, a, gr, out, rows, d_expert, l);
+  else hipLaunchKernelGGL((act_bwd_kernel<bf16_t, SMOE_ACT_NONE>), g, b, 0, s, a, gr, out, rows, d_expert, l);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
 
+template <typename T, int K>
+static void combine_k(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, RowLanes l, int blocks) {
+  hipLaunchKernelGGL((combine_kernel<T, K>), dim3(blocks), dim3(l.lanes * l.rows), 0, s, (const T *)Yhat, g, (T *)Y, T_rows, k, d, l);
+}
 template <typename T>
 static int combine_t(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d) {
   if (!vec_ok<T>(d)) return SMOE_ERR_UNSUPPORTED;
-  size_t items = (size_t)T_rows * (d / (16 / sizeof(T)));
-  if (!items) return SMOE_OK;
-  hipLaunchKernelGGL((combine_kernel<T>), dim3(grid_for(items)), dim3(256), 0, s, (const T *)Yhat, g, (T *)Y, (size_t)T_rows, k, d);
+  if (T_rows < 1) return SMOE_OK;
+  const RowLanes l = row_lanes(d / (16 / (int)sizeof(T)));
+  const int blocks = row_blocks(T_rows, l.rows);
+  switch (k) {
+    case 2: combine_k<T, 2>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
+    case 4: combine_k<T, 4>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
+    case 8: combine_k<T, 8>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
+    default: combine_k<T, 0>(s, Yhat, g, Y, T_rows, k, d, l, blocks);
+  }
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
@@ -213,9 +322,10 @@ int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *
 template <typename T>
 static int group_t(hipStream_t s, const void *in, const int32_t *o, int fan, const float *g, void *out, int Tk, int d) {
   if (!vec_ok<T>(d)) return SMOE_ERR_UNSUPPORTED;
-  size_t items = (size_t)Tk * (d / (16 / sizeof(T)));
-  if (!items) return SMOE_OK;
-  hipLaunchKernelGGL((group_kernel<T>), dim3(grid_for(items)), dim3(256), 0, s, (const T *)in, o, fan, g, (T *)out, (size_t)Tk, d);
+  if (Tk < 1) return SMOE_OK;
+  const RowLanes l = row_lanes(d / (16 / (int)sizeof(T)));
+  hipLaunchKernelGGL((group_kernel<T>), dim3(row_blocks(Tk, l.rows * GROUP_ROWS)), dim3(l.lanes * l.rows), 0, s, (const T *)in, o, fan, g,
+                     (T *)out, Tk, d, l);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
@@ -223,21 +333,36 @@ int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o,
   return dt == SMOE_BF16 ? group_t<bf16_t>(s, in, o, fan, g, out, Tk, d) : group_t<float>(s, in, o, fan, g, out, Tk, d);
 }
 
-__global__ void __launch_bounds__(256) sorted_weights_kernel(const int32_t *__restrict__ o, const float *__restrict__ g,
-                                                             float *__restrict__ g_sorted, int Tk) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < Tk) g_sorted[i] = g[o[i]];
+int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk) {
+  if (Tk < 1) return SMOE_OK;
+  hipLaunchKernelGGL(invert_kernel, dim3(ceil_div(Tk, 256)), dim3(256), 0, s, o, inv, g, g_sorted, Tk);
+  SMOE_LAUNCH_CHECK();
+  return SMOE_OK;
 }
-int launch_sorted_weights(hipStream_t s, const int32_t *o, const float *g, float *g_sorted, int Tk) {
-  if (!Tk) return SMOE_OK;
-  hipLaunchKernelGGL(sorted_weights_kernel, dim3(ceil_div(Tk, 256)), dim3(256), 0, s, o, g, g_sorted, Tk);
+template <int K>
+static void spread_k(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int rows, int d, RowLanes l) {
+  hipLaunchKernelGGL(spread_kernel<K>, dim3(row_blocks(rows, l.rows)), dim3(l.lanes * l.rows), 0, s, (const bf16_t *)in, inv, fan, g,
+                     (bf16_t *)out, rows, d, l);
+}
+int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d) {
+  if (!vec_ok<bf16_t>(d)) return SMOE_ERR_UNSUPPORTED;
+  if (Tk < 1) return SMOE_OK;
+  const RowLanes l = row_lanes(d / 8);
+  const int rows = Tk / fan;
+  switch (fan) {
+    case 2: spread_k<2>(s, in, inv, fan, g, out, rows, d, l); break;
+    case 4: spread_k<4>(s, in, inv, fan, g, out, rows, d, l); break;
+    case 8: spread_k<8>(s, in, inv, fan, g, out, rows, d, l); break;
+    default: spread_k<0>(s, in, inv, fan, g, out, rows, d, l);
+  }
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
 
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int Tk) {
   if (!Tk) return SMOE_OK;
-  hipLaunchKernelGGL(dp_reduce_kernel, dim3(ceil_div(Tk, 256)), dim3(256), 0, s, part, ld, o, dg, Tk);
+  if (ld % 2) return SMOE_ERR_UNSUPPORTED;
+  hipLaunchKernelGGL(dp_reduce_kernel, dim3(ceil_div(Tk, 32)), dim3(256), 0, s, (const float2 *)part, ld / 2, o, dg, Tk);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
