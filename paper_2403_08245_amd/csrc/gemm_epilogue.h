@@ -23,9 +23,6 @@ __device__ __forceinline__ window_t make_window(const void *base, uint32_t bytes
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32));
   return __builtin_amdgcn_make_buffer_rsrc((void *)(((unsigned long long)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
-__device__ __forceinline__ bf16x4 window_load4(window_t w, uint32_t off) {
-  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(w, (int)off, 0, 0));
-}
 
 // Moves one accumulator element out of the accumulation register file right where it is
 // used.  Left to itself the register allocator copies all accumulators of a lane into
@@ -53,6 +50,10 @@ __device__ __forceinline__ char *patch_slot(char *patch, int row, int chunk) { r
 __device__ __forceinline__ void patch_put(char *patch, int lane, int f2, int g, bf16x4 v) {
   *reinterpret_cast<bf16x4 *>(patch_slot(patch, lane & 31, f2 * 4 + g) + 8 * (lane >> 5)) = v;
 }
+// and back: a lane's own four columns of a block whose whole rows were written by put_patch_rows
+__device__ __forceinline__ bf16x4 patch_get(char *patch, int lane, int f2, int g) {
+  return *reinterpret_cast<const bf16x4 *>(patch_slot(patch, lane & 31, f2 * 4 + g) + 8 * (lane >> 5));
+}
 struct PatchRows {
   bf16x8 v[4];
 };
@@ -61,6 +62,10 @@ __device__ __forceinline__ PatchRows read_patch_rows(char *patch, int lane) {
 #pragma unroll
   for (int it = 0; it < 4; ++it) r.v[it] = *reinterpret_cast<const bf16x8 *>(patch_slot(patch, it * 8 + (lane >> 3), lane & 7));
   return r;
+}
+__device__ __forceinline__ void put_patch_rows(const PatchRows &r, char *patch, int lane) {
+#pragma unroll
+  for (int it = 0; it < 4; ++it) *reinterpret_cast<bf16x8 *>(patch_slot(patch, it * 8 + (lane >> 3), lane & 7)) = r.v[it];
 }
 
 // Destination of one 32 x 64 block: a window and the lane's byte offset for each of its four 16-byte row chunks.
@@ -89,6 +94,12 @@ template <typename Dest> struct RowStore {
 template <typename Dest> __device__ __forceinline__ void issue_row_store(const RowStore<Dest> &p) {
 #pragma unroll
   for (int it = 0; it < 4; ++it) p.dest.put(it, p.rows.v[it]);
+}
+// Sends a finished block's stores out before the next block starts where registers are short.
+template <typename Dest> __device__ __forceinline__ void flush_row_store(RowStore<Dest> &p) {
+  if (p.have) issue_row_store(p);
+  p.have = false;
+  sched_fence();
 }
 // One block through the pipeline: write_block() fills the patch from the accumulators; the previous block's
 // stores go out behind this block's LDS traffic.
@@ -191,27 +202,38 @@ __device__ __forceinline__ float row_weight(const BwdRows &b, int fm, int lane) 
 
 // Epilogue of the second ParallelLinear's input-gradient product with the SwiGLU derivative and Alg. 2's dp folded in.
 // The accumulators hold dH / p for 128 hidden units of 32 * FM expert-sorted rows (the product ran on the unweighted
-// upstream rows).  Per 32-row fragment row the lane fetches the matching gate and up pre-activations (its own row,
-// its own 4-column groups: 8-byte loads; AHEAD: the next 64 columns requested before the current ones are used), forms
+// upstream rows).  Per 32 x 64 block the wavefront fetches the matching gate and up pre-activations (whole rows, turned to the
+// accumulators' layout through the patch; AHEAD: the next block requested before the current one is used), forms
 // h = silu(gate) * up and the partial dot <acc, h> (summed over the wavefront's 128 columns: one slab of dp), scales
 // the accumulators by the row's routing weight and writes
 //   dgate = dh * up * (sig + silu * (1 - sig)),  dup = dh * silu
 // to the two halves of dHpre through the patch pipeline: dest(fm, half, 0 gate / 1 up).  Columns past the width read
 // whatever lies there and are neither stored nor added to the dot.
 struct GateUp {
-  bf16x4 gt[2][4], up[2][4];
+  PatchRows gt, up;
 };
-__device__ __forceinline__ GateUp load_gate_up(const BwdRows &b, int fm, int half, int lane) {
-  GateUp r;
-  const uint32_t base = (uint32_t)(fm * 32 + (lane & 31)) * b.saved_bytes + (uint32_t)(b.gcol + half * 64 + 4 * (lane >> 5)) * 2u;
+// A 32 x 64 block of a saved tensor as whole 128-byte rows, eight lanes each, `col` bytes into the rows.  (A lane fetching its
+// own row's 8-byte pieces touched 32 lines per instruction, each line again for every piece, and more lines than the L1
+// holds: the epilogue took 27 us a tile, on 54 us of products at a contraction of 2048.)
+__device__ __forceinline__ PatchRows load_saved_rows(const BwdRows &b, int fm, uint32_t col, int lane) {
+  PatchRows r;
+  const uint32_t base = (uint32_t)(fm * 32 + (lane >> 3)) * b.saved_bytes + col + (uint32_t)(lane & 7) * 16u;
+#pragma unroll
+  for (int it = 0; it < 4; ++it)
+    r.v[it] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b.saved, (int)(base + (uint32_t)(it * 8) * b.saved_bytes), 0, 0));
+  return r;
+}
+// ... and turned to the accumulators' layout through the patch
+__device__ __forceinline__ void saved_columns(const PatchRows &r, char *patch, int lane, bf16x4 (&v)[2][4]) {
+  put_patch_rows(r, patch, lane);
 #pragma unroll
   for (int f2 = 0; f2 < 2; ++f2)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      r.gt[f2][g] = window_load4(b.saved, base + (f2 * 32 + 8 * g) * 2);
-      r.up[f2][g] = window_load4(b.saved, base + (uint32_t)b.n * 2u + (f2 * 32 + 8 * g) * 2);
-    }
-  return r;
+    for (int g = 0; g < 4; ++g) v[f2][g] = patch_get(patch, lane, f2, g);
+}
+__device__ __forceinline__ GateUp load_gate_up(const BwdRows &b, int fm, int half, int lane) {
+  const uint32_t col = (uint32_t)(b.gcol + half * 64) * 2u;
+  return GateUp{load_saved_rows(b, fm, col, lane), load_saved_rows(b, fm, col + (uint32_t)b.n * 2u, lane)};
 }
 template <bool AHEAD, int FM, typename DestFn>
 __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
@@ -230,7 +252,13 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
     const float scale = AHEAD ? scale_next : row_weight(b, fm, lane);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      const GateUp cur = AHEAD ? in : load_gate_up(b, fm, half, lane);
+      if (!AHEAD) flush_row_store(pend);
+      const GateUp rows = AHEAD ? in : load_gate_up(b, fm, half, lane);
+      bf16x4 gt[2][4], up[2][4];
+      sched_fence();
+      saved_columns(rows.gt, patch, lane, gt);
+      saved_columns(rows.up, patch, lane, up);
+      sched_fence();
       if (AHEAD && fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
         in = load_gate_up(b, half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, lane);
         if (half == 1) scale_next = row_weight(b, fm + 1, lane);
@@ -247,7 +275,7 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               const float a = acc_read(acc[fm][half * 2 + f2][g * 4 + q]);
-              const float gate = (float)cur.gt[f2][g][q], u = (float)cur.up[f2][g][q];
+              const float gate = (float)gt[f2][g][q], u = (float)up[f2][g][q];
               const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate));
               const float silu = gate * sig;
               part = fmaf(a, silu * u, part);
@@ -272,24 +300,18 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
   issue_row_store(pend);
 }
 
-// The activation-agnostic form: the accumulators hold dH / p; the lane fetches the saved hidden activations H of its
-// row and column groups, adds <acc, H> to the row's slab of dp, and writes dH = p * acc (HW: and Hw = p * H).
+// The activation-agnostic form: the accumulators hold dH / p; the wavefront fetches the saved hidden activations H of the
+// block, adds <acc, H> to the row's slab of dp, and writes dH = p * acc (HW: and Hw = p * H).
 template <bool AHEAD, bool HW, int FM, typename DestFn, typename HwFn>
 __device__ __forceinline__ void store_wave_tile_dp(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
                                                    HwFn dest_hw, int lane) {
   acc_settle();
-  auto load_h = [&](int fm, int half, bf16x4 (&h)[2][4]) {
-    const uint32_t base = (uint32_t)(fm * 32 + (lane & 31)) * b.saved_bytes + (uint32_t)(b.gcol + half * 64 + 4 * (lane >> 5)) * 2u;
-#pragma unroll
-    for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) h[f2][g] = window_load4(b.saved, base + (f2 * 32 + 8 * g) * 2);
-  };
+  auto load_h = [&](int fm, int half) { return load_saved_rows(b, fm, (uint32_t)(b.gcol + half * 64) * 2u, lane); };
   RowStore<BlockDest> pend;
-  bf16x4 nxt[2][4];
+  PatchRows next;
   float scale_next = 0.f;
   if (AHEAD) {
-    load_h(0, 0, nxt);
+    next = load_h(0, 0);
     scale_next = row_weight(b, 0, lane);
   }
 #pragma unroll
@@ -298,18 +320,15 @@ __device__ __forceinline__ void store_wave_tile_dp(const f32x16 (&acc)[FM][FR], 
     const float scale = AHEAD ? scale_next : row_weight(b, fm, lane);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
+      if (!AHEAD) flush_row_store(pend);
+      const PatchRows rows = AHEAD ? next : load_h(fm, half);
       bf16x4 cur[2][4];
-      if (AHEAD) {
-#pragma unroll
-        for (int f2 = 0; f2 < 2; ++f2)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) cur[f2][g] = nxt[f2][g];
-        if (fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
-          load_h(half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, nxt);
-          if (half == 1) scale_next = row_weight(b, fm + 1, lane);
-        }
-      } else {
-        load_h(fm, half, cur);
+      sched_fence();
+      saved_columns(rows, patch, lane, cur);
+      sched_fence();
+      if (AHEAD && fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
+        next = load_h(half == 0 ? fm : fm + 1, half == 0 ? 1 : 0);
+        if (half == 1) scale_next = row_weight(b, fm + 1, lane);
       }
       pipe_block(pend, patch, lane, [&] {
 #pragma unroll
