@@ -2,185 +2,225 @@
 // expert, so the product is a stream of every used expert's weights past a handful of rows and
 // the only thing that matters is keeping HBM busy.
 //
-// One wavefront per block owns a 32-row x 128-column output tile of one expert and walks the whole
-// contraction by itself: no barrier anywhere, a private four-stage LDS ring filled by
-// direct-to-LDS loads (three stages = 30 KB in flight per wavefront, four wavefronts per compute
-// unit), and two matrix instructions per fragment per stage on whatever rows the tile has.  The
-// matrix cores idle most of the time by design; a 256-row tile would spend eight times the matrix
-// and LDS work per weight byte on padding rows, which is what bounds the large-tile kernels here.
+// A block of four wavefronts owns a 32-row output tile of one expert, 128 columns per wavefront across; wavefronts that share
+// columns take the contraction's 32-row steps in turn and add their sums through LDS at the end, in a fixed order.  The weights go
+// from memory straight to registers: a lane loads 8 rows x 8 columns (16 bytes of each row, 256 bytes per row and sixteen
+// lanes) and turns them into the operands of eight 16x16x32 matrix instructions with one byte permutation per register,
+// operand j holding column j of every lane's eight.  No LDS traffic, no barrier and no swizzle in the loop, and DEPTH steps of
+// 8 KB per wavefront in flight.  Weights are read once, so they pass the caches by (64 experts, 2048 -> 2 x 512: 53 -> 47 us;
+// only weights that a repeated call would still find in the last-level cache are a little dearer, 25 experts 24 -> 27 us).
+// Before, one wavefront walked a 128-column tile's whole contraction through an LDS ring: 64 tokens on 64 experts, 2048 ->
+// 2 x 512 -> 2048, 57 + 29 us (4.7 TB/s); now 47 + 25 (5.7 and 5.4).  Four tokens (25 experts): 26 + 14 us; now 26 + 12.
 // Forward products only (W as stored); the gradients of such small batches use the large-tile kernels.
 #include "mfma_common.h"
+#include <type_traits>
 
 namespace {
 
-constexpr int DM = 32;                        // rows of a tile
-constexpr int DN = 128;                       // columns of a tile
-constexpr int DST = 4;                        // LDS stages of a wavefront
-constexpr int DW_BYTES = HK * DN * 2;         // W part of a stage: 32 contraction rows x 256 B
-constexpr int DA_BYTES = DM * HK * 2;         // A part of a stage: 32 rows x 64 B
-constexpr int DSTAGE_BYTES = DW_BYTES + DA_BYTES;
-constexpr int NLW = DW_BYTES / 1024;          // load instructions per stage (1 KB per instruction)
-constexpr int NLA = DA_BYTES / 1024;
-constexpr int NLOADS = NLW + NLA;
-constexpr int DECODE_LDS_BYTES = DST * DSTAGE_BYTES;
-static_assert((DST - 1) * NLOADS < 64, "the load counter has six bits");
+constexpr int DM = 32;                        // rows of a tile: two 16-row fragments
+constexpr int DN = 128;                       // columns of a wavefront
+constexpr int DEPTH = 2;                      // steps in flight per wavefront (three: the same times)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ int dw_swz(int krow) { return (krow & 3) << 2; }
-// fragment of the W part (32 x 128, columns contiguous): lane holds column cbase + lane%32 and the
-// contraction rows kk*16 + 8*(lane/32) + 0..7, gathered by two transposing reads
-__device__ __forceinline__ bf16x8 dw_frag(const char *tile, int cbase, int kk, int lane) {
-  int col = cbase + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  int row0 = kk * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2);
-  union { bf16x8 v; s16x4 h[2]; } u;
+struct WStep {
+  u32x4 row[8];      // eight contraction rows of the lane's eight columns
+};
+// operand j of the matrix instructions: column j of the lane, its eight contraction rows
+template <int J> __device__ __forceinline__ bf16x8 w_frag(const WStep &w) {
+  union { bf16x8 v; uint32_t d[4]; } u;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    int row = row0 + 4 * t;
-    int off = row * (DN * 2) + (((col >> 3) ^ dw_swz(row)) << 4) + ((col & 7) << 1);
-    u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(tile + off));
-  }
+  for (int t = 0; t < 4; ++t) u.d[t] = __builtin_amdgcn_perm(w.row[2 * t + 1][J / 2], w.row[2 * t][J / 2], J % 2 ? 0x07060302u : 0x05040100u);
   return u.v;
 }
 
 // ACT 0: C = A W.  ACT 1 / 2: fused SwiGLU (a tile is 64 gate columns and the 64 up columns pairing with
 // them), keeping / not keeping the pre-activation.
-template <int ACT, bool SCATTER_OUT>
-__global__ void __launch_bounds__(64) s2s_decode_kernel(S2SArgs a, int n_chunks) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int lane = threadIdx.x;
+template <int ACT, bool SCATTER_OUT, int CW, int KW>
+__global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, int n_chunks) {
+  __shared__ float s_part[KW][CW][32][64];     // one fragment's sums of every wavefront
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int cw = wave % CW, kw = wave / CW;    // its 128 columns of the tile, its share of the contraction
   const int mt = (int)blockIdx.x / n_chunks, nc = (int)blockIdx.x - mt * n_chunks;
   int e, row0, row_end;
   if (!locate_rows<DM>(a.offsets, a.E, mt, lane, e, row0, row_end)) return;   // grid is an upper bound
   e = __builtin_amdgcn_readfirstlane(e);
+  row0 = __builtin_amdgcn_readfirstlane(row0);
+  row_end = __builtin_amdgcn_readfirstlane(row_end);
+  const bool two = row_end - row0 > 16;              // both fragments hold rows
   const int half_n = a.N / 2;
-  const int n0 = nc * (ACT ? DN / 2 : DN);           // first (gate) column of the tile
+  const int n0 = nc * CW * (ACT ? DN / 2 : DN);      // first (gate) column of the tile
   const int nh = a.K / HK;
-  const bf16_t *A = (const bf16_t *)a.A;
-  const bf16_t *W = (const bf16_t *)a.W + (size_t)e * a.w_stride;
+  const int c = lane & 15, q = lane >> 4;            // the lane's column group and quarter of a step
 
-  // per-lane sources at contraction offset 0
-  const bf16_t *pw[NLW], *pa[NLA];
-#pragma unroll
-  for (int I = 0; I < NLW; ++I) {
-    const int krow = I * 4 + (lane >> 4);
-    const int c = (lane & 15) ^ dw_swz(krow);         // source chunk (8 columns) landing at LDS position lane%16
-    int col;
-    if (ACT) {
-      const int gate = n0 + (c & 7) * 8;
-      col = gate < half_n ? gate + (c >> 3) * half_n : 0;
-    } else {
-      col = n0 + c * 8;
-      if (col >= a.N) col = 0;
-    }
-    pw[I] = W + (size_t)krow * a.ldw + col;
-  }
-#pragma unroll
-  for (int I = 0; I < NLA; ++I) {
-    const int r = I * 16 + (lane >> 2);
-    const int i = min(row0 + r, row_end - 1);         // rows past the segment repeat its last row
-    const int src = a.a_map.o ? a.a_map.o[i] / a.a_map.fan : i;
-    pa[I] = A + (size_t)src * a.K + (((lane & 3) ^ kc_swz(r)) << 3);
-  }
-  const size_t w_step = (size_t)HK * a.ldw;
-
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-  auto issue = [&](int step, int slot) {
-    const int st = min(step, nh - 1);                 // steps past the end repeat the last one (never read)
-    const uint32_t lds = lds0 + (uint32_t)slot * DSTAGE_BYTES;
-#pragma unroll
-    for (int I = 0; I < NLW; ++I) load16_to_lds(pw[I] + (size_t)st * w_step, lds + I * 1024);
-#pragma unroll
-    for (int I = 0; I < NLA; ++I) load16_to_lds(pa[I] + (size_t)st * HK, lds + DW_BYTES + I * 1024);
+  // First column of column group g of the wavefronts `w`.  SwiGLU: one wavefront across holds 64 gate columns and their 64 up
+  // columns, several hold gates (the first half of them) or ups.
+  constexpr int GATES = CW / 2;
+  auto column = [&](int w, int g) {
+    if (!ACT) return n0 + w * DN + g * 8;
+    if (CW == 1) return n0 + (g & 7) * 8 + (g >> 3) * half_n;
+    return n0 + (w % (CW > 1 ? GATES : 1)) * DN + g * 8 + (w / (CW > 1 ? GATES : 1)) * half_n;
   };
+  auto exists = [&](int w, int g) {
+    if (!ACT) return column(w, g) < a.N;
+    const int col = column(w, g);
+    return (CW == 1 ? g < 8 : w < GATES) ? col < half_n : col < a.N;
+  };
+  const bool have = exists(cw, c);
+  const char *W = (const char *)((const bf16_t *)a.W + (size_t)e * a.w_stride);
+  const uint32_t w_lane = (uint32_t)(8 * q) * (uint32_t)a.ldw * 2u + (uint32_t)(have ? column(cw, c) : 0) * 2u;
+  const size_t row_bytes = (size_t)a.ldw * 2;
+  auto load_w = [&](int step) {
+    WStep w;
+    const char *p = W + (size_t)(step * HK) * row_bytes;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w.row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p + (size_t)i * row_bytes + w_lane));
+    return w;
+  };
+  // Steps kw, kw + KW, ... are this wavefront's; requests past the last repeat it and are not used.
+  auto step_at = [&](int s) { return min(kw + s * KW, nh - 1); };
+  const int mine = (nh - kw + KW - 1) / KW;
+  WStep w[DEPTH];
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) w[s] = load_w(step_at(s));
 
-  f32x16 acc[4];
+  const bf16_t *pa[2];                               // rows past the segment repeat its last row
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int m = 0; m < 2; ++m) {
+    const int i = min(row0 + m * 16 + c, row_end - 1);
+    const int src = a.a_map.o ? a.a_map.o[i] / a.a_map.fan : i;
+    pa[m] = (const bf16_t *)a.A + (size_t)src * a.K + q * 8;
+  }
+  bf16x8 x[DEPTH][2];
+  auto load_x = [&](int step, bf16x8 (&v)[2]) {
+    v[0] = *reinterpret_cast<const bf16x8 *>(pa[0] + step * HK);
+    if (two) v[1] = *reinterpret_cast<const bf16x8 *>(pa[1] + step * HK);
+  };
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[f][q] = 0.f;
+  for (int s = 0; s < DEPTH; ++s) load_x(step_at(s), x[s]);
 
-#pragma unroll 1
-  for (int s = 0; s < DST - 1; ++s) issue(s, s);
-#pragma unroll 1
-  for (int s = 0; s < nh; ++s) {
-    // refills the stage read one step ago (its fragments went into matrix instructions already issued)
-    issue(s + DST - 1, (s + DST - 1) % DST);
-    wait_loads<(DST - 1) * NLOADS>();                 // stage s has landed
-    const char *tile = smem + (s % DST) * DSTAGE_BYTES;
+  f32x4 acc[2][8];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const bf16x8 fa = kc_frag(tile + DW_BYTES, 0, kk, lane);
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int f = 0; f < 4; ++f)
-        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dw_frag(tile, f * 32, kk, lane), fa, acc[f], 0, 0, 0);
+    for (int j = 0; j < 8; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](auto j, const WStep &ws, const bf16x8 (&xs)[2]) {
+    constexpr int J = decltype(j)::value;
+    const bf16x8 f = w_frag<J>(ws);
+    acc[0][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, xs[0], acc[0][J], 0, 0, 0);
+    if (two) acc[1][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, xs[1], acc[1][J], 0, 0, 0);
+  };
+  auto use = [&](const WStep &ws, const bf16x8 (&xs)[2]) {
+    multiply(std::integral_constant<int, 0>{}, ws, xs);
+    multiply(std::integral_constant<int, 1>{}, ws, xs);
+    multiply(std::integral_constant<int, 2>{}, ws, xs);
+    multiply(std::integral_constant<int, 3>{}, ws, xs);
+    multiply(std::integral_constant<int, 4>{}, ws, xs);
+    multiply(std::integral_constant<int, 5>{}, ws, xs);
+    multiply(std::integral_constant<int, 6>{}, ws, xs);
+    multiply(std::integral_constant<int, 7>{}, ws, xs);
+  };
+#pragma unroll 1
+  for (int s = 0; s < mine; s += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      if (s + u < mine) use(w[u], x[u]);
+      const int next = step_at(s + u + DEPTH);
+      w[u] = load_w(next);
+      load_x(next, x[u]);
     }
   }
-  wait_loads<0>();
 
-  // a lane holds row lane%32 and, per fragment f and group g, the four columns f*32 + 8g + 4*(lane/32) + 0..3
-  const int i = row0 + (lane & 31);
-  if (i >= row_end) return;
-  const size_t dst = SCATTER_OUT ? (size_t)a.c_map.o[i] : (size_t)i;
-  if (ACT == 0) {
-    bf16_t *C = (bf16_t *)a.C + dst * a.N;
+  // Sums over the contraction's shares, in their order.  Lane (c, q) holds row c of the fragment and, in element r of the
+  // accumulators, columns 0..7 (j) of column group 4 * q + r.
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+  for (int m = 0; m < 2; ++m) {
+    if (m == 1 && !two) break;
+    if (m == 1) __syncthreads();
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = n0 + f * 32 + 8 * g + 4 * (lane >> 5);
-        if (col < a.N) {
-          bf16x4 v;
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = (bf16_t)acc[f][4 * g + q];
-          *reinterpret_cast<bf16x4 *>(C + col) = v;
+      for (int r = 0; r < 4; ++r) s_part[kw][cw][r * 8 + j][lane] = acc[m][j][r];
+    __syncthreads();
+    const int i = row0 + m * 16 + c;
+    auto rounded = [](const float (&v)[8]) {
+      bf16x8 o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = (bf16_t)v[j];
+      return o;
+    };
+    constexpr int ACROSS = ACT && CW > 1 ? GATES : CW;
+    for (int t = wave; t < ACROSS * 4; t += CW * KW) {   // element r of every lane of the wavefronts w
+      const int w = t / 4, r = t % 4, g = 4 * q + r;
+      auto total = [&](int from, int from_lane, float (&v)[8]) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          v[j] = 0.f;
+#pragma unroll
+          for (int p = 0; p < KW; ++p) v[j] += s_part[p][from][r * 8 + j][from_lane];
         }
-      }
-  } else {
-    bf16_t *Hpre = ACT == 1 ? (bf16_t *)a.C + dst * a.N : nullptr;
-    bf16_t *H = (bf16_t *)a.H + dst * half_n;
+      };
+      if (ACT == 0) {
+        float v[8];
+        total(w, lane, v);
+        if (i < row_end && exists(w, g)) {
+          const size_t dst = SCATTER_OUT ? (size_t)a.c_map.o[i] : (size_t)i;
+          *reinterpret_cast<bf16x8 *>((bf16_t *)a.C + dst * a.N + column(w, g)) = rounded(v);
+        }
+      } else if (CW > 1 || q < 2) {   // one wavefront across: column groups 0..7 are gates, 8..15 (lane + 32) their ups
+        float gate[8], up[8], h[8];
+        total(w, lane, gate);
+        if (CW > 1) total(w + GATES, lane, up);
+        else total(w, lane + 32, up);
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = n0 + f * 32 + 8 * g + 4 * (lane >> 5);   // hidden unit = gate column
-        if (col < half_n) {
-          bf16x4 vg, vu, vh;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float gate = acc[f][4 * g + q], up = acc[2 + f][4 * g + q];
-            const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate));
-            vg[q] = (bf16_t)gate;
-            vu[q] = (bf16_t)up;
-            vh[q] = (bf16_t)(gate * sig * up);
-          }
+        for (int j = 0; j < 8; ++j) {
+          const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate[j]));
+          h[j] = gate[j] * sig * up[j];
+        }
+        const int col = column(w, g);
+        if (i < row_end && col < half_n) {
           if (ACT == 1) {
-            *reinterpret_cast<bf16x4 *>(Hpre + col) = vg;
-            *reinterpret_cast<bf16x4 *>(Hpre + half_n + col) = vu;
+            bf16_t *Hpre = (bf16_t *)a.C + (size_t)i * a.N;
+            *reinterpret_cast<bf16x8 *>(Hpre + col) = rounded(gate);
+            *reinterpret_cast<bf16x8 *>(Hpre + half_n + col) = rounded(up);
           }
-          *reinterpret_cast<bf16x4 *>(H + col) = vh;
+          *reinterpret_cast<bf16x8 *>((bf16_t *)a.H + (size_t)i * half_n + col) = rounded(h);
         }
       }
+    }
   }
 }
 
-template <int ACT, bool SCATTER_OUT> int launch_decode(hipStream_t s, const S2SArgs &a) {
-  const int n_chunks = ACT ? ceil_div(a.N / 2, DN / 2) : ceil_div(a.N, DN);
+template <int ACT, bool SCATTER_OUT, int CW, int KW> int launch_decode_as(hipStream_t s, const S2SArgs &a) {
+  const int n_chunks = ACT ? ceil_div(a.N / 2, CW * DN / 2) : ceil_div(a.N, CW * DN);
   const long long m_bound = a.Tk / DM + a.E;           // >= sum_e ceil(n_e / 32)
-  hipLaunchKernelGGL((s2s_decode_kernel<ACT, SCATTER_OUT>), dim3((unsigned)(m_bound * n_chunks)), dim3(64), DECODE_LDS_BYTES, s, a,
-                     n_chunks);
+  hipLaunchKernelGGL((s2s_decode_kernel<ACT, SCATTER_OUT, CW, KW>), dim3((unsigned)(m_bound * n_chunks)), dim3(64 * CW * KW), 0, s, a, n_chunks);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
+}
+// Four wavefronts: as many of them side by side as leave a tile for every compute unit, the rest share the contraction.  Wide
+// tiles read longer runs of a row of W (64 experts, weights not in the cache: 2048 -> 2 x 512 in 55 us one across, 47 two
+// across, 56 four across on half the chip; 512 -> 2048 in 29, 27, 25 us), narrow ones fill the chip (25 experts: 2048 -> 2 x 512
+// in 26 us one across, 31 two).
+template <int ACT, bool SCATTER_OUT> int launch_decode(hipStream_t s, const S2SArgs &a) {
+  const long long experts = a.Tk < a.E ? a.Tk : a.E;
+  auto tiles = [&](int cw) { return experts * ceil_div(ACT ? a.N / 2 : a.N, ACT ? cw * DN / 2 : cw * DN); };
+  if (tiles(4) >= a.grid) return launch_decode_as<ACT, SCATTER_OUT, 4, 1>(s, a);
+  if (tiles(2) >= a.grid) return launch_decode_as<ACT, SCATTER_OUT, 2, 2>(s, a);
+  return launch_decode_as<ACT, SCATTER_OUT, 1, 4>(s, a);
 }
 
 }  // namespace
 
 // The decoding regime: on average at most one 32-row tile per expert.  Gathered or expert-sorted input,
-// W as stored, any output order; widths as the 16-byte loads and 8-byte stores need them.
+// W as stored, any output order; widths as the 16-byte loads and stores need them, and rows of W that 24 of them fit a
+// lane's 32-bit offset.
 bool s2s_decode_supported(const S2SArgs &a) {
   if (a.trans_w || a.Tk <= 0 || a.E < 1 || (long long)a.Tk > (long long)DM * a.E) return false;
-  if (a.K < HK || a.K % HK || a.N % 8) return false;
+  if (a.K < HK || a.K % HK || a.N % 8 || a.ldw % 8 || a.ldw > (1 << 25)) return false;
   if (a.H && (a.N % 16 || a.c_map.o)) return false;
   const long long blocks = ((long long)a.Tk / DM + a.E) * ceil_div(a.N, DN / 2);
-  return blocks < 0x7fffffffLL;
+  return blocks * 256 <= 0xffffffffLL;
 }
 
 int launch_s2s_decode(hipStream_t s, const S2SArgs &a) {
