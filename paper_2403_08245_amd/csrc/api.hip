@@ -726,6 +726,33 @@ S2SArgs dense_s2s(const void *A, const void *W, void *C, const int32_t *offsets,
   smoe_routing r{nullptr, nullptr, offsets, n, 1};
   return make_s2s(A, W, C, &r, d_in, d_out, trans_w, true, 1, true);
 }
+// Two dense products (two weight gradients) of the same sizes, in one launch where the persistent kernels take them: alone
+// each fills half of the chip at the widths of a key or value projection (8192 rows, 2048 -> 512: 2 x 41 us, paired 43; the
+// weight gradients 2 x 57 us, paired 58).
+int run_s2s_pair(smoe_ctx *ctx, hipStream_t s, const S2SArgs &a, const S2SArgs &b) {
+  S2SArgs p = a;
+  p.E = 2;
+  p.Tk = 2 * a.Tk;
+  p.A2 = (const void *)((uintptr_t)b.A - (uintptr_t)a.Tk * a.K * 2);
+  p.W2 = (const void *)((uintptr_t)b.W - (uintptr_t)a.w_stride * 2);
+  p.C2 = (void *)((uintptr_t)b.C - (uintptr_t)a.Tk * a.N * 2);
+  set_launch(ctx, p);
+  if (ctx->kernel_mode == 0 && a.Tk < (1 << 30) && !s2s_decode_supported(a) && s2s_stream_supported(p)) return launch_s2s_stream(s, p);
+  const int rc = run_s2s(ctx, s, SMOE_BF16, a);
+  return rc != SMOE_OK ? rc : run_s2s(ctx, s, SMOE_BF16, b);
+}
+int run_dw_pair(smoe_ctx *ctx, hipStream_t s, const DWArgs &a, const DWArgs &b) {
+  DWArgs p = a;
+  p.E = 2;
+  p.Tk = 2 * a.Tk;
+  p.A2 = (const void *)((uintptr_t)b.A - (uintptr_t)a.Tk * a.M * 2);
+  p.B2 = (const void *)((uintptr_t)b.B - (uintptr_t)a.Tk * a.N * 2);
+  p.dW2 = (void *)((uintptr_t)b.dW - (uintptr_t)a.M * a.N * 2);
+  p.grid = ctx->stream_grid;
+  if (ctx->kernel_mode == 0 && a.Tk < (1 << 30) && dw_stream_supported(p)) return launch_dw_stream(s, p);
+  const int rc = run_dw(ctx, s, SMOE_BF16, a);
+  return rc != SMOE_OK ? rc : run_dw(ctx, s, SMOE_BF16, b);
+}
 }  // namespace
 
 size_t smoe_momha_fwd_workspace_bytes(int B, int T, int k, int d_model, int h_expert, int d_head, int training) {
@@ -763,9 +790,10 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
   if (rc != SMOE_OK) return rc;
   // V = X W_V, K = X W_K
   auto product = [&](S2SArgs a) { a.tail_ws = tail_ws; return run_s2s(ctx, s, dtype, a); };
-  rc = product(dense_s2s(X, W_V, saved_V, dense_off, N, d_model, d_out, false));
-  if (rc != SMOE_OK) return rc;
-  rc = product(dense_s2s(X, W_K, saved_K, dense_off, N, d_model, d_out, false));
+  S2SArgs pv = dense_s2s(X, W_V, saved_V, dense_off, N, d_model, d_out, false);
+  S2SArgs pk = dense_s2s(X, W_K, saved_K, dense_off, N, d_model, d_out, false);
+  pv.tail_ws = pk.tail_ws = tail_ws;
+  rc = run_s2s_pair(ctx, s, pv, pk);
   if (rc != SMOE_OK) return rc;
   // Q = ParallelLinear(X, W_Q, o, no p, scattered -> scattered)
   rc = product(make_s2s(X, W_Q, saved_Q, r, d_model, d_out, false, false, k, false));
@@ -832,16 +860,12 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   // dense key / value projections
   DWArgs wk{X, dK, dW_K, dense_off, 1, N, d_model, d_out}, wv{X, dV, dW_V, dense_off, 1, N, d_model, d_out};
   wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q + z.inv);
-  rc = run_dw(ctx, s, dtype, wk);
-  if (rc != SMOE_OK) return rc;
-  rc = run_dw(ctx, s, dtype, wv);
+  rc = run_dw_pair(ctx, s, wk, wv);
   if (rc != SMOE_OK) return rc;
   S2SArgs xk = dense_s2s(dK, W_K, dXk, dense_off, N, d_model, d_out, true);
   S2SArgs xv = dense_s2s(dV, W_V, dXv, dense_off, N, d_model, d_out, true);
   xk.tail_ws = xv.tail_ws = tail_ws;
-  rc = run_s2s(ctx, s, dtype, xk);
-  if (rc != SMOE_OK) return rc;
-  rc = run_s2s(ctx, s, dtype, xv);
+  rc = run_s2s_pair(ctx, s, xk, xv);
   if (rc != SMOE_OK) return rc;
   return launch_add3(s, dXq, dXk, dXv, dX, (size_t)N * d_model);
 }

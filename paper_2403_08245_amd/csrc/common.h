@@ -109,6 +109,11 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   int grid = 256;     // blocks of the persistent kernel (smoe_ctx::stream_grid)
   int tile_shape = 0; // persistent scatter2scatter tiles: 0 chosen by size, 1 128 x 256 only, 2 256 x 256 only (smoe_ctx::tile_shape)
   int group_m = 4;    // tiles are numbered in groups of this many M-tiles x all N-tiles (smoe_ctx::group_m)
+  // Optional second dense product of the same sizes in the same launch (persistent kernels, no order indices, no fused
+  // activation; E = 2, both segments Tk / 2 rows): segment 1 reads A2 and W2 and writes C2, which point to where segment
+  // 0's numbering would have them (pair_with sets them).
+  const void *A2 = nullptr, *W2 = nullptr;
+  void *C2 = nullptr;
   // Optional fused SwiGLU of Alg. 3 (forward, expert-sorted output only): W's columns are
   // [gate | up] halves of width N / 2 and H [*, N / 2] receives silu(gate) * up; C may then be
   // NULL when the pre-activation is not kept.
@@ -148,6 +153,9 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both 
   // that leave fp32 partial tiles here, added in chunk order by a second kernel.
   float *split_ws = nullptr;
   int grid = 256;     // blocks of the persistent kernel (smoe_ctx::stream_grid)
+  // Optional second weight gradient of the same sizes in the same launch (persistent kernel; E = 2), as S2SArgs has it.
+  const void *A2 = nullptr, *B2 = nullptr;
+  void *dW2 = nullptr;
   // fp32 kernels (gemm_plain.hip): rows of A and B read through the order indices instead of from sorted copies, and B's rows
   // scaled by the routing weights (fp32, slot order; needs b_map).
   RowMap a_map{nullptr, 1}, b_map{nullptr, 1};

@@ -179,6 +179,7 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4, boo
 __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs a, int tiles_n, int group_m, uint32_t magic_a) {
   constexpr bool SWIGLU = ACT == 1 || ACT == 2;
   constexpr bool KTAIL = !STATIC4;
+  constexpr bool DENSE_PAIR = ACT == 0 && !SCATTER_OUT;   // S2SArgs::C2 may be set
   constexpr int STORES = EpilogueStores<S::FM, ACT>;
   static_assert(!SWIGLU || (!TRANS_W && !SCATTER_OUT), "the fused activation belongs to the forward, sorted-output product");
   static_assert(ACT < 3 || (TRANS_W && !SCATTER_OUT), "the fused derivative belongs to the W^T product with sorted rows out");
@@ -272,9 +273,10 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
     const uint32_t row_bytes = (uint32_t)K * 2u, ldw_bytes = (uint32_t)p->ldw * 2u;
     const bool gathered = p->a_map.o != nullptr;
     // gathered rows are addressed from the start of A, expert-sorted rows from the tile's first row
-    ops.win_a = buffer_window((const bf16_t *)p->A + (gathered ? 0 : (size_t)t.row0 * K),
+    const bool second = DENSE_PAIR && p->C2 && t.e == 1;
+    ops.win_a = buffer_window((const bf16_t *)(second ? p->A2 : p->A) + (gathered ? 0 : (size_t)t.row0 * K),
                               (uint32_t)(gathered ? p->Tk / p->a_map.fan : min(S::TM, t.row_end - t.row0)) * row_bytes);
-    ops.win_b = buffer_window((const bf16_t *)p->W + (size_t)t.e * p->w_stride, (uint32_t)(TRANS_W ? N : K) * ldw_bytes);
+    ops.win_b = buffer_window((const bf16_t *)(second ? p->W2 : p->W) + (size_t)t.e * p->w_stride, (uint32_t)(TRANS_W ? N : K) * ldw_bytes);
     const int *idx = &s_idx[t.seq & 3][0];
 #pragma unroll
     for (int I = 0; I < S::NLA; ++I) {
@@ -468,7 +470,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
           return d;
         }, lane);
       } else {
-        const window_t win = sorted_window(p->C, N, 2);
+        const window_t win = sorted_window(p->C2 && ct.e == 1 ? p->C2 : p->C, N, 2);
         store_wave_tile(acc, patch, [&](int fm, int half) { return sorted_block(win, N, fm, wcol + half * 64, N - wcol - half * 64); },
                         lane);
       }
@@ -509,7 +511,7 @@ __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int til
   locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
   const int n0 = nt * TB;
   const float *part = a.tail_ws + (size_t)blockIdx.x * plan.split * S::PART;
-  bf16_t *C = (bf16_t *)a.C;
+  bf16_t *C = (bf16_t *)(!SCATTER_OUT && a.C2 && e == 1 ? a.C2 : a.C);
   constexpr int PER_SLICE = S::PART / 4 / TAIL_SLICES;
   for (int i = (int)blockIdx.y * PER_SLICE + threadIdx.x; i < ((int)blockIdx.y + 1) * PER_SLICE; i += 256) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -580,7 +582,8 @@ __device__ __forceinline__ void dw_chunk_rows(int lo, int hi, int split, int chu
 
 // split > 1 (only when all experts' tiles times split fit one round of the grid): unit T is chunk T % split of
 // tile T / split, experts in their own order, and the result is an fp32 partial tile number T in a.split_ws.
-__global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split) {
+// DENSE_PAIR: segment 1 is the second weight gradient of DWArgs (a kernel of its own: the choice of operands sits in every slot).
+template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_off[MAX_E + 1];
   __shared__ int s_order[MAX_E];      // experts, largest segment first
@@ -646,8 +649,9 @@ __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int ti
     const int left = c.live ? max(c.hi - first, 0) : 0;          // rows of the segment from there on
     const int base_row = left > 0 ? first : 0;
     const unsigned long long cap = 0xffffffffull;
-    ops.win_a = buffer_window(A + (size_t)base_row * a.M, (uint32_t)min((unsigned long long)left * row_a, cap));
-    ops.win_b = buffer_window(B + (size_t)base_row * a.N, (uint32_t)min((unsigned long long)left * row_b, cap));
+    const bool second = DENSE_PAIR && c.e == 1;
+    ops.win_a = buffer_window((second ? (const bf16_t *)a.A2 : A) + (size_t)base_row * a.M, (uint32_t)min((unsigned long long)left * row_a, cap));
+    ops.win_b = buffer_window((second ? (const bf16_t *)a.B2 : B) + (size_t)base_row * a.N, (uint32_t)min((unsigned long long)left * row_b, cap));
     ops.sub_a = (uint32_t)(c.step & 3) * HK * row_a;
     ops.sub_b = (uint32_t)(c.step & 3) * HK * row_b;
     if (c.m0 != shown_m0 || c.n0 != shown_n0) {                  // a new tile: its columns' offsets inside a slot
@@ -716,7 +720,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int ti
       store_wave_partial(acc, a.split_ws + (size_t)(cc.seq * G + slot_in_round) * TB * TB + (size_t)(uwm * (TB / 2)) * TB + uwn * (TB / 2), lane);
     } else {
       const int left = max(min(TB / 2, a.M - mbase), 0);
-      const window_t win = make_window((const bf16_t *)a.dW + (size_t)cc.e * a.M * a.N + (size_t)min(mbase, a.M) * a.N, (uint32_t)left * row_b);
+      const window_t win = make_window((const bf16_t *)(DENSE_PAIR && cc.e == 1 ? a.dW2 : a.dW) + (size_t)cc.e * a.M * a.N + (size_t)min(mbase, a.M) * a.N, (uint32_t)left * row_b);
       store_wave_tile(acc, patch, [&](int fm, int half) {
         BlockDest d{win, {}};
         const int col = wcol + half * 64 + (lane & 7) * 8;
@@ -739,7 +743,7 @@ __global__ void __launch_bounds__(256) dw_split_reduce_kernel(DWArgs a, int tile
   int m0, n0;
   dw_tile_origin(T - e * per_expert, tiles_m, tiles_n, m0, n0);
   const float *part = a.split_ws + (size_t)T * split * TB * TB;
-  bf16_t *dW = (bf16_t *)a.dW + (size_t)e * a.M * a.N;
+  bf16_t *dW = (bf16_t *)(a.dW2 && e == 1 ? a.dW2 : a.dW) + (size_t)e * a.M * a.N;
   constexpr int PER_SLICE = TB * TB / 4 / TAIL_SLICES;
   for (int i = (int)blockIdx.y * PER_SLICE + threadIdx.x; i < ((int)blockIdx.y + 1) * PER_SLICE; i += 256) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -787,7 +791,7 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4, boo
 template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static4, bool may_split, long long &total) {
   const float rows = (float)a.Tk / a.E;
   const int nh = ceil_div(a.K, HK), G = a.grid * S::BLOCKS;
-  const float m_tiles = a.E == 1 ? (float)ceil_div(a.Tk, S::TM) : (rows >= S::TM ? rows / S::TM + 0.5f : 1.0f) * (a.Tk < a.E ? a.Tk : a.E);
+  const float m_tiles = a.E == 1 || a.C2 ? (float)a.E * ceil_div(a.Tk / a.E, S::TM) : (rows >= S::TM ? rows / S::TM + 0.5f : 1.0f) * (a.Tk < a.E ? a.Tk : a.E);
   total = (long long)(m_tiles * tiles_n + 0.5f);
   const float full = (S::BLOCKS == 1 ? 0.85f : 1.03f) * nh + 6.f, one = S::BLOCKS == 1 ? full : 0.5f * nh + 4.f;
   const int rem = (int)(total % G), whole = S::BLOCKS > 1 && rem > a.grid ? a.grid : 0, rest = rem - whole;
@@ -831,7 +835,8 @@ int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
     split = (int)(a.grid / tiles < 8 ? a.grid / tiles : 8);
     if (nh - nh / split < SPLIT_MIN_SAVED) split = 1;
   }
-  hipLaunchKernelGGL(dw_stream_kernel, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  if (a.dW2) hipLaunchKernelGGL(dw_stream_kernel<true>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  else hipLaunchKernelGGL(dw_stream_kernel<false>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
   SMOE_LAUNCH_CHECK();
   if (split > 1) {
     hipLaunchKernelGGL(dw_split_reduce_kernel, dim3((unsigned)tiles, TAIL_SLICES), dim3(256), 0, s, a, tiles_m, tiles_n, split);
@@ -911,6 +916,7 @@ int init_stream_kernels() {
   if (rc == SMOE_OK) rc = init_s2s<true, false, 3>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 4>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
-  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<false>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<true>, Big::LDS_BYTES);
   return rc;
 }

@@ -1,0 +1,48 @@
+"""GPU parity of the attention layer's key and value projections and their gradients where they run as one launch: sequence
+lengths that end inside a tile, widths of less than and more than a tile, and every tile shape."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import smoe_inputs as si
+from helpers import assert_close, oracle_gates_f32, oracle_routing
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(params=[0, 2, 3, 4], ids=["auto", "per-tile", "tiles128", "tiles256"])
+def smoe(request):
+    import paper_2403_08245_amd as m
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    m.set_kernel_mode(request.param)
+    yield m
+    m.set_kernel_mode(0)
+
+
+@pytest.mark.parametrize("B,T,d_model,h", [(1, 129, 264, 1), (1, 257, 136, 3), (3, 111, 520, 2)])
+def test_key_and_value_projections(smoe, B, T, d_model, h):
+    E, k, N, d_out = 4, 2, B * T, h * 128
+    print("pair", B, T, d_model, h, flush=True)
+    gen = torch.Generator().manual_seed(5)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=gen) * std).bfloat16()
+    X, dO = rnd(N, d_model), rnd(N, d_model)
+    W_K, W_V = rnd(d_model, d_out, std=0.05), rnd(d_model, d_out, std=0.05)
+    W_Q, W_O = rnd(E, d_model, d_out, std=0.05), rnd(E, d_out, d_model, std=0.05)
+    logits = torch.randn(N, E, generator=gen)
+    ei, g, _, _, _ = oracle_routing(logits, k, E)
+    gi, gg = smoe.topk_gate(logits.cuda(), k)
+    assert np.array_equal(gi.cpu().numpy(), ei)
+    r = smoe.route(gi, E)
+    args = [t.cuda() for t in (X, W_K, W_V, W_Q, W_O)]
+    O, buf = smoe.momha_fwd(*args, r, k, gg, B, T, h, 128)
+    dX, dW_K, dW_V, _, _, _ = smoe.momha_bwd(dO.cuda(), *args, r, k, gg, B, T, h, 128, buf)
+    ref_args = [si.as_f64(t) for t in (X, W_K, W_V, W_Q, W_O)]
+    g64 = oracle_gates_f32(g)
+    ref = oracle.momha_fwd(*ref_args, ei, g64, B, T, h, 128)
+    gref = oracle.momha_bwd(si.as_f64(dO), *ref_args, ei, g64, B, T, h, 128)
+    bf = torch.bfloat16
+    for got, want, name in ((buf.K, ref["K"], "K"), (buf.V, ref["V"], "V"), (O, ref["O"], "O"), (dX, gref["dX"], "dX"),
+                            (dW_K, gref["dW_K"], "dW_K"), (dW_V, gref["dW_V"], "dW_V")):
+        assert_close(got.reshape(want.shape), want, bf, name)
+
