@@ -29,13 +29,14 @@
 
 namespace {
 
-template <int FM_, int SLOTS_, int BLOCKS_> struct Shape {
+template <int FM_, int SLOTS_, int BLOCKS_, bool ONCE_ = false> struct Shape {
   static constexpr int FM = FM_;                        // 32-row fragments per wavefront (2 x 2 wavefronts, FR = 4 column fragments)
   static constexpr int TM = FM * 64;                    // tile rows; tile columns are TB = 256
   static constexpr int A_BYTES = TM * HK * 2;
   static constexpr int SLOT_BYTES = A_BYTES + TILE_BYTES;
   static constexpr int SLOTS = SLOTS_;
   static constexpr int BLOCKS = BLOCKS_;                // blocks per compute unit
+  static constexpr bool ONCE = ONCE_;                   // W is read past the caches
   static constexpr int NLA = FM;                        // load instructions per wavefront and stage: A part,
   static constexpr int NL = NLA + NLD;                  // both parts
   static constexpr int HALF = NL / 2;                   // issued in phase B; the rest in the next phase A
@@ -49,6 +50,7 @@ template <int FM_, int SLOTS_, int BLOCKS_> struct Shape {
 };
 using Big = Shape<4, 4, 1>;
 using Pair = Shape<2, 3, 2>;
+using PairOnce = Shape<2, 3, 2, true>;
 constexpr int MAX_STREAM_GRID = 256;                    // compute units used; the partial-tile scratch holds this many big tiles
 
 template <typename S> struct Frags {                    // one wavefront's fragments for 16 contraction elements
@@ -159,7 +161,8 @@ template <typename S, bool TRANS_W, bool KTAIL> struct S2SOps {
       const int J = I - S::NLA;
       uint32_t off = ob[J] + (uint32_t)step * b_step;
       if (KTAIL && TRANS_W) off |= step == last ? tb[J] : 0u;
-      load16_to_lds_checked(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
+      if (S::ONCE) load16_to_lds_once(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
+      else load16_to_lds_checked(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
     }
   }
   __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int lane) const { return kc_frag(tile, base, kk, lane); }
@@ -818,8 +821,15 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
   }
   const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
   const bool may_split = ACT == 0 && a.tail_ws;
-  if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split)))
+  if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split))) {
+    // At most one tile row per expert: W is read about once, and more of it than half the 256 MB last-level cache would only
+    // push other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53; with reuse, 8192 rows and
+    // 8 experts, 1024 -> 5632: 113 us, past the caches 156).
+    if constexpr (!TRANS_W)
+      if ((long long)a.Tk <= (long long)a.E * Pair::TM && (long long)a.E * a.K * a.N * 2 > 128000000LL)
+        return launch_s2s_one<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
     return launch_s2s_one<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+  }
   if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, false>(s, a);
   return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
 }
@@ -900,6 +910,8 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s() {
   int rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, false>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, false>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
+  if constexpr (!TRANS_W)
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
   if (SCATTER_OUT) {
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, SCATTER_OUT>, Big::LDS_BYTES);
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, SCATTER_OUT>, Big::LDS_BYTES);

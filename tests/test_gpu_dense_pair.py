@@ -1,5 +1,6 @@
 """GPU parity of the attention layer's key and value projections and their gradients where they run as one launch: sequence
-lengths that end inside a tile, widths of less than and more than a tile, and every tile shape."""
+lengths that end inside a tile, widths of less than and more than a tile, and every tile shape; plus the weights that are read
+past the caches by launches with at most one tile row per expert."""
 import numpy as np
 import pytest
 import torch
@@ -46,3 +47,21 @@ def test_key_and_value_projections(smoe, B, T, d_model, h):
                             (dW_K, gref["dW_K"], "dW_K"), (dW_V, gref["dW_V"], "dW_V")):
         assert_close(got.reshape(want.shape), want, bf, name)
 
+
+def test_weights_read_past_the_caches(smoe):
+    """More than 128 MB of weights and at most one tile of rows per expert, empty experts among them."""
+    E, k, T, d_in, d_out = 24, 1, 1000, 1032, 2696
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    X = torch.randn(T, d_in, generator=gen, device="cuda").bfloat16()
+    W = (torch.randn(E, d_in, d_out, generator=gen, device="cuda") * 0.03).bfloat16()
+    assert W.numel() * 2 > 128e6 and T * k <= 128 * E and T * k > 32 * E
+    logits = torch.randn(T, E, generator=gen, device="cuda")
+    logits[:, 5:8] = -100.0
+    ei, _ = smoe.topk_gate(logits, k)
+    r = smoe.route(ei, E)
+    Y, _ = smoe.plinear_fwd(X, W, r, k)
+    for e in range(E):
+        t = (ei[:, 0] == e).nonzero()[:, 0]
+        assert len(t) or 5 <= e < 8
+        if len(t):
+            assert_close(Y[t], (X[t].float() @ W[e].float()).cpu().numpy(), torch.bfloat16, f"Y of expert {e}")
