@@ -242,24 +242,17 @@ int smoe_plinear_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   return rc;
 }
 
-// Sorted copies of rows that k slots share are spread from the source rows when that saves more than the launch that inverts
-// the order indices costs (about 3 us): grouping 20500 rows of 3 KB took 21 us and spreading them 15, so from 16 MB on.  With
-// k = 1 no row is read twice and there is nothing to save.
-static bool spreads(int Tk, int k, int d) { return k > 1 && (size_t)Tk * d >= ((size_t)8 << 20); }
-
 // ------------------------------------------------------------------------------ Alg. 2
 // Workspace: [dYbar: Tk x d_out, when dY arrives scattered (weighted or not) -- Alg. 2's group(dY, o, p)]
 //            [Xbar:  Tk x d_in, when X was scattered -- Alg. 2's group(X, o); the same array then
 //                    receives dXbar, the reuse Sec. 3.2.1 points out]
-//            [inverse of the order indices: Tk]
+//            [64 MiB of fp32 partial tiles; before the first product they hold the inverse of the order indices]
 static void plinear_bwd_layout(smoe_dtype dt, int d_in, int d_out, int Tk, int grouped_in, int grouped_out,
-                               size_t &off_dybar, size_t &off_xbar, size_t &off_inv, size_t &total) {
+                               size_t &off_dybar, size_t &off_xbar, size_t &total) {
   size_t es = dtype_size(dt), off = 0;
   off_dybar = off_xbar = (size_t)-1;
   if (!grouped_out) { off_dybar = off; off += align256((size_t)Tk * d_out * es); }
   if (!grouped_in) { off_xbar = off; off += align256((size_t)Tk * d_in * es); }
-  off_inv = off;
-  off += align256((size_t)Tk * sizeof(int32_t));
   total = off + S2S_TAIL_WS_BYTES;   // fp32 partial tiles of the input-gradient product's split last round
 }
 
@@ -267,15 +260,16 @@ size_t smoe_plinear_bwd_workspace_bytes(smoe_dtype dtype, int x_rows, int d_in, 
                                         int has_gates, int grouped_in, int grouped_out) {
   (void)x_rows; (void)k; (void)has_gates;
   if (!dtype_ok(dtype) || d_in < 1 || d_out < 1 || Tk < 0) return 0;
-  size_t a, b, c, total;
-  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, a, b, c, total);
+  size_t a, b, total;
+  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, a, b, total);
   return total;
 }
 
-int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dY, const void *X, int x_rows,
+// more0, more1: two further contributions to dX [x_rows, d_in], added where the k slots are summed (scattered X with k > 1)
+static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dY, const void *X, int x_rows,
                      int d_in, const void *W, int d_out, const void *Yhat, const smoe_routing *r, int k,
                      const float *gates, int gates_k, int grouped_in, int grouped_out, void *dX, void *dW,
-                     float *dgates, void *ws, size_t ws_bytes) {
+                     float *dgates, void *ws, size_t ws_bytes, const void *more0, const void *more1) {
   if (!ctx || !dtype_ok(dtype) || !routing_ok(r) || d_in < 1 || d_out < 1 || k < 1 || x_rows < 0)
     return SMOE_ERR_INVALID_ARG;
   const int Tk = r->Tk;
@@ -285,8 +279,8 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   if (dgates && !Yhat) return SMOE_ERR_INVALID_ARG;
   if (!width_ok(dtype, d_in) || !width_ok(dtype, d_out)) return SMOE_ERR_UNSUPPORTED;
   if (!W && dX) return SMOE_ERR_INVALID_ARG;
-  size_t off_dybar, off_xbar, off_inv, need;
-  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, off_dybar, off_xbar, off_inv, need);
+  size_t off_dybar, off_xbar, need;
+  plinear_bwd_layout(dtype, d_in, d_out, Tk, grouped_in, grouped_out, off_dybar, off_xbar, need);
   if (need && (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)) return SMOE_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   int rc = SMOE_OK;
@@ -330,9 +324,15 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
   }
 
   // dp = bmm(dY, Yhat); dYbar = group(dY, o, p)  (Alg. 2: "weight and group")
-  int32_t *inv = (int32_t *)((char *)ws + off_inv);
-  const bool spread_y = spreads(Tk, gates ? gates_k : 1, d_out), spread_x = spreads(Tk, k, d_in);
-  if ((!grouped_out && spread_y) || (!grouped_in && dW && spread_x)) {
+  int32_t *inv = (int32_t *)((char *)ws + need - S2S_TAIL_WS_BYTES);   // read before the first product writes partial tiles there
+  // Rows that several slots share are spread from the source rows when that saves more than the launch that inverts the order
+  // indices costs (about 3 us): on 20500 rows of 3 and 4 KB 39 us of group copies became 28, on 8192 rows of 2 KB the launch was
+  // dearer by 1.5 us, so from 24 Mi elements on.
+  size_t shared = 0;
+  if (!grouped_out && gates && gates_k > 1) shared += (size_t)Tk * d_out;
+  if (!grouped_in && dW && k > 1) shared += (size_t)Tk * d_in;
+  const bool spread = shared >= ((size_t)24 << 20) && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES, spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1;
+  if (spread) {
     rc = launch_invert(s, r->sorted_scattered_idxs, inv, nullptr, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
   }
@@ -372,9 +372,17 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
     a.tail_ws = (float *)((char *)ws + need - S2S_TAIL_WS_BYTES);
     rc = run_s2s(ctx, s, dtype, a);
     if (rc != SMOE_OK) return rc;
-    if (need_sum) rc = launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in);
+    if (need_sum) rc = launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in, more0, more1);
   }
   return rc;
+}
+
+int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dY, const void *X, int x_rows,
+                     int d_in, const void *W, int d_out, const void *Yhat, const smoe_routing *r, int k,
+                     const float *gates, int gates_k, int grouped_in, int grouped_out, void *dX, void *dW,
+                     float *dgates, void *ws, size_t ws_bytes) {
+  return plinear_bwd(ctx, stream, dtype, dY, X, x_rows, d_in, W, d_out, Yhat, r, k, gates, gates_k, grouped_in, grouped_out, dX, dW, dgates,
+                     ws, ws_bytes, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------------------ Alg. 3
@@ -385,10 +393,11 @@ static inline int hidden_width(smoe_act act, int d_expert) { return act == SMOE_
 // (when the activation is applied in the product's epilogue it is otherwise never stored).
 static int hidden_forward(smoe_ctx *ctx, hipStream_t s, smoe_dtype dtype, smoe_act act, const void *X, int d_model,
                           int d_expert, const void *W1, const smoe_routing *r, int k, void *Hpre, bool keep_hpre, void *H,
-                          float *tail_ws) {
+                          float *tail_ws, size_t call_weights) {
   const int d_h = hidden_width(act, d_expert);
   S2SArgs a1 = make_s2s(X, W1, Hpre, r, d_model, d_h, false, false, k, true);
   a1.tail_ws = tail_ws;
+  a1.call_weights = call_weights;
   S2SArgs fused = a1;
   fused.H = H;
   set_launch(ctx, fused);
@@ -432,7 +441,7 @@ int smoe_plinear_act_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act
   float *tail_ws = (float *)((char *)ws + need - S2S_TAIL_WS_BYTES);
   void *pre = Hpre ? Hpre : ws;
   if (!aligned16(X) || !aligned16(W1) || !aligned16(H) || !aligned16(pre)) return SMOE_ERR_UNSUPPORTED;
-  return hidden_forward(ctx, (hipStream_t)stream, dtype, act, X, d_model, d_expert, W1, r, k, pre, Hpre != nullptr, H, tail_ws);
+  return hidden_forward(ctx, (hipStream_t)stream, dtype, act, X, d_model, d_expert, W1, r, k, pre, Hpre != nullptr, H, tail_ws, 0);
 }
 
 size_t smoe_mlp_fwd_workspace_bytes(smoe_dtype dtype, smoe_act act, int T, int k, int d_model, int d_expert,
@@ -474,11 +483,13 @@ int smoe_mlp_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
       !aligned16(saved_H) || !aligned16(saved_Yhat))
     return SMOE_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  int rc = hidden_forward(ctx, s, dtype, act, X, d_model, d_expert, W1, r, k, saved_Hpre, nsaved != 0, saved_H, tail_ws);
+  const size_t call_weights = (size_t)r->E * d_model * (d_h + d_expert) * es;
+  int rc = hidden_forward(ctx, s, dtype, act, X, d_model, d_expert, W1, r, k, saved_Hpre, nsaved != 0, saved_H, tail_ws, call_weights);
   if (rc != SMOE_OK) return rc;
   // Y = ParallelLinear(H, W2, p, grouped -> scattered)
   S2SArgs a2 = make_s2s(saved_H, W2, saved_Yhat, r, d_expert, d_model, false, true, 1, false);
   a2.tail_ws = tail_ws;
+  a2.call_weights = call_weights;
   rc = run_s2s(ctx, s, dtype, a2);
   if (rc != SMOE_OK) return rc;
   return launch_combine(s, dtype, saved_Yhat, gates, Y, T, k, d_model);
@@ -494,9 +505,11 @@ int smoe_mlp_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
 //   mode 2 (other activations): dp from the saved H; scratch = the weighted sorted copy of dY or, when d_expert < d_model
 //     makes them the smaller tensor, the plain sorted copy plus the routing-weighted hidden rows Hw [Tk,d_expert] that let
 //     groupXTY form dW2 from the plain copy; dH [Tk,d_expert]; dHpre [Tk,d_h].
-//   both: the sorted routing weights [Tk], the inverse of the order indices [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
+//   both: the sorted routing weights [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
+// The inverse of the order indices sits where the slabs come to lie while dY is spread, and again, written by the kernel that
+// adds the slabs, in the dead sorted weights while X is.
 struct MlpBwdEpiLayout {
-  size_t dybar_u, second, dh, dhpre, gsorted, inv, dp_part, total;
+  size_t dybar_u, second, dh, dhpre, gsorted, dp_part, total;
   int part_ld;
   bool use_hw;
 };
@@ -510,7 +523,6 @@ static MlpBwdEpiLayout mlp_bwd_epi_layout(int mode, size_t es, size_t Tk, int d_
   L.dh = off;       off += mode == 2 ? align256(Tk * (size_t)d_expert * es) : 0;
   L.dhpre = off;    off += align256(Tk * (size_t)d_h * es);
   L.gsorted = off;  off += align256(Tk * sizeof(float));
-  L.inv = off;      off += align256(Tk * sizeof(int32_t));
   L.dp_part = off;  off += align256(Tk * (size_t)L.part_ld * sizeof(float));
   L.total = off + S2S_TAIL_WS_BYTES;
   return L;
@@ -591,15 +603,15 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     float *tail_ws = (float *)(base + L.total - S2S_TAIL_WS_BYTES);
     // The W2^T product gathers the rows of dY itself (Alg. 1's scattered input, fan-out k); groupXTY needs sorted rows, so
     // one sorted copy is made for it: the routing-weighted one, or the plain one when the weights go into Hw instead.
-    int32_t *inv = (int32_t *)(base + L.inv);
+    int32_t *inv_y = (int32_t *)dp_part, *inv_x = (int32_t *)gsorted;
     const bool spread = k > 1;   // the order indices are walked for the sorted weights anyway
-    auto sorted_copy = [&](const void *rows, const float *weights, void *out) {
+    auto sorted_copy = [&](const void *rows, const int32_t *inv, const float *weights, void *out) {
       return spread ? launch_spread(s, rows, inv, k, weights, out, Tk, d_model)
                     : launch_group(s, dtype, rows, r->sorted_scattered_idxs, k, weights, out, Tk, d_model);
     };
-    rc = launch_invert(s, r->sorted_scattered_idxs, spread ? inv : nullptr, gates, gsorted, Tk);
+    rc = launch_invert(s, r->sorted_scattered_idxs, spread ? inv_y : nullptr, gates, gsorted, Tk);
     if (rc != SMOE_OK) return rc;
-    rc = sorted_copy(dY, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
+    rc = sorted_copy(dY, inv_y, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
     if (rc != SMOE_OK) return rc;
     S2SArgs x2 = make_s2s(dY, W2, mode == 1 ? dHpre : dH, r, d_expert, d_model, true, false, k, true);
     if (mode == 1) {
@@ -613,7 +625,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     set_launch(ctx, x2);
     rc = launch_s2s_stream(s, x2);
     if (rc != SMOE_OK) return rc;
-    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, Tk);
+    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, spread ? inv_x : nullptr, Tk);
     if (rc != SMOE_OK) return rc;
     if (mode == 2) {
       rc = launch_act_bwd(s, act, saved_Hpre, dH, dHpre, Tk, d_expert);
@@ -625,7 +637,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     rc = run_dw(ctx, s, dtype, w2);
     if (rc != SMOE_OK) return rc;
     void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead: its array holds Xbar, then dXbar
-    rc = sorted_copy(X, nullptr, Xbar);
+    rc = sorted_copy(X, inv_x, nullptr, Xbar);
     if (rc != SMOE_OK) return rc;
     DWArgs w1{Xbar, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
     w1.split_ws = tail_ws;
@@ -705,12 +717,12 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
 // ------------------------------------------------------------------------------ Alg. 4
 namespace {
 struct MomhaSizes {
-  size_t kv, q, lse, yhat, x, inv;   // bytes, each rounded up to 256
+  size_t kv, q, lse, yhat, x;   // bytes, each rounded up to 256
 };
 MomhaSizes momha_sizes(int B, int T, int k, int d_model, int h_expert, int d_head) {
   size_t N = (size_t)B * T, Tk = N * k, d_out = (size_t)h_expert * d_head;
   return MomhaSizes{align256(N * d_out * 2), align256(Tk * d_out * 2), align256(Tk * h_expert * sizeof(float)),
-                    align256(Tk * d_model * 2), align256(N * d_model * 2), align256(Tk * sizeof(int32_t))};
+                    align256(Tk * d_model * 2), align256(N * d_model * 2)};
 }
 int momha_args_ok(smoe_ctx *ctx, smoe_dtype dtype, int B, int T, int d_model, int h_expert, int d_head,
                   const smoe_routing *r, int k) {
@@ -811,9 +823,9 @@ size_t smoe_momha_bwd_workspace_bytes(int B, int T, int k, int d_model, int h_ex
   if (B < 1 || T < 1 || k < 1 || d_model < 1 || h_expert < 1 || d_head < 1) return 0;
   MomhaSizes z = momha_sizes(B, T, k, d_model, h_expert, d_head);
   // dense offsets, dOhat, dQ, dK, dV, three partial dX, delta, and the ParallelLinear backward scratch
-  // (a grouped [Tk, d_model] and a grouped [Tk, d_out] array and the inverse order indices, used by both projections in turn)
+  // (a grouped [Tk, d_model] and a grouped [Tk, d_out] array, used by both projections in turn)
   return 256 + 2 * z.q + 2 * z.kv + 3 * z.x + smoe_attention_bwd_workspace_bytes(B, T, k, h_expert) + z.yhat + z.q +
-         z.inv + S2S_TAIL_WS_BYTES;
+         S2S_TAIL_WS_BYTES;
 }
 
 int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO, const void *X, int B, int T,
@@ -842,8 +854,8 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   void *dXv = p;    p += z.x;
   void *attn_ws = p;  p += smoe_attention_bwd_workspace_bytes(B, T, k, h_expert);
   void *sub = p;
-  const size_t sub_bytes = z.yhat + z.q + z.inv + S2S_TAIL_WS_BYTES;
-  float *tail_ws = (float *)((char *)sub + z.yhat + z.q + z.inv);   // where the ParallelLinear backward puts its own, too
+  const size_t sub_bytes = z.yhat + z.q + S2S_TAIL_WS_BYTES;
+  float *tail_ws = (float *)((char *)sub + z.yhat + z.q);   // where the ParallelLinear backward puts its own, too
   hipStream_t s = (hipStream_t)stream;
   rc = launch_dense_offsets(s, dense_off, N);
   if (rc != SMOE_OK) return rc;
@@ -853,13 +865,9 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   if (rc != SMOE_OK) return rc;
   rc = launch_attn_bwd(s, saved_Q, saved_K, saved_V, saved_Ohat, dOhat, saved_LSE, attn_ws, dQ, dK, dV, B, T, k, h_expert);
   if (rc != SMOE_OK) return rc;
-  // query projection (Alg. 2 without p, scattered in with fan-out k, scattered out): dX part, dW_Q
-  rc = smoe_plinear_bwd(ctx, stream, dtype, dQ, X, N, d_model, W_Q, d_out, nullptr, r, k, nullptr, 0, 0, 0, dXq, dW_Q,
-                        nullptr, sub, sub_bytes);
-  if (rc != SMOE_OK) return rc;
   // dense key / value projections
   DWArgs wk{X, dK, dW_K, dense_off, 1, N, d_model, d_out}, wv{X, dV, dW_V, dense_off, 1, N, d_model, d_out};
-  wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q + z.inv);
+  wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q);
   rc = run_dw_pair(ctx, s, wk, wv);
   if (rc != SMOE_OK) return rc;
   S2SArgs xk = dense_s2s(dK, W_K, dXk, dense_off, N, d_model, d_out, true);
@@ -867,6 +875,11 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   xk.tail_ws = xv.tail_ws = tail_ws;
   rc = run_s2s_pair(ctx, s, xk, xv);
   if (rc != SMOE_OK) return rc;
+  // query projection (Alg. 2 without p, scattered in with fan-out k, scattered out): dW_Q, and dX = its part + dXk + dXv
+  const bool in_sum = k > 1;   // added where the k slots are summed
+  rc = plinear_bwd(ctx, stream, dtype, dQ, X, N, d_model, W_Q, d_out, nullptr, r, k, nullptr, 0, 0, 0, in_sum ? dX : dXq, dW_Q, nullptr, sub,
+                   sub_bytes, in_sum ? dXk : nullptr, in_sum ? dXv : nullptr);
+  if (rc != SMOE_OK || in_sum) return rc;
   return launch_add3(s, dXq, dXk, dXv, dX, (size_t)N * d_model);
 }
 

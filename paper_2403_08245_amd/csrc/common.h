@@ -76,8 +76,9 @@ int launch_route(hipStream_t s, const int32_t *expert_idxs, int Tk, int E, int32
 // ---- elementwise.hip
 int launch_act_fwd(hipStream_t s, smoe_act act, const void *Hpre, void *H, int rows, int d_expert);
 int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH, void *dHpre, int rows, int d_expert);
-// Y[t] = sum_j g[t*k+j] * Yhat[t*k+j]; g == nullptr means all ones.
-int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d);
+// Y[t] = sum_j g[t*k+j] * Yhat[t*k+j] (+ more0[t] + more1[t], both or neither); g == nullptr means all ones.
+int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d, const void *more0 = nullptr,
+                   const void *more1 = nullptr);
 // out[i] = g[o[i]] * in[o[i] / fan]; g == nullptr means all ones
 int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o, int fan, const float *g,
                  void *out, int Tk, int d);
@@ -85,9 +86,9 @@ int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o,
 int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk);
 // the copy launch_group makes of bf16 rows, by the inverse of the order indices: Tk / fan source rows, each read once
 int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d);
-// dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even): finishes the routing-weight gradient left in slabs by the fused
+// dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even), and inv[o[i]] = i unless inv is NULL: finishes the routing-weight gradient left in slabs by the fused
 // backward epilogues.
-int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int Tk);
+int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk);
 // dg[s] = <dY[s / kp], Yhat[s]>
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 
@@ -109,6 +110,10 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   int grid = 256;     // blocks of the persistent kernel (smoe_ctx::stream_grid)
   int tile_shape = 0; // persistent scatter2scatter tiles: 0 chosen by size, 1 128 x 256 only, 2 256 x 256 only (smoe_ctx::tile_shape)
   int group_m = 4;    // tiles are numbered in groups of this many M-tiles x all N-tiles (smoe_ctx::group_m)
+  // Bytes of all the weights that the call reads, this product's among them (0: only this product's).  More than the
+  // last-level cache holds will not be there when the call is repeated, and launches that read each weight about once then
+  // read them past the caches.
+  size_t call_weights = 0;
   // Optional second dense product of the same sizes in the same launch (persistent kernels, no order indices, no fused
   // activation; E = 2, both segments Tk / 2 rows): segment 1 reads A2 and W2 and writes C2, which point to where segment
   // 0's numbering would have them (pair_with sets them).
@@ -161,6 +166,10 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both 
   RowMap a_map{nullptr, 1}, b_map{nullptr, 1};
   const float *gates = nullptr;
 };
+constexpr size_t LAST_LEVEL_CACHE = (size_t)256 << 20;
+static inline bool weights_pass_caches(const S2SArgs &a) {
+  return (a.call_weights ? a.call_weights : (size_t)a.E * a.K * a.N * 2) > LAST_LEVEL_CACHE;
+}
 int launch_s2s_plain(hipStream_t s, smoe_dtype dt, const S2SArgs &a);
 int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a);
 bool s2s_mfma_supported(const S2SArgs &a);

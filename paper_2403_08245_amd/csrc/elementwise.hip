@@ -113,11 +113,13 @@ __global__ void __launch_bounds__(256) act_bwd_kernel(const T *__restrict__ Hpre
   }
 }
 
-// ---- weighted sum over a token's k slots: Y[t] = sum_j g[t*k+j] * Yhat[t*k+j]  (g may be null = 1)
+// ---- weighted sum over a token's k slots: Y[t] = sum_j g[t*k+j] * Yhat[t*k+j] + more[0][t] + more[1][t]  (g may be null = 1,
+// and both arrays of `more`)
 // Bound by HBM (the k slot rows are read once).  K > 0: k known, all slot rows of a chunk in flight at once.
 template <typename T, int K>
 __global__ void __launch_bounds__(256) combine_kernel(const T *__restrict__ Yhat, const float *__restrict__ g,
-                                                      T *__restrict__ Y, int T_rows, int k_any, int d, RowLanes l) {
+                                                      T *__restrict__ Y, int T_rows, int k_any, int d, RowLanes l,
+                                                      const T *__restrict__ more0, const T *__restrict__ more1) {
   constexpr int V = 16 / sizeof(T);
   const int k = K ? K : k_any;
   const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
@@ -146,6 +148,13 @@ __global__ void __launch_bounds__(256) combine_kernel(const T *__restrict__ Yhat
 #pragma unroll
           for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, a[i], acc[i]);
         }
+      }
+      if (more0) {
+        float a[V], b[V];
+        load_vec<T>(more0 + t * d + c, a);
+        load_vec<T>(more1 + t * d + c, b);
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] += a[i] + b[i];
       }
       store_vec<T>(Y + t * d + c, acc);
     }
@@ -224,17 +233,21 @@ __global__ void __launch_bounds__(256) spread_kernel(const bf16_t *__restrict__ 
   }
 }
 
-// ---- dg[o[i]] = sum_c part[i, c]: eight lanes per sorted row, each adds the pairs of slabs lane, lane + 8, ... in ascending
+// ---- dg[o[i]] = sum_c part[i, c] (and inv[o[i]] = i, inv may be null): eight lanes per sorted row, each adds the pairs of slabs lane, lane + 8, ... in ascending
 // order, then a fixed tree (a thread per row read its 448 bytes at a stride: 23 us for 32768 rows of 112 slabs)
 __global__ void __launch_bounds__(256) dp_reduce_kernel(const float2 *__restrict__ part, int ld2, const int32_t *__restrict__ o,
-                                                        float *__restrict__ dg, int Tk) {
+                                                        float *__restrict__ dg, int32_t *__restrict__ inv, int Tk) {
   const int i = blockIdx.x * 32 + ((int)threadIdx.x >> 3), lane = (int)threadIdx.x & 7;
   const float2 *p = part + (size_t)min(i, Tk - 1) * ld2;
   float acc = 0.f;
   for (int c = lane; c < ld2; c += 8) acc += p[c].x + p[c].y;
 #pragma unroll
   for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0 && i < Tk) dg[o[i]] = acc;
+  if (lane == 0 && i < Tk) {
+    const int slot = o[i];
+    dg[slot] = acc;
+    if (inv) inv[slot] = i;
+  }
 }
 
 // ---- dg[s] = <dY[s / kp], Yhat[s]> : one wavefront per slot, lanes stride the row.
@@ -297,26 +310,29 @@ int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH
 }
 
 template <typename T, int K>
-static void combine_k(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, RowLanes l, int blocks) {
-  hipLaunchKernelGGL((combine_kernel<T, K>), dim3(blocks), dim3(l.lanes * l.rows), 0, s, (const T *)Yhat, g, (T *)Y, T_rows, k, d, l);
+static void combine_k(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, RowLanes l, int blocks,
+                      const void *more0, const void *more1) {
+  hipLaunchKernelGGL((combine_kernel<T, K>), dim3(blocks), dim3(l.lanes * l.rows), 0, s, (const T *)Yhat, g, (T *)Y, T_rows, k, d, l,
+                     (const T *)more0, (const T *)more1);
 }
 template <typename T>
-static int combine_t(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d) {
+static int combine_t(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, const void *m0, const void *m1) {
   if (!vec_ok<T>(d)) return SMOE_ERR_UNSUPPORTED;
   if (T_rows < 1) return SMOE_OK;
   const RowLanes l = row_lanes(d / (16 / (int)sizeof(T)));
   const int blocks = row_blocks(T_rows, l.rows);
   switch (k) {
-    case 2: combine_k<T, 2>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
-    case 4: combine_k<T, 4>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
-    case 8: combine_k<T, 8>(s, Yhat, g, Y, T_rows, k, d, l, blocks); break;
-    default: combine_k<T, 0>(s, Yhat, g, Y, T_rows, k, d, l, blocks);
+    case 2: combine_k<T, 2>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
+    case 4: combine_k<T, 4>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
+    case 8: combine_k<T, 8>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
+    default: combine_k<T, 0>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1);
   }
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
-int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d) {
-  return dt == SMOE_BF16 ? combine_t<bf16_t>(s, Yhat, g, Y, T, k, d) : combine_t<float>(s, Yhat, g, Y, T, k, d);
+int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *g, void *Y, int T, int k, int d, const void *more0,
+                   const void *more1) {
+  return dt == SMOE_BF16 ? combine_t<bf16_t>(s, Yhat, g, Y, T, k, d, more0, more1) : combine_t<float>(s, Yhat, g, Y, T, k, d, more0, more1);
 }
 
 template <typename T>
@@ -359,10 +375,10 @@ int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, co
   return SMOE_OK;
 }
 
-int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int Tk) {
+int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk) {
   if (!Tk) return SMOE_OK;
   if (ld % 2) return SMOE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(dp_reduce_kernel, dim3(ceil_div(Tk, 32)), dim3(256), 0, s, (const float2 *)part, ld / 2, o, dg, Tk);
+  hipLaunchKernelGGL(dp_reduce_kernel, dim3(ceil_div(Tk, 32)), dim3(256), 0, s, (const float2 *)part, ld / 2, o, dg, inv, Tk);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

@@ -50,7 +50,7 @@ def test_row_kernels_in_the_mlp(smoe, d_model, k, act):
 def test_sorted_copies_spread_from_the_source_rows(smoe, k):
     """The weight gradient of a product large enough for its operands to be spread, next to half of its rows (grouped)."""
     E, d = 5, 1024
-    full = (8 << 20) // d // k + 1
+    full = (24 << 20) // (2 * d) // k + 1
     for T in (full, full // 2):
         print("spread", T, k, flush=True)
         gen = torch.Generator(device="cuda").manual_seed(7)
