@@ -7,8 +7,8 @@
 // from memory straight to registers: a lane loads 8 rows x 8 columns (16 bytes of each row, 256 bytes per row and sixteen
 // lanes) and turns them into the operands of eight 16x16x32 matrix instructions with one byte permutation per register,
 // operand j holding column j of every lane's eight.  No LDS traffic, no barrier and no swizzle in the loop, and DEPTH steps of
-// 8 KB per wavefront in flight.  Weights are read once, so they pass the caches by (64 experts, 2048 -> 2 x 512: 53 -> 47 us;
-// only weights that a repeated call would still find in the last-level cache are a little dearer, 25 experts 24 -> 27 us).
+// 8 KB per wavefront in flight.  Weights are read once, so where a call's exceed the last-level cache they pass the caches by (64
+// experts, 2048 -> 2 x 512: 53 -> 47 us; weights that a repeated call would still find there are dearer, 25 experts 24 -> 27).
 // Before, one wavefront walked a 128-column tile's whole contraction through an LDS ring: 64 tokens on 64 experts, 2048 ->
 // 2 x 512 -> 2048, 57 + 29 us (4.7 TB/s); now 47 + 25 (5.7 and 5.4).  Four tokens (25 experts): 26 + 14 us; now 26 + 12.
 // Forward products only (W as stored); the gradients of such small batches use the large-tile kernels.
@@ -36,7 +36,7 @@ template <int J> __device__ __forceinline__ bf16x8 w_frag(const WStep &w) {
 
 // ACT 0: C = A W.  ACT 1 / 2: fused SwiGLU (a tile is 64 gate columns and the 64 up columns pairing with
 // them), keeping / not keeping the pre-activation.
-template <int ACT, bool SCATTER_OUT, int CW, int KW>
+template <int ACT, bool SCATTER_OUT, int CW, int KW, bool ONCE>
 __global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, int n_chunks) {
   __shared__ float s_part[KW][CW][32][64];     // one fragment's sums of every wavefront
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -74,7 +74,10 @@ __global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, 
     WStep w;
     const char *p = W + (size_t)(step * HK) * row_bytes;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w.row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p + (size_t)i * row_bytes + w_lane));
+    for (int i = 0; i < 8; ++i) {
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(p + (size_t)i * row_bytes + w_lane);
+      w.row[i] = ONCE ? __builtin_nontemporal_load(src) : *src;
+    }
     return w;
   };
   // Steps kw, kw + KW, ... are this wavefront's; requests past the last repeat it and are not used.
@@ -194,7 +197,9 @@ __global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, 
 template <int ACT, bool SCATTER_OUT, int CW, int KW> int launch_decode_as(hipStream_t s, const S2SArgs &a) {
   const int n_chunks = ACT ? ceil_div(a.N / 2, CW * DN / 2) : ceil_div(a.N, CW * DN);
   const long long m_bound = a.Tk / DM + a.E;           // >= sum_e ceil(n_e / 32)
-  hipLaunchKernelGGL((s2s_decode_kernel<ACT, SCATTER_OUT, CW, KW>), dim3((unsigned)(m_bound * n_chunks)), dim3(64 * CW * KW), 0, s, a, n_chunks);
+  const dim3 grid((unsigned)(m_bound * n_chunks)), block(64 * CW * KW);
+  if (weights_pass_caches(a)) hipLaunchKernelGGL((s2s_decode_kernel<ACT, SCATTER_OUT, CW, KW, true>), grid, block, 0, s, a, n_chunks);
+  else hipLaunchKernelGGL((s2s_decode_kernel<ACT, SCATTER_OUT, CW, KW, false>), grid, block, 0, s, a, n_chunks);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

@@ -822,11 +822,11 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
   const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
   const bool may_split = ACT == 0 && a.tail_ws;
   if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split))) {
-    // At most one tile row per expert: W is read about once, and more of it than half the 256 MB last-level cache would only
-    // push other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53; with reuse, 8192 rows and
-    // 8 experts, 1024 -> 5632: 113 us, past the caches 156).
+    // At most one tile row per expert: W is read about once, and where the call's weights exceed the last-level cache keeping
+    // its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53; with reuse,
+    // 8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156).
     if constexpr (!TRANS_W)
-      if ((long long)a.Tk <= (long long)a.E * Pair::TM && (long long)a.E * a.K * a.N * 2 > 128000000LL)
+      if ((long long)a.Tk <= (long long)a.E * Pair::TM && weights_pass_caches(a))
         return launch_s2s_one<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
     return launch_s2s_one<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
   }

@@ -49,12 +49,12 @@ def test_key_and_value_projections(smoe, B, T, d_model, h):
 
 
 def test_weights_read_past_the_caches(smoe):
-    """More than 128 MB of weights and at most one tile of rows per expert, empty experts among them."""
-    E, k, T, d_in, d_out = 24, 1, 1000, 1032, 2696
+    """More weights than the last-level cache holds and at most one tile of rows per expert, empty experts among them."""
+    E, k, T, d_in, d_out = 24, 1, 1000, 1032, 5640
     gen = torch.Generator(device="cuda").manual_seed(9)
     X = torch.randn(T, d_in, generator=gen, device="cuda").bfloat16()
     W = (torch.randn(E, d_in, d_out, generator=gen, device="cuda") * 0.03).bfloat16()
-    assert W.numel() * 2 > 128e6 and T * k <= 128 * E and T * k > 32 * E
+    assert W.numel() * 2 > 256 << 20 and T * k <= 128 * E and T * k > 32 * E
     logits = torch.randn(T, E, generator=gen, device="cuda")
     logits[:, 5:8] = -100.0
     ei, _ = smoe.topk_gate(logits, k)
