@@ -56,9 +56,10 @@ template <int NW> struct TileLoader {
 // the larger value of lanes l and l + 32, for both
 __device__ __forceinline__ float max_halves(float x) {
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  const unsigned int b = __builtin_bit_cast(unsigned int, x);
+  const unsigned int b = __float_as_uint(x);
   const u32x2 r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  return fmaxf(__builtin_bit_cast(float, r[0]), __builtin_bit_cast(float, r[1]));
+  const unsigned int low = r[0], high = r[1];   // scalars first: a bit cast of a vector's element reads element 0 whichever is named
+  return fmaxf(__uint_as_float(low), __uint_as_float(high));
 }
 
 // A operand, tile rows as matrix rows: lane -> row (lane % 32), columns 16*ks + 8*(lane/32) + 0..7

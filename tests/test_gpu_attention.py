@@ -44,6 +44,31 @@ def test_attention_forward(smoe, B, T, G, h):
     assert np.abs(L.cpu().numpy() - Lref).max() <= 2e-2        # log-sum-exp of O(10) scores from bf16 products
 
 
+@pytest.mark.parametrize("peak", [0, 1, 2, 3, 4, 5, 6, 7, 13, 30, 36])
+def test_attention_peaked_scores(smoe, peak):
+    """One key whose score exceeds all others by 113 (in units of the exponent, more than fp32's range holds), at every
+    position modulo 8 and in either tile of 32 keys: from that key's token on, O is its value row and the log-sum-exp its
+    score.  Scores are exact in fp32 (1280 / sqrt(128)); the log-sum-exp is then good to a few fp32 roundings of 163 (its
+    value in exp2 units), 4e-5, and is compared at 1e-3."""
+    _log(f"attention peaked key={peak}")
+    B, T, G, h = 1, 40, 2, 1
+    Q, K, V = torch.full((B, T, G, h, 128), 10.0).bfloat16(), torch.zeros(B, T, h, 128).bfloat16(), _bf16((B, T, h, 128), 3)
+    K[:, peak] = 1.0
+    dO = _bf16((B, T, G, h, 128), 4)
+    Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
+    O, L = smoe.attention_fwd(Qd, Kd, Vd)
+    f64 = lambda t: t.float().cpu().numpy().astype(np.float64)
+    Oref, Lref = oracle.attention_fwd(si.as_f64(Q), si.as_f64(K), si.as_f64(V))
+    assert np.isfinite(f64(O)).all() and np.isfinite(f64(L)).all()
+    assert _rel(f64(O), Oref) <= TOL[torch.bfloat16]
+    assert torch.equal(O.cpu()[:, peak:], V[:, peak].reshape(B, 1, 1, h, 128).expand(B, T - peak, G, h, 128))
+    assert np.abs(f64(L) - Lref).max() <= 1e-3
+    dQ, dK, dV = smoe.attention_bwd(dO.cuda(), Qd, Kd, Vd, O, L)
+    rv = oracle.attention_bwd(si.as_f64(dO), si.as_f64(Q), si.as_f64(K), si.as_f64(V))[2]
+    assert np.isfinite(f64(dQ)).all() and np.isfinite(f64(dK)).all()
+    assert _rel(f64(dV), rv) <= TOL[torch.bfloat16]
+
+
 @pytest.mark.parametrize("B,T,G,h", ATTN_SHAPES)
 def test_attention_backward(smoe, B, T, G, h):
     _log(f"attention bwd B={B} T={T} G={G} h={h}")
