@@ -841,6 +841,9 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
     return SMOE_ERR_INVALID_ARG;
   size_t need = smoe_momha_bwd_workspace_bytes(B, T, k, d_model, h_expert, d_head);
   if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need) return SMOE_ERR_WORKSPACE;
+  // what the two ParallelLinears' backward passes ask of their operands, asked before anything is enqueued
+  if (!aligned16(dO) || !aligned16(X) || !aligned16(saved_Ohat) || !aligned16(W_Q) || !aligned16(W_O) || !aligned16(dW_Q) || !aligned16(dW_O))
+    return SMOE_ERR_UNSUPPORTED;
   const int N = B * T, Tk = r->Tk, d_out = h_expert * d_head;
   MomhaSizes z = momha_sizes(B, T, k, d_model, h_expert, d_head);
   char *p = (char *)ws;
@@ -876,7 +879,7 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   rc = run_s2s_pair(ctx, s, xk, xv);
   if (rc != SMOE_OK) return rc;
   // query projection (Alg. 2 without p, scattered in with fan-out k, scattered out): dW_Q, and dX = its part + dXk + dXv
-  const bool in_sum = k > 1;   // added where the k slots are summed
+  const bool in_sum = k > 1 && aligned16(dX);   // added where the k slots are summed, whose kernel writes 16-byte lines
   rc = plinear_bwd(ctx, stream, dtype, dQ, X, N, d_model, W_Q, d_out, nullptr, r, k, nullptr, 0, 0, 0, in_sum ? dX : dXq, dW_Q, nullptr, sub,
                    sub_bytes, in_sum ? dXk : nullptr, in_sum ? dXv : nullptr);
   if (rc != SMOE_OK || in_sum) return rc;

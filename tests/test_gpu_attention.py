@@ -1,4 +1,5 @@
 """GPU parity of the attention kernels and of the SMoE attention layer (Alg. 4) against the fp64 oracle."""
+import ctypes
 import sys
 
 import numpy as np
@@ -232,3 +233,49 @@ def test_attention_is_deterministic(smoe):
     assert torch.equal(O1, O2) and torch.equal(L1, L2)
     for a, b in zip(g1, g2):
         assert torch.equal(a, b)
+
+
+def _raw_layer_backward(m, c, r, k, gates, B, T, h, buf, dO, X, dX, dW):
+    """smoe_momha_bwd with the caller's own dX and dW tensors; returns the status."""
+    d_model = c["X"].shape[1]
+    nb = m.lib.smoe_momha_bwd_workspace_bytes(B, T, k, d_model, h, 128)
+    ws = m._ws(nb, "cuda")
+    rc = r.c()
+    weights = [c[n].cuda() for n in ("W_K", "W_V", "W_Q", "W_O")]
+    dg = torch.full_like(gates, 7.0)
+    status = m.lib.smoe_momha_bwd(m.ctx(), m._stream(), m.BF16, m._p(dO), m._p(X), B, T, d_model, h, 128, *(m._p(w) for w in weights),
+                                  ctypes.byref(rc), k, m._p(gates), m._p(buf.K), m._p(buf.V), m._p(buf.Q), m._p(buf.Ohat),
+                                  m._p(buf.LSE), m._p(buf.Yhat), m._p(dX), *(m._p(w) for w in dW), m._p(dg), m._p(ws), nb)
+    torch.cuda.synchronize()
+    return status, dg
+
+
+@pytest.mark.parametrize("k", [1, 2])
+def test_momha_backward_pointers_off_16_byte_lines(smoe, k):
+    """dX may lie anywhere its elements can: the call writes it like an aligned one.  An X the sorted copies cannot read is
+    refused before anything is written."""
+    B, T, d_model, E, h = 1, 70, 64, 4, 1
+    _log(f"momha backward off 16-byte lines k={k}")
+    c = _layer_case(5, B, T, d_model, E, k, h)
+    ei, gates = smoe.topk_gate(c["logits"].cuda(), k)
+    r = smoe.route(ei, E)
+    X, dO = c["X"].cuda(), c["dO"].cuda()
+    args = [X] + [c[n].cuda() for n in ("W_K", "W_V", "W_Q", "W_O")]
+    _, buf = smoe.momha_fwd(*args, r, k, gates, B, T, h, 128)
+    want = smoe.momha_bwd(dO, *args, r, k, gates, B, T, h, 128, buf)
+    off = lambda t: torch.full((t.numel() + 8,), 7.0, dtype=t.dtype, device="cuda")[4:4 + t.numel()].view(t.shape)
+    empty = lambda: [torch.full_like(t, 7.0) for t in want[1:5]]
+    dX, dW = off(X), empty()
+    assert dX.data_ptr() % 16 == 8
+    status, dg = _raw_layer_backward(smoe, c, r, k, gates, B, T, h, buf, dO, X, dX, dW)
+    assert status == 0
+    for got, ref in zip([*dW, dg], want[1:]):
+        assert torch.equal(got, ref)
+    # the three parts of dX may be added in two steps here and in one there: one rounding to 8 bits more
+    assert float((dX.float() - want[0].float()).abs().max()) <= 2 ** -7 * float(want[0].float().abs().max())
+    X_off = off(X)
+    X_off.copy_(X)
+    dX, dW = torch.full_like(X, 7.0), empty()
+    status, dg = _raw_layer_backward(smoe, c, r, k, gates, B, T, h, buf, dO, X_off, dX, dW)
+    assert status == -2
+    assert all(bool((t == 7.0).all()) for t in [dX, dg, *dW]), "a refused call wrote to an output"
