@@ -70,38 +70,9 @@ __global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, 
   const char *W = (const char *)((const bf16_t *)a.W + (size_t)e * a.w_stride);
   const uint32_t w_lane = (uint32_t)(8 * q) * (uint32_t)a.ldw * 2u + (uint32_t)(have ? column(cw, c) : 0) * 2u;
   const size_t row_bytes = (size_t)a.ldw * 2;
-  auto load_w = [&](int step) {
-    WStep w;
-    const char *p = W + (size_t)(step * HK) * row_bytes;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const u32x4 *src = reinterpret_cast<const u32x4 *>(p + (size_t)i * row_bytes + w_lane);
-      w.row[i] = ONCE ? __builtin_nontemporal_load(src) : *src;
-    }
-    return w;
-  };
   // Steps kw, kw + KW, ... are this wavefront's; requests past the last repeat it and are not used.
   auto step_at = [&](int s) { return min(kw + s * KW, nh - 1); };
   const int mine = (nh - kw + KW - 1) / KW;
-  WStep w[DEPTH];
-#pragma unroll
-  for (int s = 0; s < DEPTH; ++s) w[s] = load_w(step_at(s));
-
-  const bf16_t *pa[2];                               // rows past the segment repeat its last row
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int i = min(row0 + m * 16 + c, row_end - 1);
-    const int src = a.a_map.o ? a.a_map.o[i] / a.a_map.fan : i;
-    pa[m] = (const bf16_t *)a.A + (size_t)src * a.K + q * 8;
-  }
-  bf16x8 x[DEPTH][2];
-  auto load_x = [&](int step, bf16x8 (&v)[2]) {
-    v[0] = *reinterpret_cast<const bf16x8 *>(pa[0] + step * HK);
-    if (two) v[1] = *reinterpret_cast<const bf16x8 *>(pa[1] + step * HK);
-  };
-#pragma unroll
-  for (int s = 0; s < DEPTH; ++s) load_x(step_at(s), x[s]);
-
   f32x4 acc[2][8];
 #pragma unroll
   for (int m = 0; m < 2; ++m)
@@ -123,15 +94,53 @@ __global__ void __launch_bounds__(64 * CW * KW, 2) s2s_decode_kernel(S2SArgs a, 
     multiply(std::integral_constant<int, 6>{}, ws, xs);
     multiply(std::integral_constant<int, 7>{}, ws, xs);
   };
-#pragma unroll 1
-  for (int s = 0; s < mine; s += DEPTH) {
+  auto contract = [&](auto past_caches) {
+    auto load_w = [&](int s) {
+      WStep w;
+      const char *p = W + (size_t)(step_at(s) * HK) * row_bytes;
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) {
-      if (s + u < mine) use(w[u], x[u]);
-      const int next = step_at(s + u + DEPTH);
-      w[u] = load_w(next);
-      load_x(next, x[u]);
+      for (int i = 0; i < 8; ++i) {
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(p + (size_t)i * row_bytes + w_lane);
+        w.row[i] = decltype(past_caches)::value ? __builtin_nontemporal_load(src) : *src;
+      }
+      return w;
+    };
+    WStep w[DEPTH];
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) w[s] = load_w(s);
+
+    const bf16_t *pa[2];                               // rows past the segment repeat its last row
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int i = min(row0 + m * 16 + c, row_end - 1);
+      const int src = a.a_map.o ? a.a_map.o[i] / a.a_map.fan : i;
+      pa[m] = (const bf16_t *)a.A + (size_t)src * a.K + q * 8;
     }
+    bf16x8 x[DEPTH][2];
+    auto load_x = [&](int step, bf16x8 (&v)[2]) {
+      v[0] = *reinterpret_cast<const bf16x8 *>(pa[0] + step * HK);
+      if (two) v[1] = *reinterpret_cast<const bf16x8 *>(pa[1] + step * HK);
+    };
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) load_x(step_at(s), x[s]);
+#pragma unroll 1
+    for (int s = 0; s < mine; s += DEPTH) {
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        if (s + u < mine) use(w[u], x[u]);
+        w[u] = load_w(s + u + DEPTH);
+        load_x(step_at(s + u + DEPTH), x[u]);
+      }
+    }
+  };
+  // An expert with more rows than one tile has its weights read again, by other blocks, which should find them in the caches (200
+  // tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass 116 us with all weights past the caches,
+  // 107 with none, 105 so).
+  if (ONCE && row_end - __builtin_amdgcn_readfirstlane(a.offsets[e]) <= DM) {
+    __asm__ volatile("" ::: "memory");   // keeps the compiler from folding the two forms into one, which drops the hint
+    contract(std::true_type{});
+  } else {
+    contract(std::false_type{});
   }
 
   // Sums over the contraction's shares, in their order.  Lane (c, q) holds row c of the fragment and, in element r of the

@@ -152,6 +152,7 @@ template <typename S, bool TRANS_W, bool KTAIL> struct S2SOps {
   uint32_t b_step;                   // bytes the W source moves per half-step
   int step, last;                    // half-step the next loads fetch; the contraction's last half-step
   int uwave;
+  int again;                         // S::ONCE: above 0 where the expert has further tiles, which read the same weights
   __device__ __forceinline__ void load(int I, uint32_t slot_lds) const {
     if (I < S::NLA) {
       uint32_t off = oa[I] + (uint32_t)step * (HK * 2);
@@ -161,8 +162,9 @@ template <typename S, bool TRANS_W, bool KTAIL> struct S2SOps {
       const int J = I - S::NLA;
       uint32_t off = ob[J] + (uint32_t)step * b_step;
       if (KTAIL && TRANS_W) off |= step == last ? tb[J] : 0u;
-      if (S::ONCE) load16_to_lds_once(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
-      else load16_to_lds_checked(win_b, off, slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024);
+      const uint32_t lds = slot_lds + S::A_BYTES + (uwave * NLD + J) * 1024;
+      if (S::ONCE) load16_to_lds_checked_or_once(win_b, off, lds, again);
+      else load16_to_lds_checked(win_b, off, lds);
     }
   }
   __device__ __forceinline__ bf16x8 frag_a(const char *tile, int base, int kk, int lane) const { return kc_frag(tile, base, kk, lane); }
@@ -280,6 +282,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
     ops.win_a = buffer_window((const bf16_t *)(second ? p->A2 : p->A) + (gathered ? 0 : (size_t)t.row0 * K),
                               (uint32_t)(gathered ? p->Tk / p->a_map.fan : min(S::TM, t.row_end - t.row0)) * row_bytes);
     ops.win_b = buffer_window((const bf16_t *)(second ? p->W2 : p->W) + (size_t)t.e * p->w_stride, (uint32_t)(TRANS_W ? N : K) * ldw_bytes);
+    if (S::ONCE) ops.again = t.row_end - __builtin_amdgcn_readfirstlane(s_off[t.e]) - S::TM;
     const int *idx = &s_idx[t.seq & 3][0];
 #pragma unroll
     for (int I = 0; I < S::NLA; ++I) {
@@ -822,9 +825,11 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
   const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
   const bool may_split = ACT == 0 && a.tail_ws;
   if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split))) {
-    // At most one tile row per expert: W is read about once, and where the call's weights exceed the last-level cache keeping
-    // its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53; with reuse,
-    // 8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156).
+    // At most one tile row per expert on average: most of W is read once, and where the call's weights exceed the last-level cache
+    // keeping its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53).  With
+    // reuse they belong there (8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156), so a tile of an expert that has
+    // several takes them the ordinary way (777 tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass
+    // 133 us with all of W past the caches, 129 with none, 125 so).
     if constexpr (!TRANS_W)
       if ((long long)a.Tk <= (long long)a.E * Pair::TM && weights_pass_caches(a))
         return launch_s2s_one<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);

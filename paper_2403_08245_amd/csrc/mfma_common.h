@@ -53,10 +53,11 @@ __device__ __forceinline__ void load16_to_lds_checked(int32x4 window, uint32_t b
   __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window)
                    : "memory", "m0");
 }
-// The same for bytes that nothing will read again: no cache keeps them.
-__device__ __forceinline__ void load16_to_lds_once(int32x4 window, uint32_t byte_off, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_addr), "v"(byte_off), "s"(window)
-                   : "memory", "m0");
+// The same with a wave-uniform choice: bytes that nothing will read again (`again` 0 or less) are kept by no cache.
+__device__ __forceinline__ void load16_to_lds_checked_or_once(int32x4 window, uint32_t byte_off, uint32_t lds_addr, int again) {
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, 0\n\ts_cbranch_scc1 1f\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds\n\ts_branch 2f\n"
+                   "1:\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds\n2:" ::"s"(lds_addr), "v"(byte_off), "s"(window), "s"(again)
+                   : "memory", "m0", "scc");
 }
 __device__ __forceinline__ void load4_to_lds(const void *gsrc, uint32_t lds_addr) {
   __asm__ volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");

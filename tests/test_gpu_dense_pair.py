@@ -65,3 +65,26 @@ def test_weights_read_past_the_caches(smoe):
         assert len(t) or 5 <= e < 8
         if len(t):
             assert_close(Y[t], (X[t].float() @ W[e].float()).cpu().numpy(), torch.bfloat16, f"Y of expert {e}")
+
+
+@pytest.mark.parametrize("T,d_in", [(1000, 1032), (700, 1056)], ids=["tiles", "decode"])
+def test_weights_of_a_popular_expert_among_those_read_past_the_caches(smoe, T, d_in):
+    """As above with half of the rows on one expert: its several tiles read its weights through the caches, the others' one
+    tile past them, in the same launch."""
+    E, k, d_out = 24, 1, 5640
+    print("popular", T, d_in, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    X = torch.randn(T, d_in, generator=gen, device="cuda").bfloat16()
+    W = (torch.randn(E, d_in, d_out, generator=gen, device="cuda") * 0.03).bfloat16()
+    assert W.numel() * 2 > 256 << 20 and (T > 32 * E or d_in % 32 == 0)
+    logits = torch.randn(T, E, generator=gen, device="cuda")
+    logits[:, 5:8] = -100.0
+    logits[::2, 3] = 100.0
+    ei, _ = smoe.topk_gate(logits, k)
+    r = smoe.route(ei, E)
+    Y, _ = smoe.plinear_fwd(X, W, r, k)
+    for e in range(E):
+        t = (ei[:, 0] == e).nonzero()[:, 0]
+        assert len(t) >= T // 2 if e == 3 else len(t) <= 128
+        if len(t):
+            assert_close(Y[t], (X[t].float() @ W[e].float()).cpu().numpy(), torch.bfloat16, f"Y of expert {e}")
