@@ -71,3 +71,24 @@ def test_sorted_copies_spread_from_the_source_rows(smoe, k):
 def test_decode_tiles_of_every_width(smoe, d_model, d_expert, act):
     print("decode", d_model, d_expert, act, flush=True)
     _mlp_all(smoe, si.custom("dec", T=40, d_model=d_model, d_expert=d_expert, E=64, k=8, act=act, dtype="bf16"), 73, backward=False)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 8, 9, 13])
+@pytest.mark.parametrize("d_out", [264, 8200, 16392], ids=["four-shares", "two-shares", "one-share"])
+def test_decode_contractions_of_every_remainder(smoe, steps, d_out):
+    """Contractions of few 32-row steps, shared by four, two and one wavefronts: shares of no step, of fewer than are asked for
+    ahead, and every remainder of the loop that keeps two in flight."""
+    T, E, d_in = 70, 8, 32 * steps
+    print("decode steps", steps, d_out, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(steps)
+    X = torch.randn(T, d_in, generator=gen, device="cuda").bfloat16()
+    W = (torch.randn(E, d_in, d_out, generator=gen, device="cuda") * 0.1).bfloat16()
+    logits = torch.randn(T, E, generator=gen, device="cuda")
+    logits[:40, 1] += 100.0                       # one expert with two row tiles
+    ei, _ = smoe.topk_gate(logits, 1)
+    r = smoe.route(ei, E)
+    Y, _ = smoe.plinear_fwd(X, W, r, 1)
+    for e in range(E):
+        t = (ei[:, 0] == e).nonzero()[:, 0]
+        if len(t):
+            assert_close(Y[t], (X[t].float() @ W[e].float()).cpu().numpy(), torch.bfloat16, f"Y of expert {e}")
