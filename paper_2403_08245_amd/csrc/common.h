@@ -110,13 +110,15 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   int grid = 256;     // blocks of the persistent kernel (smoe_ctx::stream_grid)
   int tile_shape = 0; // persistent scatter2scatter tiles: 0 chosen by size, 1 128 x 256 only, 2 256 x 256 only (smoe_ctx::tile_shape)
   int group_m = 4;    // tiles are numbered in groups of this many M-tiles x all N-tiles (smoe_ctx::group_m)
-  // Bytes of all the weights that the call reads, this product's among them (0: only this product's).  More than the
-  // last-level cache holds will not be there when the call is repeated, and launches that read each weight about once then
-  // read them past the caches.
+  // Bytes of all the weights that the call may read, of all its experts and of its other product too (0: only this product's).
+  // More than the last-level cache holds will not be there at the next call, and launches that read each weight about once then
+  // read them past the caches.  All experts count, also where a few tokens use a part of them: the next tokens use others (4 tokens
+  // on 64 experts, 157 of 402 MB read, the forward pass past the caches / through them: other tokens at every call 42.4 / 42.1 us,
+  // another layer of the same size at every call 43.1 / 48.7; only the very same tokens again are dearer, 42.9 / 37.8).
   size_t call_weights = 0;
   // Optional second dense product of the same sizes in the same launch (persistent kernels, no order indices, no fused
   // activation; E = 2, both segments Tk / 2 rows): segment 1 reads A2 and W2 and writes C2, which point to where segment
-  // 0's numbering would have them (pair_with sets them).
+  // 0's numbering would have them (run_s2s_pair in api.hip sets them).
   const void *A2 = nullptr, *W2 = nullptr;
   void *C2 = nullptr;
   // Optional fused SwiGLU of Alg. 3 (forward, expert-sorted output only): W's columns are
@@ -187,7 +189,7 @@ bool s2s_stream_swiglu_supported(const S2SArgs &a);
 bool s2s_stream_swiglu_bwd_supported(const S2SArgs &a);
 bool s2s_stream_dp_supported(const S2SArgs &a);
 int launch_s2s_stream(hipStream_t s, const S2SArgs &a);
-// Small-batch (decoding) forward products: 32-row tiles, one wavefront each, bound by the weight stream.
+// Small-batch (decoding) forward products: 32-row tiles of four wavefronts, bound by the weight stream.
 // Takes a.H like the persistent kernel (fused SwiGLU).
 bool s2s_decode_supported(const S2SArgs &a);
 int launch_s2s_decode(hipStream_t s, const S2SArgs &a);

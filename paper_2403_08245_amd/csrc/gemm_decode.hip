@@ -8,7 +8,7 @@
 // lanes) and turns them into the operands of eight 16x16x32 matrix instructions with one byte permutation per register,
 // operand j holding column j of every lane's eight.  No LDS traffic, no barrier and no swizzle in the loop, and DEPTH steps of
 // 8 KB per wavefront in flight.  Weights are read once, so where a call's exceed the last-level cache they pass the caches by (64
-// experts, 2048 -> 2 x 512: 53 -> 47 us; weights that a repeated call would still find there are dearer, 25 experts 24 -> 27).
+// experts, 2048 -> 2 x 512: 53 -> 47 us; S2SArgs::call_weights says which count).
 // Before, one wavefront walked a 128-column tile's whole contraction through an LDS ring: 64 tokens on 64 experts, 2048 ->
 // 2 x 512 -> 2048, 57 + 29 us (4.7 TB/s); now 47 + 25 (5.7 and 5.4).  Four tokens (25 experts): 26 + 14 us; now 26 + 12.
 // Forward products only (W as stored); the gradients of such small batches use the large-tile kernels.
@@ -244,6 +244,20 @@ template <int ACT, bool SCATTER_OUT> int launch_decode(hipStream_t s, const S2SA
 // The decoding regime: on average at most one 32-row tile per expert.  Gathered or expert-sorted input,
 // W as stored, any output order; widths as the 16-byte loads and stores need them, and rows of W that 24 of them fit a
 // lane's 32-bit offset.
+// The line at 32 rows per expert, forward pass of the layer in us, these kernels / the large tiles (uniform router, other tokens
+// at every call):
+//   8 experts, 1024 -> 2 x 2816 -> 1024: 8 rows 35 / 57, 24 rows 39 / 58, 32 rows 46 / 59, 64 rows 55 / 60, 96 rows 58 / 62;
+//   32 experts, 1024 -> 512 -> 1024: 8 rows 23 / 41, 32 rows 29 / 42, 64 rows 38 / 43, 96 rows 41 / 45;
+//   8 experts, 4096 -> 2 x 14336 -> 4096: 8 rows 434 / 581, 24 rows 476 / 594, 32 rows 644 / 597;
+//   16 experts, 4096 -> 2 x 1024 -> 4096: 8 rows 80 / 104, 20 rows 87 / 105, 24 rows 105 / 106, 32 rows 115 / 107;
+//   64 experts, 2048 -> 512 -> 2048: 8 rows 53 / 70, 20 rows 62 / 74, 24 rows 80 / 75, 32 rows 87 / 77;
+//   64 experts, 2048 -> 2 x 512 -> 2048: 8 rows 73 / 78, 18 rows 78 / 82, 22 rows 100 / 82, 32 rows 120 / 85;
+//   128 experts, the same: 8 rows 133 / 152, 18 rows 143 / 157, 22 rows 190 / 159, 32 rows 217 / 162.
+// So it is late for layers whose weights exceed the last-level cache and whose tiles are about one per compute unit: as soon as
+// one expert has more than 32 rows, some compute units get a second tile and the launch lasts longer by half.  A line drawn from
+// the number of experts expected above 32 rows and the tiles per compute unit won 1.3 to 1.6 times there, but lost where tiles are
+// fewer (24 experts, 3072 -> 1024 -> 3072, 25 rows: 84 -> 111) or contractions long (8 experts, 14336, 25 rows: 518 -> 588); where it
+// lies under uneven routing depends on counts that only the device has.  So it stays at a tile for the average expert.
 bool s2s_decode_supported(const S2SArgs &a) {
   if (a.trans_w || a.Tk <= 0 || a.E < 1 || (long long)a.Tk > (long long)DM * a.E) return false;
   if (a.K < HK || a.K % HK || a.N % 8 || a.ldw % 8 || a.ldw > (1 << 25)) return false;
