@@ -96,6 +96,7 @@ int smoe_create(smoe_ctx **out, int device) {
   if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(device) == hipSuccess) {
     rc = init_stream_kernels();
     if (rc == SMOE_OK) rc = init_mfma_kernels();
+    if (rc == SMOE_OK) rc = init_route_kernels();
     if (rc == SMOE_OK) rc = route_scratch_address(&c->route_scratch);
     if (hipSetDevice(prev) != hipSuccess && rc == SMOE_OK) rc = SMOE_ERR_HIP;
   }

@@ -65,11 +65,12 @@ int launch_dense_offsets(hipStream_t s, int32_t *off, int n);
 int launch_add3(hipStream_t s, const void *a, const void *b, const void *c, void *out, size_t n);
 int launch_topk_gate_bwd(hipStream_t s, const int32_t *idx, const float *gates, const float *dgates, int T, int E, int k,
                          float *dlogits);
-constexpr int ROUTE_MAX_E = 16384;   // the routing kernels keep one 4-byte counter per expert in LDS (64 KB without raising the limit)
+constexpr int ROUTE_MAX_E = 16384;   // the routing kernels keep one or two 4-byte counters per expert in LDS (up to 128 KB of 160)
 size_t route_workspace_bytes(int Tk, int E);
 // Static device scratch of smoe_route_noalloc: its size, and the address of the current device's copy.
 constexpr size_t ROUTE_SCRATCH_BYTES = (size_t)1 << 20;
 int route_scratch_address(int32_t **ptr);
+int init_route_kernels();            // with the context's device current
 int launch_route(hipStream_t s, const int32_t *expert_idxs, int Tk, int E, int32_t *sorted_e,
                  int32_t *sorted_s, int32_t *offsets, void *ws);
 

@@ -430,6 +430,21 @@ int route_scratch_address(int32_t **ptr) {
   return SMOE_OK;
 }
 
+// Raises the dynamic LDS limit of the kernels that pass 64 KB together with their static arrays (once per context): two counters
+// per expert, or one.
+int init_route_kernels() {
+  int rc = SMOE_OK;
+  auto raise = [&](const void *kernel, size_t bytes) {
+    if (rc == SMOE_OK && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) rc = SMOE_ERR_HIP;
+  };
+  raise((const void *)route_one_launch_kernel<64>, 65536);
+  raise((const void *)route_one_launch_kernel<256>, 65536);
+  raise((const void *)route_one_launch_kernel<ROUTE_CHUNK>, (size_t)2 * ROUTE_MAX_E * sizeof(int32_t));
+  raise((const void *)route_place_kernel, 65536);
+  raise((const void *)route_scan_kernel, (size_t)ROUTE_MAX_E * sizeof(int32_t));
+  return rc;
+}
+
 size_t route_workspace_bytes(int Tk, int E) {
   size_t nchunk = (size_t)ceil_div(Tk > 0 ? Tk : 1, ROUTE_CHUNK);
   return align256(nchunk * (size_t)E * sizeof(int32_t));
@@ -440,11 +455,13 @@ int launch_route(hipStream_t s, const int32_t *expert_idxs, int Tk, int E, int32
   const int nchunk = ceil_div(Tk > 0 ? Tk : 1, ROUTE_CHUNK);
   int32_t *counts = (int32_t *)ws;
   const size_t one = (size_t)E * sizeof(int32_t), hist = one * route_copies(E, ROUTE_CHUNK);
-  if (Tk <= ROUTE_ONE_LAUNCH && 2 * hist <= 65536) {
-    // a decoding batch fits one or four wavefronts, which start and meet sooner than sixteen (32 slots: 4.8 us with sixteen, 3.9 with four)
-    if (Tk <= 64)
+  // one chunk is always one launch, which leaves the scratch alone (up to 128 KB of LDS for two histograms)
+  if (nchunk == 1 || (Tk <= ROUTE_ONE_LAUNCH && 2 * hist <= 65536)) {
+    // a decoding batch fits one or four wavefronts, which start and meet sooner than sixteen (32 slots: 4.8 us with sixteen, 3.9 with
+    // four); beyond 8192 experts their walk over the experts takes longer than the slots do
+    if (Tk <= 64 && E <= 8192)
       hipLaunchKernelGGL(route_one_launch_kernel<64>, dim3(1), dim3(64), 2 * one, s, expert_idxs, Tk, E, offsets, sorted_e, sorted_s);
-    else if (Tk <= 256)
+    else if (Tk <= 256 && E <= 8192)
       hipLaunchKernelGGL(route_one_launch_kernel<256>, dim3(1), dim3(256), 2 * one, s, expert_idxs, Tk, E, offsets, sorted_e, sorted_s);
     else
       hipLaunchKernelGGL(route_one_launch_kernel<ROUTE_CHUNK>, dim3(nchunk), dim3(ROUTE_CHUNK), 2 * hist, s, expert_idxs, Tk, E, offsets, sorted_e,
