@@ -2,6 +2,7 @@
 // sum over a token's k slots (Alg. 1), the `group` copy and the routing-weight gradient of
 // Alg. 2.  All read/write 16 bytes per lane when the row width allows it.
 #include "common.h"
+#include <type_traits>
 
 template <typename T> struct Vec16 { static constexpr int N = 16 / sizeof(T); T v[N]; } __attribute__((aligned(16)));
 
@@ -115,13 +116,14 @@ __global__ void __launch_bounds__(256) act_bwd_kernel(const T *__restrict__ Hpre
 
 // ---- weighted sum over a token's k slots: Y[t] = sum_j g[t*k+j] * Yhat[t*k+j] + more[0][t] + more[1][t]  (g may be null = 1,
 // and both arrays of `more`)
-// Bound by HBM (the k slot rows are read once).  K > 0: k known, all slot rows of a chunk in flight at once.
+// Bound by HBM (the k slot rows are read once): K rows are in flight at once, all of them up to k = 8, and past the caches.  65536
+// rows of 4 KB: k = 3 61.5 -> 54.5 us, 5 59.5 -> 52, 6 59.5 -> 50.5, 7 57 -> 50.5, 12 56 -> 49.5 (one row at a time, through the
+// caches, before); k = 2, 4 and 8 61, 53 and 50.
 template <typename T, int K>
 __global__ void __launch_bounds__(256) combine_kernel(const T *__restrict__ Yhat, const float *__restrict__ g,
-                                                      T *__restrict__ Y, int T_rows, int k_any, int d, RowLanes l,
+                                                      T *__restrict__ Y, int T_rows, int k, int d, RowLanes l,
                                                       const T *__restrict__ more0, const T *__restrict__ more1) {
   constexpr int V = 16 / sizeof(T);
-  const int k = K ? K : k_any;
   const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
   for (long long t = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); t < T_rows; t += (long long)gridDim.x * l.rows) {
     const T *in = Yhat + t * k * d;
@@ -130,25 +132,20 @@ __global__ void __launch_bounds__(256) combine_kernel(const T *__restrict__ Yhat
       float acc[V];
 #pragma unroll
       for (int i = 0; i < V; ++i) acc[i] = 0.f;
-      if constexpr (K > 0) {
+      auto add = [&](int j, const Vec16<T> &row) {
+        const float gj = gt ? gt[j] : 1.0f;
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, to_f32<T>(row.v[i]), acc[i]);
+      };
+      int j = 0;
+      for (; j + K <= k; j += K) {
         Vec16<T> rows[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) rows[j] = load_once<T>(in + (size_t)j * d + c);
+        for (int u = 0; u < K; ++u) rows[u] = load_once<T>(in + (size_t)(j + u) * d + c);
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-          const float gj = gt ? gt[j] : 1.0f;
-#pragma unroll
-          for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, to_f32<T>(rows[j].v[i]), acc[i]);
-        }
-      } else {
-        for (int j = 0; j < k; ++j) {
-          float a[V];
-          load_vec<T>(in + (size_t)j * d + c, a);
-          const float gj = gt ? gt[j] : 1.0f;
-#pragma unroll
-          for (int i = 0; i < V; ++i) acc[i] = fmaf(gj, a[i], acc[i]);
-        }
+        for (int u = 0; u < K; ++u) add(j + u, rows[u]);
       }
+      for (; j < k; ++j) add(j, load_once<T>(in + (size_t)j * d + c));
       if (more0) {
         float a[V], b[V];
         load_vec<T>(more0 + t * d + c, a);
@@ -209,7 +206,7 @@ __global__ void __launch_bounds__(256) invert_kernel(const int32_t *__restrict__
 
 // ---- spread: the copy `group` makes, from the side of the source: out[inv[t * fan + j]] = g[t * fan + j] * in[t].  Bound by the
 // write of the Tk rows; `group` read every source row fan times as well, from whichever XCD's L2 its sorted row fell to.
-template <int K>
+template <int K>   // fan where it is at most 8 (its stores then need no loop: k = 2 65 -> 63.5 us, k = 4 52.5 -> 51), else 0
 __global__ void __launch_bounds__(256) spread_kernel(const bf16_t *__restrict__ in, const int32_t *__restrict__ inv, int fan_any,
                                                      const float *__restrict__ g, bf16_t *__restrict__ out, int rows, int d, RowLanes l) {
   const int fan = K ? K : fan_any;
@@ -309,24 +306,30 @@ int launch_act_bwd(hipStream_t s, smoe_act act, const void *Hpre, const void *dH
   return SMOE_OK;
 }
 
-template <typename T, int K>
-static void combine_k(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, RowLanes l, int blocks,
-                      const void *more0, const void *more1) {
-  hipLaunchKernelGGL((combine_kernel<T, K>), dim3(blocks), dim3(l.lanes * l.rows), 0, s, (const T *)Yhat, g, (T *)Y, T_rows, k, d, l,
-                     (const T *)more0, (const T *)more1);
+// calls f with k as a constant, or 8 where it is larger
+template <typename F> static void with_rows(int k, F f) {
+  switch (k) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    default: f(std::integral_constant<int, 8>{});
+  }
 }
+
 template <typename T>
 static int combine_t(hipStream_t s, const void *Yhat, const float *g, void *Y, int T_rows, int k, int d, const void *m0, const void *m1) {
   if (!vec_ok<T>(d)) return SMOE_ERR_UNSUPPORTED;
   if (T_rows < 1) return SMOE_OK;
   const RowLanes l = row_lanes(d / (16 / (int)sizeof(T)));
   const int blocks = row_blocks(T_rows, l.rows);
-  switch (k) {
-    case 2: combine_k<T, 2>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
-    case 4: combine_k<T, 4>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
-    case 8: combine_k<T, 8>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1); break;
-    default: combine_k<T, 0>(s, Yhat, g, Y, T_rows, k, d, l, blocks, m0, m1);
-  }
+  with_rows(k, [&](auto rows) {
+    hipLaunchKernelGGL((combine_kernel<T, decltype(rows)::value>), dim3(blocks), dim3(l.lanes * l.rows), 0, s, (const T *)Yhat, g, (T *)Y, T_rows,
+                       k, d, l, (const T *)m0, (const T *)m1);
+  });
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
@@ -355,22 +358,17 @@ int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g,
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
-template <int K>
-static void spread_k(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int rows, int d, RowLanes l) {
-  hipLaunchKernelGGL(spread_kernel<K>, dim3(row_blocks(rows, l.rows)), dim3(l.lanes * l.rows), 0, s, (const bf16_t *)in, inv, fan, g,
-                     (bf16_t *)out, rows, d, l);
-}
 int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d) {
   if (!vec_ok<bf16_t>(d)) return SMOE_ERR_UNSUPPORTED;
   if (Tk < 1) return SMOE_OK;
   const RowLanes l = row_lanes(d / 8);
   const int rows = Tk / fan;
-  switch (fan) {
-    case 2: spread_k<2>(s, in, inv, fan, g, out, rows, d, l); break;
-    case 4: spread_k<4>(s, in, inv, fan, g, out, rows, d, l); break;
-    case 8: spread_k<8>(s, in, inv, fan, g, out, rows, d, l); break;
-    default: spread_k<0>(s, in, inv, fan, g, out, rows, d, l);
-  }
+  auto launch = [&](auto k) {
+    hipLaunchKernelGGL(spread_kernel<decltype(k)::value>, dim3(row_blocks(rows, l.rows)), dim3(l.lanes * l.rows), 0, s, (const bf16_t *)in, inv,
+                       fan, g, (bf16_t *)out, rows, d, l);
+  };
+  if (fan <= 8) with_rows(fan, launch);
+  else launch(std::integral_constant<int, 0>{});
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

@@ -22,7 +22,7 @@ def smoe():
 
 @pytest.mark.parametrize("act", [si.ACT_NONE, si.ACT_GELU, si.ACT_SWIGLU])
 @pytest.mark.parametrize("T,d_model,d_expert,E,k,masked", [(1, 4, 4, 1, 1, 0), (64, 32, 64, 1, 1, 0), (130, 28, 36, 2, 2, 0), (200, 36, 28, 3, 1, 0),
-                                                           (257, 68, 100, 5, 3, 2), (193, 128, 132, 70, 4, 10)])
+                                                           (257, 68, 100, 5, 3, 2), (193, 128, 132, 70, 4, 10), (40, 36, 32, 11, 9, 0)])
 def test_mlp_every_row(smoe, T, d_model, d_expert, E, k, masked, act):
     cfg = si.custom("f32-edges", T=T, d_model=d_model, d_expert=d_expert, E=E, k=k, act=act, dtype="f32", masked_experts=masked)
     case = si.mlp_case(cfg, 71)

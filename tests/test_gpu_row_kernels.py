@@ -46,6 +46,13 @@ def test_row_kernels_in_the_mlp(smoe, d_model, k, act):
     _mlp_all(smoe, si.custom("rows", T=67, d_model=d_model, d_expert=136, E=9, k=k, act=act, dtype="bf16"), 71)
 
 
+# numbers of slots with a kernel of their own (1 to 8), and above: batches of eight with and without rows left over
+@pytest.mark.parametrize("k", [5, 6, 7, 9, 16, 19])
+def test_row_kernels_for_every_number_of_slots(smoe, k):
+    print("slots", k, flush=True)
+    _mlp_all(smoe, si.custom("slots", T=37, d_model=104, d_expert=72, E=19, k=k, act=si.ACT_SWIGLU, dtype="bf16"), 79)
+
+
 @pytest.mark.parametrize("k", [3, 4])
 def test_sorted_copies_spread_from_the_source_rows(smoe, k):
     """The weight gradient of a product large enough for its operands to be spread, next to half of its rows (grouped)."""
