@@ -490,7 +490,9 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
   const int key = min(k0 + wave * 32 + (lane & 31), d.T - 1);
   const bool key_valid = k0 + wave * 32 + (lane & 31) < d.T;
   const int wave_key0 = k0 + uwave * 32;
-  const int wave_row0 = wave_key0 * d.G, first_row = key * d.G;   // first rows that see the wavefront's first key and the lane's key
+  // First rows that see the wavefront's first key, its last one and the lane's key.  Keys past the sequence (clamped, never stored)
+  // take no part, so no row number passes T * G: a product with a number of keys alone could pass 31 bits.
+  const int wave_row0 = min(wave_key0, d.T) * d.G, last_key_row = min(wave_key0 + 31, d.T - 1) * d.G, first_row = key * d.G;
 
   const size_t krow = ((size_t)b * d.T + key) * d.ldkv + hh * AD;
   // K fragments stay in registers; the V fragments are re-read from LDS at every use (keeping both
@@ -578,7 +580,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     }
     // rows of this tile that are earlier than the wavefront's last key, or past the end, are masked (wave-uniform): the key
     // neither receives from them nor sees what they hold
-    if (r0 < wave_row0 + 31 * d.G || r0 + AKT > rows) {
+    if (r0 < last_key_row || r0 + AKT > rows) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int r = r0 + acc_row(q, lane);
