@@ -68,3 +68,23 @@ def oracle_gates_f32(g):
 
 def dev(t):
     return t.cuda() if isinstance(t, torch.Tensor) else torch.from_numpy(np.ascontiguousarray(t)).cuda()
+
+
+def last_round_plan(segment_rows, tile_rows, N, K, contraction_steps_of_four):
+    """(whole tiles, leftover tiles, chunks per leftover tile) of the last round of a product with partial-tile scratch on 256
+    compute units, as the persistent kernels plan it: tiles of `tile_rows` x 256, two blocks per compute unit for the 128-row
+    ones; a contraction is cut when that saves at least 64 of its steps of 32."""
+    per_cu = 2 if tile_rows == 128 else 1
+    grid, nh = 256 * per_cu, -(-K // 32)
+    tiles = sum(-(-int(n) // tile_rows) for n in segment_rows) * (-(-N // 256))
+    rem, half = tiles % grid, grid // per_cu
+    whole = half if per_cu > 1 and rem > half else 0
+    rest = rem - whole
+    if rest:
+        for s in range(min(4, (grid - half if whole else grid) // rest), 1, -1):
+            chunk = -(-nh // s)
+            if contraction_steps_of_four:
+                chunk = (chunk + 3) & ~3
+            if (s - 1) * chunk < nh and nh - chunk >= 64:
+                return whole, rest, s
+    return whole, rest, 1

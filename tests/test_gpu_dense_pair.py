@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import smoe_inputs as si
-from helpers import assert_close, oracle_gates_f32, oracle_routing
+from helpers import assert_close, last_round_plan, oracle_gates_f32, oracle_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +46,43 @@ def test_key_and_value_projections(smoe, B, T, d_model, h):
     for got, want, name in ((buf.K, ref["K"], "K"), (buf.V, ref["V"], "V"), (O, ref["O"], "O"), (dX, gref["dX"], "dX"),
                             (dW_K, gref["dW_K"], "dW_K"), (dW_V, gref["dW_V"], "dW_V")):
         assert_close(got.reshape(want.shape), want, bf, name)
+
+
+@pytest.mark.parametrize("mode", [3, 4], ids=["tiles128", "tiles256"])
+@pytest.mark.parametrize("d_model,h,product", [(2840, 1, "forward"), (2816, 1, "forward"), (264, 22, "dX")])
+def test_key_and_value_products_with_a_split_contraction(mode, d_model, h, product):
+    """Both projections (their input gradients) in one launch whose contraction is cut into chunks: partial tiles of two segments,
+    added and stored by the second kernel to the right one's output."""
+    import paper_2403_08245_amd as m
+    B, T, E, k, N, d_out = 1, 200, 3, 2, 200, h * 128
+    K, width = (d_model, d_out) if product == "forward" else (d_out, d_model)
+    tile = 128 if mode == 3 else 256
+    whole, rest, chunks = last_round_plan([N, N], tile, width, K, mode == 4 and K % 128 == 0)
+    assert whole == 0 and chunks == 4, (whole, rest, chunks)
+    print("pair split", d_model, h, mode, flush=True)
+    gen = torch.Generator().manual_seed(6)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=gen) * std).bfloat16()
+    X, dO = rnd(N, d_model), rnd(N, d_model)
+    W_K, W_V = rnd(d_model, d_out, std=0.02), rnd(d_model, d_out, std=0.02)
+    W_Q, W_O = rnd(E, d_model, d_out, std=0.02), rnd(E, d_out, d_model, std=0.02)
+    logits = torch.randn(N, E, generator=gen)
+    ei, g, _, _, _ = oracle_routing(logits, k, E)
+    gi, gg = m.topk_gate(logits.cuda(), k)
+    r = m.route(gi, E)
+    args = [t.cuda() for t in (X, W_K, W_V, W_Q, W_O)]
+    m.set_kernel_mode(mode)
+    try:
+        _, buf = m.momha_fwd(*args, r, k, gg, B, T, h, 128)
+        dX = m.momha_bwd(dO.cuda(), *args, r, k, gg, B, T, h, 128, buf)[0]
+        torch.cuda.synchronize()
+    finally:
+        m.set_kernel_mode(0)
+    ref_args = [si.as_f64(t) for t in (X, W_K, W_V, W_Q, W_O)]
+    bf = torch.bfloat16
+    assert_close(buf.K, ref_args[0] @ ref_args[1], bf, "K")
+    assert_close(buf.V, ref_args[0] @ ref_args[2], bf, "V")
+    gref = oracle.momha_bwd(si.as_f64(dO), *ref_args, ei, oracle_gates_f32(g), B, T, h, 128)
+    assert_close(dX, gref["dX"], bf, "dX")
 
 
 def test_weights_read_past_the_caches(smoe):

@@ -1,7 +1,7 @@
 """GPU parity of the two tile shapes of the persistent scatter2scatter kernels (256 x 256 tiles with one block per compute
 unit, 128 x 256 with two) where they can go wrong: contractions that end inside a half-step of 32, the shortest ones they
 take, segments at and around the tile heights, outputs narrower than a tile, and launches whose last round is one tile per
-compute unit, splits its contraction, or both.  Every row is compared with the oracle; outputs and workspaces are poisoned
+compute unit, cuts its contraction into chunks (with an end inside a half-step and without), or both.  Every row is compared with the oracle; outputs and workspaces are poisoned
 and guard-banded (conftest.py)."""
 import numpy as np
 import pytest
@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import smoe_inputs as si
-from helpers import assert_close, oracle_gates_f32, oracle_routing
+from helpers import assert_close, last_round_plan, oracle_gates_f32, oracle_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -35,10 +35,10 @@ def _rows_at_tile_edges(T, E, k):
 CASES = [
     pytest.param(1500, 72, 264, 9, 1, id="K72-edges"),               # three half-steps, the last with 8 elements
     pytest.param(1500, 200, 96, 9, 1, id="K200-N96-edges"),
-    pytest.param(1500, 2056, 1032, 9, 1, id="K2056-edges-split"),    # last round of few tiles: contraction split, tail of 8
+    pytest.param(1500, 2056, 1032, 9, 1, id="K2056-edges"),          # last round of few tiles, contraction with a tail of 8
     pytest.param(700, 96, 72, 3, 2, id="K96-N72"),
     pytest.param(9000, 136, 1304, 5, 2, id="K136-N1304-rounds"),     # several tiles per block, 128-row and 256-row last rounds ragged
-    pytest.param(8500, 2832, 520, 8, 2, id="K2832-whole-and-split"),
+    pytest.param(8500, 2832, 520, 8, 2, id="K2832-N520"),
 ]
 
 
@@ -68,6 +68,45 @@ def test_plinear_every_row(smoe, T, d_in, d_out, E, k):
         assert_close(dW[:, rt, :], dW_ref, td, f"dW grouped_out={gout}")
         for name, t in (("Y", Y), ("dX", dX), ("dW", dW)):
             assert bool(torch.isfinite(t.float()).all()), f"{name} holds entries no kernel wrote"
+
+
+# Input gradients with partial-tile scratch (plinear_bwd): contraction d_out, output width d_in; tile rows, and what the last round
+# must plan (whole tiles, leftover tiles, chunks), so that a case cannot silently stop splitting.
+SPLIT_CASES = [
+    # 89 half-steps, the last with 24 elements; all tiles are leftovers
+    pytest.param(1500, 1032, 2840, 9, 128, (0, 75, 4), id="tiles128-K2840-edges"),
+    pytest.param(1500, 1032, 2840, 9, 256, (0, 50, 4), id="tiles256-K2840-edges"),
+    # a multiple of 128: chunks of the 256-row tiles are whole groups of four half-steps
+    pytest.param(1500, 1032, 2816, 9, 128, (0, 75, 4), id="tiles128-K2816-edges"),
+    pytest.param(1500, 1032, 2816, 9, 256, (0, 50, 4), id="tiles256-K2816-edges"),
+    # one 128-row tile on every compute unit and a few left over for the free halves of the grid
+    pytest.param(6700, 1032, 2840, 3, 128, (256, 14, 4), id="tiles128-K2840-whole-and-split"),
+    # a full round of 256-row tiles before the split one
+    pytest.param(8000, 2056, 2840, 3, 256, (0, 41, 4), id="tiles256-K2840-round-and-split"),
+]
+
+
+@pytest.mark.parametrize("T,d_in,d_out,E,tile,planned", SPLIT_CASES)
+@pytest.mark.parametrize("grouped_in", [False, True])
+def test_split_last_round_every_row(T, d_in, d_out, E, tile, planned, grouped_in):
+    import paper_2403_08245_amd as smoe
+    c = si.plinear_case(T, d_in, d_out, E, 1, "bf16", seed=53)
+    ei = _rows_at_tile_edges(T, E, 1) if E == 9 else oracle_routing(c["logits"], 1, E)[0]
+    se, o, off = oracle.route(ei, E)
+    assert last_round_plan(np.diff(off), tile, d_in, d_out, tile == 256 and d_out % 128 == 0) == planned
+    r = smoe.route(torch.from_numpy(ei).cuda(), E)
+    X, W, dY = c["X"].cuda(), c["W"].cuda(), c["dY_Tk"].cuda()
+    print("split", T, d_in, d_out, E, tile, grouped_in, np.diff(off).tolist(), flush=True)
+    rows = np.unique(np.concatenate([np.arange(0, d_in, 101), np.arange(max(0, d_in - 9), d_in)]))
+    smoe.set_kernel_mode(3 if tile == 128 else 4)
+    try:
+        dX, again = (smoe.plinear_bwd(dY, X, W, None, r, 1, None, grouped_in, False)[0] for _ in range(2))
+    finally:
+        smoe.set_kernel_mode(0)
+    dX_ref, _, _ = oracle.plinear_bwd(si.as_f64(c["dY_Tk"]), si.as_f64(c["X"])[:, rows], si.as_f64(c["W"])[:, rows, :], se, o, 1, None, grouped_in, False)
+    assert_close(dX[:, torch.from_numpy(rows).cuda()], dX_ref, torch.bfloat16, "dX")
+    assert bool(torch.isfinite(dX.float()).all()), "dX holds entries no kernel wrote"
+    assert torch.equal(dX, again)          # the chunks are added in a fixed order
 
 
 @pytest.mark.parametrize("act", [si.ACT_GELU, si.ACT_SWIGLU])
