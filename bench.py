@@ -389,9 +389,8 @@ def main():
     rc = r.c()
     d_h = cfg.d_h
     dt_code = smoe.BF16 if cfg.dtype == "bf16" else smoe.F32
-    fused = cfg.act == si.ACT_SWIGLU and cfg.dtype == "bf16" and cfg.d_model % 32 == 0 and cfg.d_model >= 96 and cfg.E <= 256
+    fused = cfg.act == si.ACT_SWIGLU and cfg.dtype == "bf16" and cfg.d_model % 8 == 0 and cfg.d_model > 64 and cfg.E <= 256
     decode = cfg.dtype == "bf16" and cfg.Tk <= 32 * cfg.E and cfg.d_model % 32 == 0
-    static4 = "true" if cfg.d_model % 128 == 0 else "false"
     if fused:
         ws_act = smoe._ws(smoe.lib.smoe_plinear_act_fwd_workspace_bytes(dt_code, cfg.act, cfg.T, cfg.k, cfg.d_model,
                                                                      cfg.d_expert, 1), dev)
@@ -399,17 +398,17 @@ def main():
         def s2s_once():
             smoe.plinear_act_fwd(X, W1, r, cfg.k, cfg.act, out=(buf.H, buf.Hpre), ws=ws_act)
 
-        kname = (f"s2s_stream_kernel<false,false,1,{static4}> (ParallelLinear #1 scattered->grouped with SwiGLU in its "
+        kname = ("s2s_stream_kernel, W as stored, sorted output, ACT 1 (ParallelLinear #1 scattered->grouped with SwiGLU in its "
                  "epilogue, as launched inside the step)")
         if decode:
-            kname = "s2s_decode_kernel<1,false> (ParallelLinear #1 with SwiGLU, small batch)"
+            kname = "s2s_decode_kernel, sorted output, ACT 1 (ParallelLinear #1 with SwiGLU, small batch)"
     else:
         def s2s_once():
             smoe._check(smoe.lib.smoe_plinear_fwd(smoe.ctx(), stream.cuda_stream, dt_code, X.data_ptr(), cfg.T, cfg.d_model,
                                                   W1.data_ptr(), d_h, ctypes.byref(rc), cfg.k, None, 0, 0, 1,
                                                   buf.Hpre.data_ptr(), None), "smoe_plinear_fwd")
 
-        kname = (f"s2s_stream_kernel<false,false,0,{static4}>" if cfg.dtype == "bf16" else "s2s_plain_kernel") + \
+        kname = ("s2s_stream_kernel, W as stored, sorted output, ACT 0" if cfg.dtype == "bf16" else "s2s_plain_kernel") + \
                 " (ParallelLinear #1, scattered->grouped)"
 
     ms_s2s = timed(s2s_once, reps)

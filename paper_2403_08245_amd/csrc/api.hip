@@ -321,7 +321,7 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
     a.slots = r->sorted_scattered_idxs;
     rc = launch_s2s_plain(s, dtype, a);
     if (rc != SMOE_OK || !need_sum) return rc;
-    return launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in);
+    return launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in, more0, more1);
   }
 
   // dp = bmm(dY, Yhat); dYbar = group(dY, o, p)  (Alg. 2: "weight and group")
