@@ -7,7 +7,7 @@
 // activation and its derivative sit in the epilogues instead of launches of their own, the tile search runs across the
 // lanes of a wavefront, row addresses are worked out once, and each 32-deep contraction step is loaded into registers while
 // the previous one is multiplied.  Before (scalar FMAs, 16-deep steps, an index and a row fetched per element) and now:
-// 256 tokens, 64 -> 128 -> 64, 4 experts: a product 14 to 26 us -> 6.5 to 9, a training step 157 us -> 74;
+// 256 tokens, 64 -> 128 -> 64, 4 experts: a product 14 to 26 us -> 6.5 to 9, a training step 160 us -> 78;
 // 1024 tokens, 256 -> 896 -> 256, 8 experts, k = 2, SwiGLU: forward 293 -> 63, backward 541 -> 136 us;
 // 8192 tokens, 512 -> 1024 -> 512: 35 -> 92 TFLOP/s forward (157 is the card's fp32 matrix rate).
 #include "mfma_common.h"
