@@ -36,6 +36,22 @@ int run_dw(smoe_ctx *ctx, hipStream_t s, smoe_dtype dt, DWArgs a) {
   return launch_dw_plain(s, dt, a);
 }
 
+// Do two arrays share memory?  (An output over an input that only an earlier launch reads is fine while these are launches of their
+// own, and not where one launch does it all.)
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return a && b && p < q + b_bytes && q < p + a_bytes;
+}
+// The parts of an fp32 backward pass that wait for nothing but their inputs: in one launch, or (`apart`) in the order row dots,
+// weight gradient, input gradient.
+int run_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d, bool apart) {
+  if (!apart) return launch_f32_backward(s, x, w, d);
+  int rc = d.dg ? launch_rowdot(s, SMOE_F32, d.dY, d.Yhat, d.dg, d.Tk, d.kp, d.d) : SMOE_OK;
+  if (rc == SMOE_OK && w.dW) rc = launch_dw_plain(s, SMOE_F32, w);
+  if (rc == SMOE_OK && x.C) rc = launch_s2s_plain(s, SMOE_F32, x);
+  return rc;
+}
+
 S2SArgs make_s2s(const void *A, const void *W, void *C, const smoe_routing *r, int d_in, int d_out, bool trans_w,
                  bool a_grouped, int a_fan, bool c_grouped) {
   S2SArgs a;
@@ -299,28 +315,23 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   if (dtype == SMOE_F32) {
     // The fp32 kernels read the rows of dY and X through the order indices and apply the routing weights themselves: no
     // sorted copies, and no launches to make them.
-    if (gates && dgates) {
-      rc = launch_rowdot(s, dtype, dY, Yhat, dgates, Tk, gates_k, d_out);
-      if (rc != SMOE_OK) return rc;
-    }
-    const RowMap x_map{grouped_in ? nullptr : r->sorted_scattered_idxs, k};
+    const RowDots d{dY, Yhat, gates ? dgates : nullptr, Tk, gates_k, d_out};
     const RowMap y_map{grouped_out ? nullptr : r->sorted_scattered_idxs, gates ? gates_k : 1};
-    if (dW) {
-      DWArgs a{X, dY, dW, r->expert_offsets, r->E, Tk, d_in, d_out};
-      a.a_map = x_map;
-      a.b_map = y_map;
-      a.gates = gates;
-      rc = launch_dw_plain(s, dtype, a);
-      if (rc != SMOE_OK) return rc;
-    }
-    if (!dX) return rc;
+    DWArgs w{X, dY, dW, r->expert_offsets, r->E, Tk, d_in, d_out};
+    w.a_map = RowMap{grouped_in ? nullptr : r->sorted_scattered_idxs, k};
+    w.b_map = y_map;
+    w.gates = gates;
     const bool need_sum = !grouped_in && k > 1;
-    void *dst = need_sum ? (void *)((char *)ws + off_xbar) : dX;
+    void *dst = need_sum && dX ? (void *)((char *)ws + off_xbar) : dX;
     S2SArgs a = make_s2s(dY, W, dst, r, d_in, d_out, true, grouped_out != 0, y_map.fan, grouped_in != 0);
     a.gates = gates;
     a.slots = r->sorted_scattered_idxs;
-    rc = launch_s2s_plain(s, dtype, a);
-    if (rc != SMOE_OK || !need_sum) return rc;
+    const size_t x_bytes = (size_t)x_rows * d_in * 4, w_bytes = (size_t)r->E * d_in * d_out * 4, dst_bytes = (size_t)Tk * d_in * 4;
+    const size_t yhat_bytes = d.dg ? (size_t)Tk * d_out * 4 : 0;
+    const bool apart = overlap(dst, dst_bytes, X, x_bytes) || overlap(dst, dst_bytes, Yhat, yhat_bytes) || overlap(dW, w_bytes, Yhat, yhat_bytes) || overlap(dst, dst_bytes, dgates, (size_t)Tk * 4) ||
+                       overlap(dst, dst_bytes, dW, w_bytes) || overlap(dW, w_bytes, d.dg, (size_t)Tk * 4);
+    rc = run_f32_backward(s, a, w, d, apart);
+    if (rc != SMOE_OK || !need_sum || !dX) return rc;
     return launch_combine(s, dtype, dst, nullptr, dX, x_rows, k, d_in, more0, more1);
   }
 
@@ -658,31 +669,32 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
   void *Xbar = dYbar;  // dYbar is dead once dH and dW2 are done; its array then holds Xbar, then dXbar
 
   // ---- second ParallelLinear (grouped in, scattered weighted out)
-  rc = launch_rowdot(s, dtype, dY, saved_Yhat, dgates, Tk, k, d_model);                 // dp = bmm(dY, Yhat)
-  if (rc != SMOE_OK) return rc;
   if (dtype == SMOE_F32) {
     // The fp32 kernels gather and weight rows where they read them and apply the activation's derivative in the epilogue.
     const RowMap tokens{r->sorted_scattered_idxs, k};
     DWArgs w2{saved_H, dY, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};
     w2.b_map = tokens;
     w2.gates = gates;
-    rc = launch_dw_plain(s, dtype, w2);
-    if (rc != SMOE_OK) return rc;
     S2SArgs x2 = make_s2s(dY, W2, dHpre, r, d_expert, d_model, true, false, k, true);
     x2.Hpre_in = saved_Hpre;
     x2.act = act;
     x2.gates = gates;
     x2.slots = r->sorted_scattered_idxs;
-    rc = launch_s2s_plain(s, dtype, x2);
+    const RowDots d{dY, saved_Yhat, dgates, Tk, k, d_model};                              // dp = bmm(dY, Yhat)
+    const size_t w2_bytes = (size_t)r->E * d_expert * d_model * 4, row_bytes = (size_t)Tk * 4;
+    rc = run_f32_backward(s, x2, w2, d, overlap(dW2, w2_bytes, saved_Yhat, row_bytes * d_model) || overlap(dW2, w2_bytes, dgates, row_bytes));
     if (rc != SMOE_OK) return rc;
     DWArgs w1{X, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
     w1.a_map = tokens;
-    rc = launch_dw_plain(s, dtype, w1);
-    if (rc != SMOE_OK) return rc;
-    rc = launch_s2s_plain(s, dtype, make_s2s(dHpre, W1, k == 1 ? dX : Xbar, r, d_model, d_h, true, true, 1, false));
+    void *dst = k == 1 ? dX : Xbar;
+    rc = run_f32_backward(s, make_s2s(dHpre, W1, dst, r, d_model, d_h, true, true, 1, false), w1, RowDots{},
+                          overlap(dst, row_bytes * d_model, X, (size_t)T * d_model * 4) ||
+                              overlap(dst, row_bytes * d_model, dW1, (size_t)r->E * d_model * d_h * 4));
     if (rc != SMOE_OK || k == 1) return rc;
     return launch_combine(s, dtype, Xbar, nullptr, dX, T, k, d_model);
   }
+  rc = launch_rowdot(s, dtype, dY, saved_Yhat, dgates, Tk, k, d_model);                 // dp = bmm(dY, Yhat)
+  if (rc != SMOE_OK) return rc;
   rc = launch_group(s, dtype, dY, r->sorted_scattered_idxs, k, gates, dYbar, Tk, d_model);  // weight and group
   if (rc != SMOE_OK) return rc;
   DWArgs w2{saved_H, dYbar, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};

@@ -93,6 +93,27 @@ int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o,
 // dg[s] = <dY[s / kp], Yhat[s]>
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 
+struct RowDots {      // dg[s] = <dY[s / kp], Yhat[s]> for s < Tk, rows of d elements (16-byte multiples)
+  const void *dY, *Yhat;
+  float *dg;
+  int Tk, kp, d;
+};
+// one of them, by one wavefront
+template <typename T> __device__ __forceinline__ void row_dot(const RowDots &r, int s, int lane) {
+  constexpr int V = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(V)));
+  const T *a = (const T *)r.dY + (size_t)(s / r.kp) * r.d, *b = (const T *)r.Yhat + (size_t)s * r.d;
+  float acc = 0.f;
+  for (int c = lane * V; c < r.d; c += 64 * V) {
+    const vec x = *reinterpret_cast<const vec *>(a + c), y = *reinterpret_cast<const vec *>(b + c);
+#pragma unroll
+    for (int i = 0; i < V; ++i) acc = fmaf(to_f32<T>(x[i]), to_f32<T>(y[i]), acc);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (lane == 0) r.dg[s] = acc;
+}
+
 // ---- GEMM launchers (gemm_plain.hip, gemm_mfma.hip)
 struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted rows i
   const void *A;      // [*, K] rows addressed through a_map
@@ -175,6 +196,7 @@ static inline bool weights_pass_caches(const S2SArgs &a) {
 }
 int launch_s2s_plain(hipStream_t s, smoe_dtype dt, const S2SArgs &a);
 int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a);
+int launch_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d);
 bool s2s_mfma_supported(const S2SArgs &a);
 bool dw_mfma_supported(const DWArgs &a);
 int launch_s2s_mfma(hipStream_t s, const S2SArgs &a);

@@ -248,26 +248,9 @@ __global__ void __launch_bounds__(256) dp_reduce_kernel(const float2 *__restrict
 }
 
 // ---- dg[s] = <dY[s / kp], Yhat[s]> : one wavefront per slot, lanes stride the row.
-template <typename T>
-__global__ void __launch_bounds__(256) rowdot_kernel(const T *__restrict__ dY, const T *__restrict__ Yhat,
-                                                     float *__restrict__ dg, int Tk, int kp, int d) {
-  constexpr int V = 16 / sizeof(T);
-  int lane = threadIdx.x & 63;
-  int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (s >= Tk) return;
-  const T *a = dY + (size_t)(s / kp) * d;
-  const T *b = Yhat + (size_t)s * d;
-  float acc = 0.f;
-  for (int c = lane * V; c < d; c += 64 * V) {
-    float x[V], y[V];
-    load_vec<T>(a + c, x);
-    load_vec<T>(b + c, y);
-#pragma unroll
-    for (int i = 0; i < V; ++i) acc = fmaf(x[i], y[i], acc);
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) dg[s] = acc;
+template <typename T> __global__ void __launch_bounds__(256) rowdot_kernel(RowDots r) {
+  const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (s < r.Tk) row_dot<T>(r, s, threadIdx.x & 63);
 }
 
 // -----------------------------------------------------------------------------------------
@@ -385,7 +368,7 @@ template <typename T>
 static int rowdot_t(hipStream_t s, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d) {
   if (!vec_ok<T>(d)) return SMOE_ERR_UNSUPPORTED;
   if (!Tk) return SMOE_OK;
-  hipLaunchKernelGGL((rowdot_kernel<T>), dim3(ceil_div(Tk, 4)), dim3(256), 0, s, (const T *)dY, (const T *)Yhat, dg, Tk, kp, d);
+  hipLaunchKernelGGL((rowdot_kernel<T>), dim3(ceil_div(Tk, 4)), dim3(256), 0, s, RowDots{dY, Yhat, dg, Tk, kp, d});
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

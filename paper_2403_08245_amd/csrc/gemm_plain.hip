@@ -5,11 +5,11 @@
 // The fp32 layers are small, so what bounds them is latency: launches, and in a launch the chain offsets -> order index ->
 // operand row -> result.  Hence: rows are gathered (and weighted) where they are read instead of by a `group` launch, the
 // activation and its derivative sit in the epilogues instead of launches of their own, the tile search runs across the
-// lanes of a wavefront, row addresses are worked out once, and each 32-deep contraction step is loaded into registers while
-// the previous one is multiplied.  Before (scalar FMAs, 16-deep steps, an index and a row fetched per element) and now:
-// 256 tokens, 64 -> 128 -> 64, 4 experts: a product 14 to 26 us -> 6.5 to 9, a training step 160 us -> 78;
-// 1024 tokens, 256 -> 896 -> 256, 8 experts, k = 2, SwiGLU: forward 293 -> 63, backward 541 -> 136 us;
-// 8192 tokens, 512 -> 1024 -> 512: 35 -> 92 TFLOP/s forward (157 is the card's fp32 matrix rate).
+// lanes of a wavefront, row addresses are worked out once, each 32-deep contraction step is loaded into registers two steps
+// ahead, and the parts of a backward pass that wait for nothing but their inputs are one launch (f32_backward_kernel).
+// 256 tokens, 64 -> 128 -> 64, 4 experts: a launch 7 to 9.5 us; the nine launches of a training step 44 us in a captured graph,
+// 48 us under a profiler (twelve of them: 64), called one by one 78 -> 67 us (host and launches bound it then);
+// 500 tokens, 128 -> 2 x 512 -> 128, 8 experts, k = 2: 101 -> 87 us; 1024 tokens, 256 -> 2 x 896 -> 256: 202 -> 194 us.
 #include "mfma_common.h"
 
 namespace {
@@ -81,16 +81,21 @@ __device__ __forceinline__ void multiply_step(const float *As, const float *Bs, 
 //           ACT_BWD  C = act'(Hpre) * product (SwiGLU: both halves).
 // Rows of the product are scaled by the routing weight of their slot when a.gates is given.
 enum { EPI_NONE = 0, EPI_ACT_FWD = 1, EPI_ACT_BWD = 2 };
+//
+// A step's operands are requested two steps ahead, and what the epilogue reads before the first step: a block walks two to a
+// few dozen steps by itself, so every latency that stands alone shows.
+constexpr int TILE_FLOATS = PT * KROW > PK * NROW ? PT * KROW : PK * NROW;
+struct PlainTiles {
+  float a[2][TILE_FLOATS], b[2][TILE_FLOATS];   // of even and odd steps: one barrier per step
+};
 template <typename T, bool TRANS_W, int EPI>
-__global__ void __launch_bounds__(256) s2s_plain_kernel(S2SArgs a) {
-  __shared__ float As[PT * KROW];
-  __shared__ float Bs[PT * KROW > PK * NROW ? PT * KROW : PK * NROW];
-  constexpr int V = TileRegs<T>::V, U = TileRegs<T>::U;
+__device__ __forceinline__ void s2s_plain_tile(const S2SArgs &a, int mt, int nt, PlainTiles &tiles) {
+  constexpr int U = TileRegs<T>::U;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
   int e, row0, row_end;
-  if (!locate_rows<PT>(a.offsets, a.E, blockIdx.x, lane, e, row0, row_end)) return;
+  if (!locate_rows<PT>(a.offsets, a.E, mt, lane, e, row0, row_end)) return;
   const bool swiglu = a.act == SMOE_ACT_SWIGLU, paired = EPI == EPI_ACT_FWD && swiglu;
-  const int half_n = a.N / 2, n0 = blockIdx.y * (paired ? 32 : PT);
+  const int half_n = a.N / 2, n0 = nt * (paired ? 32 : PT);
   const T *W = (const T *)a.W + (size_t)e * a.w_stride;
   // column of the product that tile column c stands for
   auto column = [&](int c) { return !paired ? n0 + c : (c < 32 ? (n0 + c < half_n ? n0 + c : a.N) : (n0 + c - 32 < half_n ? half_n + n0 + c - 32 : a.N)); };
@@ -112,38 +117,53 @@ __global__ void __launch_bounds__(256) s2s_plain_kernel(S2SArgs a) {
       pb[u] = W + (size_t)cc_k<T>(u) * a.ldw + (okb[u] ? n : 0);
     }
   }
-  TileRegs<T> ra, rb;
-  auto fetch = [&](int k0) {
+  TileRegs<T> ra[2], rb[2];
+  auto fetch = [&](int set, int k0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      ra.r[u] = load_or_zero(pa[u] + k0, oka[u] && k0 + kc_k<T>(u) < a.K);
-      rb.r[u] = TRANS_W ? load_or_zero(pb[u] + k0, okb[u] && k0 + kc_k<T>(u) < a.K)
-                        : load_or_zero(pb[u] + (size_t)k0 * a.ldw, okb[u] && k0 + cc_k<T>(u) < a.K);
+      ra[set].r[u] = load_or_zero(pa[u] + k0, oka[u] && k0 + kc_k<T>(u) < a.K);
+      rb[set].r[u] = TRANS_W ? load_or_zero(pb[u] + k0, okb[u] && k0 + kc_k<T>(u) < a.K)
+                             : load_or_zero(pb[u] + (size_t)k0 * a.ldw, okb[u] && k0 + cc_k<T>(u) < a.K);
     }
   };
-  f32x16 acc;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  fetch(0);
-  for (int k0 = 0; k0 < a.K; k0 += PK) {
-    if (k0) __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      put_floats<T>(As + kc_row<T>(u) * KROW + kc_k<T>(u), ra.r[u], 1.0f);
-      if (TRANS_W) put_floats<T>(Bs + kc_row<T>(u) * KROW + kc_k<T>(u), rb.r[u], 1.0f);
-      else put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb.r[u], 1.0f);
-    }
-    __syncthreads();
-    if (k0 + PK < a.K) fetch(k0 + PK);
-    multiply_step<true, TRANS_W>(As, Bs, wm, wn, lane, acc);
-  }
-
+  fetch(0, 0);
+  fetch(1, PK);
   // a lane holds row lane % 32 and the columns 8 g + 4 * (lane / 32) + 0..3 of its wavefront's 32 x 32 block
   const int i = row0 + wm * 32 + (lane & 31);
   const bool live = i < row_end;
   const size_t dst = live ? (size_t)map_row(a.c_map, i) : 0;
   const float scale = a.gates && live ? a.gates[a.slots[i]] : 1.0f;
-  float4 *exchange = reinterpret_cast<float4 *>(As);     // SwiGLU: the up columns cross over to the gate columns' wavefront
+  Vec16<float> pre[4], pre_up[4];          // EPI_ACT_BWD (fp32): the saved pre-activations of the lane's elements
+  if (EPI == EPI_ACT_BWD) {
+    const float *h = (const float *)a.Hpre_in + (size_t)(live ? i : 0) * (swiglu ? 2 * a.N : a.N);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = column(wn * 32 + 8 * g + 4 * (lane >> 5));
+      pre[g] = load_or_zero(h + n, live && n < a.N);
+      pre_up[g] = load_or_zero(h + a.N + n, swiglu && live && n < a.N);
+    }
+  }
+  f32x16 acc;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
+  auto step = [&](int set, int k0) {
+    float *As = tiles.a[set], *Bs = tiles.b[set];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      put_floats<T>(As + kc_row<T>(u) * KROW + kc_k<T>(u), ra[set].r[u], 1.0f);
+      if (TRANS_W) put_floats<T>(Bs + kc_row<T>(u) * KROW + kc_k<T>(u), rb[set].r[u], 1.0f);
+      else put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb[set].r[u], 1.0f);
+    }
+    __syncthreads();
+    fetch(set, k0 + 2 * PK);
+    multiply_step<true, TRANS_W>(As, Bs, wm, wn, lane, acc);
+  };
+  for (int k0 = 0; k0 < a.K; k0 += 2 * PK) {
+    step(0, k0);
+    if (k0 + PK < a.K) step(1, k0 + PK);
+  }
+
+  float4 *exchange = reinterpret_cast<float4 *>(tiles.a[0]);     // SwiGLU: the up columns cross over to the gate columns' wavefront
   if (paired) {
     __syncthreads();
     if (wn == 1)
@@ -160,14 +180,13 @@ __global__ void __launch_bounds__(256) s2s_plain_kernel(S2SArgs a) {
     for (int q = 0; q < 4; ++q) v[q] = scale * acc[4 * g + q];
     if (EPI == EPI_ACT_BWD) {
       const int d_h = swiglu ? 2 * a.N : a.N;
-      const T *pre = (const T *)a.Hpre_in + (size_t)i * d_h + n;
       T *out = (T *)a.C + dst * d_h + n;
       float x[4], y[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float h = to_f32<T>(pre[q]);
+        const float h = pre[g].v[q];
         if (swiglu) {
-          const float u = to_f32<T>(pre[a.N + q]), sg = sigmoid_f(h), silu = h * sg;
+          const float u = pre_up[g].v[q], sg = sigmoid_f(h), silu = h * sg;
           x[q] = v[q] * u * (sg + silu * (1.0f - sg));
           y[q] = v[q] * silu;
         } else {
@@ -197,54 +216,60 @@ __global__ void __launch_bounds__(256) s2s_plain_kernel(S2SArgs a) {
   }
 }
 
+template <typename T, bool TRANS_W, int EPI>
+__global__ void __launch_bounds__(256) s2s_plain_kernel(S2SArgs a) {
+  __shared__ PlainTiles tiles;
+  s2s_plain_tile<T, TRANS_W, EPI>(a, blockIdx.x, blockIdx.y, tiles);
+}
+
 // dW[e] = sum_i A[i, :]^T B[i, :] over the expert's rows; both operands may be gathered, B's rows weighted.
-template <typename T>
-__global__ void __launch_bounds__(256) dw_plain_kernel(DWArgs a) {
-  __shared__ float As[PK * NROW];
-  __shared__ float Bs[PK * NROW];
+template <typename T> __device__ __forceinline__ void dw_plain_tile(const DWArgs &a, int nt, int mt, int e, PlainTiles &tiles) {
   constexpr int U = TileRegs<T>::U;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
-  const int e = blockIdx.z;
   const int lo = a.offsets[e], hi = a.offsets[e + 1];
-  const int m0 = blockIdx.y * PT, n0 = blockIdx.x * PT;
-  TileRegs<T> ra, rb;
-  float weight[U];
-  // Order indices are fetched a step ahead of the rows they lead to, so that a step waits for one memory latency, not two.
+  const int m0 = mt * PT, n0 = nt * PT;
+  TileRegs<T> ra[2], rb[2];
+  float weight[2][U];
+  // Order indices are fetched two steps ahead of the rows they lead to, and the rows two steps ahead of their products.
   const int32_t *o = a.a_map.o ? a.a_map.o : a.b_map.o;   // both maps use the same order indices
-  int slot[U];
-  auto fetch_slots = [&](int i0) {
+  int slot[2][U];
+  auto fetch_slots = [&](int set, int i0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot[u] = o && i0 + cc_k<T>(u) < hi ? o[i0 + cc_k<T>(u)] : 0;
+    for (int u = 0; u < U; ++u) slot[set][u] = o && i0 + cc_k<T>(u) < hi ? o[i0 + cc_k<T>(u)] : 0;
   };
-  auto source = [&](const RowMap &map, int i, int u) { return (size_t)(map.o ? (map.fan > 1 ? slot[u] / map.fan : slot[u]) : i); };
-  auto fetch = [&](int i0) {
+  auto fetch = [&](int set, int i0) {
+    auto source = [&](const RowMap &map, int i, int u) { return (size_t)(map.o ? (map.fan > 1 ? slot[set][u] / map.fan : slot[set][u]) : i); };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + cc_k<T>(u), m = m0 + cc_col<T>(u), n = n0 + cc_col<T>(u);
       const bool ok = i < hi;
-      weight[u] = a.gates && ok ? a.gates[slot[u]] : 1.0f;
-      ra.r[u] = load_or_zero((const T *)a.A + (ok ? source(a.a_map, i, u) : 0) * a.M + (m < a.M ? m : 0), ok && m < a.M);
-      rb.r[u] = load_or_zero((const T *)a.B + (ok ? source(a.b_map, i, u) : 0) * a.N + (n < a.N ? n : 0), ok && n < a.N);
+      weight[set][u] = a.gates && ok ? a.gates[slot[set][u]] : 1.0f;
+      ra[set].r[u] = load_or_zero((const T *)a.A + (ok ? source(a.a_map, i, u) : 0) * a.M + (m < a.M ? m : 0), ok && m < a.M);
+      rb[set].r[u] = load_or_zero((const T *)a.B + (ok ? source(a.b_map, i, u) : 0) * a.N + (n < a.N ? n : 0), ok && n < a.N);
     }
-    fetch_slots(i0 + PK);
+    fetch_slots(set, i0 + 2 * PK);
   };
   f32x16 acc;
 #pragma unroll
   for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  if (lo < hi) {
-    fetch_slots(lo);
-    fetch(lo);
-  }
-  for (int i0 = lo; i0 < hi; i0 += PK) {
-    if (i0 > lo) __syncthreads();
+  fetch_slots(0, lo);
+  fetch_slots(1, lo + PK);
+  fetch(0, lo);
+  fetch(1, lo + PK);
+  auto step = [&](int set, int i0) {
+    float *As = tiles.a[set], *Bs = tiles.b[set];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      put_floats<T>(As + cc_k<T>(u) * NROW + cc_col<T>(u), ra.r[u], 1.0f);
-      put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb.r[u], weight[u]);
+      put_floats<T>(As + cc_k<T>(u) * NROW + cc_col<T>(u), ra[set].r[u], 1.0f);
+      put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb[set].r[u], weight[set][u]);
     }
     __syncthreads();
-    if (i0 + PK < hi) fetch(i0 + PK);
+    fetch(set, i0 + 2 * PK);
     multiply_step<false, false>(As, Bs, wm, wn, lane, acc);
+  };
+  for (int i0 = lo; i0 < hi; i0 += 2 * PK) {
+    step(0, i0);
+    if (i0 + PK < hi) step(1, i0 + PK);
   }
   const int m = m0 + wm * 32 + (lane & 31);
   if (m >= a.M) return;
@@ -254,6 +279,34 @@ __global__ void __launch_bounds__(256) dw_plain_kernel(DWArgs a) {
     const int n = n0 + wn * 32 + 8 * g + 4 * (lane >> 5);
     if (n < a.N) store4<T>(dst + n, acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
   }
+}
+
+template <typename T> __global__ void __launch_bounds__(256) dw_plain_kernel(DWArgs a) {
+  __shared__ PlainTiles tiles;
+  dw_plain_tile<T>(a, blockIdx.x, blockIdx.y, blockIdx.z, tiles);
+}
+
+// What the backward pass of one fp32 ParallelLinear has to do, none of which waits for another part: the input-gradient product
+// (EPI_ACT_BWD: with the activation's derivative), the weight gradient and the row dots of dp.  One launch instead of three: at
+// these sizes a launch has 24 blocks or fewer for 256 compute units, and the gap to the next is 4 us (256 tokens, 64 -> 128 -> 64, 4
+// experts: 2.9 + 9.2 + 9.4 us and two gaps became 9.5, 8.3 + 6.1 us and one gap 9.1).
+template <int EPI> __global__ void __launch_bounds__(256) f32_backward_kernel(S2SArgs x, DWArgs w, RowDots d, int w_blocks, int x_blocks) {
+  __shared__ PlainTiles tiles;
+  int b = blockIdx.x;
+  if (b < w_blocks) {
+    const int tn = (w.N + PT - 1) / PT, tm = (w.M + PT - 1) / PT;
+    dw_plain_tile<float>(w, b % tn, b / tn % tm, b / tn / tm, tiles);
+    return;
+  }
+  b -= w_blocks;
+  if (b < x_blocks) {
+    const int tn = (x.N + PT - 1) / PT;
+    s2s_plain_tile<float, true, EPI>(x, b / tn, b % tn, tiles);
+    return;
+  }
+  b -= x_blocks;
+  const int s = b * 4 + (threadIdx.x >> 6);
+  if (s < d.Tk) row_dot<float>(d, s, threadIdx.x & 63);
 }
 
 template <typename T, int EPI> void launch_s2s_plain_t(hipStream_t s, const S2SArgs &a) {
@@ -278,6 +331,20 @@ int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a) {
   dim3 grid(ceil_div(a.N, PT), ceil_div(a.M, PT), a.E), block(256);
   if (dt == SMOE_BF16) hipLaunchKernelGGL((dw_plain_kernel<bf16_t>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((dw_plain_kernel<float>), grid, block, 0, s, a);
+  SMOE_LAUNCH_CHECK();
+  return SMOE_OK;
+}
+
+// x (with W^T), w or d may be absent (C, dW, dg NULL).
+int launch_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d) {
+  const long long w_blocks = w.dW ? (long long)ceil_div(w.N, PT) * ceil_div(w.M, PT) * w.E : 0;
+  const long long x_blocks = x.C ? ((long long)ceil_div(x.Tk, PT) + x.E) * ceil_div(x.N, PT) : 0;
+  const long long d_blocks = d.dg ? ceil_div(d.Tk, 4) : 0;
+  if (w_blocks + x_blocks + d_blocks > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
+  if (!(w_blocks + x_blocks + d_blocks)) return SMOE_OK;
+  const dim3 grid((unsigned)(w_blocks + x_blocks + d_blocks));
+  if (x.Hpre_in) hipLaunchKernelGGL(f32_backward_kernel<EPI_ACT_BWD>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks);
+  else hipLaunchKernelGGL(f32_backward_kernel<EPI_NONE>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
