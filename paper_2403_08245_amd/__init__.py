@@ -132,7 +132,9 @@ def set_clock_probe(buf: torch.Tensor | None):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle of torch's current stream on the current device; torch.cuda.current_stream() makes a Stream object first, 2.8 us
+    # a call of 0.2 (41 us of host work in a four-token forward pass with routing, three calls)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dt(t: torch.Tensor) -> int:
