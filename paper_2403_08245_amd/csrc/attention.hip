@@ -24,6 +24,7 @@ constexpr int AFS = 3;              // LDS stages of the forward's key walk: til
 constexpr int ADS = 4;              // the same for the dQ pass (two blocks per CU)
 constexpr int DKV_WAVES = 4;        // wavefronts (32 keys each) per block of the dK/dV kernel
 constexpr int DKV_SORT_MAX = 512;   // key blocks up to which the dK/dV units are dealt in exact longest-first order
+constexpr float LOG2_ROOT_D = 3.5f; // log2(sqrt(AD))
 constexpr float NEG_BIG = -1.0e30f; // finite stand-in for -inf: exp2 of it is 0 and no inf - inf appears
 
 // 16-byte chunk swizzle of a 256-byte row: conflict free both for the row-per-lane reads
@@ -284,10 +285,11 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
 
 
 // ======================================================================================
-// backward, part 0: delta[row][head] = <dO, O> over the head's 128 columns (sixteen lanes each)
+// backward, part 0: minus_delta[row][head] = -<dO, O> over the head's 128 columns (sixteen lanes each).  Negated, it is what
+// the products dP start from in the two passes below, instead of a subtraction per score.
 // ======================================================================================
 __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restrict__ O, const bf16_t *__restrict__ dO,
-                                                         float *__restrict__ delta, size_t n) {
+                                                         float *__restrict__ minus_delta, size_t n) {
   // sixteen lanes per (row, head) pair, 16 bytes each; both tensors are [rows][h][128]
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) >> 4;
   const int part = threadIdx.x & 15;
@@ -300,17 +302,20 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restric
   }
 #pragma unroll
   for (int d = 8; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-  if (part == 0 && i < n) delta[i] = v;
+  if (part == 0 && i < n) minus_delta[i] = -v;
 }
 
 // ======================================================================================
 // backward, part 1: dQ.  Same walk as the forward; a lane owns one query row.
-//   S^T = K Q^T, P^T = exp2(S^T * c - lse), dP^T = V dO^T, dS^T = P^T (dP^T - delta) / sqrt(d),
+//   S^T = K Q^T, P^T / sqrt(d) = exp2(S^T * c - lse - log2(d) / 2), dP^T = V dO^T - delta, dS^T = P^T / sqrt(d) * dP^T,
 //   dQ^T += K^T dS^T
+// Neither delta nor 1 / sqrt(d) costs an instruction per score: the one is what the products dP^T start from, the other sits in the
+// exponent, whose row constant it joins (98 -> 66 vector instructions per 16 x 64 scores beside 24 matrix instructions; 2 x 4096
+// positions, k = 4, 4 heads: 214 -> 205 us).
 // ======================================================================================
 __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
-                                                          const float *__restrict__ LSE, const float *__restrict__ delta,
+                                                          const float *__restrict__ LSE, const float *__restrict__ minus_delta,
                                                           bf16_t *__restrict__ dQ, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[ADS * 2 * ATILE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -336,20 +341,21 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
     dof[ks] = *reinterpret_cast<const bf16x8 *>(dO + qrow + 16 * ks + 8 * (lane >> 5));
   }
   const size_t stat = ((size_t)b * rows + r_mine) * d.h + hh;
-  float lse2 = LSE[stat] * 1.4426950408889634f;
-  float dlt = delta[stat];
-  const float scale = d.scale_log2 * 0.6931471805599453f;
+  float lse2 = LSE[stat] * 1.4426950408889634f + LOG2_ROOT_D;
+  float dlt = minus_delta[stat];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) { settle(qf[ks]); settle(dof[ks]); }
   settle(lse2);
   settle(dlt);
 
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-  f32x16 acc[4];
+  f32x16 acc[4], start;        // start: minus delta of the lane's row, for all keys
 #pragma unroll
   for (int f = 0; f < 4; ++f)
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[f][q] = 0.f;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) start[q] = dlt;
 
   const TileLoader<4> tiles(d.ldkv, wave, lane);
   auto request = [&](int tile, int stage) {   // as in the forward: one tile per step, also past the end
@@ -370,9 +376,9 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
     if (key0 > wave_last) return;
     const char *kt = smem + STAGE * 2 * ATILE;
     const char *vt = kt + ATILE;
-    f32x16 s, dp;
+    f32x16 s, dp = start;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
+    for (int q = 0; q < 16; ++q) s[q] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(kt, fo, ks), qf[ks], s, 0, 0, 0);
 #pragma unroll
@@ -385,8 +391,8 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
     }
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      float p = __builtin_amdgcn_exp2f(fmaf(s[q], d.scale_log2, -lse2));
-      s[q] = p * (dp[q] - dlt) * scale;
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[q], d.scale_log2, -lse2));
+      s[q] = p * dp[q];
     }
     bf16x8 db[2] = {pack8(s, 0), pack8(s, 1)};
 #pragma unroll
@@ -420,13 +426,13 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
 // ======================================================================================
 // backward, part 2: dK and dV.  Block = 32 * NW keys of one (sequence, head), 32 per wavefront, a
 // lane owns one key; the slot rows that can see them stream through LDS 32 at a time.
-//   S = Q K^T, P = exp2(S c - lse[row]), dV^T += dO^T P, dP = dO V^T,
-//   dS = P (dP - delta[row]) / sqrt(d), dK^T += Q^T dS
+//   S = Q K^T, P = exp2(S c - lse[row]), dV^T += dO^T P, dP = dO V^T - delta[row],
+//   dS = P dP / sqrt(d), dK^T += Q^T dS
 // ======================================================================================
 template <int NW, bool DK, bool DV>
 __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                            const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
-                                                           const float *__restrict__ LSE, const float *__restrict__ delta,
+                                                           const float *__restrict__ LSE, const float *__restrict__ minus_delta,
                                                            bf16_t *__restrict__ dK, bf16_t *__restrict__ dV,
                                                            float *__restrict__ part, DkvPlan plan, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * ATILE];
@@ -508,7 +514,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
   const bf16_t *Qb = Q + (size_t)b * rows * d.ldq + hh * AD;
   const bf16_t *dOb = dO + (size_t)b * rows * d.ldq + hh * AD;
   const float *Lb = LSE + (size_t)b * rows * d.h + hh;
-  const float *Db = delta + (size_t)b * rows * d.h + hh;
+  const float *Db = minus_delta + (size_t)b * rows * d.h + hh;
   const float scale = d.scale_log2 * 0.6931471805599453f;
 
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -555,10 +561,15 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     const char *dot = qt + ATILE;
     f32x16 s, dp;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
+    for (int q = 0; q < 16; ++q) s[q] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(qt, fo, ks), kf[ks], s, 0, 0, 0);
     if (DK) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 d4 = *reinterpret_cast<const float4 *>(&s_dlt[j & 1][8 * g + 4 * (lane >> 5)]);
+        dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
+      }
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks)
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(dot, fo, ks), rows_frag(vmine, fo, ks), dp, 0, 0, 0);
@@ -568,14 +579,13 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     for (int g = 0; g < 4; ++g) {
       const int rr = 8 * g + 4 * (lane >> 5);
       const float4 l4 = *reinterpret_cast<const float4 *>(&s_lse[j & 1][rr]);
-      const float4 d4 = *reinterpret_cast<const float4 *>(&s_dlt[j & 1][rr]);
-      const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
+      const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int q = 4 * g + c;
         const float pv = __builtin_amdgcn_exp2f(fmaf(s[q], d.scale_log2, lv[c] * -1.4426950408889634f));
         p[q] = pv;
-        s[q] = pv * (dp[q] - dv[c]) * scale;
+        if (DK) s[q] = pv * dp[q] * scale;
       }
     }
     // rows of this tile that are earlier than the wavefront's last key, or past the end, are masked (wave-uniform): the key
@@ -702,19 +712,19 @@ int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, 
                     const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h) {
   AttnDims d{B, T, G, h, (size_t)h * AD, (size_t)h * AD, 1.4426950408889634f / sqrtf((float)AD)};
   size_t n = (size_t)B * T * G * h;
-  float *delta = (float *)ws;
+  float *minus_delta = (float *)ws;
   float *part = (float *)((char *)ws + ((n * sizeof(float) + 255) & ~(size_t)255));
   constexpr int NW = DKV_WAVES;
   const DkvPlan plan = dkv_plan(T, G, B * h);
   if ((long long)plan.units * h * B > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
   hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, (const bf16_t *)O, (const bf16_t *)dO,
-                     delta, n);
+                     minus_delta, n);
   SMOE_LAUNCH_CHECK();
   hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(ceil_div(T * G, AQ) * h * B), dim3(256), 0, s, (const bf16_t *)Q,
-                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)delta, (bf16_t *)dQ, d);
+                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dQ, d);
   SMOE_LAUNCH_CHECK();
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, true, true>), dim3(plan.units * h * B), dim3(64 * NW), 0, s, (const bf16_t *)Q,
-                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)delta, (bf16_t *)dK,
+                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dK,
                      (bf16_t *)dV, part, plan, d);
   SMOE_LAUNCH_CHECK();
   if (plan.ch < ceil_div(T * G, AKT)) {   // some key block was cut into chunks
