@@ -498,12 +498,13 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
   }
 }
 
-// Second pass of a split last round: adds the chunks' fp32 partial tiles in chunk order, rounds once and
-// stores the rows where the unsplit epilogue would have (expert-sorted or scattered).  TAIL_SLICES blocks
-// per tile of the last round; the plan is recomputed from the same inputs as in the main kernel.  Few tiles are left over
-// (16 of 256 rows at 8192 x 1024 outputs), so a tile is spread over 32 blocks: with 8 the pass took 22 us there, latency of
-// each thread's chain of loads rather than bandwidth.
-constexpr int TAIL_SLICES = 32;
+// Second pass of a split last round: adds the chunks' fp32 partial tiles in chunk order, rounds once and stores the rows where the
+// unsplit epilogue would have (expert-sorted or scattered).  The plan is recomputed from the same inputs as in the main kernel.
+// How many tiles are left over only the device knows, so a fixed number of blocks deals itself the TAIL_SLICES slices of however
+// many there are: latency of each thread's chain of loads bounds it, not bandwidth, so a tile is spread over many threads, but a
+// block for every slice of every tile that could be left (8192, most of which rebuilt the plan and left) took 16 us for the 16 tiles
+// of an 8192 x 1024 output, 12 for those of 6002 x 1280 and 7 where nothing was left; TAIL_BLOCKS blocks take 6, 5 and 5.
+constexpr int TAIL_SLICES = 32, TAIL_BLOCKS = 1024;
 template <typename S, bool SCATTER_OUT>
 __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int tiles_n, int group_m, int G, int static4) {
   __shared__ int s_off[MAX_E + 1];
@@ -511,25 +512,28 @@ __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int til
   for (int i = threadIdx.x; i <= a.E; i += 256) s_off[i] = a.offsets[i];
   __syncthreads();
   const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, (a.K + HK - 1) / HK, G, static4 != 0, true, lane);
-  if (plan.split <= 1 || (int)blockIdx.x >= plan.rest) return;
-  int mt, nt, e, row0, row_end;
-  tile_coords(plan.rounds * G + plan.whole + (int)blockIdx.x, plan.m_tiles, tiles_n, group_m, mt, nt);
-  locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
-  const int n0 = nt * TB;
-  const float *part = a.tail_ws + (size_t)blockIdx.x * plan.split * S::PART;
-  bf16_t *C = (bf16_t *)(!SCATTER_OUT && a.C2 && e == 1 ? a.C2 : a.C);
+  if (plan.split <= 1) return;
   constexpr int PER_SLICE = S::PART / 4 / TAIL_SLICES;
-  for (int i = (int)blockIdx.y * PER_SLICE + threadIdx.x; i < ((int)blockIdx.y + 1) * PER_SLICE; i += 256) {
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int c = 0; c < plan.split; ++c) {
-      const float4 v = reinterpret_cast<const float4 *>(part + (size_t)c * S::PART)[i];
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-    const int row = row0 + (i * 4) / TB, col = n0 + (i * 4) % TB;
-    if (row < row_end && col < a.N) {
+  for (int unit = blockIdx.x; unit < plan.rest * TAIL_SLICES; unit += TAIL_BLOCKS) {
+    const int tile = unit / TAIL_SLICES, slice = unit % TAIL_SLICES;
+    int mt, nt, e, row0, row_end;
+    tile_coords(plan.rounds * G + plan.whole + tile, plan.m_tiles, tiles_n, group_m, mt, nt);
+    locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
+    const int n0 = nt * TB;
+    const float *part = a.tail_ws + (size_t)tile * plan.split * S::PART;
+    bf16_t *C = (bf16_t *)(!SCATTER_OUT && a.C2 && e == 1 ? a.C2 : a.C);
+    for (int i = slice * PER_SLICE + threadIdx.x; i < (slice + 1) * PER_SLICE; i += 256) {
+      const int row = row0 + (i * 4) / TB, col = n0 + (i * 4) % TB;
+      if (row >= row_end || col >= a.N) continue;
       const int dst = SCATTER_OUT ? a.c_map.o[row] : row;
+      float4 v[MAX_SPLIT];                      // all chunks in flight before the first is added
+#pragma unroll
+      for (int c = 0; c < MAX_SPLIT; ++c)
+        v[c] = c < plan.split ? reinterpret_cast<const float4 *>(part + (size_t)c * S::PART)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int c = 1; c < MAX_SPLIT; ++c) { v[0].x += v[c].x; v[0].y += v[c].y; v[0].z += v[c].z; v[0].w += v[c].w; }
       bf16x4 o;
-      o[0] = (bf16_t)acc.x; o[1] = (bf16_t)acc.y; o[2] = (bf16_t)acc.z; o[3] = (bf16_t)acc.w;
+      o[0] = (bf16_t)v[0].x; o[1] = (bf16_t)v[0].y; o[2] = (bf16_t)v[0].z; o[3] = (bf16_t)v[0].w;
       *reinterpret_cast<bf16x4 *>(C + (size_t)dst * a.N + col) = o;
     }
   }
@@ -778,7 +782,7 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC4, boo
                      tiles_n, group_m, division_magic(a.a_map.o ? a.a_map.fan : 1));
   SMOE_LAUNCH_CHECK();
   if (args.tail_ws) {   // adds and stores the partial tiles of a split last round (no-op when nothing was split)
-    hipLaunchKernelGGL((s2s_tail_reduce_kernel<S, SCATTER_OUT>), dim3(a.grid, TAIL_SLICES), dim3(256), 0, s, a, tiles_n, group_m, grid, STATIC4 ? 1 : 0);
+    hipLaunchKernelGGL((s2s_tail_reduce_kernel<S, SCATTER_OUT>), dim3(TAIL_BLOCKS), dim3(256), 0, s, a, tiles_n, group_m, grid, STATIC4 ? 1 : 0);
     SMOE_LAUNCH_CHECK();
   }
   return SMOE_OK;

@@ -162,9 +162,10 @@ constexpr int MAX_E = 256;          // the persistent kernels cache the expert o
 // A chunk's fp32 partial tile costs a 256 KB write and a 256 KB read on top of the second kernel's launch,
 // about what 48 half-steps of multiplying take: a split must shorten the last round by more than that.
 constexpr int SPLIT_MIN_SAVED = 64;
-// Largest number of chunks <= max_split (and <= 4) that pays, with the chunk length; 1 = keep whole tiles.
+constexpr int MAX_SPLIT = 4;
+// Largest number of chunks <= max_split (and <= MAX_SPLIT) that pays, with the chunk length; 1 = keep whole tiles.
 __host__ __device__ inline int choose_split(int nh, int max_split, bool static4, int &chunk) {
-  for (int s = max_split < 4 ? max_split : 4; s > 1; --s) {
+  for (int s = max_split < MAX_SPLIT ? max_split : MAX_SPLIT; s > 1; --s) {
     int c = (nh + s - 1) / s;
     if (static4) c = (c + 3) & ~3;
     if ((s - 1) * c < nh && nh - c >= SPLIT_MIN_SAVED) {
