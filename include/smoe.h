@@ -283,7 +283,9 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
 
 /* Backward of smoe_momha_fwd: Alg. 2 for the two ParallelLinears, smoe_attention_bwd between
  * them, plain products for the dense key/value projections.
- *   dO [B*T, d_model] upstream gradient; dX like X; dW_* like W_*; dgates [Tk] fp32 (all out). */
+ *   dO [B*T, d_model] upstream gradient; dX like X; dW_* like W_*; dgates [Tk] fp32 (all out).
+ *   Large layers with k > 1 form dgates as <dO W_O^T, Ohat> in the product's epilogue instead of <dO, Yhat> from saved_Yhat
+ *   (the same number with the two sums exchanged); saved_Yhat has to be given either way. */
 size_t smoe_momha_bwd_workspace_bytes(int B, int T, int k, int d_model, int h_expert, int d_head);
 int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO, const void *X, int B, int T,
                    int d_model, int h_expert, int d_head, const void *W_K, const void *W_V, const void *W_Q,

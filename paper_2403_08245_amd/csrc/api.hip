@@ -282,11 +282,12 @@ size_t smoe_plinear_bwd_workspace_bytes(smoe_dtype dtype, int x_rows, int d_in, 
   return total;
 }
 
+// given_inv: the inverse of the order indices where the caller has it already (NULL: made here when it pays).
 // more0, more1: two further contributions to dX [x_rows, d_in], added where the k slots are summed (scattered X with k > 1)
 static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dY, const void *X, int x_rows,
                      int d_in, const void *W, int d_out, const void *Yhat, const smoe_routing *r, int k,
                      const float *gates, int gates_k, int grouped_in, int grouped_out, void *dX, void *dW,
-                     float *dgates, void *ws, size_t ws_bytes, const void *more0, const void *more1) {
+                     float *dgates, void *ws, size_t ws_bytes, const void *more0, const void *more1, const int32_t *given_inv) {
   if (!ctx || !dtype_ok(dtype) || !routing_ok(r) || d_in < 1 || d_out < 1 || k < 1 || x_rows < 0)
     return SMOE_ERR_INVALID_ARG;
   const int Tk = r->Tk;
@@ -336,16 +337,18 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   }
 
   // dp = bmm(dY, Yhat); dYbar = group(dY, o, p)  (Alg. 2: "weight and group")
-  int32_t *inv = (int32_t *)((char *)ws + need - S2S_TAIL_WS_BYTES);   // read before the first product writes partial tiles there
+  int32_t *own_inv = (int32_t *)((char *)ws + need - S2S_TAIL_WS_BYTES);   // read before the first product writes partial tiles there
+  const int32_t *inv = given_inv ? given_inv : own_inv;
   // Rows that several slots share are spread from the source rows when that saves more than the launch that inverts the order
   // indices costs (about 3 us): on 20500 rows of 3 and 4 KB 39 us of group copies became 28, on 8192 rows of 2 KB the launch was
   // dearer by 1.5 us, so from 24 Mi elements on.
   size_t shared = 0;
   if (!grouped_out && gates && gates_k > 1) shared += (size_t)Tk * d_out;
   if (!grouped_in && dW && k > 1) shared += (size_t)Tk * d_in;
-  const bool spread = shared >= ((size_t)24 << 20) && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES, spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1;
-  if (spread) {
-    rc = launch_invert(s, r->sorted_scattered_idxs, inv, nullptr, nullptr, Tk);
+  const bool spread = given_inv || (shared >= ((size_t)24 << 20) && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES);
+  const bool spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1;
+  if (spread && !given_inv) {
+    rc = launch_invert(s, r->sorted_scattered_idxs, own_inv, nullptr, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
   }
   const void *dYbar = dY;
@@ -394,7 +397,7 @@ int smoe_plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *
                      const float *gates, int gates_k, int grouped_in, int grouped_out, void *dX, void *dW,
                      float *dgates, void *ws, size_t ws_bytes) {
   return plinear_bwd(ctx, stream, dtype, dY, X, x_rows, d_in, W, d_out, Yhat, r, k, gates, gates_k, grouped_in, grouped_out, dX, dW, dgates,
-                     ws, ws_bytes, nullptr, nullptr);
+                     ws, ws_bytes, nullptr, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------------------ Alg. 3
@@ -754,28 +757,33 @@ S2SArgs dense_s2s(const void *A, const void *W, void *C, const int32_t *offsets,
 // Two dense products (two weight gradients) of the same sizes, in one launch where the persistent kernels take them: alone
 // each fills half of the chip at the widths of a key or value projection (8192 rows, 2048 -> 512: 2 x 41 us, paired 43; the
 // weight gradients 2 x 57 us, paired 58).
-int run_s2s_pair(smoe_ctx *ctx, hipStream_t s, const S2SArgs &a, const S2SArgs &b) {
+// The persistent kernels know two segments of equal length without being given their offsets; the others read them from `off`.
+int run_s2s_pair(smoe_ctx *ctx, hipStream_t s, const S2SArgs &a, const S2SArgs &b, int32_t *off) {
   S2SArgs p = a;
   p.E = 2;
   p.Tk = 2 * a.Tk;
+  p.offsets = nullptr;
   p.A2 = (const void *)((uintptr_t)b.A - (uintptr_t)a.Tk * a.K * 2);
   p.W2 = (const void *)((uintptr_t)b.W - (uintptr_t)a.w_stride * 2);
   p.C2 = (void *)((uintptr_t)b.C - (uintptr_t)a.Tk * a.N * 2);
   set_launch(ctx, p);
   if (ctx->kernel_mode == 0 && a.Tk < (1 << 30) && !s2s_decode_supported(a) && s2s_stream_supported(p)) return launch_s2s_stream(s, p);
-  const int rc = run_s2s(ctx, s, SMOE_BF16, a);
+  int rc = launch_dense_offsets(s, off, a.Tk);
+  if (rc == SMOE_OK) rc = run_s2s(ctx, s, SMOE_BF16, a);
   return rc != SMOE_OK ? rc : run_s2s(ctx, s, SMOE_BF16, b);
 }
-int run_dw_pair(smoe_ctx *ctx, hipStream_t s, const DWArgs &a, const DWArgs &b) {
+int run_dw_pair(smoe_ctx *ctx, hipStream_t s, const DWArgs &a, const DWArgs &b, int32_t *off) {
   DWArgs p = a;
   p.E = 2;
   p.Tk = 2 * a.Tk;
+  p.offsets = nullptr;
   p.A2 = (const void *)((uintptr_t)b.A - (uintptr_t)a.Tk * a.M * 2);
   p.B2 = (const void *)((uintptr_t)b.B - (uintptr_t)a.Tk * a.N * 2);
   p.dW2 = (void *)((uintptr_t)b.dW - (uintptr_t)a.M * a.N * 2);
   p.grid = ctx->stream_grid;
   if (ctx->kernel_mode == 0 && a.Tk < (1 << 30) && dw_stream_supported(p)) return launch_dw_stream(s, p);
-  const int rc = run_dw(ctx, s, SMOE_BF16, a);
+  int rc = launch_dense_offsets(s, off, a.Tk);
+  if (rc == SMOE_OK) rc = run_dw(ctx, s, SMOE_BF16, a);
   return rc != SMOE_OK ? rc : run_dw(ctx, s, SMOE_BF16, b);
 }
 }  // namespace
@@ -811,14 +819,12 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
     saved_Yhat = p;
   }
   hipStream_t s = (hipStream_t)stream;
-  rc = launch_dense_offsets(s, dense_off, N);
-  if (rc != SMOE_OK) return rc;
   // V = X W_V, K = X W_K
   auto product = [&](S2SArgs a) { a.tail_ws = tail_ws; return run_s2s(ctx, s, dtype, a); };
   S2SArgs pv = dense_s2s(X, W_V, saved_V, dense_off, N, d_model, d_out, false);
   S2SArgs pk = dense_s2s(X, W_K, saved_K, dense_off, N, d_model, d_out, false);
   pv.tail_ws = pk.tail_ws = tail_ws;
-  rc = run_s2s_pair(ctx, s, pv, pk);
+  rc = run_s2s_pair(ctx, s, pv, pk, dense_off);
   if (rc != SMOE_OK) return rc;
   // Q = ParallelLinear(X, W_Q, o, no p, scattered -> scattered)
   rc = product(make_s2s(X, W_Q, saved_Q, r, d_model, d_out, false, false, k, false));
@@ -830,6 +836,16 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
   rc = product(make_s2s(saved_Ohat, W_O, saved_Yhat, r, d_out, d_model, false, false, 1, false));
   if (rc != SMOE_OK) return rc;
   return launch_combine(s, dtype, saved_Yhat, gates, O, N, k, d_model);
+}
+
+// Does forming dp and delta in the epilogue of the output projection's input-gradient product pay?  It saves passes over rows of
+// [Tk, d_model], but the product then runs on 256 x 256 tiles, of which there have to be enough.  With it / without, training step
+// of the layer in us: 16384 rows of 1024, 4 heads 700 / 717; 32768 of 512, 2 heads 572 / 594; 24000 of 720, 4 heads 523 / 548;
+// 32768 of 2048, 4 heads 1467 / 1520; but 8192 of 2048, 4 heads 513 / 509; 6000 of 2000, 8 heads 579 / 572; 8192 of 1024, 1 head
+// 276 / 271; 4096 of 4096, 2 heads 542 / 507.
+static bool output_projection_in_epilogue(const smoe_ctx *ctx, int Tk, int d_model, int d_out) {
+  if (ctx->tile_shape == 2) return true;   // forced, for the tests
+  return (size_t)Tk * d_model >= ((size_t)16 << 20) && (long long)ceil_div(Tk, 256) * ceil_div(d_out, 256) * 2 >= ctx->stream_grid;
 }
 
 size_t smoe_momha_bwd_workspace_bytes(int B, int T, int k, int d_model, int h_expert, int d_head) {
@@ -873,28 +889,58 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   const size_t sub_bytes = z.yhat + z.q + S2S_TAIL_WS_BYTES;
   float *tail_ws = (float *)((char *)sub + z.yhat + z.q);   // where the ParallelLinear backward puts its own, too
   hipStream_t s = (hipStream_t)stream;
-  rc = launch_dense_offsets(s, dense_off, N);
+  const bool in_sum = k > 1 && aligned16(dX);   // dXk and dXv are added where the k slots of dX are summed, whose kernel writes 16-byte lines
+  // the array of dX's third part is free then: it holds the inverse of the order indices
+  int32_t *inv = in_sum && (size_t)Tk * sizeof(int32_t) <= z.x ? (int32_t *)dXq : nullptr;
+  // Output projection (Alg. 2 with p, scattered in with fan-out 1, scattered out): dOhat, dW_O, dp.  Where the persistent kernels take
+  // the product, its epilogue reads the saved Ohat and leaves <dO W_O^T, Ohat> per head: summed over the heads that is dp, times the
+  // routing weight it is delta, the attention's <dOhat, Ohat>; and it writes the weighted, sorted rows of Ohat that groupXTY needs.
+  // No pass over Yhat, no delta kernel, no `group` of Ohat (34 + 13 + 14 us at 8192 tokens, k = 4, 4 heads, 2048 wide).
+  const int part_ld = 2 * ceil_div(d_out, 256);
+  float *gsorted = tail_ws, *dp_part = (float *)((char *)tail_ws + align256((size_t)Tk * sizeof(float)));
+  void *dYu = sub, *Ow = (char *)sub + z.yhat;
+  S2SArgs xo = make_s2s(dO, W_O, dOhat, r, d_out, d_model, true, false, k, false);
+  xo.H_in = saved_Ohat;
+  xo.Hw_out = Ow;
+  xo.row_scale = gsorted;
+  xo.dp_part = dp_part;
+  set_launch(ctx, xo);
+  const bool in_epilogue = inv && ctx->kernel_mode == 0 && s2s_stream_dp_supported(xo) && output_projection_in_epilogue(ctx, Tk, d_model, d_out) &&
+                           align256((size_t)Tk * sizeof(float)) + (size_t)Tk * part_ld * sizeof(float) <= S2S_TAIL_WS_BYTES;
+  if (in_epilogue) {
+    rc = launch_invert(s, r->sorted_scattered_idxs, inv, gates, gsorted, Tk);
+    if (rc != SMOE_OK) return rc;
+    rc = launch_s2s_stream(s, xo);
+    if (rc != SMOE_OK) return rc;
+    rc = launch_dp_delta(s, dp_part, part_ld, h_expert, r->sorted_scattered_idxs, gates, dgates, (float *)attn_ws, Tk);
+    if (rc != SMOE_OK) return rc;
+    rc = launch_spread(s, dO, inv, k, nullptr, dYu, Tk, d_model);
+    if (rc != SMOE_OK) return rc;
+    DWArgs wo{Ow, dYu, dW_O, r->expert_offsets, r->E, Tk, d_out, d_model};
+    wo.split_ws = tail_ws;
+    rc = run_dw(ctx, s, dtype, wo);
+  } else {
+    rc = smoe_plinear_bwd(ctx, stream, dtype, dO, saved_Ohat, Tk, d_out, W_O, d_model, saved_Yhat, r, 1, gates, k, 0, 0,
+                          dOhat, dW_O, dgates, sub, sub_bytes);
+    if (rc == SMOE_OK && inv) rc = launch_invert(s, r->sorted_scattered_idxs, inv, nullptr, nullptr, Tk);
+  }
   if (rc != SMOE_OK) return rc;
-  // output projection (Alg. 2 with p, scattered in with fan-out 1, scattered out): dOhat, dW_O, dp
-  rc = smoe_plinear_bwd(ctx, stream, dtype, dO, saved_Ohat, Tk, d_out, W_O, d_model, saved_Yhat, r, 1, gates, k, 0, 0,
-                        dOhat, dW_O, dgates, sub, sub_bytes);
-  if (rc != SMOE_OK) return rc;
-  rc = launch_attn_bwd(s, saved_Q, saved_K, saved_V, saved_Ohat, dOhat, saved_LSE, attn_ws, dQ, dK, dV, B, T, k, h_expert);
+  // with the inverse at hand dQ is written in expert-sorted order, as the query projection's gradients read it
+  rc = launch_attn_bwd(s, saved_Q, saved_K, saved_V, saved_Ohat, dOhat, saved_LSE, attn_ws, dQ, dK, dV, B, T, k, h_expert, in_epilogue, inv);
   if (rc != SMOE_OK) return rc;
   // dense key / value projections
   DWArgs wk{X, dK, dW_K, dense_off, 1, N, d_model, d_out}, wv{X, dV, dW_V, dense_off, 1, N, d_model, d_out};
   wk.split_ws = wv.split_ws = (float *)((char *)sub + z.yhat + z.q);
-  rc = run_dw_pair(ctx, s, wk, wv);
+  rc = run_dw_pair(ctx, s, wk, wv, dense_off);
   if (rc != SMOE_OK) return rc;
   S2SArgs xk = dense_s2s(dK, W_K, dXk, dense_off, N, d_model, d_out, true);
   S2SArgs xv = dense_s2s(dV, W_V, dXv, dense_off, N, d_model, d_out, true);
   xk.tail_ws = xv.tail_ws = tail_ws;
-  rc = run_s2s_pair(ctx, s, xk, xv);
+  rc = run_s2s_pair(ctx, s, xk, xv, dense_off);
   if (rc != SMOE_OK) return rc;
   // query projection (Alg. 2 without p, scattered in with fan-out k, scattered out): dW_Q, and dX = its part + dXk + dXv
-  const bool in_sum = k > 1 && aligned16(dX);   // added where the k slots are summed, whose kernel writes 16-byte lines
-  rc = plinear_bwd(ctx, stream, dtype, dQ, X, N, d_model, W_Q, d_out, nullptr, r, k, nullptr, 0, 0, 0, in_sum ? dX : dXq, dW_Q, nullptr, sub,
-                   sub_bytes, in_sum ? dXk : nullptr, in_sum ? dXv : nullptr);
+  rc = plinear_bwd(ctx, stream, dtype, dQ, X, N, d_model, W_Q, d_out, nullptr, r, k, nullptr, 0, 0, inv ? 1 : 0, in_sum ? dX : dXq, dW_Q, nullptr, sub,
+                   sub_bytes, in_sum ? dXk : nullptr, in_sum ? dXv : nullptr, inv);
   if (rc != SMOE_OK || in_sum) return rc;
   return launch_add3(s, dXq, dXk, dXv, dX, (size_t)N * d_model);
 }

@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restric
 __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                           const float *__restrict__ LSE, const float *__restrict__ minus_delta,
-                                                          bf16_t *__restrict__ dQ, AttnDims d) {
+                                                          bf16_t *__restrict__ dQ, const int32_t *__restrict__ dq_rows, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[ADS * 2 * ATILE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nbh = d.h * d.B, rank = (int)blockIdx.x / nbh, bh = (int)blockIdx.x - rank * nbh;   // as in the forward
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
   }
   wait_loads<0>();   // the requests past the last tile
   if (row_valid) {
-    bf16_t *orow = dQ + qrow;
+    bf16_t *orow = dQ + (dq_rows ? (size_t)dq_rows[(size_t)b * rows + r_mine] * d.ldq + hh * AD : qrow);
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
@@ -709,7 +709,7 @@ size_t attn_bwd_workspace_bytes(int B, int T, int G, int h) {
 }
 
 int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, const void *O, const void *dO,
-                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h) {
+                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool have_delta, const int32_t *dq_rows) {
   AttnDims d{B, T, G, h, (size_t)h * AD, (size_t)h * AD, 1.4426950408889634f / sqrtf((float)AD)};
   size_t n = (size_t)B * T * G * h;
   float *minus_delta = (float *)ws;
@@ -717,11 +717,13 @@ int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, 
   constexpr int NW = DKV_WAVES;
   const DkvPlan plan = dkv_plan(T, G, B * h);
   if ((long long)plan.units * h * B > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, (const bf16_t *)O, (const bf16_t *)dO,
-                     minus_delta, n);
-  SMOE_LAUNCH_CHECK();
+  if (!have_delta) {
+    hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, (const bf16_t *)O, (const bf16_t *)dO,
+                       minus_delta, n);
+    SMOE_LAUNCH_CHECK();
+  }
   hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(ceil_div(T * G, AQ) * h * B), dim3(256), 0, s, (const bf16_t *)Q,
-                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dQ, d);
+                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dQ, dq_rows, d);
   SMOE_LAUNCH_CHECK();
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, true, true>), dim3(plan.units * h * B), dim3(64 * NW), 0, s, (const bf16_t *)Q,
                      (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dK,

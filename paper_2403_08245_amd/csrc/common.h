@@ -59,8 +59,11 @@ int launch_topk_gate(hipStream_t s, const float *logits, int T, int E, int k, in
 int launch_attn_fwd(hipStream_t s, const void *Q, const void *K, const void *V, void *O, float *LSE, int B, int T, int G,
                     int h);
 size_t attn_bwd_workspace_bytes(int B, int T, int G, int h);
+// have_delta: the workspace already starts with minus_delta [B, T, G, h].  dq_rows: row of dQ that each query row's gradient goes to
+// (NULL: its own).
 int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, const void *O, const void *dO,
-                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h);
+                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool have_delta = false,
+                    const int32_t *dq_rows = nullptr);
 int launch_dense_offsets(hipStream_t s, int32_t *off, int n);
 int launch_add3(hipStream_t s, const void *a, const void *b, const void *c, void *out, size_t n);
 int launch_topk_gate_bwd(hipStream_t s, const int32_t *idx, const float *gates, const float *dgates, int T, int E, int k,
@@ -90,6 +93,9 @@ int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, co
 // dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even), and inv[o[i]] = i unless inv is NULL: finishes the routing-weight gradient left in slabs by the fused
 // backward epilogues.
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk);
+// The same for slabs that are the h heads of an attention output (ld = h rounded up to even): dg[o[i]] = sum_c part[i, c], and
+// minus_delta[o[i], c] = -g[o[i]] * part[i, c] for c < h (what the attention's backward pass starts from).
+int launch_dp_delta(hipStream_t s, const float *part, int ld, int h, const int32_t *o, const float *g, float *dg, float *minus_delta, int Tk);
 // dg[s] = <dY[s / kp], Yhat[s]>
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 
@@ -120,7 +126,7 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   const void *W;      // [E, d_in, d_out]
   void *C;            // [*, N] rows addressed through c_map
   RowMap a_map, c_map;
-  const int32_t *offsets;  // [E+1]
+  const int32_t *offsets;  // [E+1]; persistent kernels: NULL stands for E segments of Tk / E rows each
   int E, Tk;
   int K, N;           // contraction length and output width
   int ldw;            // row stride of W[e] (= d_out)
@@ -163,6 +169,7 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   // hidden activations), row_scale and dp_part set and Hpre_in NULL, the epilogue writes C = dH = row_scale * acc, the
   // slabs of dp = <acc, H>, and, when Hw_out [Tk, N] is given, Hw = row_scale * H (the routing-weighted hidden rows
   // that let groupXTY take the unweighted sorted dY for dW2 as well).  The activation's derivative stays a row kernel.
+  // With a scattered output (c_map set, Hw_out given) H and dH lie in slot order, the slabs and Hw in expert-sorted order.
   const void *H_in = nullptr;
   void *Hw_out = nullptr;
   // fp32 kernels (gemm_plain.hip): with H set the activation `act` is applied in the epilogue (C may be NULL), with Hpre_in

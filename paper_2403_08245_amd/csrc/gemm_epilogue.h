@@ -129,7 +129,7 @@ __device__ __forceinline__ void acc_block_to_patch(const f32x16 &a0, const f32x1
 }
 
 // store instructions a wavefront issues per tile, at least (a launch with fp32 partials issues more)
-template <int FM, int ACT> constexpr int EpilogueStores = FM * (ACT == 1 ? 12 : ACT == 2 ? 4 : ACT == 3 || ACT == 5 ? 16 : 8);
+template <int FM, int ACT> constexpr int EpilogueStores = FM * (ACT == 1 ? 12 : ACT == 2 ? 4 : ACT == 3 || ACT >= 5 ? 16 : 8);
 
 // dest(fm, half): where rows fm * 32 .. + 31, columns half * 64 .. + 63 of the wavefront's tile go
 template <int FM, typename DestFn>
@@ -181,9 +181,12 @@ __device__ __forceinline__ void store_wave_tile_swiglu(const f32x16 (&acc)[FM][F
 }
 
 // What the two backward epilogues read and write besides the block destinations.  All windows start at the wavefront's
-// first row (expert-sorted) and end with the segment, so rows past it read zeros and are not written.
+// first row (expert-sorted) and end with the segment, so rows past it read zeros and are not written; `saved` with `places` set
+// is a whole tensor instead, whose rows are found through the order indices.
 struct BwdRows {
   window_t saved;       // pre-activations [rows, 2 * n] (SwiGLU) or hidden rows [rows, n]
+  const int *places;    // rows of `saved` that the wavefront's rows lie in (LDS), `left` of them
+  int left;
   window_t scale;       // routing weight of every row
   window_t dp;          // slabs of dp, [rows, part_ld] fp32
   uint32_t saved_bytes; // bytes per row of `saved`
@@ -215,8 +218,17 @@ struct GateUp {
 // A 32 x 64 block of a saved tensor as whole 128-byte rows, eight lanes each, `col` bytes into the rows.  (A lane fetching its
 // own row's 8-byte pieces touched 32 lines per instruction, each line again for every piece, and more lines than the L1
 // holds: the epilogue took 27 us a tile, on 54 us of products at a contraction of 2048.)
-__device__ __forceinline__ PatchRows load_saved_rows(const BwdRows &b, int fm, uint32_t col, int lane) {
+template <bool PLACES = false> __device__ __forceinline__ PatchRows load_saved_rows(const BwdRows &b, int fm, uint32_t col, int lane) {
   PatchRows r;
+  if (PLACES) {
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int row = fm * 32 + it * 8 + (lane >> 3);
+      const uint32_t off = (uint32_t)b.places[row] * b.saved_bytes + col + (uint32_t)(lane & 7) * 16u;
+      r.v[it] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b.saved, (int)(row < b.left ? off : ~0u), 0, 0));
+    }
+    return r;
+  }
   const uint32_t base = (uint32_t)(fm * 32 + (lane >> 3)) * b.saved_bytes + col + (uint32_t)(lane & 7) * 16u;
 #pragma unroll
   for (int it = 0; it < 4; ++it)
@@ -302,11 +314,12 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
 
 // The activation-agnostic form: the accumulators hold dH / p; the wavefront fetches the saved hidden activations H of the
 // block, adds <acc, H> to the row's slab of dp, and writes dH = p * acc (HW: and Hw = p * H).
-template <bool AHEAD, bool HW, int FM, typename DestFn, typename HwFn>
+// PLACES: the hidden rows and dH lie in slot order, the slabs and Hw are expert-sorted.
+template <bool AHEAD, bool HW, bool PLACES, int FM, typename DestFn, typename HwFn>
 __device__ __forceinline__ void store_wave_tile_dp(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
                                                    HwFn dest_hw, int lane) {
   acc_settle();
-  auto load_h = [&](int fm, int half) { return load_saved_rows(b, fm, (uint32_t)(b.gcol + half * 64) * 2u, lane); };
+  auto load_h = [&](int fm, int half) { return load_saved_rows<PLACES>(b, fm, (uint32_t)(b.gcol + half * 64) * 2u, lane); };
   RowStore<BlockDest> pend;
   PatchRows next;
   float scale_next = 0.f;

@@ -175,7 +175,7 @@ template <typename S, bool TRANS_W, bool KTAIL> struct S2SOps {
 
 // ACT 1: fused SwiGLU keeping the pre-activation, 2: without, 3: fused SwiGLU derivative and dp (the W2^T input-gradient
 // product of Alg. 3's backward, see store_wave_tile_swiglu_bwd), 4: dp from the saved H in that product's epilogue for any
-// activation (store_wave_tile_dp), 5: 4 with the routing-weighted hidden rows written as well.
+// activation (store_wave_tile_dp), 5: 4 with the routing-weighted hidden rows written as well, 6: 5 with H and dH in slot order.
 // STATIC4 (Big only): the contraction is a multiple of four half-steps, so every tile starts in LDS slot 0 and the loop is
 // written out four half-steps at a time with the slot as a compile-time constant: all LDS addresses become a loop-invariant
 // register plus an immediate.  Without it the contraction may be any multiple of 8 (KTAIL masks the last half-step).
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
   constexpr bool DENSE_PAIR = ACT == 0 && !SCATTER_OUT;   // S2SArgs::C2 may be set
   constexpr int STORES = EpilogueStores<S::FM, ACT>;
   static_assert(!SWIGLU || (!TRANS_W && !SCATTER_OUT), "the fused activation belongs to the forward, sorted-output product");
-  static_assert(ACT < 3 || (TRANS_W && !SCATTER_OUT), "the fused derivative belongs to the W^T product with sorted rows out");
+  static_assert(ACT < 3 || (TRANS_W && SCATTER_OUT == (ACT == 6)), "the fused derivative belongs to the W^T product");
   static_assert(!STATIC4 || S::SLOTS == 4, "the unrolled loop walks four slots");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_off[MAX_E + 1];
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
 
   const bool probe = a.clock_probe && blockIdx.x < MAX_STREAM_GRID;
   const unsigned long long probe_c0 = probe ? clock64() : 0ull, probe_t0 = probe ? wall_clock64() : 0ull;
-  for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets[i];
+  for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
 
   const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, nh, G, STATIC4, ACT == 0 && a.tail_ws != nullptr, lane);
@@ -398,6 +398,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
       }
       half_step(No{}, Yes{}, cur, false);
     }
+    const int lane = ACT == 6 ? lane_here(threadIdx.x & 63) : (int)(threadIdx.x & 63);
     char *patch = S::PATCH_IN_SLOT ? smem + cur + S::A_BYTES + uwave * EPI_WAVE_BYTES
                                    : smem + S::SLOTS * S::SLOT_BYTES + uwave * EPI_WAVE_BYTES;
     const auto p = args();
@@ -415,6 +416,18 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
       for (int it = 0; it < 4; ++it) d.off[it] = mine + (uint32_t)(fm * 32 + it * 8) * (uint32_t)ld * 2u;
       return d;
     };
+    // the same of a tensor in slot order: the rows' places come from the order indices
+    auto slot_block = [&](window_t win, int n, const int *places, int rows, int fm, int col0) {
+      BlockDest d{win, {}};
+      const int col = col0 + (lane & 7) * 8;
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int r = fm * 32 + it * 8 + (lane >> 3);
+        const uint32_t off = (uint32_t)places[r] * ((uint32_t)n * 2u) + (uint32_t)col * 2u;
+        d.off[it] = r < rows && col < n ? off : ~0u;
+      }
+      return d;
+    };
     if constexpr (SWIGLU) {
       const int half_n = N / 2, gcol = ct.n0 + uwn * (TB / 4);
       const window_t win_h = sorted_window(p->H, half_n, 2);
@@ -424,9 +437,12 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
           [&](int fm) { return sorted_block(win_h, half_n, fm, gcol, half_n - gcol); }, lane);
     } else if constexpr (ACT >= 3) {
       const int gcol = ct.n0 + uwn * (TB / 2), ldc = ACT == 3 ? 2 * N : N;
-      const window_t win_c = sorted_window(p->C, ldc, 2);
+      const uint32_t slot_bytes = (uint32_t)p->Tk * (uint32_t)N * 2u;                 // ACT 6: of dH and of H
+      const window_t win_c = ACT == 6 ? make_window(p->C, slot_bytes) : sorted_window(p->C, ldc, 2);
       BwdRows b;
-      b.saved = sorted_window(ACT == 3 ? p->Hpre_in : p->H_in, ldc, 2);
+      b.saved = ACT == 6 ? make_window(p->H_in, slot_bytes) : sorted_window(ACT == 3 ? p->Hpre_in : p->H_in, ldc, 2);
+      b.places = &s_idx[ct.seq & 3][uwm * (S::TM / 2)];
+      b.left = left;
       b.saved_bytes = (uint32_t)ldc * 2u;
       b.scale = sorted_window(p->row_scale, 1, 4);
       b.dp = sorted_window(p->dp_part, 2 * tiles_n, 4);
@@ -439,9 +455,13 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
             acc, patch, b,
             [&](int fm, int half, int up) { return sorted_block(win_c, ldc, fm, up * N + gcol + half * 64, N - gcol - half * 64); }, lane);
       } else {
-        const window_t win_w = ACT == 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
-        store_wave_tile_dp<S::BLOCKS == 1, ACT == 5>(
-            acc, patch, b, [&](int fm, int half) { return sorted_block(win_c, ldc, fm, gcol + half * 64, N - gcol - half * 64); },
+        const window_t win_w = ACT >= 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
+        auto dest = [&](int fm, int half) {
+          if constexpr (ACT == 6) return slot_block(win_c, N, b.places, left, fm, gcol + half * 64);
+          else return sorted_block(win_c, ldc, fm, gcol + half * 64, N - gcol - half * 64);
+        };
+        store_wave_tile_dp<S::BLOCKS == 1, ACT >= 5, ACT == 6>(
+            acc, patch, b, dest,
             [&](int fm, int half) { return sorted_block(win_w, N, fm, gcol + half * 64, N - gcol - half * 64); },
             lane);
       }
@@ -464,17 +484,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
         }, lane);
       } else if constexpr (SCATTER_OUT) {
         const window_t win = make_window(p->C, (uint32_t)p->Tk * (uint32_t)N * 2u);
-        store_wave_tile(acc, patch, [&](int fm, int half) {
-          BlockDest d{win, {}};
-          const int col = wcol + half * 64 + (lane & 7) * 8;
-#pragma unroll
-          for (int it = 0; it < 4; ++it) {
-            const int r = fm * 32 + it * 8 + (lane >> 3);
-            const uint32_t off = (uint32_t)idx[r] * ((uint32_t)N * 2u) + (uint32_t)col * 2u;
-            d.off[it] = r < left && col < N ? off : ~0u;
-          }
-          return d;
-        }, lane);
+        store_wave_tile(acc, patch, [&](int fm, int half) { return slot_block(win, N, idx, left, fm, wcol + half * 64); }, lane);
       } else {
         const window_t win = sorted_window(p->C2 && ct.e == 1 ? p->C2 : p->C, N, 2);
         store_wave_tile(acc, patch, [&](int fm, int half) { return sorted_block(win, N, fm, wcol + half * 64, N - wcol - half * 64); },
@@ -509,7 +519,7 @@ template <typename S, bool SCATTER_OUT>
 __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int tiles_n, int group_m, int G, int static4) {
   __shared__ int s_off[MAX_E + 1];
   const int lane = threadIdx.x & 63;
-  for (int i = threadIdx.x; i <= a.E; i += 256) s_off[i] = a.offsets[i];
+  for (int i = threadIdx.x; i <= a.E; i += 256) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
   const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, (a.K + HK - 1) / HK, G, static4 != 0, true, lane);
   if (plan.split <= 1) return;
@@ -605,7 +615,7 @@ template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_str
   const int slot_in_round = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);  // XCD-contiguous tiles
   const int per_expert = tiles_m * tiles_n;
 
-  for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets[i];
+  for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
   for (int x = threadIdx.x; x < a.E; x += NTHREADS) {
     int nx = s_off[x + 1] - s_off[x], before = 0;
@@ -822,22 +832,27 @@ bool prefer_pair(const S2SArgs &a, int tiles_n, bool may_split) {
 }
 template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStream_t s, const S2SArgs &a) {
   const bool static4 = a.K % (4 * HK) == 0;
-  if (SCATTER_OUT && (long long)a.Tk * a.N * 2 > 0xfffffff0LL) {   // rows a 32-bit offset does not reach
-    if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, SCATTER_OUT>(s, a);
-    return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, SCATTER_OUT>(s, a);
-  }
-  const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
-  const bool may_split = ACT == 0 && a.tail_ws;
-  if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split))) {
-    // At most one tile row per expert on average: most of W is read once, and where the call's weights exceed the last-level cache
-    // keeping its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53).  With
-    // reuse they belong there (8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156), so a tile of an expert that has
-    // several takes them the ordinary way (777 tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass
-    // 133 us with all of W past the caches, 129 with none, 125 so).
-    if constexpr (!TRANS_W)
-      if ((long long)a.Tk <= (long long)a.E * Pair::TM && weights_pass_caches(a))
-        return launch_s2s_one<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
-    return launch_s2s_one<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+  if constexpr (SCATTER_OUT && ACT == 0)
+    if ((long long)a.Tk * a.N * 2 > 0xfffffff0LL) {   // rows a 32-bit offset does not reach
+      if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, true>(s, a);
+      return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, true>(s, a);
+    }
+  // The epilogue of ACT 6 (two offsets per row, two outputs) does not fit the 128 registers of a pair: 72 of them spilled, and the
+  // product of 32768 rows, 2048 -> 512, took 225 us of 121.
+  if constexpr (ACT != 6) {
+    const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
+    const bool may_split = ACT == 0 && a.tail_ws;
+    if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_pair(a, tiles_n, may_split))) {
+      // At most one tile row per expert on average: most of W is read once, and where the call's weights exceed the last-level cache
+      // keeping its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53).  With
+      // reuse they belong there (8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156), so a tile of an expert that has
+      // several takes them the ordinary way (777 tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass
+      // 133 us with all of W past the caches, 129 with none, 125 so).
+      if constexpr (!TRANS_W)
+        if ((long long)a.Tk <= (long long)a.E * Pair::TM && weights_pass_caches(a))
+          return launch_s2s_one<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+      return launch_s2s_one<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+    }
   }
   if (static4) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, false>(s, a);
   return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
@@ -882,7 +897,8 @@ bool s2s_stream_swiglu_bwd_supported(const S2SArgs &a) {
 }
 
 bool s2s_stream_dp_supported(const S2SArgs &a) {
-  return s2s_stream_supported(a) && a.trans_w && !a.c_map.o && a.H_in && !a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
+  const bool slots_fit = !a.c_map.o || (a.Hw_out && (long long)a.Tk * a.N * 2 <= 0xfffffff0LL);   // ACT 6: 32-bit offsets of slot rows
+  return s2s_stream_supported(a) && a.trans_w && slots_fit && a.H_in && !a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
 }
 
 bool s2s_stream_swiglu_supported(const S2SArgs &a) {
@@ -897,6 +913,7 @@ int launch_s2s_stream(hipStream_t s, const S2SArgs &a) {
   }
   if (a.dp_part) {
     if (!s2s_stream_dp_supported(a)) return SMOE_ERR_UNSUPPORTED;
+    if (scatter_out) return launch_s2s_cfg<true, true, 6>(s, a);
     return a.Hw_out ? launch_s2s_cfg<true, false, 5>(s, a) : launch_s2s_cfg<true, false, 4>(s, a);
   }
   if (a.H) {
@@ -918,12 +935,13 @@ int launch_dw_stream(hipStream_t s, const DWArgs &a) { return launch_dw_stream_i
 template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s() {
   int rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, false>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, false>, Big::LDS_BYTES);
-  if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
+  if constexpr (ACT != 6)
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Pair, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
   if constexpr (!TRANS_W)
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<PairOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, Pair::LDS_BYTES);
-  if (SCATTER_OUT) {
-    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, SCATTER_OUT>, Big::LDS_BYTES);
-    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, SCATTER_OUT>, Big::LDS_BYTES);
+  if constexpr (SCATTER_OUT && ACT == 0) {
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, true>, Big::LDS_BYTES);
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, true>, Big::LDS_BYTES);
   }
   return rc;
 }
@@ -937,6 +955,7 @@ int init_stream_kernels() {
   if (rc == SMOE_OK) rc = init_s2s<true, false, 3>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 4>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
+  if (rc == SMOE_OK) rc = init_s2s<true, true, 6>();
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<false>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<true>, Big::LDS_BYTES);
   return rc;

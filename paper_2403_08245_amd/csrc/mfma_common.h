@@ -67,6 +67,13 @@ template <int N> __device__ __forceinline__ void wait_loads() {
   __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ uint32_t lds_address(const char *p) { return (uint32_t)(size_t)(LDS_AS const char *)p; }
+// The same lane number, but what is computed from it stays where it is written: in code that runs once per tile the compiler
+// otherwise moves everything that depends on the lane alone in front of the tile loop and holds (or spills) it through the
+// contraction.
+__device__ __forceinline__ int lane_here(int lane) {
+  __asm__ volatile("" : "+v"(lane));
+  return lane;
+}
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
 __device__ __align__(16) const uint32_t g_zero16[4] = {0u, 0u, 0u, 0u};
