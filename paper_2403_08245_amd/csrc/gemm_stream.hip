@@ -195,6 +195,9 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
   // half-steps) the loader has opened tile n+2 and requested the rows of tile n+3 while tile n's epilogue still
   // reads its destination rows, so four entries are live at once.
   __shared__ int s_idx[4][S::TM];
+  // The open tiles themselves, left by the loader's search for the multiplying side (every wavefront writes the same values and
+  // reads its own).
+  __shared__ __attribute__((aligned(16))) int s_tile[4][4];
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = wave >> 1, wn = wave & 1;
@@ -253,6 +256,19 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
     t.row0 = __builtin_amdgcn_readfirstlane(row0);
     t.row_end = __builtin_amdgcn_readfirstlane(row_end);
     t.n0 = nt * (SWIGLU ? TB / 2 : TB);   // SwiGLU tiles hold 128 gate columns and the 128 up columns pairing with them
+    *reinterpret_cast<int4 *>(s_tile[seq & 3]) = make_int4(t.e, t.row0, t.row_end, t.n0);
+    return true;
+  };
+  // the multiplying side's next tile, which the loader has opened before
+  const int tiles = rounds + (last_tile >= 0 ? 1 : 0);
+  auto follow = [&](Tile &t) -> bool {
+    if (t.seq + 1 >= tiles) return false;
+    ++t.seq;
+    const int4 v = *reinterpret_cast<const int4 *>(s_tile[t.seq & 3]);
+    t.e = __builtin_amdgcn_readfirstlane(v.x);
+    t.row0 = __builtin_amdgcn_readfirstlane(v.y);
+    t.row_end = __builtin_amdgcn_readfirstlane(v.z);
+    t.n0 = __builtin_amdgcn_readfirstlane(v.w);
     return true;
   };
   auto half_steps = [&](const Tile &t) { return t.seq < rounds ? nh : last_hn; };
@@ -498,7 +514,7 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
       for (int g = 0; g < 3; ++g) read_frag_group<S>(ops, f0, smem + Ring<S>::after(cur), 0, g, wm, wn, lane);
     }
     if constexpr (!STATIC4) cur = Ring<S>::after(cur);
-    if (!next_tile(ct)) break;
+    if (!follow(ct)) break;
   }
   wait_loads<0>();
   if (probe && threadIdx.x == 0) {
