@@ -649,15 +649,32 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     DWArgs w2{L.use_hw ? (const void *)second : saved_H, L.use_hw ? (const void *)dYu : (const void *)second, dW2,
               r->expert_offsets, r->E, Tk, d_expert, d_model};
     w2.split_ws = tail_ws;
-    rc = run_dw(ctx, s, dtype, w2);
-    if (rc != SMOE_OK) return rc;
-    void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead: its array holds Xbar, then dXbar
-    rc = sorted_copy(X, inv_x, nullptr, Xbar);
-    if (rc != SMOE_OK) return rc;
-    DWArgs w1{Xbar, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
-    w1.split_ws = tail_ws;
-    rc = run_dw(ctx, s, dtype, w1);
-    if (rc != SMOE_OK) return rc;
+    void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead after dW2: its array holds Xbar, then dXbar
+    // Both weight gradients in one launch where that saves a round of tiles: the sorted copy of X then has to stand beside that of dY,
+    // and takes the room of the partial tiles, which nothing needs until the last product.
+    DWArgs both = w2;
+    both.grid = ctx->stream_grid;
+    both.A3 = tail_ws;
+    both.B3 = dHpre;
+    both.dW3 = dW1;
+    both.M3 = d_model;
+    both.N3 = d_h;
+    if ((size_t)Tk * d_model * es <= S2S_TAIL_WS_BYTES && !overlap(dW1, (size_t)r->E * d_model * d_h * es, saved_H, (size_t)Tk * d_expert * es) &&
+        dw_stream_supported(both) && dw_stream_two_pay(both)) {
+      rc = sorted_copy(X, inv_x, nullptr, tail_ws);
+      if (rc != SMOE_OK) return rc;
+      rc = launch_dw_stream(s, both);
+      if (rc != SMOE_OK) return rc;
+    } else {
+      rc = run_dw(ctx, s, dtype, w2);
+      if (rc != SMOE_OK) return rc;
+      rc = sorted_copy(X, inv_x, nullptr, Xbar);
+      if (rc != SMOE_OK) return rc;
+      DWArgs w1{Xbar, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
+      w1.split_ws = tail_ws;
+      rc = run_dw(ctx, s, dtype, w1);
+      if (rc != SMOE_OK) return rc;
+    }
     S2SArgs x1 = make_s2s(dHpre, W1, k == 1 ? dX : Xbar, r, d_model, d_h, true, true, 1, false);
     x1.tail_ws = tail_ws;
     rc = run_s2s(ctx, s, dtype, x1);

@@ -192,6 +192,11 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both 
   // Optional second weight gradient of the same sizes in the same launch (persistent kernel; E = 2), as S2SArgs has it.
   const void *A2 = nullptr, *B2 = nullptr;
   void *dW2 = nullptr;
+  // Optional further weight gradient over the same segments in the same launch (persistent kernel, no split): dW3 [E, M3, N3] from
+  // A3 [Tk, M3] and B3 [Tk, N3].
+  const void *A3 = nullptr, *B3 = nullptr;
+  void *dW3 = nullptr;
+  int M3 = 0, N3 = 0;
   // fp32 kernels (gemm_plain.hip): rows of A and B read through the order indices instead of from sorted copies, and B's rows
   // scaled by the routing weights (fp32, slot order; needs b_map).
   RowMap a_map{nullptr, 1}, b_map{nullptr, 1};
@@ -225,3 +230,4 @@ bool s2s_decode_supported(const S2SArgs &a);
 int launch_s2s_decode(hipStream_t s, const S2SArgs &a);
 bool dw_stream_supported(const DWArgs &a);
 int launch_dw_stream(hipStream_t s, const DWArgs &a);
+bool dw_stream_two_pay(const DWArgs &a);   // is a launch with dW3 shorter than one for each?

@@ -579,6 +579,7 @@ struct DWCursor {
   int step, ns;   // slot within the tile, slots of the tile
   int nh;         // half-steps (0 for an empty expert)
   int e, lo, hi, m0, n0;
+  bool further;   // a tile of dW3
   bool live;
 };
 
@@ -618,8 +619,11 @@ __device__ __forceinline__ void dw_chunk_rows(int lo, int hi, int split, int chu
 
 // split > 1 (only when all experts' tiles times split fit one round of the grid): unit T is chunk T % split of
 // tile T / split, experts in their own order, and the result is an fp32 partial tile number T in a.split_ws.
-// DENSE_PAIR: segment 1 is the second weight gradient of DWArgs (a kernel of its own: the choice of operands sits in every slot).
-template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split) {
+// KIND (kernels of their own: the choice of operands sits in every slot): DW_PAIR segment 1 is the second weight gradient of DWArgs;
+// DW_TWO every expert's tiles are followed by those of its dW3.
+enum { DW_ONE = 0, DW_PAIR = 1, DW_TWO = 2 };
+template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split) {
+  constexpr bool DENSE_PAIR = KIND == DW_PAIR;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_off[MAX_E + 1];
   __shared__ int s_order[MAX_E];      // experts, largest segment first
@@ -629,7 +633,8 @@ template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_str
   const int uwm = __builtin_amdgcn_readfirstlane(wm), uwn = __builtin_amdgcn_readfirstlane(wn);
   const int G = gridDim.x;
   const int slot_in_round = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);  // XCD-contiguous tiles
-  const int per_expert = tiles_m * tiles_n;
+  const int tiles_m3 = (a.M3 + TB - 1) / TB, tiles_n3 = (a.N3 + TB - 1) / TB;
+  const int per_first = tiles_m * tiles_n, per_expert = per_first + (KIND == DW_TWO ? tiles_m3 * tiles_n3 : 0);
 
   for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
@@ -655,7 +660,9 @@ template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_str
     c.lo = __builtin_amdgcn_readfirstlane(s_off[c.e]);
     c.hi = __builtin_amdgcn_readfirstlane(s_off[c.e + 1]);
     if (split > 1) dw_chunk_rows(c.lo, c.hi, split, U - T * split, c.lo, c.hi);
-    dw_tile_origin(t, tiles_m, tiles_n, c.m0, c.n0);
+    c.further = KIND == DW_TWO && t >= per_first;
+    if (c.further) dw_tile_origin(t - per_first, tiles_m3, tiles_n3, c.m0, c.n0);
+    else dw_tile_origin(t, tiles_m, tiles_n, c.m0, c.n0);
     c.nh = (c.hi - c.lo + HK - 1) / HK;
     // Slots come in groups of four so that every tile starts in LDS stage 0 and the loop can be written
     // with compile-time stages; the up to three extra slots (four for an empty expert) load the zero
@@ -677,27 +684,29 @@ template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_str
 #pragma unroll
   for (int I = 0; I < NLD; ++I) tr_lane_slot(wave, lane, I, ops.ra[I], ops.ka[I]);
   const bf16_t *A = (const bf16_t *)a.A, *B = (const bf16_t *)a.B;
-  const uint32_t row_a = (uint32_t)a.M * 2u, row_b = (uint32_t)a.N * 2u;   // bytes per operand row
   // loader cursor: publish the slot whose eight loads are issued next
-  int shown_m0 = -1, shown_n0 = -1;
+  int shown_m0 = -1, shown_n0 = -1, shown_further = -1;
   auto resolve = [&](const DWCursor &c) {
     const int first = c.lo + (c.step & ~3) * HK;                 // first row of this group of four slots
     const int left = c.live ? max(c.hi - first, 0) : 0;          // rows of the segment from there on
     const int base_row = left > 0 ? first : 0;
     const unsigned long long cap = 0xffffffffull;
-    const bool second = DENSE_PAIR && c.e == 1;
-    ops.win_a = buffer_window((second ? (const bf16_t *)a.A2 : A) + (size_t)base_row * a.M, (uint32_t)min((unsigned long long)left * row_a, cap));
-    ops.win_b = buffer_window((second ? (const bf16_t *)a.B2 : B) + (size_t)base_row * a.N, (uint32_t)min((unsigned long long)left * row_b, cap));
+    const bool second = DENSE_PAIR && c.e == 1, further = KIND == DW_TWO && c.further;
+    const int M = further ? a.M3 : a.M, N = further ? a.N3 : a.N;
+    const uint32_t row_a = (uint32_t)M * 2u, row_b = (uint32_t)N * 2u;   // bytes per operand row
+    ops.win_a = buffer_window((further ? (const bf16_t *)a.A3 : second ? (const bf16_t *)a.A2 : A) + (size_t)base_row * M, (uint32_t)min((unsigned long long)left * row_a, cap));
+    ops.win_b = buffer_window((further ? (const bf16_t *)a.B3 : second ? (const bf16_t *)a.B2 : B) + (size_t)base_row * N, (uint32_t)min((unsigned long long)left * row_b, cap));
     ops.sub_a = (uint32_t)(c.step & 3) * HK * row_a;
     ops.sub_b = (uint32_t)(c.step & 3) * HK * row_b;
-    if (c.m0 != shown_m0 || c.n0 != shown_n0) {                  // a new tile: its columns' offsets inside a slot
+    if (c.m0 != shown_m0 || c.n0 != shown_n0 || (KIND == DW_TWO && (int)c.further != shown_further)) {   // a new tile: its columns' offsets inside a slot
       shown_m0 = c.m0;
       shown_n0 = c.n0;
+      shown_further = c.further;
 #pragma unroll
       for (int J = 0; J < NLD; ++J) {
         int ca = c.m0 + ops.ka[J] * 8, cb = c.n0 + ops.ka[J] * 8;
-        if (ca >= a.M) ca = 0;
-        if (cb >= a.N) cb = 0;
+        if (ca >= M) ca = 0;
+        if (cb >= N) cb = 0;
         ops.oa[J] = (uint32_t)ops.ra[J] * row_a + (uint32_t)ca * 2u;
         ops.ob[J] = (uint32_t)ops.ra[J] * row_b + (uint32_t)cb * 2u;
       }
@@ -755,12 +764,14 @@ template <bool DENSE_PAIR> __global__ void __launch_bounds__(NTHREADS, 1) dw_str
     if (split > 1) {
       store_wave_partial(acc, a.split_ws + (size_t)(cc.seq * G + slot_in_round) * TB * TB + (size_t)(uwm * (TB / 2)) * TB + uwn * (TB / 2), lane);
     } else {
-      const int left = max(min(TB / 2, a.M - mbase), 0);
-      const window_t win = make_window((const bf16_t *)(DENSE_PAIR && cc.e == 1 ? a.dW2 : a.dW) + (size_t)cc.e * a.M * a.N + (size_t)min(mbase, a.M) * a.N, (uint32_t)left * row_b);
+      const int M = KIND == DW_TWO && cc.further ? a.M3 : a.M, N = KIND == DW_TWO && cc.further ? a.N3 : a.N;
+      const uint32_t row_b = (uint32_t)N * 2u;
+      const int left = max(min(TB / 2, M - mbase), 0);
+      const window_t win = make_window((const bf16_t *)(KIND == DW_TWO && cc.further ? a.dW3 : DENSE_PAIR && cc.e == 1 ? a.dW2 : a.dW) + (size_t)cc.e * M * N + (size_t)min(mbase, M) * N, (uint32_t)left * row_b);
       store_wave_tile(acc, patch, [&](int fm, int half) {
         BlockDest d{win, {}};
         const int col = wcol + half * 64 + (lane & 7) * 8;
-        const uint32_t mine = col < a.N ? (uint32_t)(lane >> 3) * row_b + (uint32_t)col * 2u : OFF_WINDOW;
+        const uint32_t mine = col < N ? (uint32_t)(lane >> 3) * row_b + (uint32_t)col * 2u : OFF_WINDOW;
 #pragma unroll
         for (int it = 0; it < 4; ++it) d.off[it] = mine + (uint32_t)(fm * 32 + it * 8) * row_b;
         return d;
@@ -885,8 +896,10 @@ int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
     split = (int)(a.grid / tiles < 8 ? a.grid / tiles : 8);
     if (nh - nh / split < SPLIT_MIN_SAVED) split = 1;
   }
-  if (a.dW2) hipLaunchKernelGGL(dw_stream_kernel<true>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
-  else hipLaunchKernelGGL(dw_stream_kernel<false>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  if (a.dW3) split = 1;
+  if (a.dW3) hipLaunchKernelGGL(dw_stream_kernel<DW_TWO>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  else if (a.dW2) hipLaunchKernelGGL(dw_stream_kernel<DW_PAIR>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  else hipLaunchKernelGGL(dw_stream_kernel<DW_ONE>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
   SMOE_LAUNCH_CHECK();
   if (split > 1) {
     hipLaunchKernelGGL(dw_split_reduce_kernel, dim3((unsigned)tiles, TAIL_SLICES), dim3(256), 0, s, a, tiles_m, tiles_n, split);
@@ -941,8 +954,18 @@ int launch_s2s_stream(hipStream_t s, const S2SArgs &a) {
 }
 
 bool dw_stream_supported(const DWArgs &a) {
-  long long tiles = (long long)a.E * ceil_div(a.M, TB) * ceil_div(a.N, TB);
-  return a.M % 8 == 0 && a.N % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 && a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL;
+  long long tiles = (long long)a.E * ((long long)ceil_div(a.M, TB) * ceil_div(a.N, TB) + (long long)ceil_div(a.M3, TB) * ceil_div(a.N3, TB));
+  return a.M % 8 == 0 && a.N % 8 == 0 && a.M3 % 8 == 0 && a.N3 % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 &&
+         a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL && (long long)TB * a.N3 * 2 < 0x80000000LL;
+}
+
+// Together two weight gradients save the rounds that their last tiles fill only in part, and a launch, while a slot costs 3 % more
+// (its operands are chosen).  8 experts of 750 rows, 3416 x 1280 and 1280 x 6832 (2.2 + 4.2 rounds of tiles): 81 + 145 -> 203 us.
+bool dw_stream_two_pay(const DWArgs &a) {
+  const long long first = (long long)a.E * ceil_div(a.M, TB) * ceil_div(a.N, TB), further = (long long)a.E * ceil_div(a.M3, TB) * ceil_div(a.N3, TB);
+  auto rounds = [&](long long tiles) { return (tiles + a.grid - 1) / a.grid; };
+  if (first * 2 <= a.grid || further * 2 <= a.grid) return false;      // one of them may be cut along its rows instead
+  return rounds(first + further) * 33 <= (rounds(first) + rounds(further)) * 32;
 }
 
 int launch_dw_stream(hipStream_t s, const DWArgs &a) { return launch_dw_stream_impl(s, a); }
@@ -972,7 +995,8 @@ int init_stream_kernels() {
   if (rc == SMOE_OK) rc = init_s2s<true, false, 4>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
   if (rc == SMOE_OK) rc = init_s2s<true, true, 6>();
-  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<false>, Big::LDS_BYTES);
-  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<true>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_ONE>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_PAIR>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_TWO>, Big::LDS_BYTES);
   return rc;
 }
