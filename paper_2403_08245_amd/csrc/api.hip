@@ -351,24 +351,26 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
     rc = launch_invert(s, r->sorted_scattered_idxs, own_inv, nullptr, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
   }
+  void *xbar = grouped_in ? nullptr : (void *)((char *)ws + off_xbar);
+  const bool spread_both = spread_y && spread_x && !grouped_in && dW && gates_k == k;
   const void *dYbar = dY;
   if (!grouped_out) {
-    if (gates && dgates) {
+    const RowDots dots{dY, Yhat, gates ? dgates : nullptr, Tk, gates_k, d_out};
+    if (dots.dg && !spread_y) {
       rc = launch_rowdot(s, dtype, dY, Yhat, dgates, Tk, gates_k, d_out);
       if (rc != SMOE_OK) return rc;
     }
     void *buf = (char *)ws + off_dybar;
-    rc = spread_y ? launch_spread(s, dY, inv, gates_k, gates, buf, Tk, d_out)
+    rc = spread_y ? launch_spread(s, dY, inv, gates_k, gates, buf, Tk, d_out, dots, spread_both ? X : nullptr, spread_both ? xbar : nullptr, d_in)
                   : launch_group(s, dtype, dY, r->sorted_scattered_idxs, gates ? gates_k : 1, gates, buf, Tk, d_out);
     if (rc != SMOE_OK) return rc;
     dYbar = buf;
   }
   // Xbar = group(X, o);  dW = groupXTY(Xbar, dYbar)
-  void *xbar = grouped_in ? nullptr : (void *)((char *)ws + off_xbar);
   if (dW) {
     const void *Xg = X;
     if (!grouped_in) {
-      rc = spread_x ? launch_spread(s, X, inv, k, nullptr, xbar, Tk, d_in)
+      rc = spread_both ? SMOE_OK : spread_x ? launch_spread(s, X, inv, k, nullptr, xbar, Tk, d_in)
                     : launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, xbar, Tk, d_in);
       if (rc != SMOE_OK) return rc;
       Xg = xbar;

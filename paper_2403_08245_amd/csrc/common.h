@@ -88,8 +88,6 @@ int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o,
                  void *out, int Tk, int d);
 // inv[o[i]] = i and g_sorted[i] = g[o[i]] (inv, and g with g_sorted, may be NULL)
 int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk);
-// the copy launch_group makes of bf16 rows, by the inverse of the order indices: Tk / fan source rows, each read once
-int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d);
 // dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even), and inv[o[i]] = i unless inv is NULL: finishes the routing-weight gradient left in slabs by the fused
 // backward epilogues.
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk);
@@ -100,9 +98,9 @@ int launch_dp_delta(hipStream_t s, const float *part, int ld, int h, const int32
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 
 struct RowDots {      // dg[s] = <dY[s / kp], Yhat[s]> for s < Tk, rows of d elements (16-byte multiples)
-  const void *dY, *Yhat;
-  float *dg;
-  int Tk, kp, d;
+  const void *dY = nullptr, *Yhat = nullptr;
+  float *dg = nullptr;    // NULL: none
+  int Tk = 0, kp = 1, d = 0;
 };
 // one of them, by one wavefront
 template <typename T> __device__ __forceinline__ void row_dot(const RowDots &r, int s, int lane) {
@@ -119,6 +117,11 @@ template <typename T> __device__ __forceinline__ void row_dot(const RowDots &r, 
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if (lane == 0) r.dg[s] = acc;
 }
+
+// The copy launch_group makes of bf16 rows, by the inverse of the order indices: Tk / fan source rows, each read once.  In the same launch,
+// where given: the row dots of dp, and a second, unweighted copy of rows of d2 elements with the same fan.
+int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d, const RowDots &dots = RowDots{},
+                  const void *in2 = nullptr, void *out2 = nullptr, int d2 = 0);
 
 // ---- GEMM launchers (gemm_plain.hip, gemm_mfma.hip)
 struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted rows i

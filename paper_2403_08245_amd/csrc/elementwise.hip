@@ -206,28 +206,53 @@ __global__ void __launch_bounds__(256) invert_kernel(const int32_t *__restrict__
 
 // ---- spread: the copy `group` makes, from the side of the source: out[inv[t * fan + j]] = g[t * fan + j] * in[t].  Bound by the
 // write of the Tk rows; `group` read every source row fan times as well, from whichever XCD's L2 its sorted row fell to.
+struct Spread {
+  const bf16_t *in;
+  const float *g;
+  bf16_t *out;
+  int rows, d, blocks;   // blocks 0: nothing to do
+  RowLanes l;
+};
 template <int K>   // fan where it is at most 8 (its stores then need no loop: k = 2 65 -> 63.5 us, k = 4 52.5 -> 51), else 0
-__global__ void __launch_bounds__(256) spread_kernel(const bf16_t *__restrict__ in, const int32_t *__restrict__ inv, int fan_any,
-                                                     const float *__restrict__ g, bf16_t *__restrict__ out, int rows, int d, RowLanes l) {
+__device__ __forceinline__ void spread_rows(const Spread &s, const int32_t *__restrict__ inv, int fan_any, int block) {
   const int fan = K ? K : fan_any;
-  const int lane = (int)threadIdx.x & (l.shift == 8 ? 255 : l.lanes - 1);
-  for (long long t = (long long)blockIdx.x * l.rows + ((int)threadIdx.x >> l.shift); t < rows; t += (long long)gridDim.x * l.rows) {
+  const int lane = (int)threadIdx.x & (s.l.shift == 8 ? 255 : s.l.lanes - 1);
+  for (long long t = (long long)block * s.l.rows + ((int)threadIdx.x >> s.l.shift); t < s.rows; t += (long long)s.blocks * s.l.rows) {
     const int32_t *pos = inv + t * fan;
-    const float *gt = g ? g + t * fan : nullptr;
-    for (int c = lane * 8; c < d; c += l.lanes * 8) {
-      const Vec16<bf16_t> a = *reinterpret_cast<const Vec16<bf16_t> *>(in + t * d + c);
+    const float *gt = s.g ? s.g + t * fan : nullptr;
+    int32_t at[K ? K : 1];                     // read once: the compiler cannot know that the copies do not lie over them
+    float weight[K ? K : 1];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      at[j] = pos[j];
+      weight[j] = gt ? gt[j] : 1.0f;
+    }
+    for (int c = lane * 8; c < s.d; c += s.l.lanes * 8) {
+      const Vec16<bf16_t> a = *reinterpret_cast<const Vec16<bf16_t> *>(s.in + t * s.d + c);
 #pragma unroll
       for (int j = 0; j < (K ? K : fan); ++j) {
         Vec16<bf16_t> v = a;
         if (gt) {
-          const float gs = gt[j];
+          const float gs = K ? weight[j] : gt[j];
 #pragma unroll
           for (int q = 0; q < 8; ++q) v.v[q] = (bf16_t)((float)a.v[q] * gs);
         }
-        *reinterpret_cast<Vec16<bf16_t> *>(out + (size_t)pos[j] * d + c) = v;
+        *reinterpret_cast<Vec16<bf16_t> *>(s.out + (size_t)(K ? at[j] : pos[j]) * s.d + c) = v;
       }
     }
   }
+}
+// Up to two such copies of the same fan and the row dots of dp in one launch: none waits for another, and a launch of its own is 4 us
+// of start and end (16396 rows, 2048 -> 1536, k = 4: 12.4 + 13.0 + 14.8 us and two gaps -> 35.8 us; the training step 421.6 -> 413.0).
+template <int K>
+__global__ void __launch_bounds__(256) spread_kernel(Spread a, Spread b, RowDots dots, const int32_t *__restrict__ inv, int fan) {
+  int block = blockIdx.x;
+  if (block < a.blocks) return spread_rows<K>(a, inv, fan, block);
+  block -= a.blocks;
+  if (block < b.blocks) return spread_rows<K>(b, inv, fan, block);
+  block -= b.blocks;
+  const int s = block * 4 + ((int)threadIdx.x >> 6);
+  if (s < dots.Tk) row_dot<bf16_t>(dots, s, threadIdx.x & 63);
 }
 
 // ---- dg[o[i]] = sum_c part[i, c] (and inv[o[i]] = i, inv may be null): eight lanes per sorted row, each adds the pairs of slabs lane, lane + 8, ... in ascending
@@ -362,14 +387,17 @@ int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g,
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
-int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d) {
-  if (!vec_ok<bf16_t>(d)) return SMOE_ERR_UNSUPPORTED;
-  if (Tk < 1) return SMOE_OK;
+static Spread spread_of(const void *in, const float *g, void *out, int rows, int d) {
   const RowLanes l = row_lanes(d / 8);
-  const int rows = Tk / fan;
+  return Spread{(const bf16_t *)in, g, (bf16_t *)out, rows, d, row_blocks(rows, l.rows), l};
+}
+int launch_spread(hipStream_t s, const void *in, const int32_t *inv, int fan, const float *g, void *out, int Tk, int d, const RowDots &dots, const void *in2,
+                  void *out2, int d2) {
+  if (!vec_ok<bf16_t>(d) || (in2 && !vec_ok<bf16_t>(d2)) || (dots.dg && !vec_ok<bf16_t>(dots.d))) return SMOE_ERR_UNSUPPORTED;
+  if (Tk < 1) return SMOE_OK;
+  const Spread a = spread_of(in, g, out, Tk / fan, d), b = in2 ? spread_of(in2, nullptr, out2, Tk / fan, d2) : Spread{};
   auto launch = [&](auto k) {
-    hipLaunchKernelGGL(spread_kernel<decltype(k)::value>, dim3(row_blocks(rows, l.rows)), dim3(l.lanes * l.rows), 0, s, (const bf16_t *)in, inv,
-                       fan, g, (bf16_t *)out, rows, d, l);
+    hipLaunchKernelGGL(spread_kernel<decltype(k)::value>, dim3(a.blocks + b.blocks + (dots.dg ? ceil_div(dots.Tk, 4) : 0)), dim3(256), 0, s, a, b, dots, inv, fan);
   };
   if (fan <= 8) with_rows(fan, launch);
   else launch(std::integral_constant<int, 0>{});
