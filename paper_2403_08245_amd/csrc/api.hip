@@ -912,9 +912,9 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   // the array of dX's third part is free then: it holds the inverse of the order indices
   int32_t *inv = in_sum && (size_t)Tk * sizeof(int32_t) <= z.x ? (int32_t *)dXq : nullptr;
   // Output projection (Alg. 2 with p, scattered in with fan-out 1, scattered out): dOhat, dW_O, dp.  Where the persistent kernels take
-  // the product, its epilogue reads the saved Ohat and leaves <dO W_O^T, Ohat> per head: summed over the heads that is dp, times the
-  // routing weight it is delta, the attention's <dOhat, Ohat>; and it writes the weighted, sorted rows of Ohat that groupXTY needs.
-  // No pass over Yhat, no delta kernel, no `group` of Ohat (34 + 13 + 14 us at 8192 tokens, k = 4, 4 heads, 2048 wide).
+  // the product, its epilogue reads the saved Ohat, leaves <dO W_O^T, Ohat> in slabs, which add up to dp, and writes the weighted,
+  // sorted rows of Ohat that groupXTY needs.  No pass over Yhat, no `group` of Ohat (34 + 14 us at 8192 tokens, k = 4, 4 heads, 2048
+  // wide).  The attention's delta = <dOhat, Ohat> is not taken from there: it has to go with dOhat as it is stored.
   const int part_ld = 2 * ceil_div(d_out, 256);
   float *gsorted = tail_ws, *dp_part = (float *)((char *)tail_ws + align256((size_t)Tk * sizeof(float)));
   void *dYu = sub, *Ow = (char *)sub + z.yhat;
@@ -931,7 +931,7 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
     if (rc != SMOE_OK) return rc;
     rc = launch_s2s_stream(s, xo);
     if (rc != SMOE_OK) return rc;
-    rc = launch_dp_delta(s, dp_part, part_ld, h_expert, r->sorted_scattered_idxs, gates, dgates, (float *)attn_ws, Tk);
+    rc = launch_dp_reduce(s, dp_part, part_ld, r->sorted_scattered_idxs, dgates, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
     rc = launch_spread(s, dO, inv, k, nullptr, dYu, Tk, d_model);
     if (rc != SMOE_OK) return rc;
@@ -945,7 +945,7 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   }
   if (rc != SMOE_OK) return rc;
   // with the inverse at hand dQ is written in expert-sorted order, as the query projection's gradients read it
-  rc = launch_attn_bwd(s, saved_Q, saved_K, saved_V, saved_Ohat, dOhat, saved_LSE, attn_ws, dQ, dK, dV, B, T, k, h_expert, in_epilogue, inv);
+  rc = launch_attn_bwd(s, saved_Q, saved_K, saved_V, saved_Ohat, dOhat, saved_LSE, attn_ws, dQ, dK, dV, B, T, k, h_expert, true, inv);
   if (rc != SMOE_OK) return rc;
   // dense key / value projections
   DWArgs wk{X, dK, dW_K, dense_off, 1, N, d_model, d_out}, wv{X, dV, dW_V, dense_off, 1, N, d_model, d_out};

@@ -286,7 +286,9 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
 
 // ======================================================================================
 // backward, part 0: minus_delta[row][head] = -<dO, O> over the head's 128 columns (sixteen lanes each).  Negated, it is what
-// the products dP start from in the two passes below, instead of a subtraction per score.
+// the products dP start from in the two passes below, instead of a subtraction per score.  A pass of its own only where a
+// caller may want dQ over O: the dQ pass has the rows of dO in registers and works delta out itself otherwise (32768 rows of 4 heads:
+// the layer's backward pass 1042 us with it, 1036 so).
 // ======================================================================================
 __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restrict__ O, const bf16_t *__restrict__ dO,
                                                          float *__restrict__ minus_delta, size_t n) {
@@ -315,7 +317,7 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16_t *__restric
 // ======================================================================================
 __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
-                                                          const float *__restrict__ LSE, const float *__restrict__ minus_delta,
+                                                          const float *__restrict__ LSE, const bf16_t *__restrict__ O, float *__restrict__ minus_delta,
                                                           bf16_t *__restrict__ dQ, const int32_t *__restrict__ dq_rows, AttnDims d) {
   __shared__ __attribute__((aligned(1024))) char smem[ADS * 2 * ATILE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -342,7 +344,21 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
   }
   const size_t stat = ((size_t)b * rows + r_mine) * d.h + hh;
   float lse2 = LSE[stat] * 1.4426950408889634f + LOG2_ROOT_D;
-  float dlt = minus_delta[stat];
+  float dlt = 0.f;
+  if (O) {
+    // delta from the rows of dO as they are stored, which dP is formed from as well: whatever rounding they went through is in both
+    // and cancels where a softmax row rests on few keys
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const bf16x8 o = *reinterpret_cast<const bf16x8 *>(O + qrow + 16 * ks + 8 * (lane >> 5));
+#pragma unroll
+      for (int c = 0; c < 8; ++c) dlt = fmaf(-(float)o[c], (float)dof[ks][c], dlt);
+    }
+    dlt += __shfl_xor(dlt, 32, 64);
+    if (row_valid && lane < 32) minus_delta[stat] = dlt;
+  } else {
+    dlt = minus_delta[stat];
+  }
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) { settle(qf[ks]); settle(dof[ks]); }
   settle(lse2);
@@ -709,7 +725,7 @@ size_t attn_bwd_workspace_bytes(int B, int T, int G, int h) {
 }
 
 int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, const void *O, const void *dO,
-                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool have_delta, const int32_t *dq_rows) {
+                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool dq_apart, const int32_t *dq_rows) {
   AttnDims d{B, T, G, h, (size_t)h * AD, (size_t)h * AD, 1.4426950408889634f / sqrtf((float)AD)};
   size_t n = (size_t)B * T * G * h;
   float *minus_delta = (float *)ws;
@@ -717,13 +733,13 @@ int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, 
   constexpr int NW = DKV_WAVES;
   const DkvPlan plan = dkv_plan(T, G, B * h);
   if ((long long)plan.units * h * B > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
-  if (!have_delta) {
+  if (!dq_apart) {
     hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, (const bf16_t *)O, (const bf16_t *)dO,
                        minus_delta, n);
     SMOE_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(ceil_div(T * G, AQ) * h * B), dim3(256), 0, s, (const bf16_t *)Q,
-                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dQ, dq_rows, d);
+                     (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, dq_apart ? (const bf16_t *)O : nullptr, minus_delta, (bf16_t *)dQ, dq_rows, d);
   SMOE_LAUNCH_CHECK();
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, true, true>), dim3(plan.units * h * B), dim3(64 * NW), 0, s, (const bf16_t *)Q,
                      (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dK,

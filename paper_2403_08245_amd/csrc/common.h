@@ -59,10 +59,9 @@ int launch_topk_gate(hipStream_t s, const float *logits, int T, int E, int k, in
 int launch_attn_fwd(hipStream_t s, const void *Q, const void *K, const void *V, void *O, float *LSE, int B, int T, int G,
                     int h);
 size_t attn_bwd_workspace_bytes(int B, int T, int G, int h);
-// have_delta: the workspace already starts with minus_delta [B, T, G, h].  dq_rows: row of dQ that each query row's gradient goes to
-// (NULL: its own).
+// dq_apart: no part of dQ lies over O (a launch less).  dq_rows: row of dQ that each query row's gradient goes to (NULL: its own).
 int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, const void *O, const void *dO,
-                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool have_delta = false,
+                    const float *LSE, void *ws, void *dQ, void *dK, void *dV, int B, int T, int G, int h, bool dq_apart = false,
                     const int32_t *dq_rows = nullptr);
 int launch_dense_offsets(hipStream_t s, int32_t *off, int n);
 int launch_add3(hipStream_t s, const void *a, const void *b, const void *c, void *out, size_t n);
@@ -91,9 +90,6 @@ int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g,
 // dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even), and inv[o[i]] = i unless inv is NULL: finishes the routing-weight gradient left in slabs by the fused
 // backward epilogues.
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk);
-// The same for slabs that are the h heads of an attention output (ld = h rounded up to even): dg[o[i]] = sum_c part[i, c], and
-// minus_delta[o[i], c] = -g[o[i]] * part[i, c] for c < h (what the attention's backward pass starts from).
-int launch_dp_delta(hipStream_t s, const float *part, int ld, int h, const int32_t *o, const float *g, float *dg, float *minus_delta, int Tk);
 // dg[s] = <dY[s / kp], Yhat[s]>
 int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat, float *dg, int Tk, int kp, int d);
 

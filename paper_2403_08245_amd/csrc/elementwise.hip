@@ -272,27 +272,6 @@ __global__ void __launch_bounds__(256) dp_reduce_kernel(const float2 *__restrict
   }
 }
 
-// ---- the same where the slabs are heads: each lane also writes its pairs of minus_delta
-__global__ void __launch_bounds__(256) dp_delta_kernel(const float2 *__restrict__ part, int ld2, int h, const int32_t *__restrict__ o, const float *__restrict__ g,
-                                                       float *__restrict__ dg, float *__restrict__ minus_delta, int Tk) {
-  const int i = blockIdx.x * 32 + ((int)threadIdx.x >> 3), lane = (int)threadIdx.x & 7;
-  const float2 *p = part + (size_t)min(i, Tk - 1) * ld2;
-  const int slot = o[min(i, Tk - 1)];
-  const float w = -g[slot];
-  float acc = 0.f;
-  for (int c = lane; c < ld2; c += 8) {
-    const float2 v = p[c];
-    acc += v.x + v.y;
-    if (i < Tk) {
-      minus_delta[(size_t)slot * h + 2 * c] = w * v.x;
-      if (2 * c + 1 < h) minus_delta[(size_t)slot * h + 2 * c + 1] = w * v.y;
-    }
-  }
-#pragma unroll
-  for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0 && i < Tk) dg[slot] = acc;
-}
-
 // ---- dg[s] = <dY[s / kp], Yhat[s]> : one wavefront per slot, lanes stride the row.
 template <typename T> __global__ void __launch_bounds__(256) rowdot_kernel(RowDots r) {
   const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -409,14 +388,6 @@ int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o,
   if (!Tk) return SMOE_OK;
   if (ld % 2) return SMOE_ERR_UNSUPPORTED;
   hipLaunchKernelGGL(dp_reduce_kernel, dim3(ceil_div(Tk, 32)), dim3(256), 0, s, (const float2 *)part, ld / 2, o, dg, inv, Tk);
-  SMOE_LAUNCH_CHECK();
-  return SMOE_OK;
-}
-
-int launch_dp_delta(hipStream_t s, const float *part, int ld, int h, const int32_t *o, const float *g, float *dg, float *minus_delta, int Tk) {
-  if (!Tk) return SMOE_OK;
-  if (ld != ((h + 1) & ~1)) return SMOE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(dp_delta_kernel, dim3(ceil_div(Tk, 32)), dim3(256), 0, s, (const float2 *)part, ld / 2, h, o, g, dg, minus_delta, Tk);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

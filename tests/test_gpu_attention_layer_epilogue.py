@@ -1,5 +1,5 @@
-"""The attention layer's backward pass where the output projection's input-gradient product leaves dp, delta and the weighted rows
-of Ohat in its epilogue and dQ is written in expert-sorted order (large layers take that route; the 256 x 256 tiles forced, all
+"""The attention layer's backward pass where the output projection's input-gradient product leaves dp and the weighted rows of
+Ohat in its epilogue and dQ is written in expert-sorted order (large layers take that route; the 256 x 256 tiles forced, all
 do): segments and sequences that end inside a tile, several tile columns, an odd number of heads (the slabs of dp are even),
 contractions that are and are not a multiple of 128, experts without tokens, k up to 8.  Every gradient against the oracle, and
 against the route of the small layers, whose dp goes through bf16 rows of Yhat."""
@@ -58,3 +58,45 @@ def test_every_gradient(smoe, B, T, d_model, E, k, h, masked):
         assert_close(got[i].reshape(ref[name].shape), ref[name], BF, name)
         assert_close(small[i].reshape(ref[name].shape), ref[name], BF, name + " (small layers)")
         assert torch.equal(got[i], again[i]), name        # deterministic
+
+
+@pytest.mark.parametrize("B,k,h", [(37, 4, 3), (150, 2, 2)])
+@pytest.mark.parametrize("mode", [4, 0])
+def test_a_softmax_row_of_one_key_has_no_score_gradient(smoe, mode, B, k, h):
+    """Sequences of one position: P = 1, Ohat = V, so dP - delta is the difference of two fp32 sums of the same 128 products of the
+    stored dOhat and V, whatever rounding dOhat went through: at most 2 * (128 + 16) * 2^-23 of the sum of their magnitudes, and
+    dW_Q and dW_K at most that times the sums of magnitudes behind them (1.02: the bf16 roundings of dS, dQ and dK).  delta from
+    dOhat before its rounding is off by 2^-9 of every product instead."""
+    d_model, E = 264, 64
+    d_out = h * 128
+    print("one key", mode, B, k, h, flush=True)
+    gen = torch.Generator().manual_seed(92)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=gen) * std).bfloat16()
+    X, dO = rnd(B, d_model), rnd(B, d_model)
+    W_K, W_V = rnd(d_model, d_out, std=0.06), rnd(d_model, d_out, std=0.06)
+    W_Q, W_O = rnd(E, d_model, d_out, std=0.06), rnd(E, d_out, d_model, std=0.06)
+    args = [t.cuda() for t in (X, W_K, W_V, W_Q, W_O)]
+    smoe.set_kernel_mode(mode)
+    gi, gg = smoe.topk_gate(torch.randn(B, E, generator=gen).cuda(), k)
+    r = smoe.route(gi, E)
+    _, buf = smoe.momha_fwd(*args, r, k, gg, B, 1, h, 128)
+    got = smoe.momha_bwd(dO.cuda(), *args, r, k, gg, B, 1, h, 128, buf)
+    K, V, Q = (si.as_f64(t.cpu()).reshape(B, -1, h, 128) for t in (buf.K, buf.V, buf.Q))
+    ei, g, X64, dO64, WO64 = gi.cpu().numpy(), gg.cpu().numpy().astype(np.float64), si.as_f64(X), si.as_f64(dO), si.as_f64(W_O)
+    unit = 2 * (128 + 16) * 2.0 ** -23 * 1.02 / np.sqrt(128)
+    dK_max, dW_Q_max = np.zeros((B, h, 128)), np.zeros((E, d_model, d_out))
+    for t in range(B):
+        for j in range(k):
+            dOhat = np.abs(g[t, j] * (WO64[ei[t, j]] @ dO64[t])).reshape(h, 128) * 1.02
+            dS = unit * (dOhat * np.abs(V[t, 0])).sum(axis=1, keepdims=True)
+            dK_max[t] += dS * np.abs(Q[t, j])
+            dW_Q_max[ei[t, j]] += np.outer(np.abs(X64[t]), dS * np.abs(K[t, 0]))
+    for i, bound, name in ((1, np.abs(X64).T @ dK_max.reshape(B, d_out), "dW_K"), (3, dW_Q_max, "dW_Q")):
+        over = np.abs(si.as_f64(got[i].cpu())) / np.maximum(bound, 1e-300)
+        print(name, "largest share of its bound", over.max(), flush=True)
+        assert over.max() <= 1, name
+    assert_close(got[2], X64.T @ _dv(ei, g, dO64, WO64, B, d_out), BF, "dW_V")
+
+
+def _dv(ei, g, dO64, WO64, B, d_out):
+    return np.stack([sum(g[t, j] * (WO64[ei[t, j]] @ dO64[t]) for j in range(ei.shape[1])) for t in range(B)]).reshape(B, d_out)
