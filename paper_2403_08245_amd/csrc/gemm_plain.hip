@@ -5,11 +5,14 @@
 // The fp32 layers are small, so what bounds them is latency: launches, and in a launch the chain offsets -> order index ->
 // operand row -> result.  Hence: rows are gathered (and weighted) where they are read instead of by a `group` launch, the
 // activation and its derivative sit in the epilogues instead of launches of their own, the tile search runs across the
-// lanes of a wavefront, row addresses are worked out once, each 32-deep contraction step is loaded into registers two steps
-// ahead, and the parts of a backward pass that wait for nothing but their inputs are one launch (f32_backward_kernel).
-// 256 tokens, 64 -> 128 -> 64, 4 experts: a launch 7 to 9.5 us; the nine launches of a training step 44 us in a captured graph,
-// 48 us under a profiler (twelve of them: 64), called one by one 78 -> 67 us (host and launches bound it then);
-// 500 tokens, 128 -> 2 x 512 -> 128, 8 experts, k = 2: 101 -> 87 us; 1024 tokens, 256 -> 2 x 896 -> 256: 202 -> 194 us.
+// lanes of a wavefront, row addresses are worked out once, each 32-deep contraction step is loaded into registers while the one before
+// is multiplied, and the parts of a backward pass that wait for nothing but their inputs are one launch (f32_backward_kernel).
+// In us, and before the backward passes were one launch a layer: 256 tokens, 64 -> 128 -> 64, 4 experts: forward 16, backward 19 (36);
+// 1024 tokens, 256 -> 2 x 896 -> 256, 8 experts, k = 2: 61 and 97 (131); 4096 tokens, 256 -> 512 -> 256: 68 and 123 (160); 16384 tokens,
+// 1024 -> 4096 -> 1024: 5540 and 10640 (12240), 99 and 103 TFLOP/s of the card's 157 in fp32.
+// Steps requested two ahead into a second set of registers and LDS tiles leave 4 wavefronts a SIMD of 6 to 8 and were slower by 2 to 8 %
+// in the forward products and by up to 15 % in the backward launches (65 and 112 us for the 1024 tokens); the longest weight
+// gradients of few tiles gained 2 to 3 % (32768 tokens, 128 -> 256 -> 128, 16 experts: 356 us, 365 so).
 #include "mfma_common.h"
 
 namespace {
@@ -81,12 +84,9 @@ __device__ __forceinline__ void multiply_step(const float *As, const float *Bs, 
 //           ACT_BWD  C = act'(Hpre) * product (SwiGLU: both halves).
 // Rows of the product are scaled by the routing weight of their slot when a.gates is given.
 enum { EPI_NONE = 0, EPI_ACT_FWD = 1, EPI_ACT_BWD = 2 };
-//
-// A step's operands are requested two steps ahead, and what the epilogue reads before the first step: a block walks two to a
-// few dozen steps by itself, so every latency that stands alone shows.
 constexpr int TILE_FLOATS = PT * KROW > PK * NROW ? PT * KROW : PK * NROW;
 struct PlainTiles {
-  float a[2][TILE_FLOATS], b[2][TILE_FLOATS];   // of even and odd steps: one barrier per step
+  float a[TILE_FLOATS], b[TILE_FLOATS];
 };
 template <typename T, bool TRANS_W, int EPI>
 __device__ __forceinline__ void s2s_plain_tile(const S2SArgs &a, int mt, int nt, PlainTiles &tiles) {
@@ -117,23 +117,38 @@ __device__ __forceinline__ void s2s_plain_tile(const S2SArgs &a, int mt, int nt,
       pb[u] = W + (size_t)cc_k<T>(u) * a.ldw + (okb[u] ? n : 0);
     }
   }
-  TileRegs<T> ra[2], rb[2];
-  auto fetch = [&](int set, int k0) {
+  TileRegs<T> ra, rb;
+  auto fetch = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      ra[set].r[u] = load_or_zero(pa[u] + k0, oka[u] && k0 + kc_k<T>(u) < a.K);
-      rb[set].r[u] = TRANS_W ? load_or_zero(pb[u] + k0, okb[u] && k0 + kc_k<T>(u) < a.K)
-                             : load_or_zero(pb[u] + (size_t)k0 * a.ldw, okb[u] && k0 + cc_k<T>(u) < a.K);
+      ra.r[u] = load_or_zero(pa[u] + k0, oka[u] && k0 + kc_k<T>(u) < a.K);
+      rb.r[u] = TRANS_W ? load_or_zero(pb[u] + k0, okb[u] && k0 + kc_k<T>(u) < a.K)
+                        : load_or_zero(pb[u] + (size_t)k0 * a.ldw, okb[u] && k0 + cc_k<T>(u) < a.K);
     }
   };
-  fetch(0, 0);
-  fetch(1, PK);
+  fetch(0);
   // a lane holds row lane % 32 and the columns 8 g + 4 * (lane / 32) + 0..3 of its wavefront's 32 x 32 block
   const int i = row0 + wm * 32 + (lane & 31);
   const bool live = i < row_end;
   const size_t dst = live ? (size_t)map_row(a.c_map, i) : 0;
   const float scale = a.gates && live ? a.gates[a.slots[i]] : 1.0f;
-  Vec16<float> pre[4], pre_up[4];          // EPI_ACT_BWD (fp32): the saved pre-activations of the lane's elements
+  f32x16 acc;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
+  for (int k0 = 0; k0 < a.K; k0 += PK) {
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      put_floats<T>(tiles.a + kc_row<T>(u) * KROW + kc_k<T>(u), ra.r[u], 1.0f);
+      if (TRANS_W) put_floats<T>(tiles.b + kc_row<T>(u) * KROW + kc_k<T>(u), rb.r[u], 1.0f);
+      else put_floats<T>(tiles.b + cc_k<T>(u) * NROW + cc_col<T>(u), rb.r[u], 1.0f);
+    }
+    __syncthreads();
+    if (k0 + PK < a.K) fetch(k0 + PK);
+    multiply_step<true, TRANS_W>(tiles.a, tiles.b, wm, wn, lane, acc);
+  }
+
+  Vec16<float> pre[4], pre_up[4];          // EPI_ACT_BWD (fp32): the saved pre-activations of the lane's elements, all in flight at once
   if (EPI == EPI_ACT_BWD) {
     const float *h = (const float *)a.Hpre_in + (size_t)(live ? i : 0) * (swiglu ? 2 * a.N : a.N);
 #pragma unroll
@@ -143,27 +158,7 @@ __device__ __forceinline__ void s2s_plain_tile(const S2SArgs &a, int mt, int nt,
       pre_up[g] = load_or_zero(h + a.N + n, swiglu && live && n < a.N);
     }
   }
-  f32x16 acc;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  auto step = [&](int set, int k0) {
-    float *As = tiles.a[set], *Bs = tiles.b[set];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      put_floats<T>(As + kc_row<T>(u) * KROW + kc_k<T>(u), ra[set].r[u], 1.0f);
-      if (TRANS_W) put_floats<T>(Bs + kc_row<T>(u) * KROW + kc_k<T>(u), rb[set].r[u], 1.0f);
-      else put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb[set].r[u], 1.0f);
-    }
-    __syncthreads();
-    fetch(set, k0 + 2 * PK);
-    multiply_step<true, TRANS_W>(As, Bs, wm, wn, lane, acc);
-  };
-  for (int k0 = 0; k0 < a.K; k0 += 2 * PK) {
-    step(0, k0);
-    if (k0 + PK < a.K) step(1, k0 + PK);
-  }
-
-  float4 *exchange = reinterpret_cast<float4 *>(tiles.a[0]);     // SwiGLU: the up columns cross over to the gate columns' wavefront
+  float4 *exchange = reinterpret_cast<float4 *>(tiles.a);     // SwiGLU: the up columns cross over to the gate columns' wavefront
   if (paired) {
     __syncthreads();
     if (wn == 1)
@@ -228,48 +223,42 @@ template <typename T> __device__ __forceinline__ void dw_plain_tile(const DWArgs
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
   const int lo = a.offsets[e], hi = a.offsets[e + 1];
   const int m0 = mt * PT, n0 = nt * PT;
-  TileRegs<T> ra[2], rb[2];
-  float weight[2][U];
-  // Order indices are fetched two steps ahead of the rows they lead to, and the rows two steps ahead of their products.
+  TileRegs<T> ra, rb;
+  float weight[U];
+  // Order indices are fetched a step ahead of the rows they lead to, so that a step waits for one memory latency, not two.
   const int32_t *o = a.a_map.o ? a.a_map.o : a.b_map.o;   // both maps use the same order indices
-  int slot[2][U];
-  auto fetch_slots = [&](int set, int i0) {
+  int slot[U];
+  auto fetch_slots = [&](int i0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot[set][u] = o && i0 + cc_k<T>(u) < hi ? o[i0 + cc_k<T>(u)] : 0;
+    for (int u = 0; u < U; ++u) slot[u] = o && i0 + cc_k<T>(u) < hi ? o[i0 + cc_k<T>(u)] : 0;
   };
-  auto fetch = [&](int set, int i0) {
-    auto source = [&](const RowMap &map, int i, int u) { return (size_t)(map.o ? (map.fan > 1 ? slot[set][u] / map.fan : slot[set][u]) : i); };
+  auto source = [&](const RowMap &map, int i, int u) { return (size_t)(map.o ? (map.fan > 1 ? slot[u] / map.fan : slot[u]) : i); };
+  auto fetch = [&](int i0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + cc_k<T>(u), m = m0 + cc_col<T>(u), n = n0 + cc_col<T>(u);
       const bool ok = i < hi;
-      weight[set][u] = a.gates && ok ? a.gates[slot[set][u]] : 1.0f;
-      ra[set].r[u] = load_or_zero((const T *)a.A + (ok ? source(a.a_map, i, u) : 0) * a.M + (m < a.M ? m : 0), ok && m < a.M);
-      rb[set].r[u] = load_or_zero((const T *)a.B + (ok ? source(a.b_map, i, u) : 0) * a.N + (n < a.N ? n : 0), ok && n < a.N);
+      weight[u] = a.gates && ok ? a.gates[slot[u]] : 1.0f;
+      ra.r[u] = load_or_zero((const T *)a.A + (ok ? source(a.a_map, i, u) : 0) * a.M + (m < a.M ? m : 0), ok && m < a.M);
+      rb.r[u] = load_or_zero((const T *)a.B + (ok ? source(a.b_map, i, u) : 0) * a.N + (n < a.N ? n : 0), ok && n < a.N);
     }
-    fetch_slots(set, i0 + 2 * PK);
+    fetch_slots(i0 + PK);
   };
   f32x16 acc;
 #pragma unroll
   for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-  fetch_slots(0, lo);
-  fetch_slots(1, lo + PK);
-  fetch(0, lo);
-  fetch(1, lo + PK);
-  auto step = [&](int set, int i0) {
-    float *As = tiles.a[set], *Bs = tiles.b[set];
+  fetch_slots(lo);
+  fetch(lo);
+  for (int i0 = lo; i0 < hi; i0 += PK) {
+    if (i0 > lo) __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      put_floats<T>(As + cc_k<T>(u) * NROW + cc_col<T>(u), ra[set].r[u], 1.0f);
-      put_floats<T>(Bs + cc_k<T>(u) * NROW + cc_col<T>(u), rb[set].r[u], weight[set][u]);
+      put_floats<T>(tiles.a + cc_k<T>(u) * NROW + cc_col<T>(u), ra.r[u], 1.0f);
+      put_floats<T>(tiles.b + cc_k<T>(u) * NROW + cc_col<T>(u), rb.r[u], weight[u]);
     }
     __syncthreads();
-    fetch(set, i0 + 2 * PK);
-    multiply_step<false, false>(As, Bs, wm, wn, lane, acc);
-  };
-  for (int i0 = lo; i0 < hi; i0 += 2 * PK) {
-    step(0, i0);
-    if (i0 + PK < hi) step(1, i0 + PK);
+    if (i0 + PK < hi) fetch(i0 + PK);
+    multiply_step<false, false>(tiles.a, tiles.b, wm, wn, lane, acc);
   }
   const int m = m0 + wm * 32 + (lane & 31);
   if (m >= a.M) return;
@@ -289,10 +278,14 @@ template <typename T> __global__ void __launch_bounds__(256) dw_plain_kernel(DWA
 // What the backward pass of one fp32 ParallelLinear has to do, none of which waits for another part: the input-gradient product
 // (EPI_ACT_BWD: with the activation's derivative), the weight gradient and the row dots of dp.  One launch instead of three: at
 // these sizes a launch has 24 blocks or fewer for 256 compute units, and the gap to the next is 4 us (256 tokens, 64 -> 128 -> 64, 4
-// experts: 2.9 + 9.2 + 9.4 us and two gaps became 9.5, 8.3 + 6.1 us and one gap 9.1).
-template <int EPI> __global__ void __launch_bounds__(256) f32_backward_kernel(S2SArgs x, DWArgs w, RowDots d, int w_blocks, int x_blocks) {
+// experts: 2.9 + 9.2 + 9.4 us and two gaps became 9.5, 8.3 + 6.1 us and one gap 9.1).  The blocks with the longer walk go first (x_first:
+// the contraction is longer than the average segment), else a short row of long walks ends the launch alone while the weight
+// gradient's stores fill the memory queues (600 rows, 512 -> 2048, 8 experts: 65 us this way, 70 to 95 by where the arrays lie the
+// other way, 83 in three launches).
+template <int EPI> __global__ void __launch_bounds__(256) f32_backward_kernel(S2SArgs x, DWArgs w, RowDots d, int w_blocks, int x_blocks, bool x_first) {
   __shared__ PlainTiles tiles;
   int b = blockIdx.x;
+  if (x_first && b < w_blocks + x_blocks) b = b < x_blocks ? b + w_blocks : b - x_blocks;
   if (b < w_blocks) {
     const int tn = (w.N + PT - 1) / PT, tm = (w.M + PT - 1) / PT;
     dw_plain_tile<float>(w, b % tn, b / tn % tm, b / tn / tm, tiles);
@@ -343,8 +336,9 @@ int launch_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const 
   if (w_blocks + x_blocks + d_blocks > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
   if (!(w_blocks + x_blocks + d_blocks)) return SMOE_OK;
   const dim3 grid((unsigned)(w_blocks + x_blocks + d_blocks));
-  if (x.Hpre_in) hipLaunchKernelGGL(f32_backward_kernel<EPI_ACT_BWD>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks);
-  else hipLaunchKernelGGL(f32_backward_kernel<EPI_NONE>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks);
+  const bool x_first = x_blocks && w_blocks && (long long)x.K * w.E > w.Tk;
+  if (x.Hpre_in) hipLaunchKernelGGL(f32_backward_kernel<EPI_ACT_BWD>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks, x_first);
+  else hipLaunchKernelGGL(f32_backward_kernel<EPI_NONE>, grid, dim3(256), 0, s, x, w, d, (int)w_blocks, (int)x_blocks, x_first);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }
