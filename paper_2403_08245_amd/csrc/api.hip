@@ -863,7 +863,7 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
 // 32768 of 2048, 4 heads 1467 / 1520; but 8192 of 2048, 4 heads 513 / 509; 6000 of 2000, 8 heads 579 / 572; 8192 of 1024, 1 head
 // 276 / 271; 4096 of 4096, 2 heads 542 / 507.
 static bool output_projection_in_epilogue(const smoe_ctx *ctx, int Tk, int d_model, int d_out) {
-  if (ctx->tile_shape == 2) return true;   // forced, for the tests
+  if (ctx->tile_shape) return ctx->tile_shape == 2;   // tiles of one shape only, for the tests
   return (size_t)Tk * d_model >= ((size_t)16 << 20) && (long long)ceil_div(Tk, 256) * ceil_div(d_out, 256) * 2 >= ctx->stream_grid;
 }
 

@@ -60,6 +60,30 @@ def test_every_gradient(smoe, B, T, d_model, E, k, h, masked):
         assert torch.equal(got[i], again[i]), name        # deterministic
 
 
+@pytest.mark.parametrize("mode,in_epilogue", [(0, True), (4, True), (3, False)])
+def test_which_layers_take_the_epilogue(smoe, mode, in_epilogue):
+    """A layer large enough to take it by itself.  Only the route of the small layers reads the saved Yhat, so NaN there show in
+    dgates, and in nothing else, exactly where that route is taken: with the 128 x 256 tiles forced, which the epilogue does not fit."""
+    B, T, d_model, E, k, h = 8, 512, 512, 8, 8, 2
+    N, d_out = B * T, h * 128
+    assert N * k * d_model >= 16 << 20 and -(-N * k // 256) * -(-d_out // 256) * 2 >= 256
+    print("route", mode, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(93)
+    rnd = lambda *s, std=1.0: torch.empty(*s, dtype=BF, device="cuda").normal_(0.0, std, generator=gen)
+    X, dO = rnd(N, d_model), rnd(N, d_model)
+    args = [X, rnd(d_model, d_out, std=0.05), rnd(d_model, d_out, std=0.05), rnd(E, d_model, d_out, std=0.05), rnd(E, d_out, d_model, std=0.05)]
+    smoe.set_kernel_mode(mode)
+    gi, gg = smoe.topk_gate(torch.empty(N, E, device="cuda").normal_(0.0, 1.0, generator=gen), k)
+    r = smoe.route(gi, E)
+    _, buf = smoe.momha_fwd(*args, r, k, gg, B, T, h, 128)
+    want = smoe.momha_bwd(dO, *args, r, k, gg, B, T, h, 128, buf)
+    buf.Yhat.fill_(float("nan"))
+    got = smoe.momha_bwd(dO, *args, r, k, gg, B, T, h, 128, buf)
+    for a, b in zip(got[:5], want[:5]):
+        assert torch.equal(a, b)
+    assert torch.equal(got[5], want[5]) if in_epilogue else bool(got[5].isnan().all())
+
+
 @pytest.mark.parametrize("B,k,h", [(37, 4, 3), (150, 2, 2)])
 @pytest.mark.parametrize("mode", [4, 0])
 def test_a_softmax_row_of_one_key_has_no_score_gradient(smoe, mode, B, k, h):
