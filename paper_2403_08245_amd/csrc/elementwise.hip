@@ -405,11 +405,11 @@ int launch_rowdot(hipStream_t s, smoe_dtype dt, const void *dY, const void *Yhat
 }
 
 // ------------------------------------------------------------------------------------------
-// helpers of the attention layer: offsets of one or two all-rows segments (dense products run
-// through the grouped kernels as one or two experts), and the sum of three bf16 arrays
+// helpers of the attention layer: offsets of one all-rows segment (a dense product runs through
+// the grouped kernels as one expert), and the sum of three bf16 arrays
 // ------------------------------------------------------------------------------------------
 __global__ void dense_offsets_kernel(int32_t *off, int n) {
-  if (threadIdx.x == 0) { off[0] = 0; off[1] = n; off[2] = 2 * n; }   // off[2]: a pair of products in one launch (n < 2^30)
+  if (threadIdx.x == 0) { off[0] = 0; off[1] = n; }
 }
 int launch_dense_offsets(hipStream_t s, int32_t *off, int n) {
   hipLaunchKernelGGL(dense_offsets_kernel, dim3(1), dim3(64), 0, s, off, n);
