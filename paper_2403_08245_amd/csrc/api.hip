@@ -42,10 +42,10 @@ bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
   const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
   return a && b && p < q + b_bytes && q < p + a_bytes;
 }
-// The parts of an fp32 backward pass that wait for nothing but their inputs: in one launch, or (`apart`) in the order row dots,
-// weight gradient, input gradient.
+// The parts of an fp32 backward pass that wait for nothing but their inputs: in one launch, or (`apart`, or too many blocks for
+// one) in the order row dots, weight gradient, input gradient.
 int run_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d, bool apart) {
-  if (!apart) return launch_f32_backward(s, x, w, d);
+  if (!apart && f32_backward_fits(x, w, d)) return launch_f32_backward(s, x, w, d);
   int rc = d.dg ? launch_rowdot(s, SMOE_F32, d.dY, d.Yhat, d.dg, d.Tk, d.kp, d.d) : SMOE_OK;
   if (rc == SMOE_OK && w.dW) rc = launch_dw_plain(s, SMOE_F32, w);
   if (rc == SMOE_OK && x.C) rc = launch_s2s_plain(s, SMOE_F32, x);

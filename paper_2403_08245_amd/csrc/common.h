@@ -207,6 +207,7 @@ static inline bool weights_pass_caches(const S2SArgs &a) {
 }
 int launch_s2s_plain(hipStream_t s, smoe_dtype dt, const S2SArgs &a);
 int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a);
+bool f32_backward_fits(const S2SArgs &x, const DWArgs &w, const RowDots &d);   // into one launch
 int launch_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d);
 bool s2s_mfma_supported(const S2SArgs &a);
 bool dw_mfma_supported(const DWArgs &a);

@@ -329,11 +329,21 @@ int launch_dw_plain(hipStream_t s, smoe_dtype dt, const DWArgs &a) {
 }
 
 // x (with W^T), w or d may be absent (C, dW, dg NULL).
+static void f32_backward_blocks(const S2SArgs &x, const DWArgs &w, const RowDots &d, long long &w_blocks, long long &x_blocks, long long &d_blocks) {
+  w_blocks = w.dW ? (long long)ceil_div(w.N, PT) * ceil_div(w.M, PT) * w.E : 0;
+  x_blocks = x.C ? ((long long)ceil_div(x.Tk, PT) + x.E) * ceil_div(x.N, PT) : 0;
+  d_blocks = d.dg ? ceil_div(d.Tk, 4) : 0;
+}
+// A dimension of a launch has less than 2^32 threads (the runtime takes more without an error and drops blocks).  The parts by
+// themselves have two or three dimensions, or fewer blocks.
+bool f32_backward_fits(const S2SArgs &x, const DWArgs &w, const RowDots &d) {
+  long long w_blocks, x_blocks, d_blocks;
+  f32_backward_blocks(x, w, d, w_blocks, x_blocks, d_blocks);
+  return (w_blocks + x_blocks + d_blocks) * 256 < 1LL << 32;
+}
 int launch_f32_backward(hipStream_t s, const S2SArgs &x, const DWArgs &w, const RowDots &d) {
-  const long long w_blocks = w.dW ? (long long)ceil_div(w.N, PT) * ceil_div(w.M, PT) * w.E : 0;
-  const long long x_blocks = x.C ? ((long long)ceil_div(x.Tk, PT) + x.E) * ceil_div(x.N, PT) : 0;
-  const long long d_blocks = d.dg ? ceil_div(d.Tk, 4) : 0;
-  if (w_blocks + x_blocks + d_blocks > 0x7fffffffLL) return SMOE_ERR_UNSUPPORTED;
+  long long w_blocks, x_blocks, d_blocks;
+  f32_backward_blocks(x, w, d, w_blocks, x_blocks, d_blocks);
   if (!(w_blocks + x_blocks + d_blocks)) return SMOE_OK;
   const dim3 grid((unsigned)(w_blocks + x_blocks + d_blocks));
   const bool x_first = x_blocks && w_blocks && (long long)x.K * w.E > w.Tk;

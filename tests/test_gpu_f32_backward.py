@@ -70,3 +70,20 @@ def test_outputs_over_inputs_of_earlier_parts(smoe, over):
                                      p(gates), 1, 0, 0, p(dX), p(dW), p(dg), p(ws), nb) == 0
     for got, ref, name in zip((dX, dW, dg), want, ("dX", "dW", "dgates")):
         assert torch.equal(got, ref), name
+
+
+def test_more_blocks_than_one_launch_takes(smoe):
+    """66 million rows of four: the input gradient and the row dots are each a launch the runtime accepts (under 2^32 threads), together
+    they are not.  Four fp32 terms a sum."""
+    Tk, d = 66_000_000, 4
+    assert -(-Tk // 4) * 256 < 2 ** 32 < (-(-Tk // 4) + -(-Tk // 64) + 1) * 256
+    print("f32 backward", Tk, "rows", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(83)
+    rnd = lambda *s: torch.empty(*s, device="cuda").normal_(0.0, 1.0, generator=gen)
+    X, Yhat, dY, W, gates = rnd(Tk, d), rnd(Tk, d), rnd(Tk, d), rnd(1, d, d), rnd(Tk, 1)
+    o = torch.arange(Tk, dtype=torch.int32, device="cuda")
+    r = smoe.Routing(torch.zeros_like(o), o, torch.tensor([0, Tk], dtype=torch.int32, device="cuda"), Tk, 1)
+    dX, dW, dg = smoe.plinear_bwd(dY, X, W, Yhat, r, 1, gates, need_dW=False)
+    assert dW is None
+    assert torch.allclose(dg, (dY * Yhat).sum(1, keepdim=True), rtol=1e-5, atol=1e-5)
+    assert torch.allclose(dX, gates * (dY @ W[0].t()), rtol=1e-5, atol=2e-5)
