@@ -49,10 +49,10 @@ def test_parts_in_one_launch(smoe, T, d_in, d_out, E, k, grouped_in, grouped_out
     assert (dX is not None) == need_dX and (dW is not None) == need_dW and (dg is not None) == with_p
 
 
-@pytest.mark.parametrize("over", ["X", "Yhat"])
-def test_outputs_over_inputs_of_earlier_parts(smoe, over):
-    """dX over X (the weight gradient reads X first), dX over Yhat (the row dots read it first)."""
-    T, d, E = 150, 96, 3
+@pytest.mark.parametrize("out,over", [("dX", "X"), ("dX", "Yhat"), ("dW", "Yhat")])
+def test_outputs_over_inputs_of_earlier_parts(smoe, out, over):
+    """dX over X (the weight gradient reads X first), dX or dW over Yhat (the row dots read it first)."""
+    T, d, E = 192, 96, 2
     c = si.plinear_case(T, d, d, E, 1, "f32", seed=82)
     ei, g, _, _, _ = oracle_routing(c["logits"], 1, E)
     r = smoe.route(torch.from_numpy(ei).cuda(), E)
@@ -61,7 +61,11 @@ def test_outputs_over_inputs_of_earlier_parts(smoe, over):
     _, Yhat = smoe.plinear_fwd(X, W, r, 1, gates)
     want = smoe.plinear_bwd(dY, X, W, Yhat, r, 1, gates)
     inputs = {"X": X.clone(), "Yhat": Yhat.clone()}
-    dX, dW, dg = inputs[over], torch.empty_like(W), torch.empty_like(gates)
+    dX, dW, dg = torch.empty_like(X), torch.empty_like(W), torch.empty_like(gates)
+    if out == "dX":
+        dX = inputs[over]
+    else:
+        dW = inputs[over].view_as(W)
     nb = smoe.lib.smoe_plinear_bwd_workspace_bytes(smoe.F32, T, d, d, T, 1, 1, 0, 0)
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     rc = r.c()
@@ -70,6 +74,28 @@ def test_outputs_over_inputs_of_earlier_parts(smoe, over):
                                      p(gates), 1, 0, 0, p(dX), p(dW), p(dg), p(ws), nb) == 0
     for got, ref, name in zip((dX, dW, dg), want, ("dX", "dW", "dgates")):
         assert torch.equal(got, ref), name
+
+
+@pytest.mark.parametrize("out", ["dX over X", "dW2 over Yhat"])
+def test_mlp_outputs_over_inputs_of_earlier_parts(smoe, out):
+    """The whole MLP with k = 1: dX over X (dW1 reads X first), dW2 over the saved Yhat (the row dots read it first)."""
+    E, d_model, d_expert = 2, 64, 96
+    T = E * d_expert                     # dW2 is as large as Yhat
+    cfg = si.custom("over", T=T, d_model=d_model, d_expert=d_expert, E=E, k=1, act=si.ACT_GELU, dtype="f32")
+    case = si.mlp_case(cfg, 84)
+    ei, g, _, _, _ = oracle_routing(case["logits"], 1, E)
+    r = smoe.route(torch.from_numpy(ei).cuda(), E)
+    gates = torch.from_numpy(g.astype(np.float32)).cuda() * 0.5
+    X, W1, W2, dY = (case[n].cuda() for n in ("X", "W1", "W2", "dY"))
+    _, buf = smoe.mlp_fwd(X, W1, W2, r, 1, gates, cfg.act)
+    want = [t.clone() for t in smoe.mlp_bwd(dY, X, W1, W2, r, 1, gates, cfg.act, buf)]
+    if out == "dX over X":
+        buf.dX = X
+    else:
+        buf.dW2 = buf.Yhat.view(E, d_expert, d_model)
+    got = smoe.mlp_bwd(dY, X, W1, W2, r, 1, gates, cfg.act, buf)
+    for a, b, name in zip(got, want, ("dX", "dW1", "dW2", "dgates")):
+        assert torch.equal(a, b), name
 
 
 def test_more_blocks_than_one_launch_takes(smoe):
