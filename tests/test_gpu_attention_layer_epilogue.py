@@ -47,6 +47,8 @@ def test_every_gradient(smoe, B, T, d_model, E, k, h, masked):
         gi, gg = smoe.topk_gate(logits.cuda(), k)
         r = smoe.route(gi, E)
         _, buf = smoe.momha_fwd(*args, r, k, gg, B, T, h, 128)
+        if mode == 4:
+            buf.Yhat.fill_(float("nan"))         # only the other route reads it
         return gi, smoe.momha_bwd(dO.cuda(), *args, r, k, gg, B, T, h, 128, buf)
 
     gi, got = run(4)
@@ -58,6 +60,51 @@ def test_every_gradient(smoe, B, T, d_model, E, k, h, masked):
         assert_close(got[i].reshape(ref[name].shape), ref[name], BF, name)
         assert_close(small[i].reshape(ref[name].shape), ref[name], BF, name + " (small layers)")
         assert torch.equal(got[i], again[i]), name        # deterministic
+
+
+@pytest.mark.parametrize("d_model", [256, 136])    # contractions that are and are not a multiple of 128
+def test_several_tiles_per_block(smoe, d_model):
+    """Every block of the output projection's product works through two tiles and more, with rows of dO everywhere: dX and dgates of
+    tokens from every tile of every expert (sequences are independent, the oracle runs theirs), and every row of dW_O at sampled
+    columns (column c depends on column c of dO only)."""
+    B, T, E, k, h = 683, 3, 16, 8, 16
+    N, d_out = B * T, h * 128
+    print("epilogue, several tiles per block", d_model, flush=True)
+    gen = torch.Generator().manual_seed(94)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=gen) * std).bfloat16()
+    X, dO = rnd(N, d_model), rnd(N, d_model)
+    W_K, W_V = rnd(d_model, d_out, std=0.06), rnd(d_model, d_out, std=0.06)
+    W_Q, W_O = rnd(E, d_model, d_out, std=0.06), rnd(E, d_out, d_model, std=0.02)
+    logits = torch.randn(N, E, generator=gen) + torch.linspace(1.0, -1.0, E)      # segments of different lengths
+    ei, g, _, o, off = oracle_routing(logits, k, E)
+    tiles = [(e, a) for e in range(E) for a in range(int(off[e]), int(off[e + 1]), 256)]
+    assert len(tiles) * (d_out // 256) >= 2 * 256
+    args = [t.cuda() for t in (X, W_K, W_V, W_Q, W_O)]
+    smoe.set_kernel_mode(4)
+    gi, gg = smoe.topk_gate(logits.cuda(), k)
+    assert np.array_equal(gi.cpu().numpy(), ei)
+    r = smoe.route(gi, E)
+    _, buf = smoe.momha_fwd(*args, r, k, gg, B, T, h, 128)
+    buf.Yhat.fill_(float("nan"))                 # only the other route reads it
+    got = smoe.momha_bwd(dO.cuda(), *args, r, k, gg, B, T, h, 128, buf)
+    for t, name in zip(got, ("dX", "dW_K", "dW_V", "dW_Q", "dW_O", "dgates")):
+        assert bool(torch.isfinite(t.float()).all()), f"{name} holds entries no kernel wrote"
+    g64 = oracle_gates_f32(g)
+    X64, dO64, K64, V64, Q64, O64 = (si.as_f64(t) for t in (X, dO, W_K, W_V, W_Q, W_O))
+    rng = np.random.default_rng(7)
+    rows = [int(rng.integers(a, min(a + 256, int(off[e + 1])))) for e, a in tiles]
+    seqs = np.unique(o[rows] // k // T)
+    S = (seqs[:, None] * T + np.arange(T)).ravel()
+    ref = oracle.momha_bwd(dO64[S], X64[S], K64, V64, Q64, O64, ei[S], g64[S], len(seqs), T, h, 128)
+    st = torch.from_numpy(S).cuda()
+    assert_close(got[0][st], ref["dX"], BF, "dX (sequences from every tile)")
+    assert_close(got[5].reshape(N, k)[st], ref["dgates"], BF, "dgates (sequences from every tile)")
+    cols = np.sort(rng.choice(d_model, 6, replace=False))
+    Ohat = oracle.momha_fwd(X64, K64, V64, Q64, O64[:, :, cols], ei, g64, B, T, h, 128)["Ohat"]
+    upstream = (g64[:, :, None] * dO64[:, None, cols]).reshape(N * k, -1)
+    dW_O = np.stack([Ohat[ei.ravel() == e].T @ upstream[ei.ravel() == e] for e in range(E)])
+    got_cols = got[4][:, :, torch.from_numpy(cols).cuda()]
+    assert_close(got_cols.transpose(1, 2), dW_O.transpose(0, 2, 1), BF, "dW_O (sampled columns, every row)")
 
 
 @pytest.mark.parametrize("mode,in_epilogue", [(0, True), (4, True), (3, False)])
