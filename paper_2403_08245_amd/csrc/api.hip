@@ -653,7 +653,10 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     w2.split_ws = tail_ws;
     void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead after dW2: its array holds Xbar, then dXbar
     // Both weight gradients in one launch where that saves a round of tiles: the sorted copy of X then has to stand beside that of dY,
-    // and takes the room of the partial tiles, which nothing needs until the last product.
+    // and takes the room of the partial tiles, which nothing needs until the last product.  The workspace has no other room for it,
+    // so copies of more than 64 MiB go without, at a cost: with room for them the backward passes of 32768 and 65536 rows in 8 experts,
+    // 1280 -> 2 x 3416, take 2065 us instead of 2110 and 3840 instead of 3960, of 65536 rows in 16 experts, 1280 -> 2 x 1024, 1146 instead
+    // of 1245, of 16384 rows in 4 experts, 4096 -> 1416, 978 instead of 1082.
     DWArgs both = w2;
     both.grid = ctx->stream_grid;
     both.A3 = tail_ws;
@@ -857,11 +860,16 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
   return launch_combine(s, dtype, saved_Yhat, gates, O, N, k, d_model);
 }
 
-// Does forming dp and delta in the epilogue of the output projection's input-gradient product pay?  It saves passes over rows of
-// [Tk, d_model], but the product then runs on 256 x 256 tiles, of which there have to be enough.  With it / without, training step
-// of the layer in us: 16384 rows of 1024, 4 heads 700 / 717; 32768 of 512, 2 heads 572 / 594; 24000 of 720, 4 heads 523 / 548;
-// 32768 of 2048, 4 heads 1467 / 1520; but 8192 of 2048, 4 heads 513 / 509; 6000 of 2000, 8 heads 579 / 572; 8192 of 1024, 1 head
-// 276 / 271; 4096 of 4096, 2 heads 542 / 507.
+// Does forming dp in the epilogue of the output projection's input-gradient product pay?  It saves passes over rows of [Tk, d_model],
+// but the product then runs on 256 x 256 tiles, of which there have to be enough (half a round), and its epilogue gains on the passes
+// only where these are long enough (16 Mi elements).  Backward pass of the layer, 8 experts, sequences of 512, in us, with it /
+// without, rows x d_model, heads, k:
+//   both lines met:  32768 x 512, 2, 4: 309 / 323; 16384 x 1024, 4, 4: 361 / 372; 65536 x 256, 4, 8: 572 / 593; 65536 x 2048, 2, 8:
+//                    805 / 905; 32768 x 2048, 4, 4: 762 / 787; 32768 x 1024, 8, 2: 844 / 851; the worst 16384 x 1024, 8, 4: 513 / 503;
+//   64 tiles:        16384 x 1024, 2, 8: 311 / 303; 8192 x 2048, 4, 8: 304 / 284; 16384 x 2048, 1, 8: 362 / 350;
+//   8 Mi elements:   128 tiles 32768 x 256, 2, 4: 277 / 279, 16384 x 512, 4, 8: 320 / 317, 8192 x 1024, 8, 8: 308 / 304; 256 tiles
+//                    16384 x 512, 8, 4: 452 / 440, 32768 x 256, 4, 2: 426 / 410; 512 tiles 32768 x 256, 8, 4: 603 / 591;
+//   4 Mi:            256 tiles 16384 x 256, 8, 4: 415 / 394, 512 tiles 32768 x 128, 8, 2: 557 / 542, 128 tiles within 2 % either way.
 static bool output_projection_in_epilogue(const smoe_ctx *ctx, int Tk, int d_model, int d_out) {
   if (ctx->tile_shape) return ctx->tile_shape == 2;   // tiles of one shape only, for the tests
   return (size_t)Tk * d_model >= ((size_t)16 << 20) && (long long)ceil_div(Tk, 256) * ceil_div(d_out, 256) * 2 >= ctx->stream_grid;

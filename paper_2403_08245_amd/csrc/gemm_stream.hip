@@ -195,8 +195,9 @@ __global__ void __launch_bounds__(NTHREADS, S::BLOCKS) s2s_stream_kernel(S2SArgs
   // half-steps) the loader has opened tile n+2 and requested the rows of tile n+3 while tile n's epilogue still
   // reads its destination rows, so four entries are live at once.
   __shared__ int s_idx[4][S::TM];
-  // The open tiles themselves, left by the loader's search for the multiplying side (every wavefront writes the same values and
-  // reads its own).
+  // The open tiles themselves, left by the loader's search for the multiplying side.  One ring for the block: every wavefront writes the
+  // same values and may read what another wrote.  What keeps an entry until the slowest has read it is the barrier of each half-step: with
+  // three half-steps or more per tile no wavefront has opened a tile past n + 3 while another still fetches the entry of n + 1.
   __shared__ __attribute__((aligned(16))) int s_tile[4][4];
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -960,7 +961,11 @@ bool dw_stream_supported(const DWArgs &a) {
 }
 
 // Together two weight gradients save the rounds that their last tiles fill only in part, and a launch, while a slot costs 3 % more
-// (its operands are chosen).  8 experts of 750 rows, 3416 x 1280 and 1280 x 6832 (2.2 + 4.2 rounds of tiles): 81 + 145 -> 203 us.
+// (its operands are chosen).  8 experts of 750 rows, 3416 x 1280 and 1280 x 6832 (2.2 + 4.2 rounds of tiles): 81 + 145 -> 203 us.  Whole
+// backward passes in us, one launch for each / one for both, where a round is saved: those 8 experts 584 / 559, with Zipf(1.2) loads 614 /
+// 575, with 20000 rows 1390 / 1352; 24000 rows and Zipf loads 1705 / 1566; 4 experts, 1280 -> 2 x 2048, 6000 rows 303 / 257; 16 experts,
+// 1280 -> 2 x 1024, 12000 rows 295 / 270; 64 experts, 768 -> 512, 8000 rows 130 / 111; 16 experts, 1280 -> 2 x 3416 (14 rounds to 13),
+// 24000 rows 1632 / 1612.
 bool dw_stream_two_pay(const DWArgs &a) {
   const long long first = (long long)a.E * ceil_div(a.M, TB) * ceil_div(a.N, TB), further = (long long)a.E * ceil_div(a.M3, TB) * ceil_div(a.N3, TB);
   auto rounds = [&](long long tiles) { return (tiles + a.grid - 1) / a.grid; };
