@@ -115,6 +115,28 @@ __device__ __forceinline__ bf16x8 tr_frag(const char *tile, int cbase, int kk, i
   }
   return u.v;
 }
+// ---------------------------------------------------------------- stages of 64 contraction elements (the persistent kernels)
+// Operand rows of 64 contiguous elements, one 128-byte cache line each, eight lanes a row.  The 16-byte chunks of a row are
+// permuted so that the 16 rows a ds_read_b128 serves at a time lie in all 64 banks.
+__device__ __forceinline__ int line_swz(int row) { return (row >> 1) & 7; }
+// fragment for v_mfma_32x32x16: lane holds row (rbase + lane%32), k = kk*16 + 8*(lane/32) + 0..7; rbase a multiple of 32
+__device__ __forceinline__ uint32_t line_frag_offset(int rbase, int kk, int lane) {
+  const int row = rbase + (lane & 31);
+  return (uint32_t)(row * 128 + (((kk * 2 + (lane >> 5)) ^ line_swz(row)) << 4));
+}
+__device__ __forceinline__ bf16x8 line_frag(const char *p, int i) { return *reinterpret_cast<const bf16x8 *>(p + i * 32 * 128); }
+// Operand as 64 contraction rows of 256 columns (the layout of a TR tile, twice as long): the lane's first read of column fragment
+// cbase, contraction rows 0..15; the second lies four rows on, further sixteens 16 rows
+__device__ __forceinline__ uint32_t rows_frag_offset(int cbase, int lane) {
+  const int col = cbase + 16 * ((lane >> 4) & 1) + 4 * (lane & 3), row = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  return (uint32_t)(row * (TB * 2) + (((col >> 3) ^ tr_swz(row)) << 4) + ((col & 7) << 1));
+}
+__device__ __forceinline__ bf16x8 rows_frag(const char *p, int kk) {
+  union { bf16x8 v; s16x4 h[2]; } u;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(p + (kk * 16 + t * 4) * (TB * 2)));
+  return u.v;
+}
 // byte offset inside an operand tile of a wavefront's load instruction (both layouts: 1 KB each)
 __device__ __forceinline__ int inst_off(int wave, int inst) { return (wave * NLD + inst) * 1024; }
 
@@ -167,20 +189,20 @@ __device__ __forceinline__ int xcd_contiguous_id(int pid, int grid) {
 constexpr int MAX_E = 256;          // the persistent kernels cache the expert offsets in LDS
 
 // A chunk's fp32 partial tile costs a 256 KB write and a 256 KB read on top of the second kernel's launch,
-// about what 48 half-steps of multiplying take: a split must shorten the last round by more than that.
-constexpr int SPLIT_MIN_SAVED = 64;
+// about what 24 stages of 64 contraction elements take: a split must shorten the last round by more than that.
+constexpr int SPLIT_MIN_SAVED = 32;
 constexpr int MAX_SPLIT = 4;
-// Largest number of chunks <= max_split (and <= MAX_SPLIT) that pays, with the chunk length; 1 = keep whole tiles.
-__host__ __device__ inline int choose_split(int nh, int max_split, bool static4, int &chunk) {
+// Largest number of chunks <= max_split (and <= MAX_SPLIT) that pays, with the chunk length in stages; 1 = keep whole tiles.
+__host__ __device__ inline int choose_split(int ns, int max_split, bool even, int &chunk) {
   for (int s = max_split < MAX_SPLIT ? max_split : MAX_SPLIT; s > 1; --s) {
-    int c = (nh + s - 1) / s;
-    if (static4) c = (c + 3) & ~3;
-    if ((s - 1) * c < nh && nh - c >= SPLIT_MIN_SAVED) {
+    int c = (ns + s - 1) / s;
+    if (even) c = (c + 1) & ~1;
+    if ((s - 1) * c < ns && ns - c >= SPLIT_MIN_SAVED) {
       chunk = c;
       return s;
     }
   }
-  chunk = nh;
+  chunk = ns;
   return 1;
 }
 // dense tile number -> (M-tile, N-tile): groups of group_m M-tiles (the last group may be narrower)
