@@ -24,6 +24,11 @@ constexpr int AFS = 3;              // LDS stages of the forward's key walk: til
 constexpr int ADS = 4;              // the same for the dQ pass (two blocks per CU)
 constexpr int DKV_WAVES = 4;        // wavefronts (32 keys each) per block of the dK/dV kernel
 constexpr int DKV_SORT_MAX = 512;   // key blocks up to which the dK/dV units are dealt in exact longest-first order
+// Fragments read from LDS this many products before they are used.  Left to itself the compiler reads each one right in front of its
+// product and waits for it there, 32 waits of an LDS latency a tile in the dK/dV pass, which the two or three wavefronts of a SIMD
+// do not cover: forward 158 -> 154 us (2 x 4096 positions, k = 4, 4 heads) and 652 -> 640 (16 x 2048, k = 8), backward 521 -> 496.
+// More of them spill (dK/dV: 256 registers as it is) or gain nothing.
+constexpr int FWD_AHEAD = 4, FWD_AHEAD_V = 3, DQ_AHEAD = 4, DQ_AHEAD_C = 4, DKV_AHEAD = 2, DKV_AHEAD_C = 4;
 constexpr float LOG2_ROOT_D = 3.5f; // log2(sqrt(AD))
 constexpr float NEG_BIG = -1.0e30f; // finite stand-in for -inf: exp2 of it is 0 and no inf - inf appears
 
@@ -217,8 +222,19 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
     f32x16 s;
 #pragma unroll
     for (int q = 0; q < 16; ++q) s[q] = 0.f;
+    bf16x8 kr[FWD_AHEAD], vr[FWD_AHEAD_V];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(kt, fo, ks), qf[ks], s, 0, 0, 0);
+    for (int i = 0; i < FWD_AHEAD; ++i) kr[i] = rows_frag(kt, fo, i);
+    sched_fence();
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[ks % FWD_AHEAD], qf[ks], s, 0, 0, 0);
+      if (ks + FWD_AHEAD < 8) kr[ks % FWD_AHEAD] = rows_frag(kt, fo, ks + FWD_AHEAD);
+      sched_fence();
+    }
+#pragma unroll
+    for (int i = 0; i < FWD_AHEAD_V; ++i) vr[i] = cols_frag(vt, fo, i & 3, i >> 2);
+    sched_fence();
     const bool diag = key0 + AKT - 1 > wave_first;
     // the running maximum m stays in raw score units; the 1/sqrt(d) log2(e) factor enters the exponent's fma
     float mx = NEG_BIG;
@@ -249,11 +265,13 @@ __global__ void __launch_bounds__(256, 3) attn_fwd_kernel(const bf16_t *__restri
         for (int q = 0; q < 16; ++q) acc[f][q] *= alpha;
     }
     bf16x8 pb[2] = {pack8(s, 0), pack8(s, 1)};
+    sched_fence();
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols_frag(vt, fo, f, s2), pb[s2], acc[f], 0, 0, 0);
+    for (int i = 0; i < 8; ++i) {
+      acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[i % FWD_AHEAD_V], pb[i >> 2], acc[i & 3], 0, 0, 0);
+      if (i + FWD_AHEAD_V < 8) vr[i % FWD_AHEAD_V] = cols_frag(vt, fo, (i + FWD_AHEAD_V) & 3, (i + FWD_AHEAD_V) >> 2);
+      sched_fence();
+    }
   };
   static_assert(AFS == 3 || AFS == 4, "the walk below is written out for three or four stages");
   for (int j = 0; j < n_tiles; j += AFS) {
@@ -395,10 +413,23 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
     f32x16 s, dp = start;
 #pragma unroll
     for (int q = 0; q < 16; ++q) s[q] = 0.f;
+    bf16x8 kr[DQ_AHEAD], vr[DQ_AHEAD];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(kt, fo, ks), qf[ks], s, 0, 0, 0);
+    for (int i = 0; i < DQ_AHEAD; ++i) { kr[i] = rows_frag(kt, fo, i); vr[i] = rows_frag(vt, fo, i); }
+    sched_fence();
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(vt, fo, ks), dof[ks], dp, 0, 0, 0);
+    for (int ks = 0; ks < 8; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[ks % DQ_AHEAD], qf[ks], s, 0, 0, 0);
+      if (ks + DQ_AHEAD < 8) kr[ks % DQ_AHEAD] = rows_frag(kt, fo, ks + DQ_AHEAD);
+      sched_fence();
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[ks % DQ_AHEAD], dof[ks], dp, 0, 0, 0);
+      if (ks + DQ_AHEAD < 8) vr[ks % DQ_AHEAD] = rows_frag(vt, fo, ks + DQ_AHEAD);
+      sched_fence();
+    }
+    bf16x8 kc[DQ_AHEAD_C];
+#pragma unroll
+    for (int i = 0; i < DQ_AHEAD_C; ++i) kc[i] = cols_frag(kt, fo, i & 3, i >> 2);
+    sched_fence();
     const bool diag = key0 + AKT - 1 > wave_first;
     if (diag) {
 #pragma unroll
@@ -411,11 +442,13 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
       s[q] = p * dp[q];
     }
     bf16x8 db[2] = {pack8(s, 0), pack8(s, 1)};
+    sched_fence();
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols_frag(kt, fo, f, s2), db[s2], acc[f], 0, 0, 0);
+    for (int i = 0; i < 8; ++i) {
+      acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc[i % DQ_AHEAD_C], db[i >> 2], acc[i & 3], 0, 0, 0);
+      if (i + DQ_AHEAD_C < 8) kc[i % DQ_AHEAD_C] = cols_frag(kt, fo, (i + DQ_AHEAD_C) & 3, (i + DQ_AHEAD_C) >> 2);
+      sched_fence();
+    }
   };
   for (int j = 0; j < n_tiles; j += ADS) {
     tile_step(std::integral_constant<int, 0>{}, j);
@@ -578,17 +611,32 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     f32x16 s, dp;
 #pragma unroll
     for (int q = 0; q < 16; ++q) s[q] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(qt, fo, ks), kf[ks], s, 0, 0, 0);
     if (DK) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float4 d4 = *reinterpret_cast<const float4 *>(&s_dlt[j & 1][8 * g + 4 * (lane >> 5)]);
         dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
       }
+    }
+    bf16x8 qr[DKV_AHEAD], dr[DKV_AHEAD], vr[DKV_AHEAD];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_frag(dot, fo, ks), rows_frag(vmine, fo, ks), dp, 0, 0, 0);
+    for (int i = 0; i < DKV_AHEAD; ++i) {
+      qr[i] = rows_frag(qt, fo, i);
+      dr[i] = rows_frag(dot, fo, i);
+      vr[i] = rows_frag(vmine, fo, i);
+    }
+    sched_fence();
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qr[ks % DKV_AHEAD], kf[ks], s, 0, 0, 0);
+      if (ks + DKV_AHEAD < 8) qr[ks % DKV_AHEAD] = rows_frag(qt, fo, ks + DKV_AHEAD);
+      sched_fence();
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dr[ks % DKV_AHEAD], vr[ks % DKV_AHEAD], dp, 0, 0, 0);
+      if (ks + DKV_AHEAD < 8) {
+        dr[ks % DKV_AHEAD] = rows_frag(dot, fo, ks + DKV_AHEAD);
+        vr[ks % DKV_AHEAD] = rows_frag(vmine, fo, ks + DKV_AHEAD);
+      }
+      sched_fence();
     }
     f32x16 p;
 #pragma unroll
@@ -617,13 +665,20 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     }
     bf16x8 pb[2] = {pack8(p, 0), pack8(p, 1)};
     bf16x8 db[2] = {pack8(s, 0), pack8(s, 1)};
+    // items in turn: dV, dK for each column fragment and half of the rows
+    auto column = [&](int i) { return cols_frag(i & 1 ? qt : dot, fo, (i >> 1) & 3, i >> 3); };
+    bf16x8 cr[DKV_AHEAD_C];
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+    for (int i = 0; i < DKV_AHEAD_C; ++i) cr[i] = column(i);
+    sched_fence();
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        if (DV) accv[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols_frag(dot, fo, f, s2), pb[s2], accv[f], 0, 0, 0);
-        if (DK) acck[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols_frag(qt, fo, f, s2), db[s2], acck[f], 0, 0, 0);
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int f = (i >> 1) & 3, s2 = i >> 3;
+      if (i & 1) acck[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cr[i % DKV_AHEAD_C], db[s2], acck[f], 0, 0, 0);
+      else accv[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cr[i % DKV_AHEAD_C], pb[s2], accv[f], 0, 0, 0);
+      if (i + DKV_AHEAD_C < 16) cr[i % DKV_AHEAD_C] = column(i + DKV_AHEAD_C);
+      sched_fence();
+    }
   };
   for (int j = 0; j < n_tiles; j += 2) {
     tile_step(std::integral_constant<int, 0>{}, j);
