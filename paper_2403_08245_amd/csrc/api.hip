@@ -35,6 +35,11 @@ int run_dw(smoe_ctx *ctx, hipStream_t s, smoe_dtype dt, DWArgs a) {
   if (dt == SMOE_BF16 && ctx->kernel_mode != 1 && dw_mfma_supported(a)) return launch_dw_mfma(s, a);
   return launch_dw_plain(s, dt, a);
 }
+// Does the persistent groupXTY take these operands, rows that it reads through the order indices among them?
+bool dw_reads_rows(const smoe_ctx *ctx, DWArgs a) {
+  a.grid = ctx->stream_grid;
+  return ctx->kernel_mode == 0 && dw_stream_supported(a);
+}
 
 // Do two arrays share memory?  (An output over an input that only an earlier launch reads is fine while these are launches of their
 // own, and not where one launch does it all.)
@@ -342,11 +347,21 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   // Rows that several slots share are spread from the source rows when that saves more than the launch that inverts the order
   // indices costs (about 3 us): on 20500 rows of 3 and 4 KB 39 us of group copies became 28, on 8192 rows of 2 KB the launch was
   // dearer by 1.5 us, so from 24 Mi elements on.
+  // groupXTY reads scattered rows of X, and of dY where no weights go with them, through the order indices: no sorted copy (unless an
+  // output that is written meanwhile lies over them).  The input-gradient product gathers such rows of dY as well.
+  const size_t x_bytes = (size_t)x_rows * d_in * 2, y_bytes = (size_t)Tk * d_out * 2, w_bytes = (size_t)r->E * d_in * d_out * 2;
+  DWArgs w{X, dY, dW, r->expert_offsets, r->E, Tk, d_in, d_out};
+  if (!grouped_in && !overlap(dW, w_bytes, X, x_bytes)) w.a_map = RowMap{r->sorted_scattered_idxs, k};
+  const bool rows_x = w.a_map.o && dw_reads_rows(ctx, w);
+  if (!rows_x) w.a_map = RowMap{nullptr, 1};
+  if (!grouped_out && !gates && !overlap(dW, w_bytes, dY, y_bytes) && !overlap(dX, x_bytes, dY, y_bytes)) w.b_map = RowMap{r->sorted_scattered_idxs, 1};
+  const bool rows_y = w.b_map.o && dw_reads_rows(ctx, w);
+  if (!rows_y) w.b_map = RowMap{nullptr, 1};
   size_t shared = 0;
   if (!grouped_out && gates && gates_k > 1) shared += (size_t)Tk * d_out;
-  if (!grouped_in && dW && k > 1) shared += (size_t)Tk * d_in;
+  if (!grouped_in && dW && k > 1 && !rows_x) shared += (size_t)Tk * d_in;
   const bool spread = given_inv || (shared >= ((size_t)24 << 20) && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES);
-  const bool spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1;
+  const bool spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1 && !rows_x;
   if (spread && !given_inv) {
     rc = launch_invert(s, r->sorted_scattered_idxs, own_inv, nullptr, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
@@ -354,7 +369,7 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   void *xbar = grouped_in ? nullptr : (void *)((char *)ws + off_xbar);
   const bool spread_both = spread_y && spread_x && !grouped_in && dW && gates_k == k;
   const void *dYbar = dY;
-  if (!grouped_out) {
+  if (!grouped_out && !rows_y) {
     const RowDots dots{dY, Yhat, gates ? dgates : nullptr, Tk, gates_k, d_out};
     if (dots.dg && !spread_y) {
       rc = launch_rowdot(s, dtype, dY, Yhat, dgates, Tk, gates_k, d_out);
@@ -368,16 +383,15 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   }
   // Xbar = group(X, o);  dW = groupXTY(Xbar, dYbar)
   if (dW) {
-    const void *Xg = X;
-    if (!grouped_in) {
+    if (!grouped_in && !rows_x) {
       rc = spread_both ? SMOE_OK : spread_x ? launch_spread(s, X, inv, k, nullptr, xbar, Tk, d_in)
                     : launch_group(s, dtype, X, r->sorted_scattered_idxs, k, nullptr, xbar, Tk, d_in);
       if (rc != SMOE_OK) return rc;
-      Xg = xbar;
+      w.A = xbar;
     }
-    DWArgs a{Xg, dYbar, dW, r->expert_offsets, r->E, Tk, d_in, d_out};
-    a.split_ws = (float *)((char *)ws + need - S2S_TAIL_WS_BYTES);   // the input-gradient product below uses it afterwards
-    rc = run_dw(ctx, s, dtype, a);
+    w.B = dYbar;
+    w.split_ws = (float *)((char *)ws + need - S2S_TAIL_WS_BYTES);   // the input-gradient product below uses it afterwards
+    rc = run_dw(ctx, s, dtype, w);
     if (rc != SMOE_OK) return rc;
   }
   // dXbar = scatter2scatter(dYbar, W^T, o, 1): grouped or scattered like the forward input;
@@ -385,7 +399,7 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   if (dX) {
     bool need_sum = !grouped_in && k > 1;
     void *dst = need_sum ? xbar : dX;   // Xbar is dead once dW is done
-    S2SArgs a = make_s2s(dYbar, W, dst, r, d_in, d_out, true, true, 1, grouped_in != 0);
+    S2SArgs a = make_s2s(dYbar, W, dst, r, d_in, d_out, true, !rows_y, 1, grouped_in != 0);
     a.tail_ws = (float *)((char *)ws + need - S2S_TAIL_WS_BYTES);
     rc = run_s2s(ctx, s, dtype, a);
     if (rc != SMOE_OK) return rc;
@@ -618,17 +632,35 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     void *dYu = base + L.dybar_u, *second = base + L.second, *dH = base + L.dh, *dHpre = base + L.dhpre;
     float *gsorted = (float *)(base + L.gsorted), *dp_part = (float *)(base + L.dp_part);
     float *tail_ws = (float *)(base + L.total - S2S_TAIL_WS_BYTES);
-    // The W2^T product gathers the rows of dY itself (Alg. 1's scattered input, fan-out k); groupXTY needs sorted rows, so
-    // one sorted copy is made for it: the routing-weighted one, or the plain one when the weights go into Hw instead.
+    // The W2^T product gathers the rows of dY itself (Alg. 1's scattered input, fan-out k), and groupXTY those of X, and of dY when the
+    // weights go into Hw; otherwise it reads a routing-weighted sorted copy of dY.  Where groupXTY cannot gather (sources past 32-bit
+    // offsets) or an output lies over X or dY, sorted copies stand in.
+    const size_t x_bytes = (size_t)T * d_model * es, w1_bytes = (size_t)r->E * d_model * d_h * es, w2_bytes = (size_t)r->E * d_expert * d_model * es;
+    const bool apart = !overlap(dW1, w1_bytes, X, x_bytes) && !overlap(dW2, w2_bytes, X, x_bytes) && !overlap(dW1, w1_bytes, dY, x_bytes) &&
+                       !overlap(dW2, w2_bytes, dY, x_bytes) && !overlap(dgates, (size_t)Tk * sizeof(float), dY, x_bytes);
+    const RowMap tokens{r->sorted_scattered_idxs, k};
+    DWArgs w1{X, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
+    DWArgs w2{saved_H, second, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};
+    w1.a_map = tokens;
+    const bool rows_x = apart && dw_reads_rows(ctx, w1);
+    if (L.use_hw) {
+      w2.A = second;
+      w2.B = dY;
+      w2.b_map = tokens;
+    }
+    const bool rows_y = L.use_hw && apart && dw_reads_rows(ctx, w2);
+    if (L.use_hw && !rows_y) {
+      w2.B = dYu;
+      w2.b_map = RowMap{nullptr, 1};
+    }
     int32_t *inv_y = (int32_t *)dp_part, *inv_x = (int32_t *)gsorted;
     const bool spread = k > 1;   // the order indices are walked for the sorted weights anyway
     auto sorted_copy = [&](const void *rows, const int32_t *inv, const float *weights, void *out) {
       return spread ? launch_spread(s, rows, inv, k, weights, out, Tk, d_model)
                     : launch_group(s, dtype, rows, r->sorted_scattered_idxs, k, weights, out, Tk, d_model);
     };
-    rc = launch_invert(s, r->sorted_scattered_idxs, spread ? inv_y : nullptr, gates, gsorted, Tk);
-    if (rc != SMOE_OK) return rc;
-    rc = sorted_copy(dY, inv_y, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
+    rc = launch_invert(s, r->sorted_scattered_idxs, spread && !rows_y ? inv_y : nullptr, gates, gsorted, Tk);
+    if (rc == SMOE_OK && !rows_y) rc = sorted_copy(dY, inv_y, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
     if (rc != SMOE_OK) return rc;
     S2SArgs x2 = make_s2s(dY, W2, mode == 1 ? dHpre : dH, r, d_expert, d_model, true, false, k, true);
     if (mode == 1) {
@@ -642,40 +674,38 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     set_launch(ctx, x2);
     rc = launch_s2s_stream(s, x2);
     if (rc != SMOE_OK) return rc;
-    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, spread ? inv_x : nullptr, Tk);
+    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, spread && !rows_x ? inv_x : nullptr, Tk);
     if (rc != SMOE_OK) return rc;
     if (mode == 2) {
       rc = launch_act_bwd(s, act, saved_Hpre, dH, dHpre, Tk, d_expert);
       if (rc != SMOE_OK) return rc;
     }
-    DWArgs w2{L.use_hw ? (const void *)second : saved_H, L.use_hw ? (const void *)dYu : (const void *)second, dW2,
-              r->expert_offsets, r->E, Tk, d_expert, d_model};
     w2.split_ws = tail_ws;
-    void *Xbar = L.use_hw ? dYu : second;                // the sorted copy of dY is dead after dW2: its array holds Xbar, then dXbar
-    // Both weight gradients in one launch where that saves a round of tiles: the sorted copy of X then has to stand beside that of dY,
-    // and takes the room of the partial tiles, which nothing needs until the last product.  The workspace has no other room for it,
-    // so copies of more than 64 MiB go without, at a cost: with room for them the backward passes of 32768 and 65536 rows in 8 experts,
-    // 1280 -> 2 x 3416, take 2065 us instead of 2110 and 3840 instead of 3960, of 65536 rows in 16 experts, 1280 -> 2 x 1024, 1146 instead
-    // of 1245, of 16384 rows in 4 experts, 4096 -> 1416, 978 instead of 1082.
+    void *Xbar = L.use_hw ? dYu : second;                // dead after dW2: its array holds Xbar where that is made, then dXbar
+    // Both weight gradients in one launch where that saves a round of tiles.  A sorted copy of X would take the room of the partial
+    // tiles, which nothing needs until the last product.
     DWArgs both = w2;
-    both.grid = ctx->stream_grid;
-    both.A3 = tail_ws;
+    both.A3 = rows_x ? X : tail_ws;
+    both.a3_map = rows_x ? tokens : RowMap{nullptr, 1};
     both.B3 = dHpre;
     both.dW3 = dW1;
     both.M3 = d_model;
     both.N3 = d_h;
-    if ((size_t)Tk * d_model * es <= S2S_TAIL_WS_BYTES && !overlap(dW1, (size_t)r->E * d_model * d_h * es, saved_H, (size_t)Tk * d_expert * es) &&
+    both.grid = ctx->stream_grid;
+    if ((rows_x || (size_t)Tk * d_model * es <= S2S_TAIL_WS_BYTES) && !overlap(dW1, w1_bytes, saved_H, (size_t)Tk * d_expert * es) &&
         dw_stream_supported(both) && dw_stream_two_pay(both)) {
-      rc = sorted_copy(X, inv_x, nullptr, tail_ws);
-      if (rc != SMOE_OK) return rc;
-      rc = launch_dw_stream(s, both);
+      if (!rows_x) rc = sorted_copy(X, inv_x, nullptr, tail_ws);
+      if (rc == SMOE_OK) rc = launch_dw_stream(s, both);
       if (rc != SMOE_OK) return rc;
     } else {
       rc = run_dw(ctx, s, dtype, w2);
       if (rc != SMOE_OK) return rc;
-      rc = sorted_copy(X, inv_x, nullptr, Xbar);
-      if (rc != SMOE_OK) return rc;
-      DWArgs w1{Xbar, dHpre, dW1, r->expert_offsets, r->E, Tk, d_model, d_h};
+      if (!rows_x) {
+        rc = sorted_copy(X, inv_x, nullptr, Xbar);
+        if (rc != SMOE_OK) return rc;
+        w1.A = Xbar;
+        w1.a_map = RowMap{nullptr, 1};
+      }
       w1.split_ws = tail_ws;
       rc = run_dw(ctx, s, dtype, w1);
       if (rc != SMOE_OK) return rc;
@@ -941,9 +971,14 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
     if (rc != SMOE_OK) return rc;
     rc = launch_dp_reduce(s, dp_part, part_ld, r->sorted_scattered_idxs, dgates, nullptr, Tk);
     if (rc != SMOE_OK) return rc;
-    rc = launch_spread(s, dO, inv, k, nullptr, dYu, Tk, d_model);
-    if (rc != SMOE_OK) return rc;
-    DWArgs wo{Ow, dYu, dW_O, r->expert_offsets, r->E, Tk, d_out, d_model};
+    DWArgs wo{Ow, dO, dW_O, r->expert_offsets, r->E, Tk, d_out, d_model};
+    wo.b_map = RowMap{r->sorted_scattered_idxs, k};
+    if (overlap(dW_O, (size_t)r->E * d_out * d_model * 2, dO, (size_t)N * d_model * 2) || !dw_reads_rows(ctx, wo)) {
+      rc = launch_spread(s, dO, inv, k, nullptr, dYu, Tk, d_model);
+      if (rc != SMOE_OK) return rc;
+      wo.B = dYu;
+      wo.b_map = RowMap{nullptr, 1};
+    }
     wo.split_ws = tail_ws;
     rc = run_dw(ctx, s, dtype, wo);
   } else {

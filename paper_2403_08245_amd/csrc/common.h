@@ -177,7 +177,7 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   const float *gates = nullptr;
   const int32_t *slots = nullptr;
 };
-struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both operands expert-sorted)
+struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (rows expert-sorted, or read through the row maps)
   const void *A;      // [Tk, M]
   const void *B;      // [Tk, N]
   void *dW;           // [E, M, N]
@@ -196,9 +196,10 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (both 
   const void *A3 = nullptr, *B3 = nullptr;
   void *dW3 = nullptr;
   int M3 = 0, N3 = 0;
-  // fp32 kernels (gemm_plain.hip): rows of A and B read through the order indices instead of from sorted copies, and B's rows
-  // scaled by the routing weights (fp32, slot order; needs b_map).
-  RowMap a_map{nullptr, 1}, b_map{nullptr, 1};
+  // Persistent and fp32 kernels: rows of A, B and A3 read through the order indices (the same in all of them) instead of from
+  // sorted copies.  Persistent kernel: not A beside dW3, nothing beside dW2.
+  RowMap a_map{nullptr, 1}, b_map{nullptr, 1}, a3_map{nullptr, 1};
+  // fp32 kernels: B's rows scaled by the routing weights (fp32, slot order; needs b_map).
   const float *gates = nullptr;
 };
 constexpr size_t LAST_LEVEL_CACHE = (size_t)256 << 20;

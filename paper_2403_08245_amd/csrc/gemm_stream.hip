@@ -608,41 +608,71 @@ __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int til
 }
 
 // ======================================================================================
-// groupXTY, persistent: dW[e] = Xbar_e^T dYbar_e over expert-sorted rows (Alg. 2 groups both
-// operands first; gathering the token rows inside this kernel measured a third slower than a
-// `group` copy followed by this kernel, the same ranking the paper reports).
+// groupXTY, persistent: dW[e] = Xbar_e^T dYbar_e over the rows of each expert's segment.  An operand lies expert-sorted, or
+// (DWArgs' row maps) its rows are read from their source through the order indices, with no sorted copy.
 // ======================================================================================
-// The loader cursor runs two stages ahead of the multiplying cursor over the same sequence: the stages (of 64 rows) of a tile
-// rounded up to an even number (at least two), tiles in largest-expert-first order.  Rows past a segment's end load zeros, so a
-// tile of an empty expert multiplies zeros and writes zeros.
+// The loader's cursor runs two stages (three where it fetches order indices) ahead of the multiplying side over the same sequence: the
+// stages (of 64 rows) of a tile rounded up to an even number (at least two), tiles in largest-expert-first order.  Rows past a segment's
+// end load zeros, so a tile of an empty expert multiplies zeros and writes zeros.  One wavefront per SIMD: what a stage's bookkeeping
+// takes the matrix cores wait for, so everything that is constant over a tile is worked out once per tile, and a step to the next
+// stage is a few scalar additions.
 struct DWCursor {
-  int seq;        // position in this block's tile list
-  int step, ns;   // stage within the tile, stages of the tile
-  int e, lo, hi, m0, n0;
-  bool further;   // a tile of dW3
-  bool live;
+  int seq;               // position in this block's tile list
+  int step, ns;          // stage within the tile, stages of the tile
+  int left;              // rows of the segment from the stage's first on (0 or less: none)
+  int e, m0, n0;
+  bool further;          // a tile of dW3
+  const char *pa, *pb;   // the stage's first row of each operand; the start of a source whose rows are read through the order indices
+  uint32_t sa, sb;       // bytes from one stage to the next (0 for such a source)
+  const int32_t *po;     // order indices from the stage's first row on
+};
+struct DWTile {          // the multiplying side's tile
+  int seq, e, m0, n0, ns;
+  bool further;
 };
 
-struct DWStreamOps {
+// How the operands of a launch lie (kernels of their own: the choice sits in every load): DW_ONE sorted; DW_A, DW_B, DW_AB the rows of
+// A, of B or of both read through the order indices; DW_PAIR sorted, segment 1 is the second weight gradient of DWArgs; DW_TWO every
+// expert's tiles are followed by those of its dW3, whose A3, like the first one's B, may be read through the order indices.
+enum { DW_ONE, DW_A, DW_B, DW_AB, DW_PAIR, DW_TWO };
+
+template <int KIND> struct DWStreamOps {
+  static constexpr bool ROWS_A = KIND == DW_A || KIND == DW_AB || KIND == DW_TWO, ROWS_B = KIND == DW_B || KIND == DW_AB || KIND == DW_TWO;
   int uwave;
-  // The loader's current stage: range-checked windows that start at its first row and end with the expert's segment (rows past
-  // it, padded stages and empty experts read zeros and add nothing to the sum), and per-lane byte offsets of the tile's columns for
+  // The loader's current stage: range-checked windows that start at its first row and end with its rows of the expert's segment (rows
+  // past it, padded stages and empty experts read zeros and add nothing to the sum), and per-lane byte offsets of the tile's columns for
   // even and odd load instructions; a pair of them (four rows) lies pair_a or pair_b bytes behind the one before.
   int32x4 win_a, win_b;
   uint32_t oa[2], ob[2], pair_a, pair_b;
   uint32_t fa[4], fb[4];     // the lane's column fragments inside a slot
+  // Rows read through the order indices: the stage's indices of the lane's rows, by load instruction; bytes per source row (0: the
+  // operand lies sorted); multiply-high that divides twice an index by twice the fan-out; rows of the segment from the stage's first
+  // on, and the lane's first row.  Lanes past the segment read zeros by an offset outside the window.
+  uint32_t order[Big::NLA];
+  uint32_t mul_a, mul_b, magic_a, magic_b;
+  int left, row;
+  __device__ __forceinline__ uint32_t through(int I, uint32_t off, uint32_t mul, uint32_t magic) const {
+    off += __umul24(__umulhi(order[I] * 2u, magic), mul);
+    return row + 2 * I < left ? off : ~0u;
+  }
   __device__ static constexpr int nth(int i) { return i & 1 ? Big::NLA + i / 2 : i / 2; }
   __device__ __forceinline__ void load(int I, uint32_t fill_a, uint32_t fill_b) const {
     if (I < Big::NLA) {
-      load16_to_lds_checked(win_a, oa[I & 1] + (uint32_t)(I >> 1) * pair_a, fill_a + (uwave * Big::NLA + I) * 1024);
+      uint32_t off = oa[I & 1] + (uint32_t)(I >> 1) * pair_a;
+      if (ROWS_A) off = through(I, off, mul_a, magic_a);
+      load16_to_lds_checked(win_a, off, fill_a + (uwave * Big::NLA + I) * 1024);
     } else {
       const int J = I - Big::NLA;
-      load16_to_lds_checked(win_b, ob[J & 1] + (uint32_t)(J >> 1) * pair_b, fill_b + (uwave * Big::NLB + J) * 1024);
+      uint32_t off = ob[J & 1] + (uint32_t)(J >> 1) * pair_b;
+      if (ROWS_B) off = through(J, off, mul_b, magic_b);
+      load16_to_lds_checked(win_b, off, fill_b + (uwave * Big::NLB + J) * 1024);
     }
   }
   __device__ __forceinline__ bf16x8 frag_a(const char *slot, int i, int kk) const { return rows_frag(slot + fa[i], kk); }
   __device__ __forceinline__ bf16x8 frag_b(const char *slot, int j, int kk) const { return rows_frag(slot + fb[j], kk); }
 };
+
+constexpr uint32_t MAX_SOURCE_BYTES = 0xfffffff0u;      // window of rows read through the order indices
 
 // tile number inside an expert -> first row and column of the tile: bands of group_m M-tiles, N-tile by
 // N-tile, so that the 32 consecutive tiles an XCD holds at a time form a compact patch sharing few panels
@@ -662,11 +692,20 @@ __device__ __forceinline__ void dw_chunk_rows(int lo, int hi, int split, int chu
 
 // split > 1 (only when all experts' tiles times split fit one round of the grid): unit T is chunk T % split of
 // tile T / split, experts in their own order, and the result is an fp32 partial tile number T in a.split_ws.
-// KIND (kernels of their own: the choice of operands sits in every stage): DW_PAIR segment 1 is the second weight gradient of DWArgs;
-// DW_TWO every expert's tiles are followed by those of its dW3.
-enum { DW_ONE = 0, DW_PAIR = 1, DW_TWO = 2 };
-template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split) {
-  constexpr bool DENSE_PAIR = KIND == DW_PAIR;
+//
+// A sorted copy of the rows costs a pass over them that writes [Tk, width] and a launch, and the product reads that copy instead of a
+// source that is fan-out times smaller.  Training steps with the copies / with rows through the order indices, interleaved on one box,
+// in us: granular layer (8192 tokens, 64 experts, k = 8, 2048 -> 2 x 512) 1605 / 1544, one ParallelLinear (16396 rows, 2048 -> 1536) 408 /
+// 393, attention layer (8192 tokens, k = 4) 1443 / 1382, small layer (8192 rows, 1024 -> 2 x 2816) 610 / 605, its weight gradients 69 + 113.
+// With the tile's constants worked out in every stage instead of once per tile the same launches gained less: 1567 of 1648 where these take
+// 1544 of 1605, and the small layer lost 1 %.
+//
+// Rows through the order indices (ROWS): a wavefront needs the indices of the 16 rows of a stage that it loads itself.  It fetches them
+// into LDS by a load of its own, issued a stage before the operand loads that use them: that stage's wait covers it, so the
+// fetch adds no wait and no barrier, and an index becomes an offset in the shadow of the matrix instructions.
+template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_kernel(DWArgs a, int tiles_m, int tiles_n, int split, uint32_t magic_a, uint32_t magic_b) {
+  constexpr bool DENSE_PAIR = KIND == DW_PAIR, ROWS = DWStreamOps<KIND>::ROWS_A || DWStreamOps<KIND>::ROWS_B;
+  __shared__ __attribute__((aligned(16))) uint32_t s_rows[ROWS ? 2 : 1][ROWS ? 4 : 1][64];   // by stage parity and wavefront
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_off[MAX_E + 1];
   __shared__ int s_order[MAX_E];      // experts, largest segment first
@@ -691,28 +730,62 @@ template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_ker
   }
   __syncthreads();
 
+  // the tiles that the loader has opened, for the multiplying side; a ring per wavefront (the loader is at most two tiles ahead)
+  __shared__ __attribute__((aligned(16))) int s_tile[4][4][4];
+  constexpr int FURTHER = 1 << 30;
+  auto rows_a = [&](const DWCursor &c) { return KIND == DW_A || KIND == DW_AB || (KIND == DW_TWO && c.further && a.a3_map.o); };
+  auto rows_b = [&](const DWCursor &c) { return KIND == DW_B || KIND == DW_AB || (KIND == DW_TWO && !c.further && a.b_map.o); };
   auto open_tile = [&](DWCursor &c, int seq) {
     c.seq = seq;
+    c.step = 0;
     const int U = seq * G + slot_in_round;
-    const int T = U / split;
-    int rank = T / per_expert;
-    c.live = rank < a.E && (split == 1 || seq == 0);
-    if (!c.live) return;
-    int t = T - rank * per_expert;
+    const int T = split > 1 ? U / split : U;
+    const int rank = T / per_expert;
+    if (rank >= a.E || (split > 1 && seq > 0)) {   // past the last tile: stages without rows
+      c.left = 0;
+      c.ns = 0x7fffffff;
+      *reinterpret_cast<int4 *>(s_tile[wave][seq & 3]) = make_int4(0, 0, 0, 0);
+      return;
+    }
+    const int t = T - rank * per_expert;
     c.e = split > 1 ? rank : __builtin_amdgcn_readfirstlane(s_order[rank]);   // LDS reads land in vector registers: make them scalar again
-    c.lo = __builtin_amdgcn_readfirstlane(s_off[c.e]);
-    c.hi = __builtin_amdgcn_readfirstlane(s_off[c.e + 1]);
-    if (split > 1) dw_chunk_rows(c.lo, c.hi, split, U - T * split, c.lo, c.hi);
+    int lo = __builtin_amdgcn_readfirstlane(s_off[c.e]), hi = __builtin_amdgcn_readfirstlane(s_off[c.e + 1]);
+    if (split > 1) dw_chunk_rows(lo, hi, split, U - T * split, lo, hi);
     c.further = KIND == DW_TWO && t >= per_first;
     if (c.further) dw_tile_origin(t - per_first, tiles_m3, tiles_n3, c.m0, c.n0);
     else dw_tile_origin(t, tiles_m, tiles_n, c.m0, c.n0);
+    c.left = hi - lo;
     // Stages come in pairs so that every tile starts in LDS slot 0 and the loop can be written with compile-time slots; the extra
     // stage (two for an empty expert) loads zeros and adds nothing.
-    c.ns = max(((c.hi - c.lo + SK - 1) / SK + 1) & ~1, 2);
-    c.step = 0;
+    c.ns = max(((c.left + SK - 1) / SK + 1) & ~1, 2);
+    const bool second = KIND == DW_PAIR && c.e == 1;
+    const uint32_t row_a = (uint32_t)(c.further ? a.M3 : a.M) * 2u, row_b = (uint32_t)(c.further ? a.N3 : a.N) * 2u;
+    c.pa = (const char *)(c.further ? a.A3 : second ? a.A2 : a.A);
+    c.pb = (const char *)(c.further ? a.B3 : second ? a.B2 : a.B);
+    const bool through_a = rows_a(c), through_b = rows_b(c);
+    c.sa = through_a ? 0u : SK * row_a;
+    c.sb = through_b ? 0u : SK * row_b;
+    if (!through_a) c.pa += (size_t)lo * row_a;
+    if (!through_b) c.pb += (size_t)lo * row_b;
+    if (ROWS) c.po = (a.b_map.o ? a.b_map.o : KIND == DW_TWO ? a.a3_map.o : a.a_map.o) + lo;   // every map has the same order indices
+    *reinterpret_cast<int4 *>(s_tile[wave][seq & 3]) = make_int4(c.e | (c.further ? FURTHER : 0), c.m0, c.n0, c.ns);
+  };
+  auto follow = [&](DWTile &t, int seq) -> bool {
+    const int4 v = *reinterpret_cast<const int4 *>(s_tile[wave][seq & 3]);
+    const int e = __builtin_amdgcn_readfirstlane(v.x);
+    t.seq = seq;
+    t.e = e & ~FURTHER;
+    t.further = KIND == DW_TWO && (e & FURTHER);
+    t.m0 = __builtin_amdgcn_readfirstlane(v.y);
+    t.n0 = __builtin_amdgcn_readfirstlane(v.z);
+    t.ns = __builtin_amdgcn_readfirstlane(v.w);
+    return t.ns > 0;
   };
   auto advance = [&](DWCursor &c) {
-    if (!c.live) return;
+    c.left -= SK;
+    c.pa += c.sa;
+    c.pb += c.sb;
+    if (ROWS) c.po += SK;
     if (++c.step < c.ns) return;
     // keeps the tile lookup behind this (rarely taken) branch: without it the compiler evaluates
     // the lookup's integer divisions in every stage and selects the results
@@ -720,60 +793,92 @@ template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_ker
     open_tile(c, c.seq + 1);
   };
 
-  DWStreamOps ops;
+  DWStreamOps<KIND> ops;
   ops.uwave = __builtin_amdgcn_readfirstlane(wave);
+  ops.magic_a = magic_a;
+  ops.magic_b = magic_b;
+  ops.row = wave * 16 + (lane >> 5);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     ops.fa[q] = rows_frag_offset(wm * (TB / 2) + q * 32, lane);
     ops.fb[q] = rows_frag_offset(wn * (TB / 2) + q * 32, lane);
   }
-  const bf16_t *A = (const bf16_t *)a.A, *B = (const bf16_t *)a.B;
-  // loader cursor: publish the stage whose loads are issued next
-  int shown_m0 = -1, shown_n0 = -1, shown_further = -1;
-  auto resolve = [&](const DWCursor &c) {
-    const int first = c.lo + c.step * SK;                        // first row of the stage
-    const int left = c.live ? max(c.hi - first, 0) : 0;          // rows of the segment from there on
-    const int base_row = left > 0 ? first : 0;
-    const unsigned long long cap = 0xffffffffull;
-    const bool second = DENSE_PAIR && c.e == 1, further = KIND == DW_TWO && c.further;
-    const int M = further ? a.M3 : a.M, N = further ? a.N3 : a.N;
-    const uint32_t row_a = (uint32_t)M * 2u, row_b = (uint32_t)N * 2u;   // bytes per operand row
-    ops.win_a = buffer_window((further ? (const bf16_t *)a.A3 : second ? (const bf16_t *)a.A2 : A) + (size_t)base_row * M, (uint32_t)min((unsigned long long)left * row_a, cap));
-    ops.win_b = buffer_window((further ? (const bf16_t *)a.B3 : second ? (const bf16_t *)a.B2 : B) + (size_t)base_row * N, (uint32_t)min((unsigned long long)left * row_b, cap));
-    ops.pair_a = 4u * row_a;
-    ops.pair_b = 4u * row_b;
-    if (c.m0 != shown_m0 || c.n0 != shown_n0 || (KIND == DW_TWO && (int)c.further != shown_further)) {   // a new tile: its columns' offsets inside a stage
-      shown_m0 = c.m0;
-      shown_n0 = c.n0;
-      shown_further = c.further;
+  const uint32_t rows_lds = __builtin_amdgcn_readfirstlane(lds_address((const char *)&s_rows[0][0][0])) + (ROWS ? ops.uwave * 256 : 0);
+  const uint32_t rows_lane = (uint32_t)(wave * 16 + (lane & 7) * 2 + ((lane >> 3) & 1)) * 4u;
+  // rows of the segment in a stage (by hand: the compiler's median instruction is a vector one, and takes all that follows with it)
+  auto stage_rows = [](const DWCursor &c) {
+    uint32_t n;
+    __asm__("s_max_i32 %0, %1, 0\n\ts_min_i32 %0, %0, %2" : "=&s"(n) : "s"(c.left), "n"(SK) : "scc");
+    return n;
+  };
+  // order indices of the rows that this wavefront loads of a stage -> s_rows[parity], the even rows in front (four copies)
+  auto fetch_rows = [&](const DWCursor &c, int parity) {
+    load4_to_lds_checked(scalar_window(c.po, stage_rows(c) * 4u), rows_lane, rows_lds + parity * 1024);
+  };
+  // publishes the stage whose loads are issued next
+  uint32_t row_a = 0, row_b = 0;
+  auto resolve = [&](const DWCursor &c, int parity) {
+    const bool through_a = rows_a(c), through_b = rows_b(c);
+    if (c.step == 0) {   // a new tile
+      const int M = c.further ? a.M3 : a.M, N = c.further ? a.N3 : a.N;
+      row_a = (uint32_t)M * 2u;   // bytes per operand row
+      row_b = (uint32_t)N * 2u;
+      ops.pair_a = through_a ? 0u : 4u * row_a;
+      ops.pair_b = through_b ? 0u : 4u * row_b;
+      ops.mul_a = through_a ? row_a : 0u;
+      ops.mul_b = through_b ? row_b : 0u;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const int r = p * 2 + (lane >> 5), col = ((lane & 31) ^ tr_swz(r)) * 8;
         int ca = c.m0 + col, cb = c.n0 + col;
         if (ca >= M) ca = 0;
         if (cb >= N) cb = 0;
-        ops.oa[p] = (uint32_t)(wave * 16 + r) * row_a + (uint32_t)ca * 2u;
-        ops.ob[p] = (uint32_t)(wave * 16 + r) * row_b + (uint32_t)cb * 2u;
+        ops.oa[p] = (through_a ? 0u : (uint32_t)(wave * 16 + r) * row_a) + (uint32_t)ca * 2u;
+        ops.ob[p] = (through_b ? 0u : (uint32_t)(wave * 16 + r) * row_b) + (uint32_t)cb * 2u;
       }
+    }
+    const uint32_t rows = stage_rows(c);
+    ops.win_a = scalar_window(c.pa, through_a ? MAX_SOURCE_BYTES : rows * row_a);
+    ops.win_b = scalar_window(c.pb, through_b ? MAX_SOURCE_BYTES : rows * row_b);
+    if (ROWS) {
+      ops.left = c.left;
+      const uint4 *o = reinterpret_cast<const uint4 *>(&s_rows[parity][wave][(lane >> 5) * 8]);
+      const uint4 lo = o[0], hi = o[1];
+      ops.order[0] = lo.x; ops.order[1] = lo.y; ops.order[2] = lo.z; ops.order[3] = lo.w;
+      ops.order[4] = hi.x; ops.order[5] = hi.y; ops.order[6] = hi.z; ops.order[7] = hi.w;
     }
   };
 
-  DWCursor cc, lc;
-  open_tile(cc, 0);
-  if (!cc.live) return;
-  lc = cc;
+  DWCursor lc;
+  DWTile cc;
+  open_tile(lc, 0);
+  if (!follow(cc, 0)) return;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
   char *patch = smem + Big::RING_BYTES + ops.uwave * EPI_WAVE_BYTES;
+  DWCursor rc = lc;                           // ROWS: the stage whose order indices are fetched next
+  auto fetch_next = [&](int parity) {
+    if (!ROWS) return;
+    fetch_rows(rc, parity);
+    advance(rc);
+  };
+  fetch_next(0);
+  fetch_next(1);
+  if (ROWS) wait_loads<0>();
 #pragma unroll 1
   for (int st = 0; st < Big::SLOTS; ++st) {
-    resolve(lc);
+    resolve(lc, st);
 #pragma unroll
     for (int I = 0; I < Big::NL; ++I) ops.load(I, lds0 + st * Big::A_BYTES, lds0 + Big::SLOTS * Big::A_BYTES + st * B_BYTES);
     advance(lc);
+    if (st == 0) fetch_next(0);               // in front of the second stage's loads, like all later ones
   }
-  resolve(lc);
   wait_loads<(Big::SLOTS - 1) * Big::NL>();   // the first stage has landed
   __syncthreads();
+  resolve(lc, 0);
+  if (ROWS) {
+    advance(lc);
+    fetch_rows(lc, 1);
+  }
   f32x16 acc[FR][FR];
   Frags<Big> f[4];
 #pragma unroll
@@ -781,22 +886,30 @@ template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_ker
 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  auto next_stage = [&]() {
-    advance(lc);
-    resolve(lc);
+  // Behind the stage in slot `cur`: the operands of the loads that the next stage issues.  With ROWS the cursor is one stage further,
+  // that of the indices fetched here; the ones read here landed at the wait of the stage just done.
+  auto next_stage = [&](int cur) {
+    if (ROWS) {
+      resolve(lc, cur ^ 1);
+      advance(lc);
+      fetch_rows(lc, cur);
+    } else {
+      advance(lc);
+      resolve(lc, 0);
+    }
   };
   for (;;) {   // one tile per trip
     // the stores of the previous tile's epilogue lie behind the loads that the first stage's wait is for
     if (cc.seq > 0) stage_step<true, false, EpilogueStores<Big::FM, 0>, Big>(ops, f, acc, smem, lds0, I0{}, I1{});
     else stage_step<true, false, 0, Big>(ops, f, acc, smem, lds0, I0{}, I1{});
-    next_stage();
+    next_stage(0);
     stage_step<false, false, 0, Big>(ops, f, acc, smem, lds0, I1{}, I0{});
-    next_stage();
+    next_stage(1);
     for (int h = 2; h < cc.ns; h += 2) {
       stage_step<false, false, 0, Big>(ops, f, acc, smem, lds0, I0{}, I1{});
-      next_stage();
+      next_stage(0);
       stage_step<false, false, 0, Big>(ops, f, acc, smem, lds0, I1{}, I0{});
-      next_stage();
+      next_stage(1);
     }
     const int mbase = cc.m0 + uwm * (TB / 2), wcol = cc.n0 + uwn * (TB / 2);
     if (split > 1) {
@@ -815,8 +928,7 @@ template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_ker
         return d;
       }, lane);
     }
-    open_tile(cc, cc.seq + 1);
-    if (!cc.live) break;
+    if (!follow(cc, cc.seq + 1)) break;
   }
   wait_loads<0>();
 }
@@ -930,9 +1042,17 @@ int launch_dw_stream_impl(hipStream_t s, const DWArgs &a) {
     if (ns - ns / split < SPLIT_MIN_SAVED) split = 1;
   }
   if (a.dW3) split = 1;
-  if (a.dW3) hipLaunchKernelGGL(dw_stream_kernel<DW_TWO>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
-  else if (a.dW2) hipLaunchKernelGGL(dw_stream_kernel<DW_PAIR>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
-  else hipLaunchKernelGGL(dw_stream_kernel<DW_ONE>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split);
+  auto magic = [](int fan) { return (uint32_t)((0x80000000ULL + fan - 1) / fan); };   // of twice the dividend: exact while Tk * fan < 2^31
+  const uint32_t magic_a = magic(a.dW3 ? a.a3_map.fan : a.a_map.fan), magic_b = magic(a.b_map.fan);
+  auto launch = [&](auto kind) {
+    hipLaunchKernelGGL(dw_stream_kernel<decltype(kind)::value>, dim3(a.grid), dim3(NTHREADS), Big::LDS_BYTES, s, a, tiles_m, tiles_n, split, magic_a, magic_b);
+  };
+  if (a.dW3) launch(std::integral_constant<int, DW_TWO>{});
+  else if (a.dW2) launch(std::integral_constant<int, DW_PAIR>{});
+  else if (a.a_map.o && a.b_map.o) launch(std::integral_constant<int, DW_AB>{});
+  else if (a.a_map.o) launch(std::integral_constant<int, DW_A>{});
+  else if (a.b_map.o) launch(std::integral_constant<int, DW_B>{});
+  else launch(std::integral_constant<int, DW_ONE>{});
   SMOE_LAUNCH_CHECK();
   if (split > 1) {
     hipLaunchKernelGGL(dw_split_reduce_kernel, dim3((unsigned)tiles, TAIL_SLICES), dim3(256), 0, s, a, tiles_m, tiles_n, split);
@@ -986,10 +1106,19 @@ int launch_s2s_stream(hipStream_t s, const S2SArgs &a) {
   return scatter_out ? launch_s2s_cfg<false, true>(s, a) : launch_s2s_cfg<false, false>(s, a);
 }
 
+// Rows that groupXTY reads through the order indices: 32-bit offsets from the source's start, made by a 24-bit multiplication, and a
+// division by the fan-out that is exact while Tk * fan < 2^31.
+static bool rows_readable(const RowMap &m, int Tk, int width) {
+  if (!m.o) return true;
+  const long long rows = Tk / m.fan, bytes = (long long)width * 2;
+  return rows < (1 << 24) && bytes < (1 << 24) && rows * bytes <= (long long)MAX_SOURCE_BYTES && (long long)Tk * m.fan < 0x80000000LL;
+}
 bool dw_stream_supported(const DWArgs &a) {
   long long tiles = (long long)a.E * ((long long)ceil_div(a.M, TB) * ceil_div(a.N, TB) + (long long)ceil_div(a.M3, TB) * ceil_div(a.N3, TB));
   return a.M % 8 == 0 && a.N % 8 == 0 && a.M3 % 8 == 0 && a.N3 % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 &&
-         a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL && (long long)TB * a.N3 * 2 < 0x80000000LL;
+         a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL && (long long)TB * a.N3 * 2 < 0x80000000LL &&
+         rows_readable(a.a_map, a.Tk, a.M) && rows_readable(a.b_map, a.Tk, a.N) && rows_readable(a.a3_map, a.Tk, a.M3) &&
+         !(a.dW3 && a.a_map.o) && !(a.dW2 && (a.a_map.o || a.b_map.o));
 }
 
 // Together two weight gradients save the rounds that their last tiles fill only in part, and a launch, while a stage costs 3 % more
@@ -1033,6 +1162,9 @@ int init_stream_kernels() {
   if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
   if (rc == SMOE_OK) rc = init_s2s<true, true, 6>();
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_ONE>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_A>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_B>, Big::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_AB>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_PAIR>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_TWO>, Big::LDS_BYTES);
   return rc;

@@ -49,6 +49,11 @@ __device__ __forceinline__ int32x4 buffer_window(const void *base, uint32_t byte
   r[3] = 0x00020000;                                                            // 32-bit raw data format
   return r;
 }
+// The same of values that are in scalar registers already.
+__device__ __forceinline__ int32x4 scalar_window(const void *base, uint32_t bytes) {
+  const unsigned long long p = (unsigned long long)base;
+  return int32x4{(int)(uint32_t)p, (int)(uint32_t)((p >> 32) & 0xffffu), (int)bytes, 0x00020000};
+}
 __device__ __forceinline__ void load16_to_lds_checked(int32x4 window, uint32_t byte_off, uint32_t lds_addr) {
   __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window)
                    : "memory", "m0");
@@ -61,6 +66,9 @@ __device__ __forceinline__ void load16_to_lds_checked_or_once(int32x4 window, ui
 }
 __device__ __forceinline__ void load4_to_lds(const void *gsrc, uint32_t lds_addr) {
   __asm__ volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");
+}
+__device__ __forceinline__ void load4_to_lds_checked(int32x4 window, uint32_t byte_off, uint32_t lds_addr) {
+  __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window) : "memory", "m0");
 }
 // Waits until at most N of this wavefront's global loads are outstanding (they finish in order).
 template <int N> __device__ __forceinline__ void wait_loads() {
