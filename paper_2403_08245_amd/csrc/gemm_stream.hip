@@ -156,19 +156,41 @@ __device__ __forceinline__ void stage_step(const Ops &ops, Frags<S> (&f)[4], f32
 struct TilePlan {
   int m_tiles, rounds, rest, split, chunk;
 };
-template <typename S>
-__device__ __forceinline__ TilePlan plan_tiles(const int32_t *offsets, int E, int tiles_n, int ns, int G, bool static2, bool may_split,
-                                               int lane) {
-  int sum = 0;
+// first[e] = M-tiles of the experts before e, by every wavefront for itself (all write the same); returns first[E].  A tile's expert is
+// then found by one comparison per lane, where a search that adds up the experts' tiles again is a chain of ten lane exchanges, which
+// the matrix cores wait for at every tile.
+template <typename S> __device__ __forceinline__ int number_tiles(const int32_t *offsets, int E, int *first, int lane) {
+  int base = 0;
+  if (lane == 0) first[0] = 0;
   for (int c0 = 0; c0 < E; c0 += 64) {
-    int x = c0 + lane;
+    const int x = c0 + lane;
     int n = x < E ? (offsets[x + 1] - offsets[x] + S::TM - 1) / S::TM : 0;
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
-    sum += n;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(n, d, 64);
+      if (lane >= d) n += up;
+    }
+    if (x < E) first[x + 1] = base + n;
+    base += __builtin_amdgcn_readlane(n, 63);
   }
+  return base;
+}
+template <typename S>
+__device__ __forceinline__ void find_tile(const int32_t *offsets, const int *first, int E, int tile, int lane, int &e, int &row0, int &row_end) {
+  e = E - 1;
+  for (int c0 = 0; c0 < E; c0 += 64) {
+    const unsigned long long owns = __ballot(first[min(c0 + lane, E - 1) + 1] > tile);
+    if (!owns) continue;
+    e = c0 + __ffsll((long long)owns) - 1;
+    break;
+  }
+  row0 = __builtin_amdgcn_readfirstlane(offsets[e]) + (tile - __builtin_amdgcn_readfirstlane(first[e])) * S::TM;
+  row_end = __builtin_amdgcn_readfirstlane(offsets[e + 1]);
+}
+template <typename S>
+__device__ __forceinline__ TilePlan plan_tiles(int m_tiles, int tiles_n, int ns, int G, bool static2, bool may_split) {
   TilePlan p;
-  p.m_tiles = __builtin_amdgcn_readfirstlane(sum);
+  p.m_tiles = m_tiles;
   const long long total = (long long)p.m_tiles * tiles_n;
   p.rounds = (int)(total / G);
   p.rest = (int)(total - (long long)p.rounds * G);
@@ -231,7 +253,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
   static_assert(ACT < 3 || (TRANS_W && SCATTER_OUT == (ACT == 6)), "the fused derivative belongs to the W^T product");
   static_assert(!STATIC2 || S::SLOTS == 2, "the unrolled loop walks two slots");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  __shared__ int s_off[MAX_E + 1];
+  __shared__ int s_off[MAX_E + 1], s_first[MAX_E + 1];
   // Order indices of the rows of up to four open tiles.  With the shortest contraction the kernel takes (two stages) the
   // loader has opened tile n+2 and requested the rows of tile n+3 while tile n's epilogue still reads its destination
   // rows, so four entries are live at once.
@@ -254,7 +276,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
   for (int i = threadIdx.x; i <= a.E; i += NTHREADS) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
 
-  const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, ns, G, STATIC2, ACT == 0 && a.tail_ws != nullptr, lane);
+  const TilePlan plan = plan_tiles<S>(number_tiles<S>(s_off, a.E, s_first, lane), tiles_n, ns, G, STATIC2, ACT == 0 && a.tail_ws != nullptr);
   // This block's part of the last, partial round: tile number (-1: none), chunk of its contraction, index of the fp32
   // partial tile it leaves (-1: the tile is whole).
   int last_tile = -1, last_h0 = 0, last_hn = ns, last_part = -1;
@@ -284,13 +306,10 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
     const int seq = t.seq + 1;
     if (seq > rounds || (seq == rounds && last_tile < 0)) return false;
     const int w = seq < rounds ? seq * G + pos : last_tile;
-    int mt, nt, e, row0, row_end;
+    int mt, nt;
     tile_coords(w, m_tiles, tiles_n, group_m, mt, nt);
-    locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
     t.seq = seq;
-    t.e = __builtin_amdgcn_readfirstlane(e);
-    t.row0 = __builtin_amdgcn_readfirstlane(row0);
-    t.row_end = __builtin_amdgcn_readfirstlane(row_end);
+    find_tile<S>(s_off, s_first, a.E, mt, lane, t.e, t.row0, t.row_end);
     t.n0 = nt * (SWIGLU ? TB / 2 : TB);   // SwiGLU tiles hold 128 gate columns and the 128 up columns pairing with them
     *reinterpret_cast<int4 *>(s_tile[seq & 3]) = make_int4(t.e, t.row0, t.row_end, t.n0);
     return true;
@@ -336,6 +355,9 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
     chunk[p] = (uint32_t)((lane & 7) ^ line_swz(p * 8 + (lane >> 3)));
     ops.ta[p] = ops.tb[p] = KTAIL && (ns - 1) * SK + (int)chunk[p] * 8 >= a.K ? ~0u : 0u;
   }
+  // order index -> source row, with no branch for fan-out 1
+  const uint32_t whole = magic_a ? 0u : ~0u;
+  auto source_row = [&](uint32_t slot) { return __umulhi(slot, magic_a) + (slot & whole); };
   auto setup_sources = [&](const Tile &t) {
     const auto p = args();
     const int K = p->K, N = p->N;
@@ -344,7 +366,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
     // gathered rows are addressed from the start of A, expert-sorted rows from the tile's first row
     const bool second = DENSE_PAIR && p->C2 && t.e == 1;
     ops.win_a = buffer_window((const bf16_t *)(second ? p->A2 : p->A) + (gathered ? 0 : (size_t)t.row0 * K),
-                              (uint32_t)(gathered ? p->Tk / p->a_map.fan : min(S::TM, t.row_end - t.row0)) * row_bytes);
+                              (gathered ? source_row((uint32_t)p->Tk) : (uint32_t)min(S::TM, t.row_end - t.row0)) * row_bytes);
     ops.win_b = buffer_window((const bf16_t *)(second ? p->W2 : p->W) + (size_t)t.e * p->w_stride, (uint32_t)(TRANS_W ? N : K) * ldw_bytes);
     if (S::ONCE) ops.again = t.row_end - __builtin_amdgcn_readfirstlane(s_off[t.e]) - S::TM;
     const int *idx = &s_idx[t.seq & 3][0];
@@ -355,10 +377,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
     for (int I = 0; I < S::NLA; ++I) {
       const int r = (wave * S::NLA + I) * 8 + (lane >> 3);
       uint32_t src = (uint32_t)r;
-      if (gathered) {
-        const uint32_t slot = (uint32_t)idx[r];
-        src = magic_a ? __umulhi(slot, magic_a) : slot;
-      }
+      if (gathered) src = source_row((uint32_t)idx[r]);
       ops.oa[I] = r < t.row_end - t.row0 ? src * row_bytes + chunk[I & 1] * 16u : past;
     }
     // Rows (W^T) or columns past N read what lies there or zeros; they end up in outputs that are never stored.
@@ -575,18 +594,18 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
 constexpr int TAIL_SLICES = 32, TAIL_BLOCKS = 1024;
 template <typename S, bool SCATTER_OUT>
 __global__ void __launch_bounds__(256) s2s_tail_reduce_kernel(S2SArgs a, int tiles_n, int group_m, int G, int static2) {
-  __shared__ int s_off[MAX_E + 1];
+  __shared__ int s_off[MAX_E + 1], s_first[MAX_E + 1];
   const int lane = threadIdx.x & 63;
   for (int i = threadIdx.x; i <= a.E; i += 256) s_off[i] = a.offsets ? a.offsets[i] : a.Tk / a.E * i;
   __syncthreads();
-  const TilePlan plan = plan_tiles<S>(s_off, a.E, tiles_n, (a.K + SK - 1) / SK, G, static2 != 0, true, lane);
+  const TilePlan plan = plan_tiles<S>(number_tiles<S>(s_off, a.E, s_first, lane), tiles_n, (a.K + SK - 1) / SK, G, static2 != 0, true);
   if (plan.split <= 1) return;
   constexpr int PER_SLICE = S::PART / 4 / TAIL_SLICES;
   for (int unit = blockIdx.x; unit < plan.rest * TAIL_SLICES; unit += TAIL_BLOCKS) {
     const int tile = unit / TAIL_SLICES, slice = unit % TAIL_SLICES;
     int mt, nt, e, row0, row_end;
     tile_coords(plan.rounds * G + tile, plan.m_tiles, tiles_n, group_m, mt, nt);
-    locate_rows<S::TM>(s_off, a.E, mt, lane, e, row0, row_end);
+    find_tile<S>(s_off, s_first, a.E, mt, lane, e, row0, row_end);
     const int n0 = nt * TB;
     const float *part = a.tail_ws + (size_t)tile * plan.split * S::PART;
     bf16_t *C = (bf16_t *)(!SCATTER_OUT && a.C2 && e == 1 ? a.C2 : a.C);
