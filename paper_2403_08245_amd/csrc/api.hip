@@ -35,6 +35,8 @@ int run_dw(smoe_ctx *ctx, hipStream_t s, smoe_dtype dt, DWArgs a) {
   if (dt == SMOE_BF16 && ctx->kernel_mode != 1 && dw_mfma_supported(a)) return launch_dw_mfma(s, a);
   return launch_dw_plain(s, dt, a);
 }
+constexpr size_t SPREAD_MIN_ELEMENTS = (size_t)24 << 20;   // plinear_bwd says why
+
 // Does the persistent groupXTY take these operands, rows that it reads through the order indices among them?
 bool dw_reads_rows(const smoe_ctx *ctx, DWArgs a) {
   a.grid = ctx->stream_grid;
@@ -360,10 +362,10 @@ static int plinear_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void
   size_t shared = 0;
   if (!grouped_out && gates && gates_k > 1) shared += (size_t)Tk * d_out;
   if (!grouped_in && dW && k > 1 && !rows_x) shared += (size_t)Tk * d_in;
-  const bool spread = given_inv || (shared >= ((size_t)24 << 20) && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES);
+  const bool spread = given_inv || (shared >= SPREAD_MIN_ELEMENTS && (size_t)Tk * sizeof(int32_t) <= S2S_TAIL_WS_BYTES);
   const bool spread_y = spread && gates && gates_k > 1, spread_x = spread && k > 1 && !rows_x;
   if (spread && !given_inv) {
-    rc = launch_invert(s, r->sorted_scattered_idxs, own_inv, nullptr, nullptr, Tk);
+    rc = launch_invert(s, r->sorted_scattered_idxs, own_inv, Tk);
     if (rc != SMOE_OK) return rc;
   }
   void *xbar = grouped_in ? nullptr : (void *)((char *)ws + off_xbar);
@@ -529,18 +531,16 @@ int smoe_mlp_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
 // Workspace of the backward pass: dYbar [Tk,d_model] (later reused for dXbar), dH [Tk,d_expert],
 // dHpre [Tk,d_h].
 // Backward passes that form dp in the epilogue of the W2^T product (bf16 through the persistent kernels).
-// That product gathers the rows of dY itself; the one expert-sorted copy of dY [Tk,d_model] is for groupXTY (its array later
-// holds Xbar, then dXbar).
-//   mode 1 (SwiGLU): the activation's derivative is applied there too; scratch = the routing-weighted sorted copy of dY,
-//     dHpre [Tk,d_h].
-//   mode 2 (other activations): dp from the saved H; scratch = the weighted sorted copy of dY or, when d_expert < d_model
-//     makes them the smaller tensor, the plain sorted copy plus the routing-weighted hidden rows Hw [Tk,d_expert] that let
-//     groupXTY form dW2 from the plain copy; dH [Tk,d_expert]; dHpre [Tk,d_h].
-//   both: the sorted routing weights [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
-// The inverse of the order indices sits where the slabs come to lie while dY is spread, and again, written by the kernel that
-// adds the slabs, in the dead sorted weights while X is.
+// That product gathers the rows of dY itself, and groupXTY those of X, and of dY where the routing weights go with the hidden rows.
+//   mode 1 (SwiGLU): the activation's derivative is applied there too; scratch = one array [Tk,d_model], dHpre [Tk,d_h].  The array
+//     holds the routing-weighted hidden rows Hw [Tk,d_expert] where they are no wider, else the weighted sorted copy of dY.
+//   mode 2 (other activations): dp from the saved H; scratch = the same array or, when d_expert < d_model, one for Hw and one for
+//     the plain sorted copy of dY that groupXTY may need beside it; dH [Tk,d_expert]; dHpre [Tk,d_h].
+//   both: room for the inverse of the order indices [Tk] and the slabs of dp [Tk, 2 * ceil(d_expert / 256)] fp32.
+// The array of dY's copy later holds dXbar (and before it Xbar, where a sorted copy of X is made).  The inverse of the order indices
+// sits where the slabs come to lie while dY is spread, and, written by the kernel that adds the slabs, in its own room while X is.
 struct MlpBwdEpiLayout {
-  size_t dybar_u, second, dh, dhpre, gsorted, dp_part, total;
+  size_t dybar_u, second, dh, dhpre, inv_x, dp_part, total;
   int part_ld;
   bool use_hw;
 };
@@ -553,7 +553,7 @@ static MlpBwdEpiLayout mlp_bwd_epi_layout(int mode, size_t es, size_t Tk, int d_
   L.second = off;   off += align256(Tk * (size_t)(L.use_hw ? d_expert : d_model) * es);
   L.dh = off;       off += mode == 2 ? align256(Tk * (size_t)d_expert * es) : 0;
   L.dhpre = off;    off += align256(Tk * (size_t)d_h * es);
-  L.gsorted = off;  off += align256(Tk * sizeof(float));
+  L.inv_x = off;    off += align256(Tk * sizeof(int32_t));
   L.dp_part = off;  off += align256(Tk * (size_t)L.part_ld * sizeof(float));
   L.total = off + S2S_TAIL_WS_BYTES;
   return L;
@@ -609,7 +609,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
   size_t need = smoe_mlp_bwd_workspace_bytes(dtype, act, T, k, d_model, d_expert);
   if (need && (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)) return SMOE_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  int rc;
+  int rc = SMOE_OK;
   if (T == 0) {
     DWArgs z1{nullptr, nullptr, dW1, r->expert_offsets, r->E, 0, d_model, d_h};
     rc = launch_dw_plain(s, dtype, z1);
@@ -630,7 +630,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     const MlpBwdEpiLayout L = mlp_bwd_epi_layout(mode, es, (size_t)Tk, d_model, d_expert, d_h);
     char *base = (char *)ws;
     void *dYu = base + L.dybar_u, *second = base + L.second, *dH = base + L.dh, *dHpre = base + L.dhpre;
-    float *gsorted = (float *)(base + L.gsorted), *dp_part = (float *)(base + L.dp_part);
+    float *dp_part = (float *)(base + L.dp_part);
     float *tail_ws = (float *)(base + L.total - S2S_TAIL_WS_BYTES);
     // The W2^T product gathers the rows of dY itself (Alg. 1's scattered input, fan-out k), and groupXTY those of X, and of dY when the
     // weights go into Hw; otherwise it reads a routing-weighted sorted copy of dY.  Where groupXTY cannot gather (sources past 32-bit
@@ -643,38 +643,44 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     DWArgs w2{saved_H, second, dW2, r->expert_offsets, r->E, Tk, d_expert, d_model};
     w1.a_map = tokens;
     const bool rows_x = apart && dw_reads_rows(ctx, w1);
-    if (L.use_hw) {
-      w2.A = second;
-      w2.B = dY;
-      w2.b_map = tokens;
-    }
-    const bool rows_y = L.use_hw && apart && dw_reads_rows(ctx, w2);
-    if (L.use_hw && !rows_y) {
-      w2.B = dYu;
+    // The weighted hidden rows Hw take the place of a weighted copy of dY where they are no wider: the layout has them beside the plain
+    // copy of dY (mode 2), or they lie in the copy's own array when groupXTY gathers dY (mode 1).
+    // Mode 1, 8192 tokens on 64 experts, k = 8, 2048 -> 2 x 512: the product that writes Hw takes 233 us, without it 232, and the copy
+    // of dY was 50 with 5 for the inverse of the order indices; the training step 1545 -> 1481.  The error of dW2 against 64 bits, with
+    // p dY / p H rounded, five layers of 264 to 2048: 2.348e-3 / 2.348e-3 (k = 1), 2.863 to 2.875 / 2.868 to 2.874.
+    w2.B = dY;
+    w2.b_map = tokens;
+    const bool rows_y = d_expert <= d_model && apart && dw_reads_rows(ctx, w2);
+    const bool hw = L.use_hw || rows_y;
+    if (hw) w2.A = second;
+    if (!rows_y) {
+      w2.B = L.use_hw ? dYu : second;
       w2.b_map = RowMap{nullptr, 1};
     }
-    int32_t *inv_y = (int32_t *)dp_part, *inv_x = (int32_t *)gsorted;
-    const bool spread = k > 1;   // the order indices are walked for the sorted weights anyway
+    int32_t *inv_y = (int32_t *)dp_part, *inv_x = k > 1 ? (int32_t *)(base + L.inv_x) : nullptr;
+    // (spread: see the line in plinear_bwd; X's copy has its inverse at no cost)
+    const bool spread_y = k > 1 && (size_t)Tk * d_model >= SPREAD_MIN_ELEMENTS;
     auto sorted_copy = [&](const void *rows, const int32_t *inv, const float *weights, void *out) {
-      return spread ? launch_spread(s, rows, inv, k, weights, out, Tk, d_model)
+      return inv ? launch_spread(s, rows, inv, k, weights, out, Tk, d_model)
                     : launch_group(s, dtype, rows, r->sorted_scattered_idxs, k, weights, out, Tk, d_model);
     };
-    rc = launch_invert(s, r->sorted_scattered_idxs, spread && !rows_y ? inv_y : nullptr, gates, gsorted, Tk);
-    if (rc == SMOE_OK && !rows_y) rc = sorted_copy(dY, inv_y, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
-    if (rc != SMOE_OK) return rc;
+    if (!rows_y) {
+      if (spread_y) rc = launch_invert(s, r->sorted_scattered_idxs, inv_y, Tk);
+      if (rc == SMOE_OK) rc = sorted_copy(dY, spread_y ? inv_y : nullptr, L.use_hw ? nullptr : gates, L.use_hw ? dYu : second);
+      if (rc != SMOE_OK) return rc;
+    }
     S2SArgs x2 = make_s2s(dY, W2, mode == 1 ? dHpre : dH, r, d_expert, d_model, true, false, k, true);
     if (mode == 1) {
       x2.Hpre_in = saved_Hpre;           // dHpre = sigma'(Hpre) p (dYu W2^T) straight from the accumulators
-    } else {
-      x2.H_in = saved_H;                 // dH = p (dYu W2^T), Hw = p H
-      x2.Hw_out = L.use_hw ? second : nullptr;
     }
-    x2.row_scale = gsorted;
+    if (mode == 2 || hw) x2.H_in = saved_H;   // mode 2: dH = p (dYu W2^T); Hw = p H
+    x2.Hw_out = hw ? second : nullptr;
+    x2.row_scale = gates;
     x2.dp_part = dp_part;
     set_launch(ctx, x2);
     rc = launch_s2s_stream(s, x2);
     if (rc != SMOE_OK) return rc;
-    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, spread && !rows_x ? inv_x : nullptr, Tk);
+    rc = launch_dp_reduce(s, dp_part, L.part_ld, r->sorted_scattered_idxs, dgates, rows_x ? nullptr : inv_x, Tk);
     if (rc != SMOE_OK) return rc;
     if (mode == 2) {
       rc = launch_act_bwd(s, act, saved_Hpre, dH, dHpre, Tk, d_expert);
@@ -954,18 +960,18 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   // sorted rows of Ohat that groupXTY needs.  No pass over Yhat, no `group` of Ohat (34 + 14 us at 8192 tokens, k = 4, 4 heads, 2048
   // wide).  The attention's delta = <dOhat, Ohat> is not taken from there: it has to go with dOhat as it is stored.
   const int part_ld = 2 * ceil_div(d_out, 256);
-  float *gsorted = tail_ws, *dp_part = (float *)((char *)tail_ws + align256((size_t)Tk * sizeof(float)));
+  float *dp_part = tail_ws;
   void *dYu = sub, *Ow = (char *)sub + z.yhat;
   S2SArgs xo = make_s2s(dO, W_O, dOhat, r, d_out, d_model, true, false, k, false);
   xo.H_in = saved_Ohat;
   xo.Hw_out = Ow;
-  xo.row_scale = gsorted;
+  xo.row_scale = gates;
   xo.dp_part = dp_part;
   set_launch(ctx, xo);
   const bool in_epilogue = inv && ctx->kernel_mode == 0 && s2s_stream_dp_supported(xo) && output_projection_in_epilogue(ctx, Tk, d_model, d_out) &&
-                           align256((size_t)Tk * sizeof(float)) + (size_t)Tk * part_ld * sizeof(float) <= S2S_TAIL_WS_BYTES;
+                           (size_t)Tk * part_ld * sizeof(float) <= S2S_TAIL_WS_BYTES;
   if (in_epilogue) {
-    rc = launch_invert(s, r->sorted_scattered_idxs, inv, gates, gsorted, Tk);
+    rc = launch_invert(s, r->sorted_scattered_idxs, inv, Tk);
     if (rc != SMOE_OK) return rc;
     rc = launch_s2s_stream(s, xo);
     if (rc != SMOE_OK) return rc;
@@ -984,7 +990,7 @@ int smoe_momha_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *dO
   } else {
     rc = smoe_plinear_bwd(ctx, stream, dtype, dO, saved_Ohat, Tk, d_out, W_O, d_model, saved_Yhat, r, 1, gates, k, 0, 0,
                           dOhat, dW_O, dgates, sub, sub_bytes);
-    if (rc == SMOE_OK && inv) rc = launch_invert(s, r->sorted_scattered_idxs, inv, nullptr, nullptr, Tk);
+    if (rc == SMOE_OK && inv) rc = launch_invert(s, r->sorted_scattered_idxs, inv, Tk);
   }
   if (rc != SMOE_OK) return rc;
   // with the inverse at hand dQ is written in expert-sorted order, as the query projection's gradients read it

@@ -85,8 +85,8 @@ int launch_combine(hipStream_t s, smoe_dtype dt, const void *Yhat, const float *
 // out[i] = g[o[i]] * in[o[i] / fan]; g == nullptr means all ones
 int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o, int fan, const float *g,
                  void *out, int Tk, int d);
-// inv[o[i]] = i and g_sorted[i] = g[o[i]] (inv, and g with g_sorted, may be NULL)
-int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk);
+// inv[o[i]] = i
+int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, int Tk);
 // dg[o[i]] = sum_c part[i, c] (a fixed order; ld is even), and inv[o[i]] = i unless inv is NULL: finishes the routing-weight gradient left in slabs by the fused
 // backward epilogues.
 int launch_dp_reduce(hipStream_t s, const float *part, int ld, const int32_t *o, float *dg, int32_t *inv, int Tk);
@@ -153,11 +153,12 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   // NULL when the pre-activation is not kept.
   void *H;
   // Optional fused SwiGLU backward of Alg. 3 (input-gradient product of the second ParallelLinear, expert-sorted
-  // out, op(W) = W^T, N = d_expert): A holds the UNWEIGHTED upstream rows (gathered through a_map or already
-  // expert-sorted), so the fp32 accumulators are dH / p.  With Hpre_in [Tk, 2N] (the saved pre-activation), row_scale [Tk] (the routing
-  // weight of every sorted row) and dp_part [Tk, 2 * ceil(N / 256)] fp32 set, the epilogue writes
-  // C = dHpre [Tk, 2N] = sigma'(Hpre) * row_scale * acc instead of dH, and per row and 128-column slab the
-  // partial dot <acc, silu(gate) * up> whose sum over the slabs is Alg. 2's dp for that row.
+  // out, op(W) = W^T, N = d_expert): A holds the UNWEIGHTED upstream rows, gathered through a_map, so the fp32 accumulators are
+  // dH / p.  With Hpre_in [Tk, 2N] (the saved pre-activation), row_scale [Tk] (the routing weights in slot order, read through
+  // the same order indices) and dp_part [Tk, 2 * ceil(N / 256)] fp32 set, the epilogue writes
+  // C = dHpre [Tk, 2N] = sigma'(Hpre) * weight * acc instead of dH, and per row and 128-column slab the
+  // partial dot <acc, silu(gate) * up> whose sum over the slabs is Alg. 2's dp for that row; with Hw_out and H_in
+  // [Tk, N] (the saved hidden activations) also Hw = weight * H.
   // Optional [2 * grid] device array: block b leaves the shader-clock cycles and the 100 MHz real-time ticks between its
   // first and last instruction in entries 2b and 2b+1 (measurement aid: the ratio is the clock the block ran at).
   unsigned long long *clock_probe = nullptr;
@@ -165,8 +166,8 @@ struct S2SArgs {      // C[out(i), :] = A[in(i), :] * op(W[e(i)])   for sorted r
   const float *row_scale = nullptr;
   float *dp_part = nullptr;
   // The same idea for any activation (still the W2^T product on unweighted rows): with H_in [Tk, N] (the saved
-  // hidden activations), row_scale and dp_part set and Hpre_in NULL, the epilogue writes C = dH = row_scale * acc, the
-  // slabs of dp = <acc, H>, and, when Hw_out [Tk, N] is given, Hw = row_scale * H (the routing-weighted hidden rows
+  // hidden activations), row_scale and dp_part set and Hpre_in NULL, the epilogue writes C = dH = weight * acc, the
+  // slabs of dp = <acc, H>, and, when Hw_out [Tk, N] is given, Hw = weight * H (the routing-weighted hidden rows
   // that let groupXTY take the unweighted sorted dY for dW2 as well).  The activation's derivative stays a row kernel.
   // With a scattered output (c_map set, Hw_out given) H and dH lie in slot order, the slabs and Hw in expert-sorted order.
   const void *H_in = nullptr;

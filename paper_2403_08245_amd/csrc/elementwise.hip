@@ -194,14 +194,10 @@ __global__ void __launch_bounds__(256) group_kernel(const T *__restrict__ in, co
   }
 }
 
-// ---- inv[o[i]] = i, the sorted position of every slot; with g_sorted, also g_sorted[i] = g[o[i]]  (either may be null)
-__global__ void __launch_bounds__(256) invert_kernel(const int32_t *__restrict__ o, int32_t *__restrict__ inv, const float *__restrict__ g,
-                                                     float *__restrict__ g_sorted, int Tk) {
+// ---- inv[o[i]] = i, the sorted position of every slot
+__global__ void __launch_bounds__(256) invert_kernel(const int32_t *__restrict__ o, int32_t *__restrict__ inv, int Tk) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Tk) return;
-  const int slot = o[i];
-  if (inv) inv[slot] = i;
-  if (g_sorted) g_sorted[i] = g[slot];
+  if (i < Tk) inv[o[i]] = i;
 }
 
 // ---- spread: the copy `group` makes, from the side of the source: out[inv[t * fan + j]] = g[t * fan + j] * in[t].  Bound by the
@@ -360,9 +356,9 @@ int launch_group(hipStream_t s, smoe_dtype dt, const void *in, const int32_t *o,
   return dt == SMOE_BF16 ? group_t<bf16_t>(s, in, o, fan, g, out, Tk, d) : group_t<float>(s, in, o, fan, g, out, Tk, d);
 }
 
-int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, const float *g, float *g_sorted, int Tk) {
+int launch_invert(hipStream_t s, const int32_t *o, int32_t *inv, int Tk) {
   if (Tk < 1) return SMOE_OK;
-  hipLaunchKernelGGL(invert_kernel, dim3(ceil_div(Tk, 256)), dim3(256), 0, s, o, inv, g, g_sorted, Tk);
+  hipLaunchKernelGGL(invert_kernel, dim3(ceil_div(Tk, 256)), dim3(256), 0, s, o, inv, Tk);
   SMOE_LAUNCH_CHECK();
   return SMOE_OK;
 }

@@ -129,7 +129,7 @@ __device__ __forceinline__ void acc_block_to_patch(const f32x16 &a0, const f32x1
 }
 
 // store instructions a wavefront issues per tile, at least (a launch with fp32 partials issues more)
-template <int FM, int ACT> constexpr int EpilogueStores = FM * (ACT == 1 ? 12 : ACT == 2 ? 4 : ACT == 3 || ACT >= 5 ? 16 : 8);
+template <int FM, int ACT> constexpr int EpilogueStores = FM * (ACT == 1 ? 12 : ACT == 2 ? 4 : ACT == 7 ? 24 : ACT == 3 || ACT >= 5 ? 16 : 8);
 
 // dest(fm, half): where rows fm * 32 .. + 31, columns half * 64 .. + 63 of the wavefront's tile go
 template <int FM, typename DestFn>
@@ -185,9 +185,11 @@ __device__ __forceinline__ void store_wave_tile_swiglu(const f32x16 (&acc)[FM][F
 // is a whole tensor instead, whose rows are found through the order indices.
 struct BwdRows {
   window_t saved;       // pre-activations [rows, 2 * n] (SwiGLU) or hidden rows [rows, n]
-  const int *places;    // rows of `saved` that the wavefront's rows lie in (LDS), `left` of them
+  const int *places;    // order indices of the wavefront's rows (LDS; past the `left` rows there are, the last one's again): where their
+                        // routing weights lie, and rows of `saved` in slot order
   int left;
-  window_t scale;       // routing weight of every row
+  window_t scale;       // routing weight of every slot
+  window_t hidden;      // hidden rows [rows, n], where they are read beside the pre-activations
   window_t dp;          // slabs of dp, [rows, part_ld] fp32
   uint32_t saved_bytes; // bytes per row of `saved`
   uint32_t part_bytes;  // bytes per row of the slabs
@@ -200,7 +202,7 @@ __device__ __forceinline__ void put_dp(const BwdRows &b, int fm, float dp, int l
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dp), b.dp, (int)off, 0, 0);
 }
 __device__ __forceinline__ float row_weight(const BwdRows &b, int fm, int lane) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b.scale, (fm * 32 + (lane & 31)) * 4, 0, 0));
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b.scale, b.places[fm * 32 + (lane & 31)] * 4, 0, 0));
 }
 
 // Epilogue of the second ParallelLinear's input-gradient product with the SwiGLU derivative and Alg. 2's dp folded in.
@@ -212,6 +214,16 @@ __device__ __forceinline__ float row_weight(const BwdRows &b, int fm, int lane) 
 //   dgate = dh * up * (sig + silu * (1 - sig)),  dup = dh * silu
 // to the two halves of dHpre through the patch pipeline: dest(fm, half, 0 gate / 1 up).  Columns past the width read
 // whatever lies there and are neither stored nor added to the dot.
+struct RowWeights {
+  float w[4];           // of the rows that a lane holds pieces of where eight lanes hold a row
+};
+__device__ __forceinline__ RowWeights row_weights(const BwdRows &b, int fm, int lane) {
+  RowWeights r;
+#pragma unroll
+  for (int it = 0; it < 4; ++it)
+    r.w[it] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b.scale, b.places[fm * 32 + it * 8 + (lane >> 3)] * 4, 0, 0));
+  return r;
+}
 struct GateUp {
   PatchRows gt, up;
 };
@@ -235,6 +247,13 @@ template <bool PLACES = false> __device__ __forceinline__ PatchRows load_saved_r
     r.v[it] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b.saved, (int)(base + (uint32_t)(it * 8) * b.saved_bytes), 0, 0));
   return r;
 }
+__device__ __forceinline__ PatchRows load_hidden_rows(const BwdRows &b, int fm, int half, int lane) {
+  PatchRows r;
+  const uint32_t row = (uint32_t)b.n * 2u, base = (uint32_t)(fm * 32 + (lane >> 3)) * row + (uint32_t)(b.gcol + half * 64 + (lane & 7) * 8) * 2u;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) r.v[it] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b.hidden, (int)(base + (uint32_t)(it * 8) * row), 0, 0));
+  return r;
+}
 // ... and turned to the accumulators' layout through the patch
 __device__ __forceinline__ void saved_columns(const PatchRows &r, char *patch, int lane, bf16x4 (&v)[2][4]) {
   put_patch_rows(r, patch, lane);
@@ -247,24 +266,36 @@ __device__ __forceinline__ GateUp load_gate_up(const BwdRows &b, int fm, int hal
   const uint32_t col = (uint32_t)(b.gcol + half * 64) * 2u;
   return GateUp{load_saved_rows(b, fm, col, lane), load_saved_rows(b, fm, col + (uint32_t)b.n * 2u, lane)};
 }
-template <bool AHEAD, int FM, typename DestFn>
+// HW: and Hw = p * H to dest_hw(fm, half), from the saved H: a block of it goes from whole rows to whole rows, so it needs no turn
+// through the patch.  (p * h from the fp32 h at hand reads nothing more, but that h comes from gates and ups rounded to bf16: the error of
+// dW2 against 64 bits was 3.45e-3 instead of 2.86e-3.)
+template <bool AHEAD, bool HW, int FM, typename DestFn, typename HwFn>
 __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
-                                                           int lane) {
+                                                           HwFn dest_hw, int lane) {
   acc_settle();
   RowStore<BlockDest> pend;
+  static_assert(AHEAD || !HW, "the hidden rows are requested ahead");
   GateUp in;
+  PatchRows hidden_next;
+  RowWeights weights_next;
   float scale_next = 0.f;
   if (AHEAD) {
     in = load_gate_up(b, 0, 0, lane);
     scale_next = row_weight(b, 0, lane);
+    if (HW) {
+      hidden_next = load_hidden_rows(b, 0, 0, lane);
+      weights_next = row_weights(b, 0, lane);
+    }
   }
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm) {
     float dp = 0.f;
     const float scale = AHEAD ? scale_next : row_weight(b, fm, lane);
+    const RowWeights weights = weights_next;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       if (!AHEAD) flush_row_store(pend);
+      const PatchRows hidden = hidden_next;
       const GateUp rows = AHEAD ? in : load_gate_up(b, fm, half, lane);
       bf16x4 gt[2][4], up[2][4];
       sched_fence();
@@ -274,6 +305,10 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
       if (AHEAD && fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
         in = load_gate_up(b, half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, lane);
         if (half == 1) scale_next = row_weight(b, fm + 1, lane);
+        if (HW) {
+          hidden_next = load_hidden_rows(b, half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, lane);
+          if (half == 1) weights_next = row_weights(b, fm + 1, lane);
+        }
       }
       bf16x4 du[2][4];
       pipe_block(pend, patch, lane, [&] {
@@ -305,6 +340,17 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
 #pragma unroll
           for (int g = 0; g < 4; ++g) patch_put(patch, lane, f2, g, du[f2][g]);
       }, dest(fm, half, 1));
+      if constexpr (HW) {
+        const BlockDest to = dest_hw(fm, half);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          bf16x8 v;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = (bf16_t)(weights.w[it] * (float)hidden.v[it][q]);
+          to.put(it, v);
+        }
+        sched_fence();
+      }
     }
     put_dp(b, fm, dp, lane);
   }

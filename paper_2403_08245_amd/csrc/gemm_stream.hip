@@ -238,7 +238,8 @@ template <typename S, bool TRANS_W, bool KTAIL, bool SWIGLU> struct S2SOps {
 
 // ACT 1: fused SwiGLU keeping the pre-activation, 2: without, 3: fused SwiGLU derivative and dp (the W2^T input-gradient
 // product of Alg. 3's backward, see store_wave_tile_swiglu_bwd), 4: dp from the saved H in that product's epilogue for any
-// activation (store_wave_tile_dp), 5: 4 with the routing-weighted hidden rows written as well, 6: 5 with H and dH in slot order.
+// activation (store_wave_tile_dp), 5: 4 with the routing-weighted hidden rows written as well, 6: 5 with H and dH in slot order, 7: 3 with the routing-weighted hidden
+// rows written as well.
 // STATIC2 (Big only): the contraction is an even number of whole stages, so every tile starts in LDS slot 0 and the loop is written
 // out two stages at a time with the slot as a compile-time constant: all LDS addresses become a loop-invariant register plus an
 // immediate.  Without it the contraction may be any multiple of 8 (KTAIL masks the last stage).
@@ -246,6 +247,7 @@ template <typename S, bool TRANS_W, bool KTAIL, bool SWIGLU> struct S2SOps {
 template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC2, bool WIDE>
 __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int tiles_n, int group_m, uint32_t magic_a) {
   constexpr bool SWIGLU = ACT == 1 || ACT == 2;
+  constexpr bool GATE_UP = ACT == 3 || ACT == 7;
   constexpr bool KTAIL = !STATIC2;
   constexpr bool DENSE_PAIR = ACT == 0 && !SCATTER_OUT;   // S2SArgs::C2 may be set
   constexpr int STORES = EpilogueStores<S::FM, ACT>;
@@ -514,34 +516,33 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
           acc, patch, [&](int fm, int half) { return sorted_block(win_p, N, fm, half * half_n + gcol, half_n - gcol); },
           [&](int fm) { return sorted_block(win_h, half_n, fm, gcol, half_n - gcol); }, lane);
     } else if constexpr (ACT >= 3) {
-      const int gcol = ct.n0 + uwn * (TB / 2), ldc = ACT == 3 ? 2 * N : N;
+      const int gcol = ct.n0 + uwn * (TB / 2), ldc = GATE_UP ? 2 * N : N;
       const uint32_t slot_bytes = (uint32_t)p->Tk * (uint32_t)N * 2u;                 // ACT 6: of dH and of H
       const window_t win_c = ACT == 6 ? make_window(p->C, slot_bytes) : sorted_window(p->C, ldc, 2);
       BwdRows b;
-      b.saved = ACT == 6 ? make_window(p->H_in, slot_bytes) : sorted_window(ACT == 3 ? p->Hpre_in : p->H_in, ldc, 2);
+      b.saved = ACT == 6 ? make_window(p->H_in, slot_bytes) : sorted_window(GATE_UP ? p->Hpre_in : p->H_in, ldc, 2);
       b.places = &s_idx[ct.seq & 3][uwm * (S::TM / 2)];
       b.left = left;
       b.saved_bytes = (uint32_t)ldc * 2u;
-      b.scale = sorted_window(p->row_scale, 1, 4);
+      if (ACT == 7) b.hidden = sorted_window(p->H_in, N, 2);
+      b.scale = make_window(p->row_scale, (uint32_t)p->Tk * 4u);
       b.dp = sorted_window(p->dp_part, 2 * tiles_n, 4);
       b.part_bytes = (uint32_t)tiles_n * 8u;
       b.part_col = (uint32_t)(ct.n0 / TB) * 2u + uwn;
       b.n = N;
       b.gcol = gcol;
-      if constexpr (ACT == 3) {
-        store_wave_tile_swiglu_bwd<true>(
+      const window_t win_w = ACT >= 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
+      auto dest_hw = [&](int fm, int half) { return sorted_block(win_w, N, fm, gcol + half * 64, N - gcol - half * 64); };
+      if constexpr (GATE_UP) {
+        store_wave_tile_swiglu_bwd<true, ACT == 7>(
             acc, patch, b,
-            [&](int fm, int half, int up) { return sorted_block(win_c, ldc, fm, up * N + gcol + half * 64, N - gcol - half * 64); }, lane);
+            [&](int fm, int half, int up) { return sorted_block(win_c, ldc, fm, up * N + gcol + half * 64, N - gcol - half * 64); }, dest_hw, lane);
       } else {
-        const window_t win_w = ACT >= 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
         auto dest = [&](int fm, int half) {
           if constexpr (ACT == 6) return slot_block(win_c, N, b.places, left, fm, gcol + half * 64);
           else return sorted_block(win_c, ldc, fm, gcol + half * 64, N - gcol - half * 64);
         };
-        store_wave_tile_dp<true, ACT >= 5, ACT == 6>(
-            acc, patch, b, dest,
-            [&](int fm, int half) { return sorted_block(win_w, N, fm, gcol + half * 64, N - gcol - half * 64); },
-            lane);
+        store_wave_tile_dp<true, ACT >= 5, ACT == 6>(acc, patch, b, dest, dest_hw, lane);
       }
     } else {
       const int wcol = ct.n0 + uwn * (TB / 2);
@@ -1094,12 +1095,12 @@ bool s2s_stream_supported(const S2SArgs &a) {
          (w_rows + SK) * a.ldw * 2 < 0x100000000LL && (long long)TB * a.N * 4 < 0x80000000LL;
 }
 bool s2s_stream_swiglu_bwd_supported(const S2SArgs &a) {
-  return s2s_stream_supported(a) && a.trans_w && !a.c_map.o && a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
+  return s2s_stream_supported(a) && a.trans_w && a.a_map.o && !a.c_map.o && a.Hpre_in && (!a.Hw_out || a.H_in) && a.row_scale && a.dp_part && a.N % 8 == 0;
 }
 
 bool s2s_stream_dp_supported(const S2SArgs &a) {
   const bool slots_fit = !a.c_map.o || (a.Hw_out && (long long)a.Tk * a.N * 2 <= 0xfffffff0LL);   // ACT 6: 32-bit offsets of slot rows
-  return s2s_stream_supported(a) && a.trans_w && slots_fit && a.H_in && !a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
+  return s2s_stream_supported(a) && a.trans_w && a.a_map.o && slots_fit && a.H_in && !a.Hpre_in && a.row_scale && a.dp_part && a.N % 8 == 0;
 }
 
 bool s2s_stream_swiglu_supported(const S2SArgs &a) {
@@ -1110,7 +1111,7 @@ int launch_s2s_stream(hipStream_t s, const S2SArgs &a) {
   const bool scatter_out = a.c_map.o != nullptr;
   if (a.dp_part && a.Hpre_in) {
     if (!s2s_stream_swiglu_bwd_supported(a)) return SMOE_ERR_UNSUPPORTED;
-    return launch_s2s_cfg<true, false, 3>(s, a);
+    return a.Hw_out ? launch_s2s_cfg<true, false, 7>(s, a) : launch_s2s_cfg<true, false, 3>(s, a);
   }
   if (a.dp_part) {
     if (!s2s_stream_dp_supported(a)) return SMOE_ERR_UNSUPPORTED;
@@ -1180,6 +1181,7 @@ int init_stream_kernels() {
   if (rc == SMOE_OK) rc = init_s2s<true, false, 4>();
   if (rc == SMOE_OK) rc = init_s2s<true, false, 5>();
   if (rc == SMOE_OK) rc = init_s2s<true, true, 6>();
+  if (rc == SMOE_OK) rc = init_s2s<true, false, 7>();
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_ONE>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_A>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(dw_stream_kernel<DW_B>, Big::LDS_BYTES);

@@ -69,3 +69,56 @@ def test_outputs_over_the_rows(over, monkeypatch):
     dX, dW, _ = smoe.plinear_bwd(args[0], args[1], W, None, r, 1)
     _same(dX, dX_want, "dX, " + over)
     _same(dW, dW_want, "dW, " + over)
+
+
+def _mlp(T, d_model, d_expert, E, k, seed):
+    import oracle
+    import paper_2403_08245_amd as smoe
+    import smoe_inputs as si
+    from helpers import oracle_gates_f32, oracle_routing
+    cfg = si.custom("weighted-hidden", T=T, d_model=d_model, d_expert=d_expert, E=E, k=k, act=si.ACT_SWIGLU, dtype="bf16", masked_experts=1)
+    case = si.mlp_case(cfg, seed)
+    ei, g, _, _, _ = oracle_routing(case["logits"], k, E)
+    print("weighted hidden rows", T, d_model, d_expert, E, k, np.bincount(ei.ravel(), minlength=E).tolist(), flush=True)
+    gi, gg = smoe.topk_gate(case["logits"].cuda(), k)
+    assert np.array_equal(gi.cpu().numpy(), ei)
+    X, W1, W2, dY = (case[n].cuda() for n in ("X", "W1", "W2", "dY"))
+    r = smoe.route(gi, E)
+    _, buf = smoe.mlp_fwd(X, W1, W2, r, k, gg, si.ACT_SWIGLU)
+    assert buf.Yhat is None          # the persistent kernels take these widths
+    ref = oracle.mlp_bwd(si.as_f64(case["dY"]), *[si.as_f64(case[n]) for n in ("X", "W1", "W2")], ei, oracle_gates_f32(g), si.ACT_SWIGLU)
+    return smoe, si, r, gg, X, W1, W2, dY, buf, ref
+
+
+def _check(smoe, si, got, ref):
+    from helpers import assert_close
+    for t, nm in zip(got, ("dX", "dW1", "dW2", "dgates")):
+        assert_close(t, ref[nm], torch.bfloat16, nm)
+
+
+@pytest.mark.parametrize("mode", [3, 4], ids=["tiles128", "tiles256"])
+@pytest.mark.parametrize("T,d_model,d_expert,E,k", [(300, 264, 264, 5, 1), (131, 520, 136, 4, 2), (90, 1032, 776, 3, 3)])
+def test_swiglu_weighted_hidden_rows(mode, T, d_model, d_expert, E, k):
+    """dW2 from routing-weighted hidden rows that the fused SwiGLU derivative leaves, where they are no wider than the model."""
+    smoe, si, r, gg, X, W1, W2, dY, buf, ref = _mlp(T, d_model, d_expert, E, k, 61)
+    smoe.set_kernel_mode(mode)
+    try:
+        got = smoe.mlp_bwd(dY, X, W1, W2, r, k, gg, si.ACT_SWIGLU, buf)
+    finally:
+        smoe.set_kernel_mode(0)
+    _check(smoe, si, got, ref)
+
+
+@pytest.mark.parametrize("over", ["dW1", "dW2"])
+@pytest.mark.parametrize("rows", ["X", "dY"])
+def test_weight_gradient_over_the_rows(over, rows):
+    if over == "dW2" and rows == "X":
+        pytest.skip("X is read for dW1 after dW2 is written")
+    smoe, si, r, gg, X, W1, W2, dY, buf, ref = _mlp(131, 264, 136, 4, 2, 62)
+    mem = torch.empty_like(getattr(buf, over))
+    src = X if rows == "X" else dY
+    place = mem.view(-1)[:src.numel()].view_as(src)
+    place.copy_(src)
+    setattr(buf, over, mem)
+    got = smoe.mlp_bwd(dY if rows == "X" else place, place if rows == "X" else X, W1, W2, r, 2, gg, si.ACT_SWIGLU, buf)
+    _check(smoe, si, got, ref)
