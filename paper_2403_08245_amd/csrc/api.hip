@@ -693,6 +693,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     DWArgs both = w2;
     both.A3 = rows_x ? X : tail_ws;
     both.a3_map = rows_x ? tokens : RowMap{nullptr, 1};
+    both.order = r->sorted_scattered_idxs;
     both.B3 = dHpre;
     both.dW3 = dW1;
     both.M3 = d_model;

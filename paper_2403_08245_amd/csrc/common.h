@@ -200,6 +200,8 @@ struct DWArgs {       // dW[e] = sum_{i in segment e} A[i, :]^T B[i, :]   (rows 
   // Persistent and fp32 kernels: rows of A, B and A3 read through the order indices (the same in all of them) instead of from
   // sorted copies.  Persistent kernel: not A beside dW3, nothing beside dW2.
   RowMap a_map{nullptr, 1}, b_map{nullptr, 1}, a3_map{nullptr, 1};
+  // The order indices, needed with dW3: that launch fetches them whichever of its operands it reads through them, and also for none.
+  const int32_t *order = nullptr;
   // fp32 kernels: B's rows scaled by the routing weights (fp32, slot order; needs b_map).
   const float *gates = nullptr;
 };

@@ -787,7 +787,7 @@ template <int KIND> __global__ void __launch_bounds__(NTHREADS, 1) dw_stream_ker
     c.sb = through_b ? 0u : SK * row_b;
     if (!through_a) c.pa += (size_t)lo * row_a;
     if (!through_b) c.pb += (size_t)lo * row_b;
-    if (ROWS) c.po = (a.b_map.o ? a.b_map.o : KIND == DW_TWO ? a.a3_map.o : a.a_map.o) + lo;   // every map has the same order indices
+    if (ROWS) c.po = (KIND == DW_TWO ? a.order : KIND == DW_A ? a.a_map.o : a.b_map.o) + lo;   // every map has the same order indices
     *reinterpret_cast<int4 *>(s_tile[wave][seq & 3]) = make_int4(c.e | (c.further ? FURTHER : 0), c.m0, c.n0, c.ns);
   };
   auto follow = [&](DWTile &t, int seq) -> bool {
@@ -1138,7 +1138,9 @@ bool dw_stream_supported(const DWArgs &a) {
   return a.M % 8 == 0 && a.N % 8 == 0 && a.M3 % 8 == 0 && a.N3 % 8 == 0 && a.Tk > 0 && a.E <= MAX_E && tiles + MAX_STREAM_GRID < 0x7fffffffLL && a.grid >= 8 &&
          a.grid % 8 == 0 && a.grid <= MAX_STREAM_GRID && (long long)TB * a.N * 2 < 0x80000000LL && (long long)TB * a.N3 * 2 < 0x80000000LL &&
          rows_readable(a.a_map, a.Tk, a.M) && rows_readable(a.b_map, a.Tk, a.N) && rows_readable(a.a3_map, a.Tk, a.M3) &&
-         !(a.dW3 && a.a_map.o) && !(a.dW2 && (a.a_map.o || a.b_map.o));
+         !(a.dW2 && (a.a_map.o || a.b_map.o)) &&
+         // beside dW3 the order indices are fetched for every stage, from `order`, also where both operands lie sorted
+         (!a.dW3 || (a.order && !a.a_map.o && (!a.b_map.o || a.b_map.o == a.order) && (!a.a3_map.o || a.a3_map.o == a.order)));
 }
 
 // Together two weight gradients save the rounds that their last tiles fill only in part, and a launch, while a stage costs 3 % more
