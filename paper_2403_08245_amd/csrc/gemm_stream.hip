@@ -18,7 +18,8 @@
 // Two shapes (Shape below), one block per compute unit, one wavefront per SIMD:
 //   Big   256 x 256 tiles, two slots of 64 KB, 256 accumulators: the fewest operand bytes per multiply-add.
 //   Half  128 x 256 tiles, three slots of 48 KB, 128 accumulators: half as many rows per tile waste fewer rows at segment ends and
-//         leave less work over when the tiles do not fill a last round; the price is 1.5 times the operand traffic.
+//         leave less work over when the tiles do not fill a last round; the price is 1.5 times the operand traffic.  HalfShort has two
+//         slots, for the short launches that launch_s2s_cfg names.
 // Measured, stages of 32 elements (there with two blocks per compute unit for the 128 x 256 tiles) / these, in us: W^T products of
 // 32768 rows, 28672 -> 4096: 6420 / 5800; 65536 rows in 64 experts, 1024 -> 2048: 306 / 287; 8192 rows in 8 experts, 5632 -> 1024:
 // 120 / 106; 6002 rows, 6832 -> 1280 (rows of W that start off the lines): 200 / 120.  W as stored, where only the rows of X gain:
@@ -61,6 +62,8 @@ template <int FM_, int SLOTS_, bool ONCE_ = false> struct Shape {
 using Big = Shape<4, 2>;
 using Half = Shape<2, 3>;
 using HalfOnce = Shape<2, 3, true>;
+using HalfShort = Shape<2, 2>;
+using HalfShortOnce = Shape<2, 2, true>;
 constexpr int MAX_STREAM_GRID = 256;                    // compute units used; the partial-tile scratch holds this many big tiles
 
 template <typename S> struct Frags {                    // one wavefront's fragments for 16 contraction elements
@@ -210,9 +213,10 @@ template <typename S, bool TRANS_W, bool KTAIL, bool SWIGLU> struct S2SOps {
   int step, last;                    // stage the next loads fetch; the contraction's last stage
   int uwave;
   int again;                         // S::ONCE: above 0 where the expert has further tiles, which read the same weights
-  // The order of a stage's load instructions: A and W in turn; with SwiGLU, whose tiles take W's columns from two places, A first.
+  // The order of a stage's load instructions: A and W in turn; with SwiGLU, whose tiles take W's columns from two places, A first (not
+  // in HalfShort, whose launches wait for W: 16 experts of 62 rows, 4096 -> 2 x 512, 61 -> 59.5 us).
   __device__ static constexpr int nth(int i) {
-    if (SWIGLU) return i;
+    if (SWIGLU && (S::NLA == S::NLB || S::SLOTS > 2)) return i;
     if (S::NLA == S::NLB) return i & 1 ? S::NLA + i / 2 : i / 2;
     return i % 3 ? S::NLA + i / 3 * 2 + i % 3 - 1 : i / 3;
   }
@@ -1003,11 +1007,14 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC2, boo
 //   6832 -> 1280 W^T 188 / 123;  2 x 8192 rows: 2048 -> 512 54 / 34;  32768 rows, 16 experts: 2048 -> 512 92 / 88, 512 -> 2048 84 / 91;
 //   65536 rows, 64 experts: 2048 -> 2 x 512 with SwiGLU 268 / 308, 512 -> 2048 152 / 183, 1024 -> 2048 W^T 287 / 325;
 //   262144 rows, 64 experts: 4096 -> 512 930 / 1060;  32768 rows, 8 experts: 14336 -> 4096 3020 / 3530.
-template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static2, bool may_split) {
+template <typename S> long long estimated_tiles(const S2SArgs &a, int tiles_n) {
   const float rows = (float)a.Tk / a.E;
-  const int ns = ceil_div(a.K, SK), G = a.grid;
   const float m_tiles = a.E == 1 || a.C2 ? (float)a.E * ceil_div(a.Tk / a.E, S::TM) : (rows >= S::TM ? rows / S::TM + 0.5f : 1.0f) * (a.Tk < a.E ? a.Tk : a.E);
-  const long long total = (long long)(m_tiles * tiles_n + 0.5f);
+  return (long long)(m_tiles * tiles_n + 0.5f);
+}
+template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static2, bool may_split) {
+  const int ns = ceil_div(a.K, SK), G = a.grid;
+  const long long total = estimated_tiles<S>(a, tiles_n);
   const float full = S::FM > 2 ? 1.5f * ns + 6.f : 0.9f * ns + 4.f;
   const int rest = (int)(total % G);
   float t = (total / G) * full;
@@ -1040,9 +1047,20 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
       // reuse they belong there (8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156), so a tile of an expert that has
       // several takes them the ordinary way (777 tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass
       // 133 us with all of W past the caches, 129 with none, 125 so).
-      if constexpr (!TRANS_W)
-        if ((long long)a.Tk <= (long long)a.E * Half::TM && weights_pass_caches(a))
-          return launch_s2s_one<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+      if constexpr (!TRANS_W) {
+        const bool once = (long long)a.Tk <= (long long)a.E * Half::TM && weights_pass_caches(a);
+        // HalfShort: launches of one round, and contractions of up to four stages.  A block that has one tile waits for W at every stage, and
+        // three slots of requests (rows of W at a stride that is a power of two fall on few cache sets) make it wait longer than two;
+        // over several rounds of longer contractions the third slot keeps the matrix cores fed.  Two / three slots in us: 16 experts of 62
+        // rows, 1024 -> 2 x 512 with SwiGLU 20.4 / 22.0, 2048 -> 2 x 512 33.6 / 35.5, of 50 rows, 4096 -> 2 x 1024 61.5 / 66.0; 16 experts of
+        // 256 rows, 128 -> 2048 11.7 / 12.7; 16 experts of 1024 rows, 128 -> 5632 54 / 57, 1024 -> 5632 199 / 203, 2048 -> 2 x 2816 405 / 389,
+        // 4096 -> 2 x 2816 796 / 750.
+        if (a.K <= 4 * SK || estimated_tiles<Half>(a, tiles_n) <= a.grid) {
+          if (once) return launch_s2s_one<HalfShortOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+          return launch_s2s_one<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+        }
+        if (once) return launch_s2s_one<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+      }
       return launch_s2s_one<Half, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
     }
   }
@@ -1164,8 +1182,11 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s() {
   if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, false>, Big::LDS_BYTES);
   if constexpr (ACT != 6)
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Half, TRANS_W, SCATTER_OUT, ACT, false, false>, Half::LDS_BYTES);
-  if constexpr (!TRANS_W)
-    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, Half::LDS_BYTES);
+  if constexpr (!TRANS_W) {
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, HalfOnce::LDS_BYTES);
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>, HalfShort::LDS_BYTES);
+    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfShortOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, HalfShortOnce::LDS_BYTES);
+  }
   if constexpr (SCATTER_OUT && ACT == 0) {
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, true>, Big::LDS_BYTES);
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, true>, Big::LDS_BYTES);
