@@ -1049,13 +1049,16 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
       // 133 us with all of W past the caches, 129 with none, 125 so).
       if constexpr (!TRANS_W) {
         const bool once = (long long)a.Tk <= (long long)a.E * Half::TM && weights_pass_caches(a);
-        // HalfShort: launches of one round, and contractions of up to four stages.  A block that has one tile waits for W at every stage, and
-        // three slots of requests (rows of W at a stride that is a power of two fall on few cache sets) make it wait longer than two;
-        // over several rounds of longer contractions the third slot keeps the matrix cores fed.  Two / three slots in us: 16 experts of 62
-        // rows, 1024 -> 2 x 512 with SwiGLU 20.4 / 22.0, 2048 -> 2 x 512 33.6 / 35.5, of 50 rows, 4096 -> 2 x 1024 61.5 / 66.0; 16 experts of
-        // 256 rows, 128 -> 2048 11.7 / 12.7; 16 experts of 1024 rows, 128 -> 5632 54 / 57, 1024 -> 5632 199 / 203, 2048 -> 2 x 2816 405 / 389,
-        // 4096 -> 2 x 2816 796 / 750.
-        if (a.K <= 4 * SK || estimated_tiles<Half>(a, tiles_n) <= a.grid) {
+        // HalfShort: contractions of up to four stages, and launches of one round whose contraction is up to eight or which read most of W
+        // once by rows at a stride of whole kilobytes.  Few stages are over before a third slot's requests come in; and a block with a
+        // single tile waits for W at every stage, where requests for many rows that fall on few cache sets wait for one another (the
+        // more so with SwiGLU, which reads each row in two places).  Two / three slots in us, W from memory (from the last-level cache), 16
+        // experts of 62 rows, SwiGLU: 512 -> 2 x 512 15.2 / 15.7, 2048 -> 2 x 512 39.6 / 40.8 (33.6 / 35.5), 4096 -> 2 x 512 69.5 / 71.6 (59.5 / 63.3);
+        // 37 experts of 60 rows, 3840 -> 512 61.9 / 63.6, 64 of 97 rows, 2048 -> 1024 54.5 / 55.6; 16 experts of 256 rows, 128 -> 2048 11.7 / 12.7.
+        // Elsewhere the third slot is worth more: other strides, 16 of 62 rows, 2048 -> 2 x 448 37.1 / 34.5; W read several times, 4 of 292 rows,
+        // 2688 -> 2048 43.7 / 41.2; several rounds, 16 of 1024 rows, 4096 -> 2 x 2816 796 / 750.
+        const bool one_round = estimated_tiles<Half>(a, tiles_n) <= a.grid, apart = a.ldw % 512 == 0 && (long long)a.Tk <= (long long)a.E * Half::TM;
+        if (a.K <= 4 * SK || (one_round && (a.K <= 8 * SK || apart))) {
           if (once) return launch_s2s_one<HalfShortOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
           return launch_s2s_one<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
         }

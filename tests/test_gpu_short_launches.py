@@ -1,5 +1,5 @@
-"""Forward products on 128 x 256 tiles, with two stages of operands in flight (one round of tiles, or contractions of up to four stages of
-64) and with three: the same bits as on the 256 x 256 tiles, whose sums run in the same order.  Contractions of two stages and a few
+"""Forward products on 128 x 256 tiles, with two stages of operands in flight (contractions of up to four stages of 64, or one round of tiles
+with up to eight stages or rows of W at a stride of whole kilobytes) and with three: the same bits as on the 256 x 256 tiles, whose sums run in the same order.  Contractions of two stages and a few
 elements up to several stages and a remainder, widths that end inside a tile, experts without rows, with one row, with a whole tile and a
 row; one round, several; W read through the caches and, where a call's weights exceed them, past them."""
 import numpy as np
@@ -46,8 +46,8 @@ def _compare(smoe, loads, k, d_in, width, seed, swiglu=True):
 LOADS = [0, 1, 129, 64, 127, 128, 200, 3, 257, 31]
 
 
-@pytest.mark.parametrize("d_in", [72, 128, 192, 200, 256, 264, 456, 512])
-@pytest.mark.parametrize("width", [272, 1040])
+@pytest.mark.parametrize("d_in,width", [(d, w) for d in (72, 128, 192, 200, 256, 264, 456, 512) for w in (272, 1040)] +
+                         [(520, 1040), (520, 1024), (776, 512), (1032, 1536)])
 def test_one_round(d_in, width):
     import paper_2403_08245_amd as smoe
     assert torch.cuda.is_available(), "these tests need the MI355X"
@@ -72,8 +72,9 @@ def test_weights_past_the_caches(E, d_in, width, rows):
     _compare(smoe, loads, 1, d_in, width, E)
 
 
-def test_weights_past_the_caches_in_one_round():
+@pytest.mark.parametrize("width", [2048, 2064])
+def test_weights_past_the_caches_in_one_round(width):
     import paper_2403_08245_amd as smoe
     loads = [0, 130] + [60] * 14 + [50]
-    assert 17 * 4104 * 2064 * 2 > 256 << 20 and 17 * -(-2064 // COLS) <= GRID and sum(loads) <= ROWS * 17
-    _compare(smoe, loads, 1, 4104, 2064, 8)
+    assert 17 * 4104 * width * 2 > 256 << 20 and 17 * -(-width // COLS) <= GRID and sum(loads) <= ROWS * 17
+    _compare(smoe, loads, 1, 4104, width, 8)
