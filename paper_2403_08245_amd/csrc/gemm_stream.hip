@@ -1007,14 +1007,19 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC2, boo
 //   6832 -> 1280 W^T 188 / 123;  2 x 8192 rows: 2048 -> 512 54 / 34;  32768 rows, 16 experts: 2048 -> 512 92 / 88, 512 -> 2048 84 / 91;
 //   65536 rows, 64 experts: 2048 -> 2 x 512 with SwiGLU 268 / 308, 512 -> 2048 152 / 183, 1024 -> 2048 W^T 287 / 325;
 //   262144 rows, 64 experts: 4096 -> 512 930 / 1060;  32768 rows, 8 experts: 14336 -> 4096 3020 / 3530.
-template <typename S> long long estimated_tiles(const S2SArgs &a, int tiles_n) {
+// Even loads make the next whole number of tiles instead, which a long contraction that stands at the end of a round pays dearly for:
+// contractions over 2048 take Half only where the mean over both counts says so too.  2937 tokens on 37 experts, k = 6, 7808 -> 720: 262 big
+// tiles by the first count, a round and a bit, 222 by the second; Big 232, Half 283.  Whole forward passes with / without that: this
+// one 589 / 641, 3150 tokens on 31 experts, k = 4, 2496 -> 6336, 1298 / 1369, 794 on 48, k = 8, 3840 -> 2 x 1216, 335 / 352, the worst (1046 on 11,
+// k = 8, 2112 -> 2944, forward and backward) 1139 / 1127.  Under 2048 the mean lost as often as it won.
+template <typename S> long long estimated_tiles(const S2SArgs &a, int tiles_n, bool even = false) {
   const float rows = (float)a.Tk / a.E;
-  const float m_tiles = a.E == 1 || a.C2 ? (float)a.E * ceil_div(a.Tk / a.E, S::TM) : (rows >= S::TM ? rows / S::TM + 0.5f : 1.0f) * (a.Tk < a.E ? a.Tk : a.E);
-  return (long long)(m_tiles * tiles_n + 0.5f);
+  const float m_tiles = even || a.E == 1 || a.C2 ? (float)ceil_div(ceil_div(a.Tk, a.E), S::TM) : rows >= S::TM ? rows / S::TM + 0.5f : 1.0f;
+  return (long long)(m_tiles * (a.Tk < a.E ? a.Tk : a.E) * tiles_n + 0.5f);
 }
-template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static2, bool may_split) {
+template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool static2, bool may_split, bool even) {
   const int ns = ceil_div(a.K, SK), G = a.grid;
-  const long long total = estimated_tiles<S>(a, tiles_n);
+  const long long total = estimated_tiles<S>(a, tiles_n, even);
   const float full = S::FM > 2 ? 1.5f * ns + 6.f : 0.9f * ns + 4.f;
   const int rest = (int)(total % G);
   float t = (total / G) * full;
@@ -1027,7 +1032,10 @@ template <typename S> float launch_estimate(const S2SArgs &a, int tiles_n, bool 
   return t;
 }
 bool prefer_half(const S2SArgs &a, int tiles_n, bool may_split) {
-  return launch_estimate<Half>(a, tiles_n, false, may_split) < 0.95f * launch_estimate<Big>(a, tiles_n, a.K % (2 * SK) == 0, may_split);
+  const bool static2 = a.K % (2 * SK) == 0;
+  const float half = launch_estimate<Half>(a, tiles_n, false, may_split, false), big = launch_estimate<Big>(a, tiles_n, static2, may_split, false);
+  if (half >= 0.95f * big || a.K <= 2048) return half < 0.95f * big;
+  return half + launch_estimate<Half>(a, tiles_n, false, may_split, true) < 0.95f * (big + launch_estimate<Big>(a, tiles_n, static2, may_split, true));
 }
 template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStream_t s, const S2SArgs &a) {
   const bool static2 = a.K % (2 * SK) == 0;
