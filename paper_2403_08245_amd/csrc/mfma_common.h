@@ -26,14 +26,16 @@ constexpr int FR = TB / 64;       // 32x32 fragments per wavefront along each ti
 // destination (a byte address in M0) is wave-uniform; lane L's data lands at lds_addr +
 // 16 * L (4 * L).  Written as inline assembly so that the waits are placed by hand: several
 // stages stay in flight while another one is read, ordered only by `wait_loads` + barrier.
+// A load to LDS needs one wait state behind a scalar write of M0; the compiler, which puts one into its own code, does not look into
+// inline assembly.  It costs nothing (12 workloads: 1.001 times the speed).
 __device__ __forceinline__ void load16_to_lds(const void *gsrc, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");
 }
 // Same with the address split into a wave-uniform 64-bit base (scalar registers) and a 32-bit
 // per-lane byte offset: half the address registers go to the memory pipeline per instruction,
 // which shortens the issue of the load inside a matrix-instruction stream.
 __device__ __forceinline__ void load16_to_lds(const void *base, uint32_t byte_off, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(byte_off), "s"(base)
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(byte_off), "s"(base)
                    : "memory", "m0");
 }
 // Range-checked form: a raw buffer descriptor (base address, byte count) in four scalar registers and a
@@ -55,7 +57,7 @@ __device__ __forceinline__ int32x4 scalar_window(const void *base, uint32_t byte
   return int32x4{(int)(uint32_t)p, (int)(uint32_t)((p >> 32) & 0xffffu), (int)bytes, 0x00020000};
 }
 __device__ __forceinline__ void load16_to_lds_checked(int32x4 window, uint32_t byte_off, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window)
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window)
                    : "memory", "m0");
 }
 // The same with a wave-uniform choice: bytes that nothing will read again (`again` 0 or less) are kept by no cache.
@@ -65,10 +67,10 @@ __device__ __forceinline__ void load16_to_lds_checked_or_once(int32x4 window, ui
                    : "memory", "m0", "scc");
 }
 __device__ __forceinline__ void load4_to_lds(const void *gsrc, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory", "m0");
 }
 __device__ __forceinline__ void load4_to_lds_checked(int32x4 window, uint32_t byte_off, uint32_t lds_addr) {
-  __asm__ volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window) : "memory", "m0");
+  __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(byte_off), "s"(window) : "memory", "m0");
 }
 // Waits until at most N of this wavefront's global loads are outstanding (they finish in order).
 template <int N> __device__ __forceinline__ void wait_loads() {
