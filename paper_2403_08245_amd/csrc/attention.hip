@@ -478,7 +478,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_kernel(const bf16_t *__res
 //   S = Q K^T, P = exp2(S c - lse[row]), dV^T += dO^T P, dP = dO V^T - delta[row],
 //   dS = P dP / sqrt(d), dK^T += Q^T dS
 // ======================================================================================
-template <int NW, bool DK, bool DV>
+template <int NW>
 __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                            const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                            const float *__restrict__ LSE, const float *__restrict__ minus_delta,
@@ -611,12 +611,10 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
     f32x16 s, dp;
 #pragma unroll
     for (int q = 0; q < 16; ++q) s[q] = 0.f;
-    if (DK) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 d4 = *reinterpret_cast<const float4 *>(&s_dlt[j & 1][8 * g + 4 * (lane >> 5)]);
-        dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
-      }
+    for (int g = 0; g < 4; ++g) {
+      const float4 d4 = *reinterpret_cast<const float4 *>(&s_dlt[j & 1][8 * g + 4 * (lane >> 5)]);
+      dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
     }
     bf16x8 qr[DKV_AHEAD], dr[DKV_AHEAD], vr[DKV_AHEAD];
 #pragma unroll
@@ -649,7 +647,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
         const int q = 4 * g + c;
         const float pv = __builtin_amdgcn_exp2f(fmaf(s[q], d.scale_log2, lv[c] * -1.4426950408889634f));
         p[q] = pv;
-        if (DK) s[q] = pv * dp[q] * scale;
+        s[q] = pv * dp[q] * scale;
       }
     }
     // rows of this tile that are earlier than the wavefront's last key, or past the end, are masked (wave-uniform): the key
@@ -693,8 +691,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int col = f * 32 + 8 * g + 4 * (lane >> 5);
-        if (DK) *reinterpret_cast<float4 *>(pk + col) = make_float4(acck[f][4 * g], acck[f][4 * g + 1], acck[f][4 * g + 2], acck[f][4 * g + 3]);
-        if (DV) *reinterpret_cast<float4 *>(pv + col) = make_float4(accv[f][4 * g], accv[f][4 * g + 1], accv[f][4 * g + 2], accv[f][4 * g + 3]);
+        *reinterpret_cast<float4 *>(pk + col) = make_float4(acck[f][4 * g], acck[f][4 * g + 1], acck[f][4 * g + 2], acck[f][4 * g + 3]);
+        *reinterpret_cast<float4 *>(pv + col) = make_float4(accv[f][4 * g], accv[f][4 * g + 1], accv[f][4 * g + 2], accv[f][4 * g + 3]);
       }
   } else if (key_valid) {
 #pragma unroll
@@ -704,8 +702,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_kernel(const bf16_t *
         bf16x4 vk, vv;
 #pragma unroll
         for (int c = 0; c < 4; ++c) { vk[c] = (bf16_t)acck[f][4 * g + c]; vv[c] = (bf16_t)accv[f][4 * g + c]; }
-        if (DK) *reinterpret_cast<bf16x4 *>(dK + krow + f * 32 + 8 * g + 4 * (lane >> 5)) = vk;
-        if (DV) *reinterpret_cast<bf16x4 *>(dV + krow + f * 32 + 8 * g + 4 * (lane >> 5)) = vv;
+        *reinterpret_cast<bf16x4 *>(dK + krow + f * 32 + 8 * g + 4 * (lane >> 5)) = vk;
+        *reinterpret_cast<bf16x4 *>(dV + krow + f * 32 + 8 * g + 4 * (lane >> 5)) = vv;
       }
   }
 }
@@ -796,7 +794,7 @@ int launch_attn_bwd(hipStream_t s, const void *Q, const void *K, const void *V, 
   hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(ceil_div(T * G, AQ) * h * B), dim3(256), 0, s, (const bf16_t *)Q,
                      (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, dq_apart ? (const bf16_t *)O : nullptr, minus_delta, (bf16_t *)dQ, dq_rows, d);
   SMOE_LAUNCH_CHECK();
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, true, true>), dim3(plan.units * h * B), dim3(64 * NW), 0, s, (const bf16_t *)Q,
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW>), dim3(plan.units * h * B), dim3(64 * NW), 0, s, (const bf16_t *)Q,
                      (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)dO, LSE, (const float *)minus_delta, (bf16_t *)dK,
                      (bf16_t *)dV, part, plan, d);
   SMOE_LAUNCH_CHECK();
