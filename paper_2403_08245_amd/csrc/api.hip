@@ -625,7 +625,7 @@ int smoe_mlp_bwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, smoe_act act, co
     return SMOE_ERR_UNSUPPORTED;
   if (mode) {
     // Alg. 2 for both ParallelLinears with dp taken in the epilogue of the W2^T product: that product runs on the
-    // UNWEIGHTED sorted copy of dY, so its fp32 accumulators are dH / p and dp[row] = <acc, H[row]> needs neither the
+    // UNWEIGHTED rows of dY, so its fp32 accumulators are dH / p and dp[row] = <acc, H[row]> needs neither the
     // forward's Yhat nor a division by a routing weight.
     const MlpBwdEpiLayout L = mlp_bwd_epi_layout(mode, es, (size_t)Tk, d_model, d_expert, d_h);
     char *base = (char *)ws;

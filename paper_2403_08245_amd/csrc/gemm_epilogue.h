@@ -95,12 +95,6 @@ template <typename Dest> __device__ __forceinline__ void issue_row_store(const R
 #pragma unroll
   for (int it = 0; it < 4; ++it) p.dest.put(it, p.rows.v[it]);
 }
-// Sends a finished block's stores out before the next block starts where registers are short.
-template <typename Dest> __device__ __forceinline__ void flush_row_store(RowStore<Dest> &p) {
-  if (p.have) issue_row_store(p);
-  p.have = false;
-  sched_fence();
-}
 // One block through the pipeline: write_block() fills the patch from the accumulators; the previous block's
 // stores go out behind this block's LDS traffic.
 template <typename Dest, typename WriteFn>
@@ -180,13 +174,13 @@ __device__ __forceinline__ void store_wave_tile_swiglu(const f32x16 (&acc)[FM][F
   issue_row_store(pend);
 }
 
-// What the two backward epilogues read and write besides the block destinations.  All windows start at the wavefront's
-// first row (expert-sorted) and end with the segment, so rows past it read zeros and are not written; `saved` with `places` set
-// is a whole tensor instead, whose rows are found through the order indices.
+// What the two backward epilogues read and write besides the block destinations.  The windows start at the wavefront's first row
+// (expert-sorted) and end with the segment, so rows past it read zeros and are not written; `scale` is a whole array, and with PLACES
+// (store_wave_tile_dp) `saved` a whole tensor, whose rows are found through `places`.
 struct BwdRows {
   window_t saved;       // pre-activations [rows, 2 * n] (SwiGLU) or hidden rows [rows, n]
-  const int *places;    // order indices of the wavefront's rows (LDS; past the `left` rows there are, the last one's again): where their
-                        // routing weights lie, and rows of `saved` in slot order
+  const int *places;    // order indices of the wavefront's rows, always set (LDS; past the `left` rows there are, the last one's again):
+                        // where their routing weights lie, and with PLACES their rows of `saved`
   int left;
   window_t scale;       // routing weight of every slot
   window_t hidden;      // hidden rows [rows, n], where they are read beside the pre-activations
@@ -208,7 +202,7 @@ __device__ __forceinline__ float row_weight(const BwdRows &b, int fm, int lane) 
 // Epilogue of the second ParallelLinear's input-gradient product with the SwiGLU derivative and Alg. 2's dp folded in.
 // The accumulators hold dH / p for 128 hidden units of 32 * FM expert-sorted rows (the product ran on the unweighted
 // upstream rows).  Per 32 x 64 block the wavefront fetches the matching gate and up pre-activations (whole rows, turned to the
-// accumulators' layout through the patch; AHEAD: the next block requested before the current one is used), forms
+// accumulators' layout through the patch, the next block requested before the current one is used), forms
 // h = silu(gate) * up and the partial dot <acc, h> (summed over the wavefront's 128 columns: one slab of dp), scales
 // the accumulators by the row's routing weight and writes
 //   dgate = dh * up * (sig + silu * (1 - sig)),  dup = dh * silu
@@ -269,40 +263,34 @@ __device__ __forceinline__ GateUp load_gate_up(const BwdRows &b, int fm, int hal
 // HW: and Hw = p * H to dest_hw(fm, half), from the saved H: a block of it goes from whole rows to whole rows, so it needs no turn
 // through the patch.  (p * h from the fp32 h at hand reads nothing more, but that h comes from gates and ups rounded to bf16: the error of
 // dW2 against 64 bits was 3.45e-3 instead of 2.86e-3.)
-template <bool AHEAD, bool HW, int FM, typename DestFn, typename HwFn>
+template <bool HW, int FM, typename DestFn, typename HwFn>
 __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
                                                            HwFn dest_hw, int lane) {
   acc_settle();
   RowStore<BlockDest> pend;
-  static_assert(AHEAD || !HW, "the hidden rows are requested ahead");
-  GateUp in;
+  GateUp in = load_gate_up(b, 0, 0, lane);
+  float scale_next = row_weight(b, 0, lane);
   PatchRows hidden_next;
   RowWeights weights_next;
-  float scale_next = 0.f;
-  if (AHEAD) {
-    in = load_gate_up(b, 0, 0, lane);
-    scale_next = row_weight(b, 0, lane);
-    if (HW) {
-      hidden_next = load_hidden_rows(b, 0, 0, lane);
-      weights_next = row_weights(b, 0, lane);
-    }
+  if (HW) {
+    hidden_next = load_hidden_rows(b, 0, 0, lane);
+    weights_next = row_weights(b, 0, lane);
   }
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm) {
     float dp = 0.f;
-    const float scale = AHEAD ? scale_next : row_weight(b, fm, lane);
+    const float scale = scale_next;
     const RowWeights weights = weights_next;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      if (!AHEAD) flush_row_store(pend);
       const PatchRows hidden = hidden_next;
-      const GateUp rows = AHEAD ? in : load_gate_up(b, fm, half, lane);
+      const GateUp rows = in;
       bf16x4 gt[2][4], up[2][4];
       sched_fence();
       saved_columns(rows.gt, patch, lane, gt);
       saved_columns(rows.up, patch, lane, up);
       sched_fence();
-      if (AHEAD && fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
+      if (fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
         in = load_gate_up(b, half == 0 ? fm : fm + 1, half == 0 ? 1 : 0, lane);
         if (half == 1) scale_next = row_weight(b, fm + 1, lane);
         if (HW) {
@@ -361,31 +349,26 @@ __device__ __forceinline__ void store_wave_tile_swiglu_bwd(const f32x16 (&acc)[F
 // The activation-agnostic form: the accumulators hold dH / p; the wavefront fetches the saved hidden activations H of the
 // block, adds <acc, H> to the row's slab of dp, and writes dH = p * acc (HW: and Hw = p * H).
 // PLACES: the hidden rows and dH lie in slot order, the slabs and Hw are expert-sorted.
-template <bool AHEAD, bool HW, bool PLACES, int FM, typename DestFn, typename HwFn>
+template <bool HW, bool PLACES, int FM, typename DestFn, typename HwFn>
 __device__ __forceinline__ void store_wave_tile_dp(const f32x16 (&acc)[FM][FR], char *patch, const BwdRows &b, DestFn dest,
                                                    HwFn dest_hw, int lane) {
   acc_settle();
   auto load_h = [&](int fm, int half) { return load_saved_rows<PLACES>(b, fm, (uint32_t)(b.gcol + half * 64) * 2u, lane); };
   RowStore<BlockDest> pend;
-  PatchRows next;
-  float scale_next = 0.f;
-  if (AHEAD) {
-    next = load_h(0, 0);
-    scale_next = row_weight(b, 0, lane);
-  }
+  PatchRows next = load_h(0, 0);
+  float scale_next = row_weight(b, 0, lane);
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm) {
     float dp = 0.f;
-    const float scale = AHEAD ? scale_next : row_weight(b, fm, lane);
+    const float scale = scale_next;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      if (!AHEAD) flush_row_store(pend);
-      const PatchRows rows = AHEAD ? next : load_h(fm, half);
+      const PatchRows rows = next;
       bf16x4 cur[2][4];
       sched_fence();
       saved_columns(rows, patch, lane, cur);
       sched_fence();
-      if (AHEAD && fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
+      if (fm * 2 + half + 1 < 2 * FM) {   // request the next 64 columns (or the next fragment row) now
         next = load_h(half == 0 ? fm : fm + 1, half == 0 ? 1 : 0);
         if (half == 1) scale_next = row_weight(b, fm + 1, lane);
       }

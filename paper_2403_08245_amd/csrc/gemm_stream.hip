@@ -538,7 +538,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
       const window_t win_w = ACT >= 5 ? sorted_window(p->Hw_out, N, 2) : win_c;
       auto dest_hw = [&](int fm, int half) { return sorted_block(win_w, N, fm, gcol + half * 64, N - gcol - half * 64); };
       if constexpr (GATE_UP) {
-        store_wave_tile_swiglu_bwd<true, ACT == 7>(
+        store_wave_tile_swiglu_bwd<ACT == 7>(
             acc, patch, b,
             [&](int fm, int half, int up) { return sorted_block(win_c, ldc, fm, up * N + gcol + half * 64, N - gcol - half * 64); }, dest_hw, lane);
       } else {
@@ -546,7 +546,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) s2s_stream_kernel(S2SArgs a, int 
           if constexpr (ACT == 6) return slot_block(win_c, N, b.places, left, fm, gcol + half * 64);
           else return sorted_block(win_c, ldc, fm, gcol + half * 64, N - gcol - half * 64);
         };
-        store_wave_tile_dp<true, ACT >= 5, ACT == 6>(acc, patch, b, dest, dest_hw, lane);
+        store_wave_tile_dp<ACT >= 5, ACT == 6>(acc, patch, b, dest, dest_hw, lane);
       }
     } else {
       const int wcol = ct.n0 + uwn * (TB / 2);
