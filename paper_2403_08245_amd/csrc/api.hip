@@ -898,15 +898,16 @@ int smoe_momha_fwd(smoe_ctx *ctx, void *stream, smoe_dtype dtype, const void *X,
 }
 
 // Does forming dp in the epilogue of the output projection's input-gradient product pay?  It saves passes over rows of [Tk, d_model],
-// but the product then runs on 256 x 256 tiles, of which there have to be enough (half a round), and its epilogue gains on the passes
-// only where these are long enough (16 Mi elements).  Backward pass of the layer, 8 experts, sequences of 512, in us, with it /
-// without, rows x d_model, heads, k:
-//   both lines met:  32768 x 512, 2, 4: 309 / 323; 16384 x 1024, 4, 4: 361 / 372; 65536 x 256, 4, 8: 572 / 593; 65536 x 2048, 2, 8:
-//                    805 / 905; 32768 x 2048, 4, 4: 762 / 787; 32768 x 1024, 8, 2: 844 / 851; the worst 16384 x 1024, 8, 4: 513 / 503;
-//   64 tiles:        16384 x 1024, 2, 8: 311 / 303; 8192 x 2048, 4, 8: 304 / 284; 16384 x 2048, 1, 8: 362 / 350;
-//   8 Mi elements:   128 tiles 32768 x 256, 2, 4: 277 / 279, 16384 x 512, 4, 8: 320 / 317, 8192 x 1024, 8, 8: 308 / 304; 256 tiles
-//                    16384 x 512, 8, 4: 452 / 440, 32768 x 256, 4, 2: 426 / 410; 512 tiles 32768 x 256, 8, 4: 603 / 591;
-//   4 Mi:            256 tiles 16384 x 256, 8, 4: 415 / 394, 512 tiles 32768 x 128, 8, 2: 557 / 542, 128 tiles within 2 % either way.
+// and its epilogue gains on them only where these are long enough (16 Mi elements).  Backward pass of the layer, 8 experts, sequences of
+// 512, in us, with it / without, rows x d_model, heads, k:
+//   both lines met:  32768 x 512, 2, 4: 290 / 305; 16384 x 1024, 4, 4: 346 / 359; 65536 x 256, 4, 8: 534 / 536; 65536 x 2048, 2, 8:
+//                    666 / 798; 32768 x 2048, 4, 4: 671 / 720; 32768 x 1024, 8, 2: 801 / 800; 16384 x 1024, 8, 4: 482 / 482;
+//   8 Mi elements:   128 tiles 32768 x 256, 2, 4: 263 / 266, 16384 x 512, 4, 8: 293 / 292, 8192 x 1024, 8, 8: 282 / 282; 256 tiles
+//                    16384 x 512, 8, 4: 426 / 414, 32768 x 256, 4, 2: 395 / 387; 512 tiles 32768 x 256, 8, 4: 559 / 539;
+//   4 Mi:            256 tiles 16384 x 256, 8, 4: 377 / 371, 512 tiles 32768 x 128, 8, 2: 518 / 493.
+// The line at 128 tiles (half a round of 256 x 256) was drawn when the product ran on such tiles alone and lost under it.  On the smaller
+// ones it wins there: 64 tiles 16384 x 1024, 2, 8: 272 / 283; 8192 x 2048, 4, 8: 258 / 269; 16384 x 2048, 1, 8: 306 / 334.  It stays for
+// dgates' sake: fp32, and rounded otherwise on the other route, by 1e-3.
 static bool output_projection_in_epilogue(const smoe_ctx *ctx, int Tk, int d_model, int d_out) {
   if (ctx->tile_shape) return ctx->tile_shape == 2;   // tiles of one shape only, for the tests
   return (size_t)Tk * d_model >= ((size_t)16 << 20) && (long long)ceil_div(Tk, 256) * ceil_div(d_out, 256) * 2 >= ctx->stream_grid;

@@ -1006,7 +1006,8 @@ template <typename S, bool TRANS_W, bool SCATTER_OUT, int ACT, bool STATIC2, boo
 //   where not; its W1^T counterpart (5632 -> 1024) 134 / 106; 2816 -> 1024 72 / 75;  6002 rows, 3416 -> 1280: 95 / 59;
 //   6832 -> 1280 W^T 188 / 123;  2 x 8192 rows: 2048 -> 512 54 / 34;  32768 rows, 16 experts: 2048 -> 512 92 / 88, 512 -> 2048 84 / 91;
 //   65536 rows, 64 experts: 2048 -> 2 x 512 with SwiGLU 268 / 308, 512 -> 2048 152 / 183, 1024 -> 2048 W^T 287 / 325;
-//   262144 rows, 64 experts: 4096 -> 512 930 / 1060;  32768 rows, 8 experts: 14336 -> 4096 3020 / 3530.
+//   262144 rows, 64 experts: 4096 -> 512 930 / 1060;  32768 rows, 8 experts: 14336 -> 4096 3020 / 3530;
+//   32768 rows, 16 experts, 2048 -> 512 W^T with dp and the weighted rows in the epilogue (ACT 6) 121 / 105.
 // Even loads make the next whole number of tiles instead, which a long contraction that stands at the end of a round pays dearly for:
 // contractions over 2048 take Half only where the mean over both counts says so too.  2937 tokens on 37 experts, k = 6, 7808 -> 720: 262 big
 // tiles by the first count, a round and a bit, 222 by the second; Big 232, Half 283.  Whole forward passes with / without that: this
@@ -1044,36 +1045,31 @@ template <bool TRANS_W, bool SCATTER_OUT, int ACT = 0> int launch_s2s_cfg(hipStr
       if (static2) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, true>(s, a);
       return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, true>(s, a);
     }
-  // The epilogue of ACT 6 (two offsets per row, two outputs) does not fit the 128 registers of a pair: 72 of them spilled, and the
-  // product of 32768 rows, 2048 -> 512, took 225 us of 121.
-  if constexpr (ACT != 6) {
-    const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
-    const bool may_split = ACT == 0 && a.tail_ws;
-    if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_half(a, tiles_n, may_split))) {
-      // At most one tile row per expert on average: most of W is read once, and where the call's weights exceed the last-level cache
-      // keeping its lines only pushes other data out (6216 rows, 64 experts: 2048 -> 2 x 512 in 60 us, past the caches 53).  With
-      // reuse they belong there (8192 rows and 8 experts, 1024 -> 5632: 113 us, past the caches 156), so a tile of an expert that has
-      // several takes them the ordinary way (777 tokens on 64 experts with Zipf(1.2) loads, 2048 -> 2 x 512 -> 2048: the forward pass
-      // 133 us with all of W past the caches, 129 with none, 125 so).
-      if constexpr (!TRANS_W) {
-        const bool once = (long long)a.Tk <= (long long)a.E * Half::TM && weights_pass_caches(a);
-        // HalfShort: contractions of up to four stages, and launches of one round whose contraction is up to eight or which read most of W
-        // once by rows at a stride of whole kilobytes.  Few stages are over before a third slot's requests come in; and a block with a
-        // single tile waits for W at every stage, where requests for many rows that fall on few cache sets wait for one another (the
-        // more so with SwiGLU, which reads each row in two places).  Two / three slots in us, W from memory (from the last-level cache), 16
-        // experts of 62 rows, SwiGLU: 512 -> 2 x 512 15.2 / 15.7, 2048 -> 2 x 512 39.6 / 40.8 (33.6 / 35.5), 4096 -> 2 x 512 69.5 / 71.6 (59.5 / 63.3);
-        // 37 experts of 60 rows, 3840 -> 512 61.9 / 63.6, 64 of 97 rows, 2048 -> 1024 54.5 / 55.6; 16 experts of 256 rows, 128 -> 2048 11.7 / 12.7.
-        // Elsewhere the third slot is worth more: other strides, 16 of 62 rows, 2048 -> 2 x 448 37.1 / 34.5; W read several times, 4 of 292 rows,
-        // 2688 -> 2048 43.7 / 41.2; several rounds, 16 of 1024 rows, 4096 -> 2 x 2816 796 / 750.
-        const bool one_round = estimated_tiles<Half>(a, tiles_n) <= a.grid, apart = a.ldw % 512 == 0 && (long long)a.Tk <= (long long)a.E * Half::TM;
-        if (a.K <= 4 * SK || (one_round && (a.K <= 8 * SK || apart))) {
-          if (once) return launch_s2s_one<HalfShortOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
-          return launch_s2s_one<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
-        }
-        if (once) return launch_s2s_one<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+  const int tiles_n = (ACT == 1 || ACT == 2) ? ceil_div(a.N / 2, TB / 2) : ceil_div(a.N, TB);
+  const bool may_split = ACT == 0 && a.tail_ws;
+  if (a.tile_shape == 1 || (a.tile_shape == 0 && prefer_half(a, tiles_n, may_split))) {
+    // At most one tile row per expert on average: most of W is read once, and where the call's weights exceed the last-level cache
+    // keeping its lines only pushes other data out; a tile of an expert that has several reads what the others do and takes it the
+    // ordinary way (777 tokens on 64 experts, 2048 -> 2 x 512 -> 2048, other weights at every call, the forward pass: 106 us with W
+    // through the caches, 94 so; with Zipf(1.2) loads 129, 131 with all of W past them, 121 so).
+    if constexpr (!TRANS_W) {
+      const bool once = (long long)a.Tk <= (long long)a.E * Half::TM && weights_pass_caches(a);
+      // HalfShort: contractions of up to four stages, and launches of one round whose contraction is up to eight or which read most of W
+      // once by rows at a stride of whole kilobytes.  Few stages are over before a third slot's requests come in; and a block with a
+      // single tile waits for W at every stage, where requests for many rows that fall on few cache sets wait for one another (the
+      // more so with SwiGLU, which reads each row in two places).  Two / three slots in us, W from memory (from the last-level cache), 16
+      // experts of 62 rows, SwiGLU: 512 -> 2 x 512 15.2 / 15.7, 2048 -> 2 x 512 39.6 / 40.8 (33.6 / 35.5), 4096 -> 2 x 512 69.5 / 71.6 (59.5 / 63.3);
+      // 37 experts of 60 rows, 3840 -> 512 61.9 / 63.6, 64 of 97 rows, 2048 -> 1024 54.5 / 55.6; 16 experts of 256 rows, 128 -> 2048 11.7 / 12.7.
+      // Elsewhere the third slot is worth more: other strides, 16 of 62 rows, 2048 -> 2 x 448 37.1 / 34.5; W read several times, 4 of 292 rows,
+      // 2688 -> 2048 43.7 / 41.2; several rounds, 16 of 1024 rows, 4096 -> 2 x 2816 796 / 750.
+      const bool one_round = estimated_tiles<Half>(a, tiles_n) <= a.grid, apart = a.ldw % 512 == 0 && (long long)a.Tk <= (long long)a.E * Half::TM;
+      if (a.K <= 4 * SK || (one_round && (a.K <= 8 * SK || apart))) {
+        if (once) return launch_s2s_one<HalfShortOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+        return launch_s2s_one<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
       }
-      return launch_s2s_one<Half, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
+      if (once) return launch_s2s_one<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
     }
+    return launch_s2s_one<Half, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
   }
   if (static2) return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, true, false>(s, a);
   return launch_s2s_one<Big, TRANS_W, SCATTER_OUT, ACT, false, false>(s, a);
@@ -1191,8 +1187,7 @@ int launch_dw_stream(hipStream_t s, const DWArgs &a) { return launch_dw_stream_i
 template <bool TRANS_W, bool SCATTER_OUT, int ACT> static int init_s2s() {
   int rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, true, false>, Big::LDS_BYTES);
   if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Big, TRANS_W, SCATTER_OUT, ACT, false, false>, Big::LDS_BYTES);
-  if constexpr (ACT != 6)
-    if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Half, TRANS_W, SCATTER_OUT, ACT, false, false>, Half::LDS_BYTES);
+  if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<Half, TRANS_W, SCATTER_OUT, ACT, false, false>, Half::LDS_BYTES);
   if constexpr (!TRANS_W) {
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfOnce, TRANS_W, SCATTER_OUT, ACT, false, false>, HalfOnce::LDS_BYTES);
     if (rc == SMOE_OK) rc = set_lds_limit(s2s_stream_kernel<HalfShort, TRANS_W, SCATTER_OUT, ACT, false, false>, HalfShort::LDS_BYTES);
