@@ -224,14 +224,14 @@ template <typename S, bool TRANS_W, bool KTAIL, bool SWIGLU> struct S2SOps {
     if (I < S::NLA) {
       uint32_t off = oa[I] + (uint32_t)step * (SK * 2);
       if (KTAIL) off |= step == last ? ta[I & 1] : 0u;
-      load16_to_lds_checked(win_a, off, fill_a + (uwave * S::NLA + I) * 1024);
+      load16_to_lds_checked(win_a, off, fill_a + uwave * (S::NLA * 1024), I * 1024);
     } else {
       const int J = I - S::NLA;
       uint32_t off = ob[J & 1] + ((uint32_t)(J >> 1) * b_rows + (uint32_t)step * b_step);
       if (KTAIL && TRANS_W) off |= step == last ? tb[J & 1] : 0u;
-      const uint32_t lds = fill_b + (uwave * S::NLB + J) * 1024;
-      if (S::ONCE) load16_to_lds_checked_or_once(win_b, off, lds, again);
-      else load16_to_lds_checked(win_b, off, lds);
+      const uint32_t lds = fill_b + uwave * (S::NLB * 1024);
+      if (S::ONCE) load16_to_lds_checked_or_once(win_b, off, lds + J * 1024, again);
+      else load16_to_lds_checked(win_b, off, lds, J * 1024);
     }
   }
   __device__ __forceinline__ bf16x8 frag_a(const char *slot, int i, int kk) const { return line_frag(slot + fa[kk], i); }
@@ -684,12 +684,12 @@ template <int KIND> struct DWStreamOps {
     if (I < Big::NLA) {
       uint32_t off = oa[I & 1] + (uint32_t)(I >> 1) * pair_a;
       if (ROWS_A) off = through(I, off, mul_a, magic_a);
-      load16_to_lds_checked(win_a, off, fill_a + (uwave * Big::NLA + I) * 1024);
+      load16_to_lds_checked(win_a, off, fill_a + uwave * (Big::NLA * 1024), I * 1024);
     } else {
       const int J = I - Big::NLA;
       uint32_t off = ob[J & 1] + (uint32_t)(J >> 1) * pair_b;
       if (ROWS_B) off = through(J, off, mul_b, magic_b);
-      load16_to_lds_checked(win_b, off, fill_b + (uwave * Big::NLB + J) * 1024);
+      load16_to_lds_checked(win_b, off, fill_b + uwave * (Big::NLB * 1024), J * 1024);
     }
   }
   __device__ __forceinline__ bf16x8 frag_a(const char *slot, int i, int kk) const { return rows_frag(slot + fa[i], kk); }
