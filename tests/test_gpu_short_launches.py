@@ -78,3 +78,29 @@ def test_weights_past_the_caches_in_one_round(width):
     loads = [0, 130] + [60] * 14 + [50]
     assert 17 * 4104 * width * 2 > 256 << 20 and 17 * -(-width // COLS) <= GRID and sum(loads) <= ROWS * 17
     _compare(smoe, loads, 1, 4104, width, 8)
+
+
+@pytest.mark.parametrize("d_expert", [4096, 4104])
+def test_cut_contraction(d_expert):
+    """The second product of an MLP, whose few tiles are cut along the contraction, from the hidden rows that the pass kept."""
+    import paper_2403_08245_amd as smoe
+    T, d_model, E, k = 480, 1024, 8, 2
+    gen = torch.Generator(device="cuda").manual_seed(d_expert)
+    normal = lambda *s: torch.empty(*s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    X, W1, W2 = normal(T, d_model), normal(E, d_model, 2 * d_expert).mul_(d_model ** -0.5), normal(E, d_expert, d_model).mul_(d_expert ** -0.5)
+    ei, g = smoe.topk_gate(torch.empty(T, E, device="cuda").normal_(generator=gen), k)
+    r = smoe.route(ei, E)
+    assert 32 * E < T * k <= ROWS * E and E * d_model // COLS * 4 <= GRID and d_model % 512 == 0
+    print("cut contraction", d_expert, flush=True)
+    smoe.set_kernel_mode(3)
+    try:
+        Y, buf = smoe.mlp_fwd(X, W1, W2, r, k, g, smoe.ACT_SWIGLU)
+    finally:
+        smoe.set_kernel_mode(0)
+    off, o = r.expert_offsets.tolist(), r.sorted_scattered_idxs.long()
+    want = torch.zeros(T, d_model, dtype=torch.float64, device="cuda")
+    for e in range(E):
+        s = o[off[e]:off[e + 1]]
+        want.index_add_(0, s // k, g.view(-1)[s].double()[:, None] * (buf.H[off[e]:off[e + 1]].double() @ W2[e].double()))
+    # every slot's row is rounded once to 8 significant bits, and their weighted sum once more
+    assert (Y.double() - want).abs().max() <= 2.0 ** -7 * want.abs().max()
